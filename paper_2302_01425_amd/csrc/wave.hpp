@@ -186,14 +186,16 @@ __device__ __forceinline__ void store_elems(float* __restrict__ p, int64_t base,
 }
 
 // ---- rows dealt to the lanes float4 by float4 ---------------------------------------------------
-// For vectorisable rows (VEC) register r of lane lr holds element ((r/4) * GL + lr) * 4 + r % 4
-// instead of lr * E + r: every load / store instruction of a row group then covers one
-// contiguous span of the row.  Which elements a lane holds is immaterial to the sort, the index
-// travels with the key.  STREAM adds the non-temporal hint.
+// For vectorisable rows (VEC) register r of lane lr holds element ((r/4) * GL + lr) * 4 + r % 4, for
+// others element r * GL + lr: every load / store instruction of a row group then covers one
+// contiguous span of the row.  (With E consecutive elements per lane, lr * E + r, every instruction
+// touched every cache line of the row: 4096 x 1001 mask JVP, p = 2: 54.8 us against 18.4, loss with
+// p = 4/3: 50.5 against 23.4; 32768 x 127: 38.1 against 18.3.)  Which elements a lane holds
+// is immaterial to the sort, the index travels with the key.  STREAM adds the non-temporal hint.
 template <int GL, int E, bool VEC>
 __device__ __forceinline__ int elem_of(int lr, int r) {
   if constexpr (VEC) return (((r >> 2) * GL + lr) << 2) + (r & 3);
-  else return lr * E + r;
+  else return r * GL + lr;
 }
 template <int GL, int E, bool VEC, bool STREAM>
 __device__ __forceinline__ void load_row(const float* __restrict__ p, int64_t base, int lr, int n,
@@ -207,7 +209,8 @@ __device__ __forceinline__ void load_row(const float* __restrict__ p, int64_t ba
       v[4 * c + 0] = q.x; v[4 * c + 1] = q.y; v[4 * c + 2] = q.z; v[4 * c + 3] = q.w;
     }
   } else {
-    load_elems<E, false>(p, base, lr * E, n, v);
+#pragma unroll
+    for (int r = 0; r < E; ++r) v[r] = (r * GL + lr < n) ? p[base + r * GL + lr] : 0.0f;
   }
 }
 template <int GL, int E, bool VEC, bool STREAM>
@@ -224,7 +227,9 @@ __device__ __forceinline__ void store_row(float* __restrict__ p, int64_t base, i
       }
     }
   } else {
-    store_elems<E, false>(p, base, lr * E, n, v);
+#pragma unroll
+    for (int r = 0; r < E; ++r)
+      if (r * GL + lr < n) p[base + r * GL + lr] = v[r];
   }
 }
 // the same registers to / from a row staged in LDS in original element order
@@ -237,7 +242,7 @@ __device__ __forceinline__ void lds_store_row(float* row, int lr, const float (&
           make_float4(v[4 * c], v[4 * c + 1], v[4 * c + 2], v[4 * c + 3]);
   } else {
 #pragma unroll
-    for (int r = 0; r < E; ++r) row[lr * E + r] = v[r];
+    for (int r = 0; r < E; ++r) row[r * GL + lr] = v[r];
   }
 }
 template <int GL, int E, bool VEC>
@@ -250,7 +255,7 @@ __device__ __forceinline__ void lds_load_row(const float* row, int lr, float (&v
     }
   } else {
 #pragma unroll
-    for (int r = 0; r < E; ++r) v[r] = row[lr * E + r];
+    for (int r = 0; r < E; ++r) v[r] = row[r * GL + lr];
   }
 }
 
