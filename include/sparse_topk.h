@@ -292,9 +292,9 @@ int topk_set_workspace(void* dev_ptr, size_t bytes);
  *                               selection, sorted (key, index) lists and scatter, for every such
  *                               row), _SORT (rows sorted completely), _WIDE (multi-launch
  *                               selection, key-only sort and outputs by value: what AUTO takes
- *                               for rows above 131072 elements), _ONE_LAUNCH_INDEXED (up to 131072
- *                               elements: the one-launch kernel that sorts (key, index) pairs,
- *                               which AUTO only takes up to 8192 elements)
+ *                               for rows above 32768 elements; up to there it finds the block by
+ *                               root search without any sort), _ONE_LAUNCH_INDEXED (up to 131072
+ *                               elements: the one-launch kernel that sorts (key, index) pairs)
  *   TOPK_ROUTE_SHORT_ROW_LANES  lanes of a wavefront that share a short row: 0 (by shape) or a
  *                               power of two up to 64 (clamped to what the row length allows)
  *   TOPK_ROUTE_SHORT_ROW_KERNEL for rows of up to 128 elements: TOPK_SHORT_ROW_KERNEL_AUTO (dense

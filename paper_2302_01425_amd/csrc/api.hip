@@ -64,6 +64,23 @@ bool value_wide(bool mag, int pc, int64_t n) {
          (pc == topk::kP2 || (pc == topk::kP43 && !mag));
 }
 
+// Rows of row_search.hpp: dense outputs from the row in registers, without a sort.  Rows above 2048
+// elements, whatever k and p.  Shorter ones only where the kernels that order values in one wavefront
+// are slower (16384 x 256: 13 us there, 27 here; us for 4 M elements, forward + JVP):
+//   * they order a few candidates when k <= 64, but about k = 48 the candidates stop fitting, and then
+//     the whole row is sorted: 1000 elements, k = 33 16 there, 18 here; k = 100 24 / 19; 2048, k = 33
+//     15.5 / 17, k = 205 23 / 18; 512, k = 256 20 / 19.  With p = 4/3 the float64 steps cost more here:
+//     700, k = 64 31 / 37, k = 350 32 / 26; 1500, k = 64 40 / 26;
+//   * top-k in magnitude with p = 4/3, which they do not have: 400 elements 121 / 48.
+bool search_rows(bool mag, int pc, int64_t n, int64_t k) {
+  if (topk::routes().short_kernel != TOPK_SHORT_ROW_KERNEL_AUTO) return false;
+  if (is_long(n) && long_mode() != kAuto) return false;
+  if (n < topk::kRowSearchMin || n > topk::kRowSearchMax) return false;
+  if (n > 2048) return true;
+  if (mag && pc == topk::kP43) return true;
+  return n > 512 && (k == 0 || k > (pc == topk::kP2 || n > 1024 ? 48 : 64));
+}
+
 struct Layout {
   size_t keys_a, keys_b, idx_a, idx_b, hist, dtot, info, hpart, bins, bins2, tcnt, tabove, toff, taboff, sel, total;
 };
@@ -149,6 +166,12 @@ int run_operator(bool mag, const float* x, const float* tangent, int64_t rows, i
     if (rc != TOPK_OK) return rc;
   }
   begin();
+  if (search_rows(mag, pc, n, k)) {
+    const int src = topk::launch_row_search(0, mag, pc, x, need_jvp ? tangent : nullptr, out,
+                                            need_jvp ? jvp : nullptr, nullptr, 0.0, rows, n, k, R, st);
+    if (src == 0) return finish();
+    if (src != -2) return TOPK_ERR_INVALID;
+  }
   if (!is_long(n)) {
     if (topk::launch_short_rows(mag, pc, x, need_jvp ? tangent : nullptr, out,
                                 need_jvp ? jvp : nullptr, rows, int(n), int(k), R, st) != 0)
@@ -166,9 +189,10 @@ int run_operator(bool mag, const float* x, const float* tangent, int64_t rows, i
   }
   // k = 0 and k = n pool nothing and read no sorted value: no sort at all
   const bool trivial = (k == 0 || k == n);
-  // Rows above 32768 elements: the streaming steps of a row are spread over many workgroups
-  // (separate launches) and only the sort + solve of its candidates is left to one.
-  if (!trivial && (mode == kWide || (mode == kAuto && n > 32768))) {
+  // Rows above 32768 elements (and the last few lengths before it where rows are not aligned): the
+  // streaming steps of a row are spread over many workgroups (separate launches) and only the
+  // sort + solve of its candidates is left to one.
+  if (!trivial && (mode == kWide || (mode == kAuto && n > 32765))) {
     const bool refine = n > (int64_t(1) << 18);
     if (topk::launch_wide_select(mag, pc, refine, x, need_jvp ? tangent : nullptr, rows, n, k, R, B,
                                  st) != 0)
@@ -181,15 +205,10 @@ int run_operator(bool mag, const float* x, const float* tangent, int64_t rows, i
     return finish();
   }
   if ((mode == kAuto || mode == kOneLaunchIndexed) && n <= topk::kMediumRowMax) {
-    // one launch, one workgroup per row; above 8192 elements the kernel that orders values only
-    const bool by_value = mode == kAuto && n > 8192 && n <= 32768;
-    const int lrc = by_value ? topk::launch_medium_rows2(mag, pc, B, x, need_jvp ? tangent : nullptr,
-                                                         out, need_jvp ? jvp : nullptr, rows, n, k,
-                                                         R, st)
-                             : topk::launch_medium_rows(mag, pc, B, x, need_jvp ? tangent : nullptr,
-                                                        out, need_jvp ? jvp : nullptr, rows, n, k,
-                                                        R, st);
-    if (lrc != 0) return TOPK_ERR_INVALID;
+    // one launch, one workgroup per row, (key, index) pairs
+    if (topk::launch_medium_rows(mag, pc, B, x, need_jvp ? tangent : nullptr, out, need_jvp ? jvp : nullptr,
+                                 rows, n, k, R, st) != 0)
+      return TOPK_ERR_INVALID;
     return finish();
   }
   const bool selected = !trivial && mode != kFullSort;
@@ -228,7 +247,8 @@ int run_abs_operator(bool signed_mask, const float* x, const float* tangent, int
   if (x == nullptr || out == nullptr) return TOPK_ERR_NULL;
   if (need_jvp && (jvp == nullptr || tangent == nullptr)) return TOPK_ERR_NULL;
   // rows of up to 2048 elements: one fused kernel, no scratch
-  if (abs_fused(n)) {
+  const bool search = search_rows(false, pc, n, k);
+  if (abs_fused(n) && !search) {
     begin();
     const int frc = topk::launch_short_rows_fused_variant(
         signed_mask ? 1 : 2, pc, x, need_jvp ? tangent : nullptr, out, need_jvp ? jvp : nullptr,
@@ -239,8 +259,15 @@ int run_abs_operator(bool signed_mask, const float* x, const float* tangent, int
   // the whole workspace is checked before the first launch: two arrays here, then the mask's own
   const size_t skip = abs_scratch_bytes(rows, n);
   const size_t need = skip + (is_long(n) ? layout_for(rows, n).total : 0);
-  if (g_ws.ptr == nullptr || g_ws.bytes < need) return TOPK_ERR_WORKSPACE;
+  if (!abs_fused(n) && (g_ws.ptr == nullptr || g_ws.bytes < need)) return TOPK_ERR_WORKSPACE;
   begin();
+  if (search) {
+    const int src = topk::launch_row_search(signed_mask ? 1 : 2, false, pc, x, need_jvp ? tangent : nullptr, out,
+                                            need_jvp ? jvp : nullptr, nullptr, 0.0, rows, n, k,
+                                            make_reg(lambda), static_cast<hipStream_t>(stream));
+    if (src == 0) return finish();
+    if (src != -2) return TOPK_ERR_INVALID;
+  }
   float* ax = static_cast<float*>(g_ws.ptr);
   float* st = reinterpret_cast<float*>(static_cast<char*>(g_ws.ptr) + skip / 2);
   hipStream_t s = static_cast<hipStream_t>(stream);
@@ -499,14 +526,27 @@ int topk_mask_loss(const float* theta, const float* target, int64_t rows, int64_
     const int rc = check_shape(rows, n, k, lambda);
     return rc != TOPK_OK ? rc : (p_code(p) < 0 ? TOPK_ERR_UNSUPPORTED_P : TOPK_ERR_NULL);
   }
-  if (rows > 0 && n <= 2048 && grad_out != nullptr && theta != nullptr &&
-      check_shape(rows, n, k, lambda) == TOPK_OK && p_code(p) >= 0) {
-    // rows of up to 2048 elements: mask, loss and gradient in one kernel
-    const double p_ex = p_code(p) == topk::kP2 ? 2.0 : 4.0 / 3.0;
-    begin();
-    const int frc = topk::launch_short_rows_fused_variant(
-        3, p_code(p), theta, target, grad_out, nullptr, loss_out, lambda / p_ex, rows, int(n),
-        int(k), make_reg(lambda), static_cast<hipStream_t>(stream));
+  if (rows > 0 && grad_out != nullptr && theta != nullptr && check_shape(rows, n, k, lambda) == TOPK_OK &&
+      p_code(p) >= 0) {
+    // mask, loss and gradient in one kernel
+    const int pc = p_code(p);
+    const double lam_over_p = lambda / (pc == topk::kP2 ? 2.0 : 4.0 / 3.0);
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    int frc = -2;
+    if (search_rows(false, pc, n, k)) {
+      if (n > 2048) {                      // (no scratch is used, but rows of this length ask for it)
+        SortBuffers B;
+        const int wrc = carve(rows, n, &B);
+        if (wrc != TOPK_OK) return wrc;
+      }
+      begin();
+      frc = topk::launch_row_search(3, false, pc, theta, target, grad_out, nullptr, loss_out, lam_over_p,
+                                    rows, n, k, make_reg(lambda), st);
+    } else if (n <= 2048) {
+      begin();
+      frc = topk::launch_short_rows_fused_variant(3, pc, theta, target, grad_out, nullptr, loss_out,
+                                                  lam_over_p, rows, int(n), int(k), make_reg(lambda), st);
+    }
     if (frc == 0) return finish();
     if (frc != -2) return TOPK_ERR_INVALID;
   }

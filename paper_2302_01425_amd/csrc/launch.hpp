@@ -120,6 +120,15 @@ int launch_short_argsort_fast(int np, int lg, bool vec, const float* x, int32_t*
 int launch_short_rows_fast_sparse(int np, int lg, bool vec, int pc, const float* x, int64_t rows,
                                   int n, int k, const Reg& R, const SparseOut& sp, hipStream_t st);
 
+// Rows of 129 .. kRowSearchMax elements, dense outputs, no scratch (row_search.hpp).  var: 0 the
+// operator itself, 1 signed mask, 2 x o mask(|x|), 3 Fenchel-Young loss (tangent = target, out = the
+// gradient, loss[rows]).  Returns 0, -1 (too many rows) or -2 (no shape: above 32765 elements where
+// rows do not all start at a 16-byte boundary).
+constexpr int64_t kRowSearchMin = 129, kRowSearchMax = 32768;
+int launch_row_search(int var, bool mag, int pc, const float* x, const float* tangent, float* out,
+                      float* jvp, float* loss, double lam_over_p, int64_t rows, int64_t n, int64_t k,
+                      const Reg& R, hipStream_t st);
+
 // Long rows: segmented radix sort (result in B.keys_a / B.idx_a), then solve + scatter.
 int radix_tiles(int64_t n);
 // workgroups per row of the first selection histogram, and the elements each of them covers
@@ -153,12 +162,6 @@ constexpr int64_t kMediumRowMax = 131072;
 int launch_medium_rows(bool mag, int pc, const SortBuffers& B, const float* x, const float* tangent,
                        float* out, float* jvp, int64_t rows, int64_t n, int64_t k, const Reg& R,
                        hipStream_t st);
-
-// The same for rows of 8193 .. kMediumRowMax elements with dense outputs computed from values:
-// keys-only sort and block growth in LDS, no permutation (medium_rows2.hip).
-int launch_medium_rows2(bool mag, int pc, const SortBuffers& B, const float* x, const float* tangent,
-                        float* out, float* jvp, int64_t rows, int64_t n, int64_t k, const Reg& R,
-                        hipStream_t st);
 
 // Long rows without a full sort (0 < k < n): two histogram levels of the leading key bits -> key
 // window around positions k, k+1 that holds every element able to pool -> those candidates, in

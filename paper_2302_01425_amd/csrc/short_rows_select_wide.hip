@@ -1,7 +1,8 @@
 // Launchers of the values-only short-row kernel (short_rows_value.hpp) for rows of 129 .. 2048
 // elements: 32 or 64 lanes per row with 8, 16 or 32 elements per lane; one row (two for 256
 // elements) per wavefront.  With k <= lanes per row only the values above the threshold T are
-// ordered; otherwise the whole row goes through the float network in registers.
+// ordered; otherwise the whole row goes through the float network in registers, up to 512 elements
+// (longer ones with k > lanes: row_search.hip).
 #include "short_rows_value.hpp"
 
 namespace topk {
@@ -16,14 +17,17 @@ int launch_wide_mode(const float* x, const float* t, float* out, float* jvp, int
   const int64_t blocks = (waves + WPB - 1) / WPB;
   if (blocks > 0x7fffffffLL) return -1;
   const float il = float(R.inv_lambda), i1 = float(R.inv_1pl);
-  if (k >= 1 && k <= GL && k < n)
+  if (k >= 1 && k <= GL && k < n) {
     hipLaunchKernelGGL((short_rows_value_kernel<GL, E, MAG, PC, VEC, FULL, MODE, true, WPB>),
                        dim3((unsigned)blocks), dim3(WPB * kWave), 0, st, x, t, out, jvp, rows, n, k, R,
                        il, i1, nullptr, 0.0);
-  else
+  } else if constexpr (C::NP <= 512) {
     hipLaunchKernelGGL((short_rows_value_kernel<GL, E, MAG, PC, VEC, FULL, MODE, false, WPB>),
                        dim3((unsigned)blocks), dim3(WPB * kWave), 0, st, x, t, out, jvp, rows, n, k, R,
                        il, i1, nullptr, 0.0);
+  } else {
+    return -1;                                           // (row_search.hip takes these)
+  }
   return 0;
 }
 

@@ -14,14 +14,17 @@ int launch_var_mode(const float* x, const float* t, float* out, float* jvp, floa
   const int64_t blocks = (waves + WPB - 1) / WPB;
   if (blocks > 0x7fffffffLL) return -1;
   const float il = float(R.inv_lambda), i1 = float(R.inv_1pl);
-  if (k >= 1 && k <= GL && k < n)
+  if (k >= 1 && k <= GL && k < n) {
     hipLaunchKernelGGL((short_rows_value_kernel<GL, E, false, PC, VEC, FULL, MODE, true, WPB, VAR>),
                        dim3((unsigned)blocks), dim3(WPB * kWave), 0, st, x, t, out, jvp, rows, n, k, R,
                        il, i1, loss, lam_over_p);
-  else
+  } else if constexpr (C::NP <= 512) {
     hipLaunchKernelGGL((short_rows_value_kernel<GL, E, false, PC, VEC, FULL, MODE, false, WPB, VAR>),
                        dim3((unsigned)blocks), dim3(WPB * kWave), 0, st, x, t, out, jvp, rows, n, k, R,
                        il, i1, loss, lam_over_p);
+  } else {
+    return -1;                                           // (row_search.hip takes these)
+  }
   return 0;
 }
 

@@ -1,0 +1,82 @@
+"""The kernel that finds a row's pooled value by root search in registers (csrc/row_search.hpp): row
+lengths at the edges of its shapes, few and many rows, unaligned arrays, blocks from none to most of
+the row, ties at the block's ends.  Bar: that of test_gpu_parity (1e-5 + one float32 ulp)."""
+import numpy as np
+import pytest
+
+from tests.test_gpu_parity import P2, P43, close, dev, gpu, host, run_case  # noqa: F401  (gpu: the fixture)
+
+pytestmark = pytest.mark.gpu
+
+EDGES = [129, 255, 256, 509, 512, 513, 1021, 1024, 1533, 1537, 2045, 2048, 2049, 3069, 3072, 3073, 4093, 4096,
+         5117, 5120, 6141, 8189, 8192, 10237, 12285, 16381, 16384, 20477, 24573, 32765, 32766, 32768]
+
+
+@pytest.mark.parametrize("n", EDGES)
+def test_lengths_at_the_edges_of_the_shapes(gpu, oracle, n):
+    r = np.random.default_rng(n)
+    x = r.normal(size=(3, n)).astype(np.float32)
+    x[1] = np.round(x[1] * 4) / 4                                   # ties
+    t = r.normal(size=x.shape).astype(np.float32)
+    # (tiny lambda: rows without a block, or blocks of two; the oracle is quadratic in a p = 4/3 block)
+    for k in (65, n // 2, n - 1):
+        for p, lam in ((P2, 1e-5), (P2, 0.1), (P43, 1e-3)):
+            run_case(gpu, oracle, "mask", x, t, k, p, lam, check_perm=False)
+            run_case(gpu, oracle, "mag", x, t, k, p, lam, check_perm=False)
+    run_case(gpu, oracle, "mask", x, t, n // 3, P2, 20.0, check_perm=False)     # a block longer than the list
+    run_case(gpu, oracle, "mag", x, t, n // 3, P2, 20.0, check_perm=False)
+
+
+@pytest.mark.parametrize("rows,n", [(300, 1000), (300, 2000), (300, 3000), (300, 4096), (600, 8190), (1100, 8192),
+                                    (520, 12289), (270, 20001)])
+def test_many_rows(gpu, oracle, rows, n):
+    r = np.random.default_rng(rows + n)
+    x = r.normal(size=(rows, n)).astype(np.float32)
+    t = r.normal(size=x.shape).astype(np.float32)
+    for p in (P2, P43):
+        run_case(gpu, oracle, "mask", x, t, n // 10, p, 0.02, check_perm=False)
+        run_case(gpu, oracle, "mag", x, t, n // 10, p, 0.02, check_perm=False)
+
+
+@pytest.mark.parametrize("n", [700, 2500, 9001])
+def test_operators_built_on_the_mask_and_the_loss(gpu, oracle, n):
+    r = np.random.default_rng(n)
+    x = r.normal(size=(5, n)).astype(np.float32)
+    t = r.normal(size=x.shape).astype(np.float32)
+    hot = np.zeros_like(x)
+    hot[np.arange(5), r.integers(0, n, size=5)] = 1.0
+    for p, lam in ((P2, 0.3), (P43, 0.01)):
+        for k in (100, n // 3):
+            for name in ("topk_signed_mask", "topk_masked_value"):
+                ref = getattr(oracle, name)(x, k, p, lam, tangent=t)
+                o, j = (host(a) for a in getattr(gpu, name + "_jvp")(dev(x), dev(t), k, p, lam))
+                close(o, ref["out"], name)
+                close(j, ref["jvp"], name + " jvp")
+            ref_loss, ref_grad = oracle.fenchel_young_loss(x, hot, k, p, lam)
+            loss, grad = (host(a) for a in gpu.topk_mask_loss(dev(x), dev(hot), k, p, lam))
+            close(grad, ref_grad, "grad")
+            # (float32 rounding of the stored value, and a small absolute term)
+            assert (np.abs(loss - ref_loss) <= 2e-6 + 1.2e-7 * np.abs(ref_loss)).all()
+
+
+@pytest.mark.parametrize("n", [1000, 4097, 9000])
+def test_unaligned_arrays_and_special_values(gpu, oracle, n):
+    import torch
+    r = np.random.default_rng(n)
+    x = r.normal(size=(4, n)).astype(np.float32)
+    x[1] = x[1] * (r.random(n) < 0.05)                             # mostly zeros: s_{k+1} = 0
+    x[2] = 2.5                                                     # constant
+    x[3] = np.round(x[3] * 2) * np.float32(1e-38)                  # denormals
+    t = r.normal(size=x.shape).astype(np.float32)
+    run_case(gpu, oracle, "mask", x, t, n // 4, P2, 0.5, check_perm=False)
+    run_case(gpu, oracle, "mag", x, t, n // 4, P2, 0.1, check_perm=False)
+    run_case(gpu, oracle, "mag", x[:2], t[:2], n // 4, P43, 0.1, check_perm=False)
+    ref = oracle.topk_mask(x, n // 4, P2, 0.5, tangent=t)
+    for off in ((1, 1, 1, 1), (0, 1, 2, 3)):                       # offsets of the four arrays, in elements
+        bufs = [torch.empty(4 * n + 8, device="cuda") for _ in range(4)]
+        v = [b[o:o + 4 * n].view(4, n) for b, o in zip(bufs, off)]
+        v[0].copy_(torch.from_numpy(x))
+        v[1].copy_(torch.from_numpy(t))
+        gpu.topk_mask_jvp(v[0], v[1], n // 4, P2, 0.5, out=v[2], jvp_out=v[3])
+        close(host(v[2]), ref["out"], "unaligned fwd")
+        close(host(v[3]), ref["jvp"], "unaligned jvp")
