@@ -64,25 +64,6 @@ __device__ __forceinline__ bool mask_test(const Mask128& m, int j) {
   return j < 64 ? ((m.lo >> j) & 1ull) != 0 : ((m.hi >> (j - 64)) & 1ull) != 0;
 }
 
-// A prefix sum over 131072 values is five orders of magnitude larger than the sum over a small
-// block, which is the difference of two of them: in plain float64 that difference would carry the
-// rounding of the large numbers (1e-9 where the block's cubic needs 1e-13 to decide near-ties as
-// the direct summation does).  So the prefix sums are kept as unevaluated pairs h + l (h the
-// rounded sum, l its error), added with the error-free two-sum, and a block's sum is
-// (h_hi - h_lo) + (l_hi - l_lo).
-__device__ __forceinline__ DD dd_add(const DD& a, const DD& b) {
-  const double s = a.h + b.h;
-  const double bb = s - a.h;
-  double e = (a.h - (s - bb)) + (b.h - bb);
-  e += a.l + b.l;
-  const double h = s + e;
-  return DD{h, e - (h - s)};
-}
-__device__ __forceinline__ DD dd_add(const DD& a, double b) { return dd_add(a, DD{b, 0.0}); }
-__device__ __forceinline__ double dd_diff(const DD& hi, const DD& lo) {
-  return (hi.h - lo.h) + (hi.l - lo.l);
-}
-
 struct ScanShared {
   DD d[4][kGW];
   double q[2][kGW];
@@ -160,10 +141,11 @@ __global__ __launch_bounds__(kGT) void general_long_kernel(
     uint32_t* keys_all, const uint32_t* __restrict__ idx_all, const float* __restrict__ x_all,
     const float* __restrict__ w_all, int64_t w_stride, const float* __restrict__ tangent_all,
     float* __restrict__ out_all, float* __restrict__ jvp_all, GeneralBuffers gb, int n, Reg R,
-    int max_rounds) {
+    int max_rounds, const uint32_t* __restrict__ todo) {
   constexpr bool CUBIC = (PC == kP43);
   __shared__ ScanShared sm;
   const int64_t row = blockIdx.x;
+  if (todo != nullptr && todo[row] == 0) return;   // solved already (general_search.hip)
   const int64_t base = row * int64_t(n);
   const int64_t qbase = row * int64_t(n + 1);
   const int t = threadIdx.x;
@@ -497,17 +479,18 @@ GeneralBuffers general_long_carve(void* ptr, int64_t rows, int64_t n, int pc) {
 }
 
 // The rows are sorted already: B.keys_a holds the sorted keys (overwritten with the sorted values),
-// B.idx_a the index payload (index * 2 + sign bit for the magnitude form).
+// B.idx_a the index payload (index * 2 + sign bit for the magnitude form).  todo (may be null): only
+// the rows whose entry is not zero.
 int launch_general_long(bool mag, int pc, const SortBuffers& B, const GeneralBuffers& gb,
                         const float* x, const float* w, int64_t w_stride, const float* tangent,
                         float* out, float* jvp, int64_t rows, int64_t n, const Reg& R,
-                        hipStream_t st) {
+                        hipStream_t st, const uint32_t* todo) {
   if (n <= 1024 || n > kGeneralLongMax || rows > 0x7fffffffLL) return -1;
   const int forced = routes().general_rounds;          // test control
   const int max_rounds = forced > 0 ? forced : (pc == kP43 ? int(n) + 1 : 32 + int(n) / 4);
 #define TOPK_GENERAL_LONG(M, P)                                                                   \
   hipLaunchKernelGGL((general_long_kernel<M, P>), dim3(unsigned(rows)), dim3(kGT), 0, st, B.keys_a, \
-                     B.idx_a, x, w, w_stride, tangent, out, jvp, gb, int(n), R, max_rounds)
+                     B.idx_a, x, w, w_stride, tangent, out, jvp, gb, int(n), R, max_rounds, todo)
   if (!mag && pc == kP2) TOPK_GENERAL_LONG(false, kP2);
   else if (!mag && pc == kP43) TOPK_GENERAL_LONG(false, kP43);
   else if (mag && pc == kP2) TOPK_GENERAL_LONG(true, kP2);

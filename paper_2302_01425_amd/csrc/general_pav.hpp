@@ -7,8 +7,28 @@
 
 #include "common.hpp"
 #include "pooling.hpp"
+#include "launch.hpp"
 
 namespace topk {
+
+// A prefix sum over 131072 values is five orders of magnitude larger than the sum over a small
+// block, which is the difference of two of them: in plain float64 that difference would carry the
+// rounding of the large numbers (1e-9 where the block's cubic needs 1e-13 to decide near-ties as
+// the direct summation does).  So the prefix sums are kept as unevaluated pairs h + l (h the
+// rounded sum, l its error), added with the error-free two-sum, and a block's sum is
+// (h_hi - h_lo) + (l_hi - l_lo).
+__device__ __forceinline__ DD dd_add(const DD& a, const DD& b) {
+  const double s = a.h + b.h;
+  const double bb = s - a.h;
+  double e = (a.h - (s - bb)) + (b.h - bb);
+  e += a.l + b.l;
+  const double h = s + e;
+  return DD{h, e - (h - s)};
+}
+__device__ __forceinline__ DD dd_add(const DD& a, double b) { return dd_add(a, DD{b, 0.0}); }
+__device__ __forceinline__ double dd_diff(const DD& hi, const DD& lo) {
+  return (hi.h - lo.h) + (hi.l - lo.l);
+}
 
 // the increasing cubic of a block: sum_B (g - s_i)^3 + lambda^3 W [g] (magnitude: times g).
 // shift: the sums are those of s_i - shift and g stands for gamma - shift (matters for the

@@ -1,0 +1,619 @@
+// General weights (Sec. 4), identity phi, p = 2, forward only, rows of 1025 .. kGeneralLongMax
+// elements, WITHOUT a sort of the row.
+//
+// For p = 2 the pooled values are the slopes of the least concave majorant of the cumulative sums
+// C(i) = sum_{j < i} (s_j - lambda w_j) of the sorted row (App. "PAV algorithm" solves exactly this).
+// Only its vertices matter, and a row whose weights differ by more than its neighbouring values
+// (relaxed ranks of many scores) has few: all but the tails of the row is one block.  Which parts of
+// the row can hold a vertex follows from a histogram of its values alone:
+//
+//   1. one pass over the row: count and EXACT sum of every bin of the 12 leading key bits (values of
+//      a bin share sign, exponent and three bits of mantissa, so the low 20 bits of mantissa are added
+//      as integers; count and sum travel in one 64-bit LDS atomic)
+//   2. C at the bins' ends from the exact sums and the prefix sums of w (a launch before this one);
+//      majorant of these points by the merging rounds of general_w.hip, on at most 2816 points
+//   3. between the ends of a bin of m values that span less than d, C exceeds its chord by at most
+//      m d / 4: the sorted values sum to a concave curve with slopes in a range of d, and -lambda w
+//      sums to a convex one (w is non-increasing).  A bin whose two ends lie further than that
+//      below the majorant holds no vertex: it stays one item.  The other bins' values are
+//      collected (second pass), sorted inside their bin, and become one item each
+//   4. majorant of the items by the same rounds: the partition of the whole row
+//   5. third pass: every element finds its bin, if need be its place in the bin, and its pooled value.
+//      Equal values have equal outputs in whatever blocks they are, so no index is needed.
+//
+// One workgroup of 1024 threads per row; the second and third pass read the row from the L2.  Rows
+// with more than 2816 items (tiny lambda: most elements are blocks of their own), more than 256
+// rounds, values that are not finite, or weights that are not non-increasing are left to the kernel
+// that sorts the row (todo[row] = 1).
+//
+// Bound by: the passes over the row on the compute units that have a row (64 rows: a quarter of
+// them) and the latency of the rounds.
+#include <hip/hip_runtime.h>
+
+#include "common.hpp"
+#include "pooling.hpp"
+#include "launch.hpp"
+#include "general_pav.hpp"
+
+namespace topk {
+namespace {
+
+constexpr int kNT = 1024;                       // threads of a row's workgroup
+constexpr int kNW = kNT / kWave;
+constexpr int kItems = 2816;                    // items of a row (44 bytes of LDS each)
+constexpr int kMaxRounds = 256;
+constexpr int kWTile = 2048;                    // positions of a tile of weights
+constexpr int kWThreads = 256;
+constexpr int kWPer = kWTile / kWThreads;
+constexpr int kWTiles = int(kGeneralLongMax / kWTile);
+constexpr int kCopies = 3;                      // copies of the histogram, lane % 3 chooses one
+static_assert(kWTiles <= kWave, "a wavefront scans the tiles' totals");
+static_assert(kItems <= 3 * kNT && kItems < 0xffff, "three items per thread, 16-bit item numbers");
+
+struct SearchShared {
+  // per bin: count << 40 | sum of the low 20 mantissa bits, bit 63 = the bin's values become items;
+  // then the lookup: high word = first item | m << 16 (m = 0: one item), low word = cursor
+  unsigned long long bins[kSelBins];
+  union {
+    unsigned long long extra[kCopies - 1][kSelBins];
+    struct {
+      DD p1[kItems + 1];                        // prefix sums of s at the items' starts
+      DD pw[kItems + 1];                        // of w
+    } i;
+  } u;
+  uint32_t pos[kItems + 1];                     // first sorted position of an item
+  uint32_t key[kItems];                         // its key (bins: bin << 20; first majorant: the bin)
+  uint16_t list[2][kItems + 2];                 // first items of the blocks, ping-pong
+  DD toff[kWTiles + 1];                         // prefix sums of w at the tiles' starts
+  DD wave_dd[kNW];
+  unsigned long long wave_u[kNW];
+  int nb, bad;
+};
+static_assert(sizeof(SearchShared) <= 160 * 1024, "LDS of a compute unit");
+
+__device__ __forceinline__ DD shfl_up_dd(const DD& v, int off) {
+  return DD{__shfl_up(v.h, off, kWave), __shfl_up(v.l, off, kWave)};
+}
+__device__ __forceinline__ DD wave_inclusive_dd(DD v, int lane) {
+#pragma unroll
+  for (int off = 1; off < kWave; off <<= 1) {
+    const DD o = shfl_up_dd(v, off);
+    if (lane >= off) v = dd_add(o, v);
+  }
+  return v;
+}
+// exclusive scans of one value per thread over NW wavefronts; two barriers each
+template <int NW>
+__device__ __forceinline__ DD scan_dd(const DD& v, DD* wave_tot, DD* total) {
+  const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+  const DD inc = wave_inclusive_dd(v, lane);
+  DD prev = shfl_up_dd(inc, 1);
+  if (lane == 0) prev = DD{0.0, 0.0};
+  if (lane == kWave - 1) wave_tot[w] = inc;
+  __syncthreads();
+  DD before{0.0, 0.0}, all{0.0, 0.0};
+#pragma unroll
+  for (int q = 0; q < NW; ++q) {
+    if (q == w) before = all;
+    all = dd_add(all, wave_tot[q]);
+  }
+  __syncthreads();
+  *total = all;
+  return dd_add(before, prev);
+}
+__device__ __forceinline__ unsigned long long scan_u64(unsigned long long v, unsigned long long* wave_tot,
+                                                       unsigned long long* total) {
+  const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+  unsigned long long inc = v;
+#pragma unroll
+  for (int off = 1; off < kWave; off <<= 1) {
+    const unsigned long long o = __shfl_up(inc, off, kWave);
+    if (lane >= off) inc += o;
+  }
+  if (lane == kWave - 1) wave_tot[w] = inc;
+  __syncthreads();
+  unsigned long long before = 0, all = 0;
+#pragma unroll
+  for (int q = 0; q < kNW; ++q) {
+    const unsigned long long c = wave_tot[q];
+    if (q < w) before += c;
+    all += c;
+  }
+  __syncthreads();
+  *total = all;
+  return before + inc - v;
+}
+
+// Prefix sums of the weights inside tiles of kWTile positions (local[r][i], i = 0 .. n), the tiles'
+// totals, and whether a tile holds weights that increase or are not finite.  grid (tiles, weight rows)
+__global__ __launch_bounds__(kWThreads) void weight_prefix_kernel(const float* __restrict__ w_all, int n,
+                                                                  DD* __restrict__ local,
+                                                                  DD* __restrict__ total,
+                                                                  uint32_t* __restrict__ bad) {
+  __shared__ DD wave_dd[kWThreads / kWave];
+  const float* w = w_all + int64_t(blockIdx.y) * n;
+  DD* loc = local + int64_t(blockIdx.y) * (n + 1);
+  const int e0 = blockIdx.x * kWTile + threadIdx.x * kWPer;
+  float v[kWPer];
+  bool odd = false;
+  float before = e0 > 0 && e0 < n ? w[e0 - 1] : 3.4028235e38f;
+  DD t{0.0, 0.0};
+#pragma unroll
+  for (int i = 0; i < kWPer; ++i) {
+    v[i] = e0 + i < n ? w[e0 + i] : 0.0f;
+    if (e0 + i < n) {
+      odd = odd || !(v[i] <= before) || !(fabsf(v[i]) <= 3.4028235e38f);
+      before = v[i];
+    }
+    t = dd_add(t, double(v[i]));
+  }
+  DD all;
+  DD run = scan_dd<kWThreads / kWave>(t, wave_dd, &all);
+#pragma unroll
+  for (int i = 0; i < kWPer; ++i) {
+    if (e0 + i <= n) loc[e0 + i] = run;
+    run = dd_add(run, double(v[i]));
+  }
+  const int any = __syncthreads_or(odd);
+  if (threadIdx.x == 0) {
+    total[blockIdx.y * kWTiles + blockIdx.x] = all;
+    bad[blockIdx.y * kWTiles + blockIdx.x] = any != 0;
+  }
+}
+
+// every element of the row, four 16-byte loads per thread in flight where rows are aligned
+template <bool VEC, class F>
+__device__ __forceinline__ void each_value(const float* __restrict__ x, int n, F f) {
+  if constexpr (VEC) {
+    for (int e0 = 4 * int(threadIdx.x); e0 < n; e0 += 16 * kNT) {
+      float4 q[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        q[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (e0 + i * 4 * kNT < n) q[i] = *reinterpret_cast<const float4*>(x + e0 + i * 4 * kNT);
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        if (e0 + i * 4 * kNT < n) {
+          f(q[i].x);
+          f(q[i].y);
+          f(q[i].z);
+          f(q[i].w);
+        }
+      }
+    }
+  } else {
+    for (int e0 = int(threadIdx.x); e0 < n; e0 += 8 * kNT) {
+      float q[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) q[i] = e0 + i * kNT < n ? x[e0 + i * kNT] : 0.0f;
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        if (e0 + i * kNT < n) f(q[i]);
+    }
+  }
+}
+
+// pooled value of the items [lo, hi) (no fused multiply-add: exact ties stay ties)
+__device__ __forceinline__ double item_gamma(const SearchShared& sm, int lo, int hi, double lambda) {
+  const double S = dd_diff(sm.u.i.p1[hi], sm.u.i.p1[lo]), W = dd_diff(sm.u.i.pw[hi], sm.u.i.pw[lo]);
+  return __ddiv_rn(__dsub_rn(S, __dmul_rn(lambda, W)), double(sm.pos[hi] - sm.pos[lo]));
+}
+
+// Majorant of the items 0 .. T-1: rounds that remove every boundary between two blocks that violate
+// (gamma_left < gamma_right), all at once, on a dense list of the blocks' first items.  Up to 64
+// blocks one wavefront goes on without barriers.  Returns the number of blocks (their first items and
+// T in sm.list[*which]), or -1 when kMaxRounds do not suffice.
+__device__ int majorant(SearchShared& sm, int T, double lambda, int* which) {
+  const int tid = threadIdx.x, lane = tid & (kWave - 1);
+  for (int i = tid; i <= T; i += kNT) sm.list[0][i] = uint16_t(i);
+  __syncthreads();
+  int cur = 0, nb = T, rounds = 0;
+  while (nb > kWave) {
+    if (++rounds > kMaxRounds) return -1;
+    const uint16_t* L = sm.list[cur];
+    uint16_t* M = sm.list[cur ^ 1];
+    const int per = (nb + kNT - 1) / kNT, i0 = tid * per;       // per <= 3
+    uint32_t first[3];
+    int kept = 0;
+    if (i0 < nb) {
+      int lo = L[i0];
+      double g = i0 > 0 ? item_gamma(sm, L[i0 - 1], lo, lambda) : 0.0;
+#pragma unroll
+      for (int r = 0; r < 3; ++r) {
+        if (r < per && i0 + r < nb) {
+          const int hi = L[i0 + r + 1];
+          const double gn = item_gamma(sm, lo, hi, lambda);
+          const bool gone = i0 + r > 0 && g < gn;
+          first[r] = gone ? 0xffffffffu : uint32_t(lo);
+          kept += !gone;
+          g = gn;
+          lo = hi;
+        } else {
+          first[r] = 0xffffffffu;
+        }
+      }
+    }
+    unsigned long long total;
+    int at = int(scan_u64(uint64_t(kept), sm.wave_u, &total));
+    if (i0 < nb) {
+#pragma unroll
+      for (int r = 0; r < 3; ++r)
+        if (first[r] != 0xffffffffu) M[at++] = uint16_t(first[r]);
+    }
+    if (tid == 0) M[total] = uint16_t(T);
+    __syncthreads();
+    cur ^= 1;
+    *which = cur;
+    if (int(total) == nb) return nb;
+    nb = int(total);
+  }
+  *which = cur;
+  if (tid < kWave) {
+    volatile uint16_t* L = sm.list[cur];
+    for (;;) {                                   // every round but the last one removes a block
+      const int lo = lane < nb ? L[lane] : T, hi = lane < nb ? L[lane + 1] : T;
+      const double g = lane < nb ? item_gamma(sm, lo, hi, lambda) : 0.0;
+      const double gp = __shfl_up(g, 1, kWave);
+      const bool keep = lane < nb && !(lane > 0 && gp < g);
+      const unsigned long long km = __ballot(keep);
+      const int left = __popcll(km);
+      if (left == nb) break;
+      __builtin_amdgcn_wave_barrier();
+      if (keep) L[__popcll(km & ((1ull << lane) - 1ull))] = uint16_t(lo);
+      if (lane == 0) L[left] = uint16_t(T);
+      nb = left;
+      __builtin_amdgcn_wave_barrier();
+    }
+    if (lane == 0) sm.nb = nb;
+  }
+  __syncthreads();
+  nb = sm.nb;
+  return nb;
+}
+
+// block of item i: the last list entry that is <= i
+__device__ __forceinline__ int block_of(const uint16_t* L, int nb, int i) {
+  int a = 0, b = nb;                             // L[a] <= i < L[b]
+  while (b - a > 1) {
+    const int m = (a + b) >> 1;
+    if (int(L[m]) <= i) a = m;
+    else b = m;
+  }
+  return a;
+}
+
+template <bool VEC>
+__global__ __launch_bounds__(kNT) void general_search_kernel(
+    const float* __restrict__ x_all, const float* __restrict__ w_all, int64_t w_stride,
+    const DD* __restrict__ wlocal, const DD* __restrict__ wtotal, const uint32_t* __restrict__ wbad,
+    float* __restrict__ out_all, uint32_t* __restrict__ todo, int n, double lambda, double inv_lambda) {
+  __shared__ SearchShared sm;
+  const int64_t row = blockIdx.x, wrow = w_stride != 0 ? row : 0;
+  const float* x = x_all + row * n;
+  float* out = out_all + row * n;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1);
+  const DD* wl = wlocal + wrow * (n + 1);
+  const int tiles = (n + kWTile - 1) / kWTile;
+
+  // ---- 1. histogram with sums; the tiles' offsets of the prefix sums of w ---------------------------
+  for (int i = tid; i < kSelBins; i += kNT) {
+    sm.bins[i] = 0;
+#pragma unroll
+    for (int c = 0; c < kCopies - 1; ++c) sm.u.extra[c][i] = 0;
+  }
+  if (tid < kWave) {
+    DD t{0.0, 0.0};
+    bool bad = false;
+    if (lane < tiles) {
+      t = wtotal[wrow * kWTiles + lane];
+      bad = wbad[wrow * kWTiles + lane] != 0;
+    }
+    t = wave_inclusive_dd(t, lane);
+    if (lane < tiles) sm.toff[lane + 1] = t;
+    if (lane == 0) {
+      sm.toff[0] = DD{0.0, 0.0};
+      sm.bad = 0;
+    }
+    if (__any(bad) && lane == 0) sm.bad = 1;
+  }
+  __syncthreads();
+  {
+    const int copy = lane % kCopies;
+    unsigned long long* hist = copy == 0 ? sm.bins : sm.u.extra[copy - 1];
+    each_value<VEC>(x, n, [&](float v) {
+      atomicAdd(&hist[desc_key(v) >> (32 - kSelBits)],
+                (1ull << 40) | (unsigned long long)(__float_as_uint(v) & 0xfffffu));
+    });
+  }
+  __syncthreads();
+
+  // ---- 2. my four bins: counts, exact sums, positions; majorant of the bins' ends -------------------
+  constexpr int kPer = kSelBins / kNT;
+  uint32_t cnt[kPer];
+  double sum[kPer];
+  uint32_t mine = 0, used = 0;
+  DD mysum{0.0, 0.0};
+  bool bad = sm.bad != 0;
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) {
+    const uint32_t b = uint32_t(tid * kPer + q);
+    unsigned long long h = sm.bins[b];
+#pragma unroll
+    for (int c = 0; c < kCopies - 1; ++c) h += sm.u.extra[c][b];
+    cnt[q] = uint32_t(h >> 40);
+    const uint32_t top = b >= uint32_t(kSelBins) / 2 ? b : (~b & 0x7ffu);     // leading bits of the float
+    const uint32_t e = (top >> 3) & 0xffu;
+    const double ulp = __longlong_as_double((long long)((e ? e : 1u) + 1023u - 150u) << 52);
+    const unsigned long long m = (unsigned long long)cnt[q] * (((top & 7u) << 20) | (e ? 1u << 23 : 0u)) +
+                                 (h & 0xffffffffffull);
+    sum[q] = double(m) * ((top & 0x800u) ? -ulp : ulp);
+    if (cnt[q] != 0 && e == 255u) bad = true;
+    mine += cnt[q];
+    used += cnt[q] != 0;
+    mysum = dd_add(mysum, sum[q]);
+  }
+  unsigned long long tot64;
+  const unsigned long long ex = scan_u64((unsigned long long)used << 32 | mine, sm.wave_u, &tot64);
+  const uint32_t my_pos = uint32_t(ex);
+  const int nbins = int(tot64 >> 32);
+  DD total_s;
+  const DD my_s = scan_dd<kNW>(mysum, sm.wave_dd, &total_s);
+  if (__syncthreads_or(bad || nbins > kItems)) {
+    if (tid == 0) todo[row] = 1;
+    return;
+  }
+  auto w_prefix = [&](uint32_t p) -> DD {
+    return p >= uint32_t(n) ? sm.toff[tiles] : dd_add(sm.toff[p / kWTile], wl[p]);
+  };
+  {
+    uint32_t p = my_pos;
+    int it = int(ex >> 32);
+    DD s = my_s;
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      if (cnt[q] != 0) {
+        sm.pos[it] = p;
+        sm.key[it] = uint32_t(tid * kPer + q);
+        sm.u.i.p1[it] = s;
+        sm.u.i.pw[it] = w_prefix(p);
+        ++it;
+        p += cnt[q];
+        s = dd_add(s, sum[q]);
+      }
+      sm.bins[tid * kPer + q] = 0;
+    }
+    if (tid == 0) {
+      sm.pos[nbins] = uint32_t(n);
+      sm.u.i.p1[nbins] = total_s;
+      sm.u.i.pw[nbins] = sm.toff[tiles];
+    }
+  }
+  __syncthreads();
+  int which = 0;
+  int nb = majorant(sm, nbins, lambda, &which);
+  if (nb < 0) {
+    if (tid == 0) todo[row] = 1;
+    return;
+  }
+
+  // ---- 3. bins that may hold a vertex inside --------------------------------------------------------
+  {
+    const float* w = w_all + wrow * w_stride;
+    const double wmax = fmax(fabs(double(w[0])), fabs(double(w[n - 1])));
+    const double smax = fmax(fabs(double(key_to_float(sm.key[0] << 20))),
+                             fabs(double(key_to_float((sm.key[nbins - 1] << 20) | 0xfffffu))));
+    // rounding of the distances below, whose terms are at most this large: 2^-53 of it, some tens of
+    // times; 1e-13 leaves a factor of ten
+    const double eps = 1e-13 * double(n) * (smax + lambda * wmax);
+    const uint16_t* L = sm.list[which];
+    for (int i = tid; i < nbins; i += kNT) {
+      const uint32_t m = sm.pos[i + 1] - sm.pos[i];
+      if (m < 2) continue;
+      const int j = block_of(L, nb, i), a = L[j];
+      const double g = item_gamma(sm, a, L[j + 1], lambda);
+      auto below = [&](int q) -> double {      // of C under the majorant, at the start of item q
+        const double c = dd_diff(sm.u.i.p1[q], sm.u.i.p1[a]) - lambda * dd_diff(sm.u.i.pw[q], sm.u.i.pw[a]);
+        return g * double(sm.pos[q] - sm.pos[a]) - c;
+      };
+      const double gap = fmin(below(i), below(i + 1));
+      const uint32_t b = sm.key[i];
+      const uint32_t e = ((b >= uint32_t(kSelBins) / 2 ? b : ~b) >> 3) & 0xffu;
+      const double width = __longlong_as_double((long long)((e ? e : 1u) + 1023u - 130u) << 52);
+      if (!(gap > 0.25 * double(m) * width + eps)) sm.bins[b] = 1ull << 63;
+    }
+  }
+  __syncthreads();
+
+  // ---- 4. items: bins without a vertex inside, and the values of the others ------------------------------
+  bool open[kPer];
+  uint32_t ni = 0, nc = 0;
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) {
+    open[q] = sm.bins[tid * kPer + q] != 0;
+    ni += open[q] ? cnt[q] : (cnt[q] != 0 ? 1u : 0u);
+    nc += open[q] ? cnt[q] : 0u;
+  }
+  const unsigned long long ex2 = scan_u64((unsigned long long)nc << 32 | ni, sm.wave_u, &tot64);
+  const uint32_t cands = uint32_t(tot64 >> 32);
+  const int T = cands > uint32_t(kItems) ? kItems + 1 : int(uint32_t(tot64));
+  if (T > kItems) {
+    if (tid == 0) todo[row] = 1;
+    return;
+  }
+  uint32_t* lookup = reinterpret_cast<uint32_t*>(sm.bins);      // [2 b] cursor, [2 b + 1] the rest
+  {
+    uint32_t it = uint32_t(ex2);
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      const uint32_t b = uint32_t(tid * kPer + q);
+      if (cnt[q] == 0) continue;
+      lookup[2 * b] = it;
+      lookup[2 * b + 1] = it | (open[q] ? cnt[q] << 16 : 0u);
+      if (open[q]) {
+        it += cnt[q];
+      } else {
+        sm.key[it] = b << 20;
+        sm.pos[it] = cnt[q];
+        sm.u.i.p1[it] = DD{sum[q], 0.0};
+        ++it;
+      }
+    }
+  }
+  __syncthreads();
+  if (cands != 0) {
+    each_value<VEC>(x, n, [&](float v) {
+      const uint32_t key = desc_key(v), b = key >> 20;
+      if (lookup[2 * b + 1] >> 16) sm.key[atomicAdd(&lookup[2 * b], 1u)] = key;
+    });
+    __syncthreads();
+    // order inside a bin by counting (a few dozen values: the row's weights separate the rest)
+    uint32_t k[3], dst[3];
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+      const uint32_t t = uint32_t(tid + r * kNT);
+      dst[r] = 0xffffffffu;
+      if (t < uint32_t(T)) {
+        k[r] = sm.key[t];
+        const uint32_t l = lookup[2 * (k[r] >> 20) + 1], m = l >> 16, at = l & 0xffffu;
+        if (m != 0) {
+          uint32_t less = 0;
+          for (uint32_t j = at; j < at + m; ++j) {
+            const uint32_t o = sm.key[j];
+            less += (o < k[r] || (o == k[r] && j < t)) ? 1u : 0u;
+          }
+          dst[r] = at + less;
+        }
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+      if (dst[r] != 0xffffffffu) {
+        sm.key[dst[r]] = k[r];
+        sm.pos[dst[r]] = 1;
+        sm.u.i.p1[dst[r]] = DD{double(key_to_float(k[r])), 0.0};
+      }
+    }
+    __syncthreads();
+  }
+  {
+    // counts and sums of the items -> positions and prefix sums
+    uint32_t c[3], cs = 0;
+    DD v[3], vs{0.0, 0.0};
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+      const int t = 3 * tid + r;
+      c[r] = t < T ? sm.pos[t] : 0u;
+      v[r] = t < T ? sm.u.i.p1[t] : DD{0.0, 0.0};
+      cs += c[r];
+      vs = dd_add(vs, v[r]);
+    }
+    uint32_t p = uint32_t(scan_u64(cs, sm.wave_u, &tot64));
+    DD s = scan_dd<kNW>(vs, sm.wave_dd, &total_s);
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+      const int t = 3 * tid + r;
+      if (t < T) {
+        sm.pos[t] = p;
+        sm.u.i.p1[t] = s;
+        sm.u.i.pw[t] = w_prefix(p);
+      }
+      p += c[r];
+      s = dd_add(s, v[r]);
+    }
+    if (tid == 0) {
+      sm.pos[T] = uint32_t(n);
+      sm.u.i.p1[T] = total_s;
+      sm.u.i.pw[T] = sm.toff[tiles];
+    }
+  }
+  __syncthreads();
+  nb = majorant(sm, T, lambda, &which);
+  if (nb < 0) {
+    if (tid == 0) todo[row] = 1;
+    return;
+  }
+  // pooled value of every item
+  double* gi = reinterpret_cast<double*>(sm.u.i.p1);
+  {
+    const uint16_t* L = sm.list[which];
+    double g[3];
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+      const int t = 3 * tid + r;
+      g[r] = 0.0;
+      if (t < T) {
+        const int j = block_of(L, nb, t);
+        g[r] = item_gamma(sm, L[j], L[j + 1], lambda);
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < 3; ++r)
+      if (3 * tid + r < T) gi[3 * tid + r] = g[r];
+  }
+  __syncthreads();
+
+  // ---- 5. outputs y = (s - gamma) / lambda --------------------------------------------------------------
+  auto value = [&](float v) -> float {
+    const uint32_t key = desc_key(v), l = lookup[2 * (key >> 20) + 1];
+    uint32_t at = l & 0xffffu;
+    if (l >> 16) {
+      uint32_t end = at + (l >> 16);             // first item of the bin whose key is not smaller
+      while (at < end) {
+        const uint32_t m = (at + end) >> 1;
+        if (sm.key[m] < key) at = m + 1;
+        else end = m;
+      }
+    }
+    return float((double(v + 0.0f) - gi[at]) * inv_lambda);
+  };
+  if constexpr (VEC) {
+    for (int e0 = 4 * tid; e0 < n; e0 += 16 * kNT) {
+      float4 q[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        q[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (e0 + i * 4 * kNT < n) q[i] = *reinterpret_cast<const float4*>(x + e0 + i * 4 * kNT);
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (e0 + i * 4 * kNT < n)
+          *reinterpret_cast<float4*>(out + e0 + i * 4 * kNT) =
+              make_float4(value(q[i].x), value(q[i].y), value(q[i].z), value(q[i].w));
+    }
+  } else {
+    for (int e = tid; e < n; e += kNT) out[e] = value(x[e]);
+  }
+  if (tid == 0) todo[row] = 0;
+}
+
+}  // namespace
+
+int launch_general_search(const GeneralBuffers& gb, const SortBuffers& B, const float* x,
+                          const float* w, int64_t w_stride, float* out, int64_t rows, int64_t n,
+                          const Reg& R, hipStream_t st, const uint32_t** todo) {
+  if (n <= 1024 || n > kGeneralLongMax || rows > 0x7fffffffLL) return -1;
+  const int64_t wrows = w_stride != 0 ? rows : 1;
+  if (wrows > 65535) return -1;
+  // scratch: the prefix sums of w where the kernel of the rounds keeps its own, the tiles' totals and
+  // marks at the front of arrays that only that kernel uses afterwards; the rows' marks outlive it
+  DD* total = gb.p1;
+  uint32_t* bad = gb.hi_of;
+  const int tiles = int((n + kWTile - 1) / kWTile);
+  // (n a multiple of the tile: one more tile would hold position n alone, which is never looked up)
+  hipLaunchKernelGGL(weight_prefix_kernel, dim3(unsigned(tiles), unsigned(wrows)), dim3(kWThreads), 0, st,
+                     w, int(n), gb.pw, total, bad);
+  const bool vec = n % 4 == 0 && ((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(out)) & 15) == 0;
+  if (vec)
+    hipLaunchKernelGGL(general_search_kernel<true>, dim3(unsigned(rows)), dim3(kNT), 0, st, x, w, w_stride,
+                       gb.pw, total, bad, out, B.dtot, int(n), R.lambda, R.inv_lambda);
+  else
+    hipLaunchKernelGGL(general_search_kernel<false>, dim3(unsigned(rows)), dim3(kNT), 0, st, x, w, w_stride,
+                       gb.pw, total, bad, out, B.dtot, int(n), R.lambda, R.inv_lambda);
+  *todo = B.dtot;
+  return 0;
+}
+
+}  // namespace topk

@@ -473,6 +473,32 @@ __global__ __launch_bounds__(kFinishThreads) void finish_kernel(uint32_t* keys_a
   if (threadIdx.x == 0) info[row] = ri;
 }
 
+// Complete sort of the rows with todo[row] != 0, one workgroup per row: (key, index) into the "a"
+// arrays.  For the few rows that general_search.hip hands over; the launch costs 3 us when there
+// are none, twelve launches of the multi-workgroup sort would cost 30.
+__global__ __launch_bounds__(kFinishThreads) void row_sort_kernel(const float* __restrict__ x_all,
+                                                     uint32_t* keys_a, uint32_t* idx_a,
+                                                     uint32_t* keys_b, uint32_t* idx_b,
+                                                     const uint32_t* __restrict__ todo, int n) {
+  __shared__ MedShared<kFinishThreads> sm;
+  if (todo[blockIdx.x] == 0) return;
+  const int64_t base = int64_t(blockIdx.x) * n;
+  uint32_t* ka = keys_a + base;
+  uint32_t* ia = idx_a + base;
+  for (int e = threadIdx.x; e < n; e += kFinishThreads) {
+    ka[e] = desc_key(x_all[base + e]);
+    ia[e] = uint32_t(e);
+  }
+  __syncthreads();
+  const SortedList sorted = sort_candidates<kFinishThreads, 16>(ka, ia, keys_b + base, idx_b + base,
+                                                                uint32_t(n), 0u, 0xffffffffu, sm);
+  if (sorted.keys != ka) {
+    for (int e = threadIdx.x; e < n; e += kFinishThreads) {
+      ka[e] = sorted.keys[e];
+      ia[e] = sorted.idx[e];
+    }
+  }
+}
 
 template <bool MAG, int PC>
 void launch(const SortBuffers& B, const float* x, const float* tangent, float* out, float* jvp,
@@ -519,6 +545,14 @@ int launch_medium_rows_sparse(int pc, const SortBuffers& B, const float* x, int6
   if (pc == kP2) launch_sparse<kP2>(B, x, rows, int(n), int(k), R, sp, st);
   else if (pc == kP43) launch_sparse<kP43>(B, x, rows, int(n), int(k), R, sp, st);
   else return -1;
+  return 0;
+}
+
+int launch_row_sort(const SortBuffers& B, const float* x, int64_t rows, int64_t n,
+                    const uint32_t* todo, hipStream_t st) {
+  if (n > kMediumRowMax || rows > 0x7fffffffLL) return -1;
+  hipLaunchKernelGGL(row_sort_kernel, dim3(unsigned(rows)), dim3(kFinishThreads), 0, st, x, B.keys_a,
+                     B.idx_a, B.keys_b, B.idx_b, todo, int(n));
   return 0;
 }
 

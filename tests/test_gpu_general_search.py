@@ -1,0 +1,63 @@
+"""General weights, identity form, p = 2, forward: the kernel that does not sort the row
+(csrc/general_search.hip) against the oracle, and against the kernel that sorts it where that one takes
+over.  Bar: that of test_gpu_parity (1e-5 + one float32 ulp)."""
+import numpy as np
+import pytest
+
+from tests.test_gpu_parity import P2, close, dev, gpu, host  # noqa: F401  (gpu: the fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+def weight_rows(n):
+    i = np.arange(n)
+    return {"ranks": (n - i), "ones_k": (i < n // 7), "steps": np.floor((n - i) / 97.0), "constant": np.full(n, 2.5),
+            "inverse": 1.0 / (1.0 + i), "negative": -0.01 * i}
+
+
+# edges of the tiles of weights (2048), of the loops over the row, odd lengths
+@pytest.mark.parametrize("n", [1025, 2047, 2048, 2049, 4095, 5001, 8192, 16388, 40000, 65536, 131071, 131072])
+def test_lengths_weights_and_lambdas(gpu, oracle, n):
+    r = np.random.default_rng(n)
+    x = r.normal(size=(3, n)).astype(np.float32)
+    x[1] = np.round(x[1] * 8) / 8                                   # ties, both zeros
+    x[2] = (x[2] * np.exp(r.normal(size=n) * 4)).astype(np.float32)  # many bins
+    for name, w in weight_rows(n).items():
+        w = w.astype(np.float32)
+        for lam in (1e-6, 1e-3, 0.1, 3.0):
+            print(n, name, lam, flush=True)
+            ref = oracle.topk_general(x, w, P2, lam, "id")["out"]
+            close(host(gpu.topk_general_fwd(dev(x), dev(w), gpu.TOPK_PHI_IDENTITY, P2, lam)), ref, f"{name} {lam}")
+    ws = np.sort(r.normal(size=(3, n)).astype(np.float32))[:, ::-1].copy()      # a row of weights per row
+    ref = oracle.topk_general(x, ws, P2, 0.05, "id")["out"]
+    close(host(gpu.topk_general_fwd(dev(x), dev(ws), gpu.TOPK_PHI_IDENTITY, P2, 0.05)), ref, "weights per row")
+
+
+def test_values_at_the_ends_of_the_type(gpu, oracle):
+    n = 3001
+    r = np.random.default_rng(5)
+    x = np.stack([r.normal(size=n) * 1e-41, r.normal(size=n) * 1e10, np.full(n, 0.7), np.where(np.arange(n) % 2, 0.0, -0.0),
+                  1.0 + 1e-6 * r.random(size=n), np.r_[r.normal(size=n - 1), 1e9]]).astype(np.float32)
+    w = np.arange(n, 0, -1, dtype=np.float32)
+    for lam in (1e-4, 1.0):
+        ref = oracle.topk_general(x, w, P2, lam, "id")["out"]
+        close(host(gpu.topk_general_fwd(dev(x), dev(w), gpu.TOPK_PHI_IDENTITY, P2, lam)), ref, f"lambda {lam}")
+
+
+def test_rows_and_weights_left_to_the_kernel_that_sorts(gpu):
+    n = 6000
+    r = np.random.default_rng(6)
+    x = r.normal(size=(6, n)).astype(np.float32)
+    x[1, 17] = np.inf
+    x[2, 5] = np.nan
+    x[3] = np.float32(1e4) * np.exp(r.normal(size=n) * 20).astype(np.float32)
+    w = np.arange(n, 0, -1, dtype=np.float32)
+    up = w[::-1].copy()                                             # increasing: everything is one block
+    for weights in (w, up):
+        for lam in (1e-7, 1e-3, 1.0):
+            got = host(gpu.topk_general_fwd(dev(x), dev(weights), gpu.TOPK_PHI_IDENTITY, P2, lam))
+            ref, _ = gpu.topk_general_jvp(dev(x), dev(weights), dev(np.zeros_like(x)), gpu.TOPK_PHI_IDENTITY, P2, lam)
+            ref = host(ref)
+            assert np.array_equal(np.isfinite(got), np.isfinite(ref))
+            ok = np.isfinite(ref)
+            assert (np.abs(got[ok] - ref[ok]) <= 1e-5 + 1.2e-7 * np.abs(ref[ok])).all()
