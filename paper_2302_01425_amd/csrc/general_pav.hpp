@@ -136,11 +136,10 @@ __device__ __forceinline__ bool blocks_violate(const Blk& p, double gp, const Bl
 // coordinates (read only when want_jvp).  On return, for every block start lo: st_g[lo] = pooled
 // value, DG[lo] = d gamma (Prop. 7), st_lo[lo] = head_mark, and no other entry of st_lo[0, n) has
 // that value (stack slots hold starts, which are smaller).  DG may be st_s1.
-template <bool MAG, bool CUBIC, typename IdxT>
-__device__ void stack_walk(int n, const float* ss, const float* lw, const float* ltau,
-                           bool want_jvp, double* st_s1, double* st_w, double* st_g,
-                           double* st_s2, double* st_s3, IdxT* st_lo, IdxT head_mark, double* DG,
-                           const Reg& R) {
+// The arrays are pointers or anything else that is indexed by position.
+template <bool MAG, bool CUBIC, typename IdxT, class FS, class FW, class DA, class IA>
+__device__ void stack_walk(int n, FS ss, FW lw, FS ltau, bool want_jvp, DA st_s1, DA st_w, DA st_g,
+                           DA st_s2, DA st_s3, IA st_lo, IdxT head_mark, DA DG, const Reg& R) {
   int top = 0;                           // blocks in LDS below the register-held top
   bool have = false;
   int tlo = 0;

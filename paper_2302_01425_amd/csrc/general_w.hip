@@ -26,6 +26,11 @@
 // whenever the float32 inputs span fewer than ~2^19 in magnitude, so exact ties are seen as ties.
 // d gamma of every block (Prop. 7) comes from two more prefix sums (weights c_j and c_j tau_j);
 // the outputs are then written by all lanes, each position looking up its block's start.
+//
+// Bound by the latency of one wavefront per row: rows of 1024 elements take 39 KB of LDS, so each
+// SIMD has one wavefront, whose vector instructions (4900, 3000 of them the sort) issue for 37 % of
+// its time.  4096 x 1024, lambda = 0.1, JVP: 166 us with linear LDS arrays (32-way bank conflicts),
+// a first round through LDS and loads of E consecutive elements per lane; 103 us now.
 #include "common.hpp"
 #include "pooling.hpp"
 #include "launch.hpp"
@@ -41,17 +46,30 @@ constexpr int kMinRounds = 32;
 template <int GL, int E, bool CUBIC>
 struct GenCfg {
   static constexpr int NP = GL * E;                 // padded row length
-  static constexpr int NQ = NP + 1;                 // entries of a prefix array
+  // entries of a prefix array: 0 .. NP by Swizzled
+  static constexpr int NQ = NP + ((NP >> 5) & (E - 1)) + 1;
   static constexpr int RPW = kWave / GL;            // rows per wavefront
   static constexpr int IDXB = ilog2(NP) + 1;
   // float64 arrays per row: prefix S1, prefix W, gamma per block start (+ prefix S2, S3)
   static constexpr int ND = CUBIC ? 5 : 3;
-  // bytes per wavefront: the float64 arrays, the cached block ends (16 bits) and their round
-  // stamps (8 bits), and the float arrays ss (sorted values), lw (weights, later y), ltau
-  static constexpr int WaveBytes = RPW * (ND * NQ * 8 + (NP + 2) * 2 + NP + 3 * NP * 4);
-  // wavefronts per workgroup: rows of 1024 elements take 40 KB (p = 2), one wavefront each, so that
+  // bytes per wavefront: the float64 arrays, the starts on the stack of the sequential walk (16
+  // bits), and the float arrays ss (sorted values), lw (weights, later y), ltau
+  static constexpr int WaveBytes = RPW * (ND * NQ * 8 + (NP + 2) * 2 + 3 * NP * 4);
+  // wavefronts per workgroup: rows of 1024 elements take 39 KB (p = 2), one wavefront each, so that
   // four workgroups fit the 160 KB of a compute unit
   static constexpr int WPB = (4 * WaveBytes <= 60 * 1024) ? 4 : ((2 * WaveBytes <= 60 * 1024) ? 2 : 1);
+};
+
+// An LDS array indexed by position.  A lane's E consecutive positions start a multiple of E words
+// apart from the next lane's, so that the lanes of an instruction would all meet in one or a few of
+// the 64 banks (16 positions per lane: a 32-way conflict for float64); the low bits of an index are
+// exchanged with the bits that tell those lanes apart.
+template <class T, int E>
+struct Swizzled {
+  T* p;
+  __device__ __forceinline__ T& operator[](int i) const {
+    return p[i ^ ((i >> (sizeof(T) == 8 ? 5 : 6)) & (E - 1))];
+  }
 };
 
 // first block start in the lanes after this one / last block start in the lanes before it
@@ -88,7 +106,6 @@ __global__ __launch_bounds__((GenCfg<GL, E, PC == kP43>::WPB * kWave)) void gene
   static_assert(NP < 0xffff, "block ends are kept in 16 bits");
   __shared__ __attribute__((aligned(16))) double ldsd[C::WPB][C::ND][RPW * NQ];
   __shared__ uint16_t lds_hi[C::WPB][RPW * (NP + 2)];
-  __shared__ uint8_t lds_ver[C::WPB][RPW * NP];
   __shared__ __attribute__((aligned(16))) float ldsf[C::WPB][3][RPW * NP];
 
   const int lane = threadIdx.x & (kWave - 1);
@@ -101,31 +118,37 @@ __global__ __launch_bounds__((GenCfg<GL, E, PC == kP43>::WPB * kWave)) void gene
   const int64_t base = row * n;
   const int e0 = lr * E;
   // float64 arrays of the row.  P*: prefix sums over sorted positions, P[i] = sum of j < i.
-  double* P1 = &ldsd[wv][0][rg * NQ];    // of s; after the rounds: of c_j tau_j (Prop. 7)
-  double* PW = &ldsd[wv][1][rg * NQ];    // of w
-  double* G = &ldsd[wv][2][rg * NQ];     // pooled value by block start; at the very end d gamma
-  double* P2 = CUBIC ? &ldsd[wv][3][rg * NQ] : nullptr;   // of s^2; after the rounds: of c_j
-  double* P3 = CUBIC ? &ldsd[wv][4][rg * NQ] : nullptr;   // of s^3
-  uint16_t* hi_of = &lds_hi[wv][rg * (NP + 2)];  // end of the block that G[lo] was computed for
-  uint8_t* ver = &lds_ver[wv][rg * NP];          // round (mod 256) in which that last changed
-  float* ss = &ldsf[wv][0][rg * NP];                     // sorted values
-  float* lw = &ldsf[wv][1][rg * NP];                     // weights by sorted position; later y
-  float* ltau = &ldsf[wv][2][rg * NP];                   // tangent in sorted order (times sign)
-  float* lt = reinterpret_cast<float*>(G);               // tangent, original order; later dy
+  using D = Swizzled<double, E>;
+  using F = Swizzled<float, E>;
+  const D P1{&ldsd[wv][0][rg * NQ]};     // of s; after the rounds: of c_j tau_j (Prop. 7)
+  const D PW{&ldsd[wv][1][rg * NQ]};     // of w
+  const D G{&ldsd[wv][2][rg * NQ]};      // pooled value by block start; at the very end d gamma
+  const D P2{CUBIC ? &ldsd[wv][CUBIC ? 3 : 0][rg * NQ] : nullptr};   // of s^2; after the rounds: of c_j
+  const D P3{CUBIC ? &ldsd[wv][CUBIC ? 4 : 0][rg * NQ] : nullptr};   // of s^3
+  uint16_t* st_lo = &lds_hi[wv][rg * (NP + 2)];          // stack of the sequential walk
+  const F ss{&ldsf[wv][0][rg * NP]};                     // sorted values
+  const F lw{&ldsf[wv][1][rg * NP]};                     // weights by sorted position; later y
+  const F ltau{&ldsf[wv][2][rg * NP]};                   // tangent in sorted order (times sign)
+  const F lt{reinterpret_cast<float*>(G.p)};             // tangent, original order; later dy
 
   // ---- load, sort ----------------------------------------------------------------------------
+  // (load_row: consecutive lanes read consecutive elements, whichever lane holds what; the weights
+  // and the tangent reach their positions through LDS)
   float xin[E], win[E];
-  load_elems<E, false>(x, base, e0, n, xin);
-  load_elems<E, false>(w_all, row * w_stride, e0, n, win);
+  load_row<GL, E, false, false>(x, base, lr, n, xin);
+  load_row<GL, E, false, false>(w_all, row * w_stride, lr, n, win);
   if (jvp != nullptr) {
     float tin[E];
-    load_elems<E, false>(tangent, base, e0, n, tin);
+    load_row<GL, E, false, false>(tangent, base, lr, n, tin);
 #pragma unroll
-    for (int r = 0; r < E; ++r) lt[e0 + r] = tin[r];
+    for (int r = 0; r < E; ++r) lt[r * GL + lr] = tin[r];
   }
+#pragma unroll
+  for (int r = 0; r < E; ++r) lw[r * GL + lr] = win[r];
   double K[E];
-  make_keys<E, MAG, IDXB>(xin, e0, n, K);
+  make_keys_row<GL, E, false, MAG, IDXB>(xin, lr, n, K);
   SortRuns<GL, E, NP>::run(K, lr);
+  __builtin_amdgcn_wave_barrier();
   float s32[E];
   uint32_t field[E];
 #pragma unroll
@@ -134,8 +157,7 @@ __global__ __launch_bounds__((GenCfg<GL, E, PC == kP43>::WPB * kWave)) void gene
     unpack<IDXB>(K[r], key, field[r]);
     s32[r] = key_to_float(key);
     ss[e0 + r] = s32[r];
-    lw[e0 + r] = win[r];
-    hi_of[e0 + r] = 0xffff;
+    win[r] = lw[e0 + r];
   }
   __builtin_amdgcn_wave_barrier();
   if (jvp != nullptr) {
@@ -206,41 +228,77 @@ __global__ __launch_bounds__((GenCfg<GL, E, PC == kP43>::WPB * kWave)) void gene
   for (int r = 0; r < E; ++r)
     if (e0 + r < n) hm |= 1u << r;
   bool gave_up = false;
-  for (int round = 0;; ++round) {
-    const uint8_t now = uint8_t(round);
+  int round = 0;
+  if (!CUBIC) {
+    // the first round, between singletons, in registers
+    double gs[E];
+#pragma unroll
+    for (int r = 0; r < E; ++r) {
+      const double sd = double(s32[r]);
+      gs[r] = block_gamma<MAG, CUBIC>(Blk{1.0, double(win[r]), sd, 0.0, 0.0}, sd, sd, R);
+    }
+    double gl = 0.0;
+    if (GL > 1) gl = __shfl_up(gs[E - 1], 1, GL);
+    uint32_t keep = hm;
+#pragma unroll
+    for (int r = 0; r < E; ++r) {
+      const double left = r > 0 ? gs[r > 0 ? r - 1 : 0] : gl;
+      if ((r > 0 || lr > 0) && left < gs[r]) keep &= ~(1u << r);
+    }
+    hm = keep;                               // (bits of padding are not set in hm)
+    round = 1;
+    if (round >= max_rounds) gave_up = true;
+  }
+  // Blocks whose end has moved since the last round have a new pooled value; a boundary between two
+  // blocks that are both those of the last round was tested then.
+  uint32_t moved = hm;                       // my blocks that are to be computed
+  int nxt_seen = -2;
+  for (; !gave_up; ++round) {
     const int first = hm ? e0 + __builtin_ctz(hm) : n;
-    const int last = hm ? e0 + 31 - __builtin_clz(hm) : -1;
+    const int top = hm ? 31 - __builtin_clz(hm) : 0;
     const int nxt = lanes_after_min<GL>(first, lr, n);
-    const int prv = lanes_before_max<GL>(last, lr, -1);
-    // pooled value of every block that is not the one of the last round
-    for (uint32_t m = hm; m != 0;) {
+    if (hm && nxt != nxt_seen) moved |= 1u << top;
+    nxt_seen = nxt;
+    // last block start of the lanes before mine, and whether that block is new
+    const int before = lanes_before_max<GL>(hm ? 2 * (e0 + top) + int((moved >> top) & 1u) : -1, lr, -1);
+    for (uint32_t m = moved; m != 0;) {
       const int r = __builtin_ctz(m);
       m &= m - 1;
-      const int lo = e0 + r, hi = m ? e0 + __builtin_ctz(m) : nxt;
-      if (int(hi_of[lo]) != hi) {
-        hi_of[lo] = uint16_t(hi);
-        ver[lo] = now;
-        G[lo] = block_gamma<MAG, CUBIC>(block_sums(lo, hi), double(ss[lo]), double(ss[hi - 1]), R);
-      }
+      const uint32_t above = hm & ~((2u << r) - 1u);
+      const int lo = e0 + r, hi = above ? e0 + __builtin_ctz(above) : nxt;
+      G[lo] = block_gamma<MAG, CUBIC>(block_sums(lo, hi), double(ss[lo]), double(ss[hi - 1]), R);
     }
     __builtin_amdgcn_wave_barrier();
-    // every boundary whose two blocks violate goes; a boundary between two blocks that are both
-    // those of the last round was tested then
+    // every boundary whose two blocks violate goes
     uint32_t keep = hm;
     for (uint32_t m = hm; m != 0;) {
       const int r = __builtin_ctz(m);
       m &= m - 1;
-      const int lo = e0 + r, hi = m ? e0 + __builtin_ctz(m) : nxt;
       const uint32_t below = hm & ((1u << r) - 1u);
-      const int p = below ? e0 + 31 - __builtin_clz(below) : prv;
+      const int pr = below ? 31 - __builtin_clz(below) : 0;
+      const int p = below ? e0 + pr : (before >= 0 ? before >> 1 : -1);
       if (p < 0) continue;                   // the first block of the row
-      if (ver[p] != now && ver[lo] != now) continue;
+      const uint32_t pnew = below ? (moved >> pr) & 1u : uint32_t(before) & 1u;
+      if ((pnew | ((moved >> r) & 1u)) == 0) continue;
+      const int lo = e0 + r;
       bool viol;
       if (!CUBIC) viol = G[p] < G[lo];
-      else viol = blocks_violate<MAG, CUBIC>(block_sums(p, lo), G[p], block_sums(lo, hi), G[lo], R);
+      else {
+        const int hi = m ? e0 + __builtin_ctz(m) : nxt;
+        viol = blocks_violate<MAG, CUBIC>(block_sums(p, lo), G[p], block_sums(lo, hi), G[lo], R);
+      }
       if (viol) keep &= ~(1u << r);
     }
     const bool changed = keep != hm;
+    // blocks that stay and whose next start (in this lane) goes
+    const uint32_t gone = hm & ~keep;
+    moved = 0;
+    for (uint32_t m = gone; m != 0;) {
+      const int r = __builtin_ctz(m);
+      m &= m - 1;
+      const uint32_t below = keep & ((1u << r) - 1u);
+      if (below) moved |= 1u << (31 - __builtin_clz(below));
+    }
     hm = keep;
     if (!__any(changed)) break;
     if (round + 1 >= max_rounds) { gave_up = true; break; }
@@ -248,7 +306,7 @@ __global__ __launch_bounds__((GenCfg<GL, E, PC == kP43>::WPB * kWave)) void gene
   }
   __builtin_amdgcn_wave_barrier();
 
-  double* DG = G;                            // d gamma by block start
+  const D DG = G;                            // d gamma by block start
   float yv[E];
   double tt[E];                              // (s - gamma) / lambda
   if (!gave_up) {
@@ -375,24 +433,17 @@ __global__ __launch_bounds__((GenCfg<GL, E, PC == kP43>::WPB * kWave)) void gene
     }
   } else {
     // ---- too many rounds: the left-to-right block stack, one lane per row ---------------------------
-    // (stack columns in the arrays of the rounds, block starts in hi_of; the block on top of the
-    // stack is kept in registers)
-    double* st_s1 = P1;
-    double* st_w = PW;
-    double* st_g = G;
-    double* st_s2 = P2;
-    double* st_s3 = P3;
-    uint16_t* st_lo = hi_of;
-    DG = P1;
+    // (stack columns in the arrays of the rounds; the block on top of the stack is kept in registers)
+    for (int i = lr; i < NP; i += GL) st_lo[i] = 0;        // no mark but those of the walk
     __builtin_amdgcn_wave_barrier();
     if (lr == 0)
-      stack_walk<MAG, CUBIC, uint16_t>(n, ss, lw, ltau, jvp != nullptr, st_s1, st_w, st_g, st_s2,
-                                       st_s3, st_lo, uint16_t(0xffff), DG, R);
+      stack_walk<MAG, CUBIC, uint16_t>(n, ss, lw, ltau, jvp != nullptr, P1, PW, G, P2, P3, st_lo,
+                                       uint16_t(0xffff), P1, R);
     __builtin_amdgcn_wave_barrier();
     hm = 0;
 #pragma unroll
     for (int r = 0; r < E; ++r)
-      if (e0 + r < n && hi_of[e0 + r] == 0xffff) hm |= 1u << r;
+      if (e0 + r < n && st_lo[e0 + r] == 0xffff) hm |= 1u << r;
     const int last = hm ? e0 + 31 - __builtin_clz(hm) : -1;
     const int prv = lanes_before_max<GL>(last, lr, -1);
 #pragma unroll
@@ -424,7 +475,7 @@ __global__ __launch_bounds__((GenCfg<GL, E, PC == kP43>::WPB * kWave)) void gene
       dv[r] = 0.0f;
       if (jvp != nullptr) {
         const double h = CUBIC ? 3.0 * tt[r] * tt[r] * R.inv_lambda : R.inv_lambda;
-        float dy = float(h * (double(ltau[e0 + r]) - DG[b]));
+        float dy = float(h * (double(ltau[e0 + r]) - (gave_up ? P1[b] : DG[b])));
         if (MAG) dy = (dy == 0.0f || s32[r] == 0.0f) ? 0.0f : (neg ? -dy : dy);
         dv[r] = dy;
       }
@@ -442,14 +493,14 @@ __global__ __launch_bounds__((GenCfg<GL, E, PC == kP43>::WPB * kWave)) void gene
   if (out != nullptr) {
     float ov[E];
 #pragma unroll
-    for (int r = 0; r < E; ++r) ov[r] = lw[e0 + r];
-    store_elems<E, false>(out, base, e0, n, ov);
+    for (int r = 0; r < E; ++r) ov[r] = lw[r * GL + lr];
+    store_row<GL, E, false, false>(out, base, lr, n, ov);
   }
   if (jvp != nullptr) {
     float jv[E];
 #pragma unroll
-    for (int r = 0; r < E; ++r) jv[r] = lt[e0 + r];
-    store_elems<E, false>(jvp, base, e0, n, jv);
+    for (int r = 0; r < E; ++r) jv[r] = lt[r * GL + lr];
+    store_row<GL, E, false, false>(jvp, base, lr, n, jv);
   }
 }
 
