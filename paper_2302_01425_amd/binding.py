@@ -91,25 +91,34 @@ def _check(rc: int, what: str) -> None:
         raise TopkError(f"{what}: {strerror(rc)} (code {rc})")
 
 
+# The calls of small batches are bound by this file: 64 x 16 takes 3 us on the GPU and took 12 us per
+# call here, of which the launch is 2.5, the foreign call 1.5 and the rest what the checks below
+# read of the tensors (each attribute 0.1 us).  So every attribute is read once, tensors allocated by
+# the call itself are not checked against the others, and the library says itself whether its
+# workspace is too small (_enqueue).
+_F32 = torch.float32
+
+
 def _dev_f32(t: torch.Tensor, name: str) -> torch.Tensor:
     if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise TopkError(f"{name} must be a tensor in GPU memory")
-    if t.dtype != torch.float32 or not t.is_contiguous() or t.dim() != 2:
+    if t.dtype is not _F32 or not t.is_contiguous() or t.dim() != 2:
         raise TopkError(f"{name} must be a contiguous 2-D float32 tensor [rows, n]")
     return t
 
 
 def _overlap(a: torch.Tensor, b: torch.Tensor) -> bool:
-    a0, b0 = a.data_ptr(), b.data_ptr()
-    return (a0 < b0 + b.numel() * b.element_size() and b0 < a0 + a.numel() * a.element_size()
-            and a.numel() > 0 and b.numel() > 0)
+    d = b.data_ptr() - a.data_ptr()
+    if d >= 0:                                  # does b start inside a?
+        return d < a.numel() * a.element_size() and b.numel() > 0
+    return -d < b.numel() * b.element_size() and a.numel() > 0
 
 
 def _like(t, ref: torch.Tensor, name: str, inputs=()) -> torch.Tensor:
     """A tensor the kernels read or write rows * n floats of: it must have the shape and the
     device of `ref` (the first input).  Outputs (`inputs` given) must not overlap any input."""
     t = _dev_f32(t, name)
-    if tuple(t.shape) != tuple(ref.shape) or t.device != ref.device:
+    if t.shape != ref.shape or t.get_device() != ref.get_device():
         raise TopkError(f"{name} must have the shape {tuple(ref.shape)} and the device {ref.device} "
                         f"of the first input (got {tuple(t.shape)} on {t.device})")
     for other in inputs:
@@ -124,11 +133,13 @@ def _out(t, ref: torch.Tensor, name: str, inputs) -> torch.Tensor:
 
 def _stream(stream) -> int:
     if stream is None:
-        stream = torch.cuda.current_stream()
+        # (the raw handle of torch.cuda.current_stream(), without the Stream object: 1.5 -> 0.2 us)
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
     return int(stream.cuda_stream) if hasattr(stream, "cuda_stream") else int(stream)
 
 
 _ws_tensor = None
+_ws_index = None     # its device
 _ws_retired = []     # superseded workspaces, never freed (see ensure_workspace)
 
 
@@ -139,14 +150,14 @@ def workspace_bytes(op: int, rows: int, n: int, k: int, p: float) -> int:
 def set_workspace(t: torch.Tensor | None) -> None:
     """Register a caller-owned uint8 GPU tensor as scratch memory (None unregisters).  The caller
     keeps it alive for as long as enqueued work or a captured graph may use it."""
-    global _ws_tensor
+    global _ws_tensor, _ws_index
     if t is None:
         _check(load().topk_set_workspace(None, 0), "topk_set_workspace")
-        _ws_tensor = None
+        _ws_tensor = _ws_index = None
         return
     _check(load().topk_set_workspace(ctypes.c_void_p(t.data_ptr()), t.numel() * t.element_size()),
            "topk_set_workspace")
-    _ws_tensor = t
+    _ws_tensor, _ws_index = t, t.get_device()
 
 
 def ensure_workspace(op: int, rows: int, n: int, k: int, p: float, device) -> None:
@@ -175,6 +186,24 @@ def ensure_workspace(op: int, rows: int, n: int, k: int, p: float, device) -> No
     set_workspace(torch.empty(need, dtype=torch.uint8, device=dev))
 
 
+_ERR_WORKSPACE = -4
+
+
+def _enqueue(name: str, op: int, rows: int, n: int, k: int, p: float, ref: torch.Tensor, *args) -> None:
+    """Calls the entry point; where it finds the workspace missing or too small (it then has enqueued
+    nothing) the workspace is made and the call repeated.  Only a workspace on another device than the
+    inputs', which the library cannot tell, is looked at first."""
+    fn = getattr(_lib or load(), name)
+    if _ws_index is not None and _ws_index != ref.get_device():
+        ensure_workspace(op, rows, n, k, p, ref.device)
+    rc = fn(*args)
+    if rc == _ERR_WORKSPACE:
+        ensure_workspace(op, rows, n, k, p, ref.device)
+        rc = fn(*args)
+    if rc != 0:
+        _check(rc, name)
+
+
 TOPK_ROUTE_LONG_ROWS, TOPK_ROUTE_SHORT_ROW_LANES, TOPK_ROUTE_SHORT_ROW_KERNEL = 0, 1, 2
 TOPK_ROUTE_GENERAL_ROUNDS = 3
 TOPK_SHORT_ROW_MAX, TOPK_GENERAL_ROW_MAX = 1024, 131072
@@ -192,9 +221,8 @@ def topk_mask_fwd(theta, k, p, lam, out=None, stream=None):
     theta = _dev_f32(theta, "theta")
     rows, n = theta.shape
     out = _out(out, theta, "out", (theta,))
-    ensure_workspace(TOPK_OP_MASK_FWD, rows, n, k, p, theta.device)
-    _check(load().topk_mask_fwd(theta.data_ptr(), rows, n, int(k), float(p), float(lam),
-                                out.data_ptr(), _stream(stream)), "topk_mask_fwd")
+    _enqueue("topk_mask_fwd", TOPK_OP_MASK_FWD, rows, n, k, p, theta,
+             theta.data_ptr(), rows, n, int(k), float(p), float(lam), out.data_ptr(), _stream(stream))
     return out
 
 
@@ -205,13 +233,13 @@ def topk_mask_jvp(theta, tangent, k, p, lam, out=None, jvp_out=None, want_out=Tr
     rows, n = theta.shape
     if out is not None or want_out:
         out = _out(out, theta, "out", (theta, tangent))
+    given = jvp_out is not None
     jvp_out = _out(jvp_out, theta, "jvp_out", (theta, tangent))
-    if out is not None and _overlap(out, jvp_out):
+    if given and out is not None and _overlap(out, jvp_out):
         raise TopkError("out and jvp_out overlap")
-    ensure_workspace(TOPK_OP_MASK_JVP, rows, n, k, p, theta.device)
-    _check(load().topk_mask_jvp(theta.data_ptr(), tangent.data_ptr(), rows, n, int(k), float(p),
-                                float(lam), None if out is None else out.data_ptr(),
-                                jvp_out.data_ptr(), _stream(stream)), "topk_mask_jvp")
+    _enqueue("topk_mask_jvp", TOPK_OP_MASK_JVP, rows, n, k, p, theta,
+             theta.data_ptr(), tangent.data_ptr(), rows, n, int(k), float(p), float(lam),
+             None if out is None else out.data_ptr(), jvp_out.data_ptr(), _stream(stream))
     return out, jvp_out
 
 
@@ -238,9 +266,8 @@ def topkmag_fwd(x, k, p, lam, out=None, stream=None):
     x = _dev_f32(x, "x")
     rows, n = x.shape
     out = _out(out, x, "out", (x,))
-    ensure_workspace(TOPK_OP_MAG_FWD, rows, n, k, p, x.device)
-    _check(load().topkmag_fwd(x.data_ptr(), rows, n, int(k), float(p), float(lam),
-                              out.data_ptr(), _stream(stream)), "topkmag_fwd")
+    _enqueue("topkmag_fwd", TOPK_OP_MAG_FWD, rows, n, k, p, x,
+             x.data_ptr(), rows, n, int(k), float(p), float(lam), out.data_ptr(), _stream(stream))
     return out
 
 
@@ -250,13 +277,13 @@ def topkmag_jvp(x, tangent, k, p, lam, out=None, jvp_out=None, want_out=True, st
     rows, n = x.shape
     if out is not None or want_out:
         out = _out(out, x, "out", (x, tangent))
+    given = jvp_out is not None
     jvp_out = _out(jvp_out, x, "jvp_out", (x, tangent))
-    if out is not None and _overlap(out, jvp_out):
+    if given and out is not None and _overlap(out, jvp_out):
         raise TopkError("out and jvp_out overlap")
-    ensure_workspace(TOPK_OP_MAG_JVP, rows, n, k, p, x.device)
-    _check(load().topkmag_jvp(x.data_ptr(), tangent.data_ptr(), rows, n, int(k), float(p),
-                              float(lam), None if out is None else out.data_ptr(),
-                              jvp_out.data_ptr(), _stream(stream)), "topkmag_jvp")
+    _enqueue("topkmag_jvp", TOPK_OP_MAG_JVP, rows, n, k, p, x,
+             x.data_ptr(), tangent.data_ptr(), rows, n, int(k), float(p), float(lam),
+             None if out is None else out.data_ptr(), jvp_out.data_ptr(), _stream(stream))
     return out, jvp_out
 
 
@@ -264,17 +291,17 @@ def _abs_variant(name, op, x, tangent, k, p, lam, out, jvp_out, stream):
     x = _dev_f32(x, "x")
     rows, n = x.shape
     out = _out(out, x, "out", (x,) if tangent is None else (x, _like(tangent, x, "tangent")))
-    ensure_workspace(op, rows, n, k, p, x.device)
     if tangent is None:
-        _check(getattr(load(), name + "_fwd")(x.data_ptr(), rows, n, int(k), float(p), float(lam),
-                                              out.data_ptr(), _stream(stream)), name + "_fwd")
+        _enqueue(name + "_fwd", op, rows, n, k, p, x,
+                 x.data_ptr(), rows, n, int(k), float(p), float(lam), out.data_ptr(), _stream(stream))
         return out
+    given = jvp_out is not None
     jvp_out = _out(jvp_out, x, "jvp_out", (x, tangent))
-    if _overlap(out, jvp_out):
+    if given and _overlap(out, jvp_out):
         raise TopkError("out and jvp_out overlap")
-    _check(getattr(load(), name + "_jvp")(x.data_ptr(), tangent.data_ptr(), rows, n, int(k),
-                                          float(p), float(lam), out.data_ptr(), jvp_out.data_ptr(),
-                                          _stream(stream)), name + "_jvp")
+    _enqueue(name + "_jvp", op, rows, n, k, p, x,
+             x.data_ptr(), tangent.data_ptr(), rows, n, int(k), float(p), float(lam), out.data_ptr(),
+             jvp_out.data_ptr(), _stream(stream))
     return out, jvp_out
 
 
@@ -285,18 +312,19 @@ def topk_mask_sparse_fwd(theta, k, p, lam, max_nnz, idx_out=None, val_out=None, 
     theta = _dev_f32(theta, "theta")
     rows, n = theta.shape
     shape = (rows, int(max_nnz))
-    idx = torch.empty(shape, dtype=torch.int32, device=theta.device) if idx_out is None else idx_out
-    val = torch.empty(shape, dtype=torch.float32, device=theta.device) if val_out is None else val_out
-    nnz = torch.empty((rows,), dtype=torch.int32, device=theta.device) if nnz_out is None else nnz_out
-    for t, dt, sh, name in ((idx, torch.int32, shape, "idx_out"), (val, torch.float32, shape, "val_out"),
-                            (nnz, torch.int32, (rows,), "nnz_out")):
-        if not isinstance(t, torch.Tensor) or not t.is_cuda or t.device != theta.device or \
-                t.dtype != dt or tuple(t.shape) != sh or not t.is_contiguous():
-            raise TopkError(f"{name} must be a contiguous {dt} tensor of shape {sh} on {theta.device}")
-    ensure_workspace(TOPK_OP_MASK_SPARSE, rows, n, k, p, theta.device)
-    _check(load().topk_mask_sparse_fwd(theta.data_ptr(), rows, n, int(k), float(p), float(lam),
-                                       int(max_nnz), idx.data_ptr(), val.data_ptr(), nnz.data_ptr(),
-                                       _stream(stream)), "topk_mask_sparse_fwd")
+    if idx_out is not None or val_out is not None or nnz_out is not None:
+        for t, dt, sh, name in ((idx_out, torch.int32, shape, "idx_out"), (val_out, _F32, shape, "val_out"),
+                                (nnz_out, torch.int32, (rows,), "nnz_out")):
+            if t is not None and (not isinstance(t, torch.Tensor) or not t.is_cuda or t.device != theta.device
+                                  or t.dtype != dt or tuple(t.shape) != sh or not t.is_contiguous()):
+                raise TopkError(f"{name} must be a contiguous {dt} tensor of shape {sh} on {theta.device}")
+    dev = theta.device
+    idx = torch.empty(shape, dtype=torch.int32, device=dev) if idx_out is None else idx_out
+    val = torch.empty(shape, dtype=_F32, device=dev) if val_out is None else val_out
+    nnz = torch.empty((rows,), dtype=torch.int32, device=dev) if nnz_out is None else nnz_out
+    _enqueue("topk_mask_sparse_fwd", TOPK_OP_MASK_SPARSE, rows, n, k, p, theta,
+             theta.data_ptr(), rows, n, int(k), float(p), float(lam), int(max_nnz), idx.data_ptr(),
+             val.data_ptr(), nnz.data_ptr(), _stream(stream))
     return idx, val, nnz
 
 
@@ -315,9 +343,9 @@ def topk_general_fwd(x, w, phi, p, lam, out=None, stream=None):
     rows, n = x.shape
     w, stride = _weights(w, rows, n, x.device)
     out = _out(out, x, "out", (x, w))
-    ensure_workspace(TOPK_OP_GENERAL, rows, n, 0, p, x.device)
-    _check(load().topk_general_fwd(x.data_ptr(), w.data_ptr(), stride, rows, n, int(phi), float(p),
-                                   float(lam), out.data_ptr(), _stream(stream)), "topk_general_fwd")
+    _enqueue("topk_general_fwd", TOPK_OP_GENERAL, rows, n, 0, p, x,
+             x.data_ptr(), w.data_ptr(), stride, rows, n, int(phi), float(p), float(lam),
+             out.data_ptr(), _stream(stream))
     return out
 
 
@@ -329,14 +357,13 @@ def topk_general_jvp(x, w, tangent, phi, p, lam, out=None, jvp_out=None, want_ou
     w, stride = _weights(w, rows, n, x.device)
     if out is not None or want_out:
         out = _out(out, x, "out", (x, w, tangent))
+    given = jvp_out is not None
     jvp_out = _out(jvp_out, x, "jvp_out", (x, w, tangent))
-    if out is not None and _overlap(out, jvp_out):
+    if given and out is not None and _overlap(out, jvp_out):
         raise TopkError("out and jvp_out overlap")
-    ensure_workspace(TOPK_OP_GENERAL, rows, n, 0, p, x.device)
-    _check(load().topk_general_jvp(x.data_ptr(), w.data_ptr(), stride, tangent.data_ptr(), rows, n,
-                                   int(phi), float(p), float(lam),
-                                   None if out is None else out.data_ptr(), jvp_out.data_ptr(),
-                                   _stream(stream)), "topk_general_jvp")
+    _enqueue("topk_general_jvp", TOPK_OP_GENERAL, rows, n, 0, p, x,
+             x.data_ptr(), w.data_ptr(), stride, tangent.data_ptr(), rows, n, int(phi), float(p),
+             float(lam), None if out is None else out.data_ptr(), jvp_out.data_ptr(), _stream(stream))
     return out, jvp_out
 
 
@@ -377,13 +404,13 @@ def topk_mask_vjp(theta, cotangent, k, p, lam, out=None, vjp_out=None, want_out=
     rows, n = theta.shape
     if out is not None or want_out:
         out = _out(out, theta, "out", (theta, cotangent))
+    given = vjp_out is not None
     vjp_out = _out(vjp_out, theta, "vjp_out", (theta, cotangent))
-    if out is not None and _overlap(out, vjp_out):
+    if given and out is not None and _overlap(out, vjp_out):
         raise TopkError("out and vjp_out overlap")
-    ensure_workspace(TOPK_OP_MASK_JVP, rows, n, k, p, theta.device)
-    _check(load().topk_mask_vjp(theta.data_ptr(), cotangent.data_ptr(), rows, n, int(k), float(p),
-                                float(lam), None if out is None else out.data_ptr(),
-                                vjp_out.data_ptr(), _stream(stream)), "topk_mask_vjp")
+    _enqueue("topk_mask_vjp", TOPK_OP_MASK_JVP, rows, n, k, p, theta,
+             theta.data_ptr(), cotangent.data_ptr(), rows, n, int(k), float(p), float(lam),
+             None if out is None else out.data_ptr(), vjp_out.data_ptr(), _stream(stream))
     return out, vjp_out
 
 
@@ -393,13 +420,13 @@ def topkmag_vjp(x, cotangent, k, p, lam, out=None, vjp_out=None, want_out=True, 
     rows, n = x.shape
     if out is not None or want_out:
         out = _out(out, x, "out", (x, cotangent))
+    given = vjp_out is not None
     vjp_out = _out(vjp_out, x, "vjp_out", (x, cotangent))
-    if out is not None and _overlap(out, vjp_out):
+    if given and out is not None and _overlap(out, vjp_out):
         raise TopkError("out and vjp_out overlap")
-    ensure_workspace(TOPK_OP_MAG_JVP, rows, n, k, p, x.device)
-    _check(load().topkmag_vjp(x.data_ptr(), cotangent.data_ptr(), rows, n, int(k), float(p),
-                              float(lam), None if out is None else out.data_ptr(),
-                              vjp_out.data_ptr(), _stream(stream)), "topkmag_vjp")
+    _enqueue("topkmag_vjp", TOPK_OP_MAG_JVP, rows, n, k, p, x,
+             x.data_ptr(), cotangent.data_ptr(), rows, n, int(k), float(p), float(lam),
+             None if out is None else out.data_ptr(), vjp_out.data_ptr(), _stream(stream))
     return out, vjp_out
 
 
@@ -415,10 +442,9 @@ def topk_mask_loss(theta, target, k, p, lam, loss_out=None, grad_out=None, strea
             tuple(loss_out.shape) != (rows,) or not loss_out.is_contiguous():
         raise TopkError(f"loss_out must be a contiguous float32 tensor of shape ({rows},) on {theta.device}")
     grad_out = _out(grad_out, theta, "grad_out", (theta, target))
-    ensure_workspace(TOPK_OP_MASK_FWD, rows, n, k, p, theta.device)
-    _check(load().topk_mask_loss(theta.data_ptr(), target.data_ptr(), rows, n, int(k), float(p),
-                                 float(lam), loss_out.data_ptr(), grad_out.data_ptr(),
-                                 _stream(stream)), "topk_mask_loss")
+    _enqueue("topk_mask_loss", TOPK_OP_MASK_FWD, rows, n, k, p, theta,
+             theta.data_ptr(), target.data_ptr(), rows, n, int(k), float(p), float(lam),
+             loss_out.data_ptr(), grad_out.data_ptr(), _stream(stream))
     return loss_out, grad_out
 
 
@@ -431,7 +457,6 @@ def topk_argsort_desc(theta, perm_out=None, stream=None):
             perm_out.device != theta.device or perm_out.dtype != torch.int32 or \
             tuple(perm_out.shape) != (rows, n) or not perm_out.is_contiguous():
         raise TopkError(f"perm_out must be a contiguous int32 tensor of shape ({rows}, {n}) on {theta.device}")
-    ensure_workspace(TOPK_OP_ARGSORT, rows, n, 0, 2.0, theta.device)
-    _check(load().topk_argsort_desc(theta.data_ptr(), rows, n, perm_out.data_ptr(),
-                                    _stream(stream)), "topk_argsort_desc")
+    _enqueue("topk_argsort_desc", TOPK_OP_ARGSORT, rows, n, 0, 2.0, theta,
+             theta.data_ptr(), rows, n, perm_out.data_ptr(), _stream(stream))
     return perm_out
