@@ -30,7 +30,8 @@
 // Bound by the latency of one wavefront per row: rows of 1024 elements take 39 KB of LDS, so each
 // SIMD has one wavefront, whose vector instructions (4900, 3000 of them the sort) issue for 37 % of
 // its time.  4096 x 1024, lambda = 0.1, JVP: 166 us with linear LDS arrays (32-way bank conflicts),
-// a first round through LDS and loads of E consecutive elements per lane; 103 us now.
+// a first round through LDS and loads of E consecutive elements per lane; 103 us without them.  (With
+// one weight vector for all rows and p = 2 the kernel at the end of this file takes these rows.)
 #include "common.hpp"
 #include "pooling.hpp"
 #include "launch.hpp"
@@ -504,6 +505,286 @@ __global__ __launch_bounds__((GenCfg<GL, E, PC == kP43>::WPB * kWave)) void gene
   }
 }
 
+// ---- p = 2 with one weight vector for all rows ------------------------------------------------------
+// The same rounds in 16 bytes of LDS per element instead of 38, so that twice (rows above 512
+// elements) to four times as many wavefronts hide each other's latency.  The prefix sums of w are those
+// of every row: one copy per workgroup.  A block of one element gets its pooled value from the
+// registers in the first round and is never computed again, so neither the sorted values nor the
+// weights are looked up; the tangent stays in registers; inputs and outputs change their order through
+// the arrays of the rounds before and after these.  There is no hand-over to the sequential walk: a
+// round costs one walk step per moved block and two lane scans, and a row of n elements settles in n - 1
+// rounds at most.
+// JVP, us, against the kernel above: 4096 x 1024 (lambda = 0.1) 103 -> 55, 6697 x 425 206 -> 94,
+// 2061 x 186 40 -> 26, 69 x 538 (lambda = 0.0065) 113 -> 58; 1024 rows of 1024 that lose one boundary per
+// round 1740 (walk after 288 rounds, at the time) -> 1060.
+template <int GL, int E>
+struct LeanCfg {
+  static constexpr int NP = GL * E, RPW = kWave / GL;
+  static constexpr int NQ = NP + ((NP >> 5) & (E - 1)) + 1;
+  static constexpr int IDXB = ilog2(NP) + 1;
+  static constexpr int WPB = 4;
+};
+
+template <int GL, int E, bool MAG>
+__global__ __launch_bounds__((LeanCfg<GL, E>::WPB * kWave)) void general_shared_kernel(
+    const float* __restrict__ x, const float* __restrict__ w, const float* __restrict__ tangent,
+    float* __restrict__ out, float* __restrict__ jvp, int64_t rows, int n, Reg R) {
+  using C = LeanCfg<GL, E>;
+  using D = Swizzled<double, E>;
+  using F = Swizzled<float, E>;
+  constexpr int NP = C::NP, NQ = C::NQ, RPW = C::RPW, IDXB = C::IDXB;
+  static_assert(E <= 16, "the block starts of a lane are kept in a 32-bit mask");
+  __shared__ __attribute__((aligned(16))) double lds_w[NQ];
+  __shared__ __attribute__((aligned(16))) double ldsd[C::WPB][2][RPW * NQ];
+
+  const int lane = threadIdx.x & (kWave - 1);
+  const int lr = lane_in_group<GL>();
+  const int wv = threadIdx.x / kWave;
+  const int rg = lane / GL;
+  int64_t row = (int64_t(blockIdx.x) * C::WPB + wv) * RPW + rg;
+  const bool valid = row < rows;
+  if (!valid) row = rows - 1;            // keep the lanes alive for the exchanges; no stores
+  const int64_t base = row * n;
+  const int e0 = lr * E;
+  const D PW{lds_w};                                     // prefix sums of w
+  const D P1{&ldsd[wv][0][rg * NQ]};                     // of s; after the rounds: of the tangent
+  const D G{&ldsd[wv][1][rg * NQ]};                      // pooled value, then d gamma, by block start
+  const F in_w{reinterpret_cast<float*>(P1.p)};          // before the prefix sums: weights
+  const F in_t{reinterpret_cast<float*>(G.p)};           // before the rounds: tangent, original order
+  const F out_y{reinterpret_cast<float*>(P1.p)};         // at the end: the outputs, original order
+  const F out_d{reinterpret_cast<float*>(G.p)};
+
+  // ---- load, sort ----------------------------------------------------------------------------
+  float xin[E], win[E], tau[E];
+  load_row<GL, E, false, false>(x, base, lr, n, xin);
+  load_row<GL, E, false, false>(w, 0, lr, n, win);
+  if (jvp != nullptr) {
+    load_row<GL, E, false, false>(tangent, base, lr, n, tau);
+#pragma unroll
+    for (int r = 0; r < E; ++r) in_t[r * GL + lr] = tau[r];
+  }
+#pragma unroll
+  for (int r = 0; r < E; ++r) in_w[r * GL + lr] = win[r];
+  double K[E];
+  make_keys_row<GL, E, false, MAG, IDXB>(xin, lr, n, K);
+  SortRuns<GL, E, NP>::run(K, lr);
+  __builtin_amdgcn_wave_barrier();
+  float s32[E];
+  uint32_t field[E];
+#pragma unroll
+  for (int r = 0; r < E; ++r) {
+    uint32_t key;
+    unpack<IDXB>(K[r], key, field[r]);
+    s32[r] = key_to_float(key);
+    win[r] = in_w[e0 + r];
+    tau[r] = 0.0f;
+    if (jvp != nullptr && e0 + r < n) {
+      float tf = in_t[MAG ? (field[r] >> 1) : field[r]];
+      if (MAG) {
+        if (field[r] & 1u) tf = -tf;
+        if (s32[r] == 0.0f) tf = 0.0f;         // sign(0) = 0
+      }
+      tau[r] = tf;
+    }
+  }
+  __builtin_amdgcn_wave_barrier();
+
+  // ---- prefix sums; pooled values of the singletons and the first round between them ---------------
+  uint32_t hm = 0;                           // block starts among my positions (bit r: e0 + r)
+  {
+    double t1 = 0.0, tw = 0.0;
+#pragma unroll
+    for (int r = 0; r < E; ++r) {
+      const bool real = e0 + r < n;
+      t1 += real ? double(s32[r]) : 0.0;
+      tw += double(win[r]);                  // (0 beyond the row)
+    }
+    double r1 = group_exclusive_scan_f64<GL>(t1, lr), rw = group_exclusive_scan_f64<GL>(tw, lr);
+    const bool weights = wv == 0 && rg == 0;
+    double gs[E];
+#pragma unroll
+    for (int r = 0; r < E; ++r) {
+      const bool real = e0 + r < n;
+      const double sd = real ? double(s32[r]) : 0.0;
+      P1[e0 + r] = r1;
+      if (weights) PW[e0 + r] = rw;
+      r1 += sd;
+      rw += double(win[r]);
+      gs[r] = block_gamma<MAG, false>(Blk{1.0, double(win[r]), sd, 0.0, 0.0}, sd, sd, R);
+      G[e0 + r] = gs[r];
+      if (real) hm |= 1u << r;
+    }
+    if (lr == GL - 1) {
+      P1[NP] = r1;
+      if (weights) PW[NP] = rw;
+    }
+    double gl = 0.0;
+    if (GL > 1) gl = __shfl_up(gs[E - 1], 1, GL);
+#pragma unroll
+    for (int r = 0; r < E; ++r) {
+      const double left = r > 0 ? gs[r > 0 ? r - 1 : 0] : gl;
+      if ((r > 0 || lr > 0) && left < gs[r]) hm &= ~(1u << r);
+    }
+  }
+  __syncthreads();                           // PW (written by the first wavefront)
+
+  // ---- pool adjacent violators in rounds (see general_rows_kernel) ---------------------------------
+  int nxt = 0, nxt_seen = 0;
+  uint32_t moved = 0;                        // my blocks that are to be computed
+  bool first_time = true;
+  for (;;) {
+    const int first = hm ? e0 + __builtin_ctz(hm) : n;
+    const int top = hm ? 31 - __builtin_clz(hm) : 0;
+    nxt = lanes_after_min<GL>(first, lr, n);
+    if (first_time) {
+      // everything longer than one element
+      moved = hm & ~(hm >> 1);
+      if (nxt == e0 + top + 1) moved &= ~(1u << top);
+      first_time = false;
+    } else if (hm && nxt != nxt_seen) {
+      moved |= 1u << top;
+    }
+    nxt_seen = nxt;
+    const int before = lanes_before_max<GL>(hm ? 2 * (e0 + top) + int((moved >> top) & 1u) : -1, lr, -1);
+    for (uint32_t m = moved; m != 0;) {
+      const int r = __builtin_ctz(m);
+      m &= m - 1;
+      const uint32_t above = hm & ~((2u << r) - 1u);
+      const int lo = e0 + r, hi = above ? e0 + __builtin_ctz(above) : nxt;
+      G[lo] = block_gamma<MAG, false>(Blk{double(hi - lo), PW[hi] - PW[lo], P1[hi] - P1[lo], 0.0, 0.0}, 0.0,
+                                      0.0, R);
+    }
+    __builtin_amdgcn_wave_barrier();
+    // boundaries next to a moved block
+    uint32_t keep = hm;
+    uint32_t test = moved;
+    {
+      const uint32_t low = hm & (0u - hm);                       // my first block: its left neighbour
+      if (before >= 0 && (before & 1)) test |= low;
+      for (uint32_t m = moved; m != 0;) {                        // right neighbours of moved blocks
+        const int r = __builtin_ctz(m);
+        m &= m - 1;
+        const uint32_t above = hm & ~((2u << r) - 1u);
+        test |= above & (0u - above);
+      }
+    }
+    for (uint32_t m = test; m != 0;) {
+      const int r = __builtin_ctz(m);
+      m &= m - 1;
+      const uint32_t below = hm & ((1u << r) - 1u);
+      const int p = below ? e0 + 31 - __builtin_clz(below) : (before >= 0 ? before >> 1 : -1);
+      if (p >= 0 && G[p] < G[e0 + r]) keep &= ~(1u << r);
+    }
+    // blocks that stay and whose next start (in this lane) goes
+    moved = 0;
+    for (uint32_t m = hm & ~keep; m != 0;) {
+      const int r = __builtin_ctz(m);
+      m &= m - 1;
+      const uint32_t below = keep & ((1u << r) - 1u);
+      if (below) moved |= 1u << (31 - __builtin_clz(below));
+    }
+    const bool changed = keep != hm;
+    hm = keep;
+    if (!__any(changed)) break;
+    __builtin_amdgcn_wave_barrier();
+  }
+
+  // ---- y; d gamma of every block (Prop. 7) from prefix sums of the tangent ----------------------------
+  const int prv = lanes_before_max<GL>(hm ? e0 + 31 - __builtin_clz(hm) : -1, lr, -1);
+  auto start_of = [&](int r) {
+    const uint32_t upto = hm & ((2u << r) - 1u);
+    const int b = upto ? e0 + 31 - __builtin_clz(upto) : prv;
+    return b < 0 ? 0 : b;                                  // (padding of an empty tail)
+  };
+  float yv[E], dv[E];
+#pragma unroll
+  for (int r = 0; r < E; ++r) {
+    const bool neg = MAG && (field[r] & 1u);
+    float y = float((double(s32[r]) - G[start_of(r)]) * R.inv_lambda);
+    if (MAG) y = (y == 0.0f || s32[r] == 0.0f) ? 0.0f : (neg ? -y : y);
+    yv[r] = y;
+    dv[r] = 0.0f;
+  }
+  if (jvp != nullptr) {
+    double tq = 0.0;
+#pragma unroll
+    for (int r = 0; r < E; ++r) tq += double(tau[r]);
+    double rq = group_exclusive_scan_f64<GL>(tq, lr);
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int r = 0; r < E; ++r) {
+      P1[e0 + r] = rq;
+      rq += double(tau[r]);
+    }
+    if (lr == GL - 1) P1[NP] = rq;
+    __builtin_amdgcn_wave_barrier();
+    uint32_t longer = hm & ~(hm >> 1);
+    if (hm && nxt == e0 + 31 - __builtin_clz(hm) + 1) longer &= ~(1u << (31 - __builtin_clz(hm)));
+#pragma unroll
+    for (int r = 0; r < E; ++r) {
+      // one element: from its own tangent and weight
+      if (((hm & ~longer) >> r) & 1u) {
+        const double t = double(tau[r]);
+        G[e0 + r] = MAG ? t / (1.0 + R.lambda * double(win[r])) : t;
+      }
+    }
+    for (uint32_t m = longer; m != 0;) {
+      const int r = __builtin_ctz(m);
+      m &= m - 1;
+      const uint32_t above = hm & ~((2u << r) - 1u);
+      const int lo = e0 + r, hi = above ? e0 + __builtin_ctz(above) : nxt;
+      double den = double(hi - lo);
+      if (MAG) den += R.lambda * (PW[hi] - PW[lo]);
+      G[lo] = (P1[hi] - P1[lo]) / den;
+    }
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int r = 0; r < E; ++r) {
+      const bool neg = MAG && (field[r] & 1u);
+      float dy = float(R.inv_lambda * (double(tau[r]) - G[start_of(r)]));
+      if (MAG) dy = (dy == 0.0f || s32[r] == 0.0f) ? 0.0f : (neg ? -dy : dy);
+      dv[r] = dy;
+    }
+  }
+  __builtin_amdgcn_wave_barrier();           // everything has been read
+
+  // ---- outputs in the original order ---------------------------------------------------------------
+#pragma unroll
+  for (int r = 0; r < E; ++r) {
+    if (e0 + r >= n) continue;
+    const uint32_t orig = MAG ? (field[r] >> 1) : field[r];
+    if (out != nullptr) out_y[orig] = yv[r];
+    if (jvp != nullptr) out_d[orig] = dv[r];
+  }
+  __builtin_amdgcn_wave_barrier();
+  if (!valid) return;
+  if (out != nullptr) {
+#pragma unroll
+    for (int r = 0; r < E; ++r) yv[r] = out_y[r * GL + lr];
+    store_row<GL, E, false, false>(out, base, lr, n, yv);
+  }
+  if (jvp != nullptr) {
+#pragma unroll
+    for (int r = 0; r < E; ++r) dv[r] = out_d[r * GL + lr];
+    store_row<GL, E, false, false>(jvp, base, lr, n, dv);
+  }
+}
+
+template <int GL, int E>
+int launch_general_shared(bool mag, const float* x, const float* w, const float* t, float* out, float* jvp,
+                          int64_t rows, int n, const Reg& R, hipStream_t st) {
+  using C = LeanCfg<GL, E>;
+  const int64_t blocks = (rows + C::RPW * C::WPB - 1) / (C::RPW * C::WPB);
+  if (blocks > 0x7fffffffLL) return -1;
+  if (mag)
+    hipLaunchKernelGGL((general_shared_kernel<GL, E, true>), dim3((unsigned)blocks), dim3(C::WPB * kWave), 0,
+                       st, x, w, t, out, jvp, rows, n, R);
+  else
+    hipLaunchKernelGGL((general_shared_kernel<GL, E, false>), dim3((unsigned)blocks), dim3(C::WPB * kWave), 0,
+                       st, x, w, t, out, jvp, rows, n, R);
+  return 0;
+}
+
 template <int GL, int E>
 int launch_general_shape(bool mag, int pc, const float* x, const float* w, int64_t w_stride,
                          const float* t, float* out, float* jvp, int64_t rows, int n, const Reg& R,
@@ -539,8 +820,12 @@ int launch_general_rows(bool mag, int pc, const float* x, const float* w, int64_
   // (n - 1 of them at most: each removes a boundary) always win.
   const int forced = routes().general_rounds;            // test control
   const int max_rounds = forced > 0 ? forced : (pc == kP43 ? n + 1 : kMinRounds + n / 4);
-#define CALL(GL, E) \
-  launch_general_shape<GL, E>(mag, pc, x, w, w_stride, tangent, out, jvp, rows, n, R, st, max_rounds)
+  // one weight vector, p = 2 (forced rounds ask for the kernel that hands over)
+  const bool shared = pc == kP2 && w_stride == 0 && forced == 0;
+#define CALL(GL, E)                                                                                \
+  (shared ? launch_general_shared<GL, E>(mag, x, w, tangent, out, jvp, rows, n, R, st)              \
+          : launch_general_shape<GL, E>(mag, pc, x, w, w_stride, tangent, out, jvp, rows, n, R, st, \
+                                        max_rounds))
   switch (np) {
     case 2: return CALL(1, 2);
     case 4: return CALL(1, 4);
