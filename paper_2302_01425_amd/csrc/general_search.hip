@@ -26,8 +26,11 @@
 // rounds, values that are not finite, or weights that are not non-increasing are left to the kernel
 // that sorts the row (todo[row] = 1).
 //
-// Bound by: the passes over the row on the compute units that have a row (64 rows: a quarter of
-// them) and the latency of the rounds.
+// 64 x 65536, lambda = 0.1: 909 us with a complete sort and the partition over all positions, 54 us
+// here; 64 x 1631 139 -> 36; 9 x 123069 1760 -> 85; 15 x 4899, lambda = 0.0034, 514 -> 40.  Bound by the
+// vector instructions of the three passes on the compute units that have a row (64 rows: a quarter of
+// them; 8, 6 and 9 us at 65536), the float64 scans (5 us each) and the rounds (1 to 2.5 us for a
+// majorant of 230 items, 95 us where 67 rounds are needed).
 #include <hip/hip_runtime.h>
 
 #include "common.hpp"
@@ -68,6 +71,9 @@ struct SearchShared {
   DD wave_dd[kNW];
   unsigned long long wave_u[kNW];
   int nb, bad;
+  struct {
+    int lo, hi;                                 // every bin in between is one item
+  } gap;
 };
 static_assert(sizeof(SearchShared) <= 160 * 1024, "LDS of a compute unit");
 
@@ -91,15 +97,16 @@ __device__ __forceinline__ DD scan_dd(const DD& v, DD* wave_tot, DD* total) {
   if (lane == 0) prev = DD{0.0, 0.0};
   if (lane == kWave - 1) wave_tot[w] = inc;
   __syncthreads();
-  DD before{0.0, 0.0}, all{0.0, 0.0};
+  DD tot = wave_tot[lane & (NW - 1)];            // the wavefronts' totals: scanned by the lanes of each
 #pragma unroll
-  for (int q = 0; q < NW; ++q) {
-    if (q == w) before = all;
-    all = dd_add(all, wave_tot[q]);
+  for (int off = 1; off < NW; off <<= 1) {
+    const DD o = shfl_up_dd(tot, off);
+    if ((lane & (NW - 1)) >= off) tot = dd_add(o, tot);
   }
+  const DD before{__shfl(tot.h, w > 0 ? w - 1 : 0, kWave), __shfl(tot.l, w > 0 ? w - 1 : 0, kWave)};
+  *total = DD{__shfl(tot.h, NW - 1, kWave), __shfl(tot.l, NW - 1, kWave)};
   __syncthreads();
-  *total = all;
-  return dd_add(before, prev);
+  return w > 0 ? dd_add(before, prev) : prev;
 }
 __device__ __forceinline__ unsigned long long scan_u64(unsigned long long v, unsigned long long* wave_tot,
                                                        unsigned long long* total) {
@@ -161,19 +168,19 @@ __global__ __launch_bounds__(kWThreads) void weight_prefix_kernel(const float* _
   }
 }
 
-// every element of the row, four 16-byte loads per thread in flight where rows are aligned
+// every element of the row, eight 16-byte loads per thread in flight where rows are aligned
 template <bool VEC, class F>
 __device__ __forceinline__ void each_value(const float* __restrict__ x, int n, F f) {
   if constexpr (VEC) {
-    for (int e0 = 4 * int(threadIdx.x); e0 < n; e0 += 16 * kNT) {
-      float4 q[4];
+    for (int e0 = 4 * int(threadIdx.x); e0 < n; e0 += 32 * kNT) {
+      float4 q[8];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
+      for (int i = 0; i < 8; ++i) {
         q[i] = make_float4(0.f, 0.f, 0.f, 0.f);
         if (e0 + i * 4 * kNT < n) q[i] = *reinterpret_cast<const float4*>(x + e0 + i * 4 * kNT);
       }
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
+      for (int i = 0; i < 8; ++i) {
         if (e0 + i * 4 * kNT < n) {
           f(q[i].x);
           f(q[i].y);
@@ -235,7 +242,23 @@ __device__ int majorant(SearchShared& sm, int T, double lambda, int* which) {
       }
     }
     unsigned long long total;
-    int at = int(scan_u64(uint64_t(kept), sm.wave_u, &total));
+    int at;
+    if (per == 1) {                              // (kept is 0 or 1)
+      const unsigned long long km = __ballot(kept != 0);
+      if (lane == 0) sm.wave_u[tid / kWave] = __popcll(km);
+      __syncthreads();
+      uint32_t before = 0, all = 0;
+#pragma unroll
+      for (int q = 0; q < kNW; ++q) {
+        const uint32_t c = uint32_t(sm.wave_u[q]);
+        if (q < tid / kWave) before += c;
+        all += c;
+      }
+      at = int(before) + __popcll(km & ((1ull << lane) - 1ull));
+      total = all;
+    } else {
+      at = int(scan_u64(uint64_t(kept), sm.wave_u, &total));
+    }
     if (i0 < nb) {
 #pragma unroll
       for (int r = 0; r < 3; ++r)
@@ -302,21 +325,13 @@ __global__ __launch_bounds__(kNT) void general_search_kernel(
 #pragma unroll
     for (int c = 0; c < kCopies - 1; ++c) sm.u.extra[c][i] = 0;
   }
-  if (tid < kWave) {
-    DD t{0.0, 0.0};
-    bool bad = false;
-    if (lane < tiles) {
-      t = wtotal[wrow * kWTiles + lane];
-      bad = wbad[wrow * kWTiles + lane] != 0;
-    }
-    t = wave_inclusive_dd(t, lane);
-    if (lane < tiles) sm.toff[lane + 1] = t;
-    if (lane == 0) {
-      sm.toff[0] = DD{0.0, 0.0};
-      sm.bad = 0;
-    }
-    if (__any(bad) && lane == 0) sm.bad = 1;
+  DD tile_total{0.0, 0.0};
+  bool tile_bad = false;
+  if (tid < kWave && lane < tiles) {
+    tile_total = wtotal[wrow * kWTiles + lane];
+    tile_bad = wbad[wrow * kWTiles + lane] != 0;
   }
+  if (tid == 0) sm.gap = {-1, kSelBins};
   __syncthreads();
   {
     const int copy = lane % kCopies;
@@ -325,6 +340,13 @@ __global__ __launch_bounds__(kNT) void general_search_kernel(
       atomicAdd(&hist[desc_key(v) >> (32 - kSelBits)],
                 (1ull << 40) | (unsigned long long)(__float_as_uint(v) & 0xfffffu));
     });
+  }
+  if (tid < kWave) {
+    const DD t = wave_inclusive_dd(tile_total, lane);
+    if (lane < tiles) sm.toff[lane + 1] = t;
+    if (lane == 0) sm.toff[0] = DD{0.0, 0.0};
+    const bool bad = __any(tile_bad);
+    if (lane == 0) sm.bad = bad;
   }
   __syncthreads();
 
@@ -363,20 +385,27 @@ __global__ __launch_bounds__(kNT) void general_search_kernel(
     if (tid == 0) todo[row] = 1;
     return;
   }
-  auto w_prefix = [&](uint32_t p) -> DD {
-    return p >= uint32_t(n) ? sm.toff[tiles] : dd_add(sm.toff[p / kWTile], wl[p]);
-  };
+  // prefix sums of w at position p < n: the tile's offset and what w_local reads
+  auto w_local = [&](uint32_t p) -> DD { return wl[p < uint32_t(n) ? p : uint32_t(n) - 1u]; };
+  auto w_prefix = [&](uint32_t p, const DD& local) -> DD { return dd_add(sm.toff[p / kWTile], local); };
   {
     uint32_t p = my_pos;
     int it = int(ex >> 32);
     DD s = my_s;
+    DD wp[kPer];                                 // (all loads in flight before the first store)
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      wp[q] = w_local(p);
+      p += cnt[q];
+    }
+    p = my_pos;
 #pragma unroll
     for (int q = 0; q < kPer; ++q) {
       if (cnt[q] != 0) {
         sm.pos[it] = p;
         sm.key[it] = uint32_t(tid * kPer + q);
         sm.u.i.p1[it] = s;
-        sm.u.i.pw[it] = w_prefix(p);
+        sm.u.i.pw[it] = w_prefix(p, wp[q]);
         ++it;
         p += cnt[q];
         s = dd_add(s, sum[q]);
@@ -427,12 +456,18 @@ __global__ __launch_bounds__(kNT) void general_search_kernel(
 
   // ---- 4. items: bins without a vertex inside, and the values of the others ------------------------------
   bool open[kPer];
-  uint32_t ni = 0, nc = 0;
+  uint32_t ni = 0, nc = 0, at = my_pos;
 #pragma unroll
   for (int q = 0; q < kPer; ++q) {
     open[q] = sm.bins[tid * kPer + q] != 0;
     ni += open[q] ? cnt[q] : (cnt[q] != 0 ? 1u : 0u);
     nc += open[q] ? cnt[q] : 0u;
+    // the nearest open bins around the middle of the row
+    if (open[q]) {
+      if (at + cnt[q] <= uint32_t(n) / 2) atomicMax(&sm.gap.lo, tid * kPer + q);
+      else atomicMin(&sm.gap.hi, tid * kPer + q);
+    }
+    at += cnt[q];
   }
   const unsigned long long ex2 = scan_u64((unsigned long long)nc << 32 | ni, sm.wave_u, &tot64);
   const uint32_t cands = uint32_t(tot64 >> 32);
@@ -461,10 +496,18 @@ __global__ __launch_bounds__(kNT) void general_search_kernel(
     }
   }
   __syncthreads();
+  // bins strictly between these hold no separate values (most of the row: neither pass below looks
+  // them up one by one)
+  const int open_lo = sm.gap.lo, open_hi = sm.gap.hi;
+  const uint32_t gap0 = uint32_t(open_lo + 1), gap_n = uint32_t(open_hi - open_lo - 1);
+  // its first and last item
+  const uint32_t l_lo = open_lo >= 0 ? lookup[2 * open_lo + 1] : 0u;
+  const int gap_first = int((l_lo & 0xffffu) + (l_lo >> 16));
+  const int gap_last = (open_hi < kSelBins ? int(lookup[2 * open_hi + 1] & 0xffffu) : T) - 1;
   if (cands != 0) {
     each_value<VEC>(x, n, [&](float v) {
       const uint32_t key = desc_key(v), b = key >> 20;
-      if (lookup[2 * b + 1] >> 16) sm.key[atomicAdd(&lookup[2 * b], 1u)] = key;
+      if (b - gap0 >= gap_n && (lookup[2 * b + 1] >> 16)) sm.key[atomicAdd(&lookup[2 * b], 1u)] = key;
     });
     __syncthreads();
     // order inside a bin by counting (a few dozen values: the row's weights separate the rest)
@@ -510,6 +553,15 @@ __global__ __launch_bounds__(kNT) void general_search_kernel(
       vs = dd_add(vs, v[r]);
     }
     uint32_t p = uint32_t(scan_u64(cs, sm.wave_u, &tot64));
+    DD wp[3];
+    {
+      uint32_t q = p;
+#pragma unroll
+      for (int r = 0; r < 3; ++r) {
+        wp[r] = w_local(q);
+        q += c[r];
+      }
+    }
     DD s = scan_dd<kNW>(vs, sm.wave_dd, &total_s);
 #pragma unroll
     for (int r = 0; r < 3; ++r) {
@@ -517,7 +569,7 @@ __global__ __launch_bounds__(kNT) void general_search_kernel(
       if (t < T) {
         sm.pos[t] = p;
         sm.u.i.p1[t] = s;
-        sm.u.i.pw[t] = w_prefix(p);
+        sm.u.i.pw[t] = w_prefix(p, wp[r]);
       }
       p += c[r];
       s = dd_add(s, v[r]);
@@ -556,8 +608,14 @@ __global__ __launch_bounds__(kNT) void general_search_kernel(
   __syncthreads();
 
   // ---- 5. outputs y = (s - gamma) / lambda --------------------------------------------------------------
+  // (pooled values never rise from item to item: equal at both ends, equal in between)
+  const bool one_block = gap_first <= gap_last && gi[gap_first] == gi[gap_last];
+  const double gap_gamma = one_block ? gi[gap_first] : 0.0;
+  const uint32_t same_n = one_block ? gap_n : 0u;
   auto value = [&](float v) -> float {
-    const uint32_t key = desc_key(v), l = lookup[2 * (key >> 20) + 1];
+    const uint32_t key = desc_key(v);
+    if ((key >> 20) - gap0 < same_n) return float((double(v + 0.0f) - gap_gamma) * inv_lambda);
+    const uint32_t l = lookup[2 * (key >> 20) + 1];
     uint32_t at = l & 0xffffu;
     if (l >> 16) {
       uint32_t end = at + (l >> 16);             // first item of the bin whose key is not smaller
@@ -570,15 +628,15 @@ __global__ __launch_bounds__(kNT) void general_search_kernel(
     return float((double(v + 0.0f) - gi[at]) * inv_lambda);
   };
   if constexpr (VEC) {
-    for (int e0 = 4 * tid; e0 < n; e0 += 16 * kNT) {
-      float4 q[4];
+    for (int e0 = 4 * tid; e0 < n; e0 += 32 * kNT) {
+      float4 q[8];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
+      for (int i = 0; i < 8; ++i) {
         q[i] = make_float4(0.f, 0.f, 0.f, 0.f);
         if (e0 + i * 4 * kNT < n) q[i] = *reinterpret_cast<const float4*>(x + e0 + i * 4 * kNT);
       }
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+      for (int i = 0; i < 8; ++i)
         if (e0 + i * 4 * kNT < n)
           *reinterpret_cast<float4*>(out + e0 + i * 4 * kNT) =
               make_float4(value(q[i].x), value(q[i].y), value(q[i].z), value(q[i].w));
