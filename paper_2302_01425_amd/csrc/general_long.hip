@@ -23,9 +23,6 @@ namespace {
 
 constexpr int kGT = 1024;                      // threads of the workgroup
 constexpr int kGW = kGT / kWave;               // wavefronts
-constexpr uint32_t kHiBits = 18;               // block ends are kept in 18 bits, a round stamp above
-constexpr uint32_t kHiMask = (1u << kHiBits) - 1u;
-static_assert(kGeneralLongMax < (1 << kHiBits) - 1, "block ends must fit their bit field");
 static_assert(kGeneralLongMax <= 128 * kGT, "a thread keeps its block starts in 128 bits");
 
 struct Mask128 {
@@ -60,6 +57,10 @@ __device__ __forceinline__ void mask_clear(Mask128& m, int j) {
   if (j < 64) m.lo &= ~(1ull << j);
   else m.hi &= ~(1ull << (j - 64));
 }
+__device__ __forceinline__ void mask_set(Mask128& m, int j) {
+  if (j < 64) m.lo |= 1ull << j;
+  else m.hi |= 1ull << (j - 64);
+}
 __device__ __forceinline__ bool mask_test(const Mask128& m, int j) {
   return j < 64 ? ((m.lo >> j) & 1ull) != 0 : ((m.hi >> (j - 64)) & 1ull) != 0;
 }
@@ -68,6 +69,7 @@ struct ScanShared {
   DD d[4][kGW];
   double q[2][kGW];
   int first[kGW], last[kGW];
+  double edge[kGT];                          // pooled value of the last element of every thread
 };
 
 // exclusive prefix sum over the threads of the workgroup (one value per thread)
@@ -171,8 +173,16 @@ __global__ __launch_bounds__(kGT) void general_long_kernel(
   double* Q3 = CUBIC ? reinterpret_cast<double*>(P3) : nullptr;
   double* G = gb.g + qbase;                    // pooled value by block start
   double* DG = gb.dg + qbase;                  // d gamma by block start
-  uint32_t* hi_of = gb.hi_of + base;           // (round stamp, end of the block G[lo] was computed for)
+  uint32_t* hi_of = gb.hi_of + base;           // stack of the sequential walk
   float* ltau = gb.ltau + base;                // tangent in sorted coordinates
+
+  Mask128 hm{0ull, 0ull};                      // block starts among my positions (bit j: p0 + j)
+  if (own >= 64) {
+    hm.lo = ~0ull;
+    hm.hi = own >= 128 ? ~0ull : ((1ull << (own - 64)) - 1ull);
+  } else {
+    hm.lo = (1ull << own) - 1ull;
+  }
 
   // ---- 1. prefix sums; keys -> values; tangent into sorted coordinates ----------------------------
   {
@@ -182,10 +192,14 @@ __global__ __launch_bounds__(kGT) void general_long_kernel(
       t1 = dd_add(t1, sd);
       tw = dd_add(tw, wd);
       if (CUBIC) { t2 = dd_add(t2, sd * sd); t3 = dd_add(t3, sd * sd * sd); }
+      if (!CUBIC && j == own - 1)
+        sm.edge[t] = block_gamma<MAG, CUBIC>(Blk{1.0, wd, sd, 0.0, 0.0}, sd, sd, R);
     }
     DD r1 = block_exclusive_scan(t1, sm.d[0]), rw = block_exclusive_scan(tw, sm.d[1]);
     DD r2{0.0, 0.0}, r3{0.0, 0.0};
     if (CUBIC) { r2 = block_exclusive_scan(t2, sm.d[2]); r3 = block_exclusive_scan(t3, sm.d[3]); }
+    // (the scans' barriers have made the edges visible; threads before one with positions own some too)
+    double left = t > 0 && own > 0 ? sm.edge[t - 1] : 0.0;
     for (int j = 0; j < own; ++j) {
       const int pos = p0 + j;
       const float sv = key_to_float(keys[pos]);
@@ -193,6 +207,12 @@ __global__ __launch_bounds__(kGT) void general_long_kernel(
       PW[pos] = rw;
       if (CUBIC) { P2[pos] = r2; P3[pos] = r3; }
       const double sd = double(sv), wd = double(lw[pos]);
+      if (!CUBIC) {                            // the first round, between single elements
+        const double g = block_gamma<MAG, CUBIC>(Blk{1.0, wd, sd, 0.0, 0.0}, sd, sd, R);
+        G[pos] = g;
+        if (pos > 0 && left < g) mask_clear(hm, j);
+        left = g;
+      }
       r1 = dd_add(r1, sd);
       rw = dd_add(rw, wd);
       if (CUBIC) { r2 = dd_add(r2, sd * sd); r3 = dd_add(r3, sd * sd * sd); }
@@ -232,54 +252,66 @@ __global__ __launch_bounds__(kGT) void general_long_kernel(
   };
 
   // ---- 2. pool adjacent violators in rounds ----------------------------------------------------------
-  Mask128 hm{0ull, 0ull};                      // block starts among my positions (bit j: p0 + j)
-  if (own >= 64) {
-    hm.lo = ~0ull;
-    hm.hi = own >= 128 ? ~0ull : ((1ull << (own - 64)) - 1ull);
-  } else {
-    hm.lo = (1ull << own) - 1ull;
-  }
+  // Blocks whose end has moved since the last round have a new pooled value; a boundary between two
+  // blocks that are both those of the last round was tested then.  (p = 2: the first round is over,
+  // blocks of one element have theirs.)
   bool gave_up = false;
-  for (int round = 0;; ++round) {
-    const uint32_t stamp = uint32_t(round) & ((1u << (32 - kHiBits)) - 1u);
+  Mask128 moved = hm;                          // my blocks that are to be computed
+  int nxt_seen = -2;
+  for (int round = CUBIC ? 0 : 1;; ++round) {
+    if (round >= max_rounds) { gave_up = true; break; }
     const int jf = mask_first(hm), jl = mask_last(hm);
-    int nxt, prv;
-    block_neighbours(jf >= 0 ? p0 + jf : n, jl >= 0 ? p0 + jl : -1, n, sm, &nxt, &prv);
-    // pooled value of every block that is not the one of the last round
-    for (int j = jf; j >= 0;) {
+    int nxt, prv, none;
+    block_neighbours(jf >= 0 ? p0 + jf : n, -1, n, sm, &nxt, &none);
+    if (nxt_seen == -2) {
+      if (!CUBIC) {                            // every block of more than one element
+        moved.lo = hm.lo & ~((hm.lo >> 1) | (hm.hi << 63));
+        moved.hi = hm.hi & ~(hm.hi >> 1);
+        if (jl >= 0 && nxt == p0 + jl + 1) mask_clear(moved, jl);
+      }
+    } else if (jl >= 0 && nxt != nxt_seen) {
+      mask_set(moved, jl);
+    }
+    nxt_seen = nxt;
+    // last block start in the threads before, and whether that block is new
+    block_neighbours(n, jl >= 0 ? 2 * (p0 + jl) + int(mask_test(moved, jl)) : -1, n, sm, &none, &prv);
+    Mask128 test = moved;                      // boundaries next to a moved block
+    if (jf >= 0 && prv >= 0 && (prv & 1)) mask_set(test, jf);
+    for (int j = mask_first(moved); j >= 0; j = mask_next(moved, j)) {
       const int jn = mask_next(hm, j);
       const int lo = p0 + j, hi = jn >= 0 ? p0 + jn : nxt;
-      if (round == 0 || int(hi_of[lo] & kHiMask) != hi) {
-        hi_of[lo] = (stamp << kHiBits) | uint32_t(hi);
-        G[lo] = block_gamma<MAG, CUBIC>(block_sums(lo, hi), double(ss[lo]), double(ss[hi - 1]), R);
-      }
-      j = jn;
+      G[lo] = block_gamma<MAG, CUBIC>(block_sums(lo, hi), double(ss[lo]), double(ss[hi - 1]), R);
+      if (jn >= 0) mask_set(test, jn);
     }
     __syncthreads();
-    // every boundary whose two blocks violate goes; a boundary between two blocks that are both
-    // those of the last round was tested then
     Mask128 keep = hm;
-    for (int j = jf; j >= 0;) {
-      const int jn = mask_next(hm, j);
-      const int lo = p0 + j, hi = jn >= 0 ? p0 + jn : nxt;
+    for (int j = mask_first(test); j >= 0; j = mask_next(test, j)) {
+      const int lo = p0 + j;
       const int jp = mask_prev(hm, j);
-      const int p = jp >= 0 ? p0 + jp : prv;
-      if (p >= 0 && ((hi_of[p] >> kHiBits) == stamp || (hi_of[lo] >> kHiBits) == stamp)) {
-        bool viol;
-        if (!CUBIC) viol = G[p] < G[lo];
-        else viol = blocks_violate<MAG, CUBIC>(block_sums(p, lo), G[p], block_sums(lo, hi), G[lo], R);
-        if (viol) mask_clear(keep, j);
+      const int p = jp >= 0 ? p0 + jp : (prv >= 0 ? prv >> 1 : -1);
+      if (p < 0) continue;                     // the first block of the row
+      bool viol;
+      if (!CUBIC) viol = G[p] < G[lo];
+      else {
+        const int jn = mask_next(hm, j);
+        const int hi = jn >= 0 ? p0 + jn : nxt;
+        viol = blocks_violate<MAG, CUBIC>(block_sums(p, lo), G[p], block_sums(lo, hi), G[lo], R);
       }
-      j = jn;
+      if (viol) mask_clear(keep, j);
     }
-    const bool changed = keep.lo != hm.lo || keep.hi != hm.hi;
+    const Mask128 gone{hm.lo & ~keep.lo, hm.hi & ~keep.hi};
+    moved = Mask128{0ull, 0ull};               // blocks that stay and whose next start goes
+    for (int j = mask_first(gone); j >= 0; j = mask_next(gone, j)) {
+      const int jp = mask_prev(keep, j);
+      if (jp >= 0) mask_set(moved, jp);
+    }
     hm = keep;
-    if (!__syncthreads_or(changed)) break;
-    if (round + 1 >= max_rounds) { gave_up = true; break; }
+    if (!__syncthreads_or((gone.lo | gone.hi) != 0ull)) break;
   }
 
   if (gave_up) {
     // ---- too many rounds: the left-to-right block stack, one thread ---------------------------------
+    for (int j = 0; j < own; ++j) hi_of[p0 + j] = 0u;          // no mark but those of the walk
     __syncthreads();
     if (t == 0)
       stack_walk<MAG, CUBIC, uint32_t>(n, ss, lw, ltau, jvp != nullptr, Q1, QW, G, Q2, Q3, hi_of,
