@@ -45,67 +45,6 @@ namespace {
 
 constexpr int kSearchPlain = 0, kSearchSigned = 1, kSearchMasked = 2, kSearchLoss = 3;
 
-// ---- wavefront reductions (all 64 lanes; the result is uniform) ---------------------------------
-template <int CTRL, int ROWS>
-__device__ __forceinline__ uint32_t dpp_or0(uint32_t v) {
-  return uint32_t(__builtin_amdgcn_update_dpp(0, int(v), CTRL, ROWS, 0xF, false));
-}
-template <int CTRL, int ROWS>
-__device__ __forceinline__ float dpp_or0_f32(float v) {
-  return __uint_as_float(dpp_or0<CTRL, ROWS>(__float_as_uint(v)));
-}
-template <int CTRL, int ROWS>
-__device__ __forceinline__ double dpp_or0_f64(double v) {
-  const uint32_t lo = dpp_or0<CTRL, ROWS>(uint32_t(__double2loint(v)));
-  const uint32_t hi = dpp_or0<CTRL, ROWS>(uint32_t(__double2hiint(v)));
-  return __hiloint2double(int(hi), int(lo));
-}
-__device__ __forceinline__ float uniform_f32(float v, int lane) {
-  return __uint_as_float(uint32_t(__builtin_amdgcn_readlane(int(__float_as_uint(v)), lane)));
-}
-__device__ __forceinline__ double uniform_f64(double v, int lane) {
-  const int lo = __builtin_amdgcn_readlane(__double2loint(v), lane);
-  const int hi = __builtin_amdgcn_readlane(__double2hiint(v), lane);
-  return __hiloint2double(hi, lo);
-}
-// sums over the first LANES lanes of every wavefront (64, or a power of two up to 16)
-template <int LANES>
-__device__ __forceinline__ float lanes_sum(float v) {
-  if constexpr (LANES >= 2) v += dpp_or0_f32<0x111, 0xF>(v);       // row_shr:1
-  if constexpr (LANES >= 4) v += dpp_or0_f32<0x112, 0xF>(v);
-  if constexpr (LANES >= 8) v += dpp_or0_f32<0x114, 0xF>(v);
-  if constexpr (LANES >= 16) v += dpp_or0_f32<0x118, 0xF>(v);
-  if constexpr (LANES == 64) {
-    v += dpp_or0_f32<0x142, 0xA>(v);                               // row_bcast:15
-    v += dpp_or0_f32<0x143, 0xC>(v);                               // row_bcast:31
-  }
-  return uniform_f32(v, LANES - 1);
-}
-template <int LANES>
-__device__ __forceinline__ double lanes_sum(double v) {
-  if constexpr (LANES >= 2) v += dpp_or0_f64<0x111, 0xF>(v);
-  if constexpr (LANES >= 4) v += dpp_or0_f64<0x112, 0xF>(v);
-  if constexpr (LANES >= 8) v += dpp_or0_f64<0x114, 0xF>(v);
-  if constexpr (LANES >= 16) v += dpp_or0_f64<0x118, 0xF>(v);
-  if constexpr (LANES == 64) {
-    v += dpp_or0_f64<0x142, 0xA>(v);
-    v += dpp_or0_f64<0x143, 0xC>(v);
-  }
-  return uniform_f64(v, LANES - 1);
-}
-template <int LANES>
-__device__ __forceinline__ uint32_t lanes_sum(uint32_t v) {
-  if constexpr (LANES >= 2) v += dpp_or0<0x111, 0xF>(v);
-  if constexpr (LANES >= 4) v += dpp_or0<0x112, 0xF>(v);
-  if constexpr (LANES >= 8) v += dpp_or0<0x114, 0xF>(v);
-  if constexpr (LANES >= 16) v += dpp_or0<0x118, 0xF>(v);
-  if constexpr (LANES == 64) {
-    v += dpp_or0<0x142, 0xA>(v);
-    v += dpp_or0<0x143, 0xC>(v);
-  }
-  return uint32_t(__builtin_amdgcn_readlane(int(v), LANES - 1));
-}
-
 // What the group reduces.  NT > 64: the wavefronts' partial results meet in LDS, in two buffers used
 // in turn, so that one barrier per reduction suffices (a wavefront writes a buffer again only after
 // the barrier of the reduction in between, which every reader of the buffer has reached).

@@ -17,20 +17,30 @@
 #include "long_solve.hpp"
 #include "pooling.hpp"
 #include "radix.hpp"
+#include "wave.hpp"
 
 namespace topk {
 
 constexpr int kWT = 1024;                      // threads
 constexpr int kWW = kWT / kWave;               // wavefronts
 constexpr int kWideBuckets = 8192;             // buckets of the one-pass sort
+// p = 2: longer lists are solved without sorting them although they fit (9037 keys: sort and growth 17.6 us,
+// selection and three classifications 13; 500 keys: about the same).  For p = 4/3 a classification
+// costs three power sums and a root: 4 x 977322, 14000 keys, 76 us a call with the sort, 88 without.
+constexpr uint32_t kSortedMax = 4096;
 constexpr int kBucketMax = 32;                 // longest bucket the one-pass sort orders by counting
 
 // CAP: keys of a list that is sorted and solved in LDS (a multiple of 16 * 1024 / 2).
 template <int CAP>
 struct ListShared {
   static constexpr int kCap = CAP;
-  uint32_t keys_a[CAP];                // the list's keys; the sorted keys end here
-  uint32_t keys_b[CAP];                // tile offsets during the gather, then sort buffer
+  union {
+    struct {
+      uint32_t keys_a[CAP];            // the list's keys; the sorted keys end here
+      uint32_t keys_b[CAP];            // tile offsets during the gather, then sort buffer
+    };
+    uint32_t keys[2 * CAP];            // the first keys of a list that is not sorted
+  };
   union {
     uint32_t bucket[kWideBuckets / 2];         // two 16-bit counters / offsets per word
     uint32_t cnt[kWW][kRadix];                 // radix passes: per-wave digit counts / offsets
@@ -539,55 +549,19 @@ __device__ RowInfo wide_solve(const uint32_t* keys, uint32_t cn_u, int64_t k64, 
 // block-wide sum of two doubles (every thread gets the totals)
 template <int CAP>
 __device__ __forceinline__ void wide_sum2(double& x, double& y, ListShared<CAP>& sm) {
-#pragma unroll
-  for (int off = kWave >> 1; off >= 1; off >>= 1) {
-    x += __shfl_xor(x, off, kWave);
-    y += __shfl_xor(y, off, kWave);
-  }
+  x = lanes_sum<kWave>(x);
+  y = lanes_sum<kWave>(y);
   __syncthreads();
   if ((threadIdx.x & (kWave - 1)) == 0) sm.wave_sums[threadIdx.x / kWave] = Sums{x, y, 0.0};
   __syncthreads();
-  x = y = 0.0;
-#pragma unroll
-  for (int q = 0; q < kWW; ++q) {
-    x += sm.wave_sums[q].s1;
-    y += sm.wave_sums[q].s2;
-  }
+  const Sums s = sm.wave_sums[threadIdx.x & (kWW - 1)];
+  x = lanes_sum<kWW>(s.s1);
+  y = lanes_sum<kWW>(s.s2);
 }
 
 
 
-// d gamma (Prop. 7) from the row's unsorted list in global memory (keys, tangent bits): the
-// block's elements are those whose value lies in [lo_incl, hi_incl].
-template <bool MAG, int PC, int CAP>
-__device__ __forceinline__ double list_dgamma(const uint32_t* ka, const uint32_t* pa, uint32_t cn,
-                                              const RowInfo& ri, int64_t k, const Reg& R,
-                                              ListShared<CAP>& sm) {
-  using P = Pool<MAG, PC>;
-  double num = 0.0, den = 0.0;
-  for (uint32_t j0 = threadIdx.x; j0 < cn; j0 += 4 * kWT) {
-    uint32_t key[4], pay[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const uint32_t j = j0 + uint32_t(i) * kWT;
-      key[i] = j < cn ? ka[j] : 0u;
-      pay[i] = j < cn ? pa[j] : 0u;
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const float sv = key_to_float(key[i]);
-      if (j0 + uint32_t(i) * kWT < cn && sv >= ri.lo_incl && sv <= ri.hi_incl) {
-        const double wgt = P::jac_weight(double(sv) - ri.center, ri.gamma);
-        num += wgt * double(__uint_as_float(pay[i]));
-        den += wgt;
-      }
-    }
-  }
-  wide_sum2(num, den, sm);
-  return num / P::jac_denominator(den, double(k - ri.a + 1), R);
-}
-
-// ---- lists that do not fit the LDS buffers: solved WITHOUT sorting them ---------------------------
+// ---- long lists: solved WITHOUT sorting them -----------------------------------------------------------
 // The block is a set of values: with gamma its pooled value, a candidate above s_k belongs to it
 // iff its singleton minimiser lies below gamma, one below s_{k+1} iff its value lies above gamma
 // (the tests of the growth, which hold for every member of the final block and fail for every
@@ -600,13 +574,34 @@ __device__ __forceinline__ double list_dgamma(const uint32_t* ka, const uint32_t
 // bracket [lo, hi] from the signs seen so far (g' > g means Psi(g) > 0) guards the iteration.
 // s_k and s_{k+1} come from a radix selection on the keys (11 bits per pass).
 
-// key of rank r (1-based) in ascending key order among list[0, cn); also the number of keys
-// below it and the number equal to it
+// The list that the passes go over: its first `near` keys in LDS (2 CAP of them at most), the others in global memory.  (36669 keys: a pass from global memory alone, eight
+// loads in flight, takes 8 us, 5 of them waiting.)
+struct KeyList {
+  const uint32_t* lds;
+  const uint32_t* mem;
+  uint32_t near, cn;
+  __device__ __forceinline__ uint32_t at(uint32_t j) const { return j < near ? lds[j] : mem[j]; }
+  template <class F>
+  __device__ __forceinline__ void each(F f) const {
+#pragma unroll 4
+    for (uint32_t j = threadIdx.x; j < near; j += kWT) f(lds[j]);
+    for (uint32_t j0 = near + threadIdx.x; j0 < cn; j0 += 8 * kWT) {     // eight loads in flight
+      uint32_t key[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) key[i] = j0 + uint32_t(i) * kWT < cn ? mem[j0 + uint32_t(i) * kWT] : 0u;
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        if (j0 + uint32_t(i) * kWT < cn) f(key[i]);
+    }
+  }
+};
+
+// key of rank r (1-based) in ascending key order of the list; also the number of keys below it and
+// the number equal to it
 template <int CAP>
-__device__ uint32_t list_select(const uint32_t* list, uint32_t cn, uint32_t klo, int nbits,
-                                uint32_t rank, uint32_t* below_out, uint32_t* equal_out,
-                                ListShared<CAP>& sm) {
-  uint32_t prefix = 0, pmask = 0, r = rank - 1, equal = cn;   // r: 0-based rank among the matches
+__device__ uint32_t list_select(const KeyList& list, uint32_t klo, int nbits, uint32_t rank,
+                                uint32_t* below_out, uint32_t* equal_out, ListShared<CAP>& sm) {
+  uint32_t prefix = 0, pmask = 0, r = rank - 1, equal = list.cn;   // r: 0-based rank among the matches
   for (int top = nbits; top > 0;) {
     const int width = top < 11 ? top : 11;
     const int shift = top - width;
@@ -614,17 +609,10 @@ __device__ uint32_t list_select(const uint32_t* list, uint32_t cn, uint32_t klo,
     uint32_t* hist = sm.u.bucket;
     for (uint32_t i = threadIdx.x; i < bins; i += kWT) hist[i] = 0;
     __syncthreads();
-    for (uint32_t j0 = threadIdx.x; j0 < cn; j0 += 8 * kWT) {     // eight loads in flight
-      uint32_t key[8];
-#pragma unroll
-      for (int i = 0; i < 8; ++i) key[i] = j0 + uint32_t(i) * kWT < cn ? list[j0 + uint32_t(i) * kWT] : 0u;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const uint32_t u = key[i] - klo;
-        if (j0 + uint32_t(i) * kWT < cn && (u & pmask) == prefix)
-          atomicAdd(&hist[(u >> shift) & (bins - 1u)], 1u);
-      }
-    }
+    list.each([&](uint32_t key) {
+      const uint32_t u = key - klo;
+      if ((u & pmask) == prefix) atomicAdd(&hist[(u >> shift) & (bins - 1u)], 1u);
+    });
     __syncthreads();
     const uint32_t b0 = 2u * threadIdx.x, b1 = b0 + 1u;       // two bins per thread (2048 at most)
     const uint32_t c0 = b0 < bins ? hist[b0] : 0u, c1 = b1 < bins ? hist[b1] : 0u;
@@ -647,7 +635,8 @@ __device__ uint32_t list_select(const uint32_t* list, uint32_t cn, uint32_t klo,
 
 struct SetStats {
   uint32_t above, cnt;       // candidates above the set, members of the set
-  uint32_t kmin, kmax;       // smallest / largest key of the set (its largest / smallest value)
+  uint32_t kmin, kmax;       // smallest / largest key of the set (its largest / smallest value); for
+                             // p = 2 the thresholds: every key from kmin to kmax is a member
   Sums S;                    // power sums of the members' centred values
 };
 
@@ -668,8 +657,8 @@ __device__ __forceinline__ uint32_t last_key_above(double T) {
 // (magnitude, p = 4/3: where the one-element cubic at g changes sign); one below s_{k+1} iff its
 // value lies above g; the values from s_{k+1} to s_k (keys kk .. kk1) always.
 template <bool MAG, int PC, int CAP>
-__device__ SetStats list_classify(const uint32_t* list, uint32_t cn, uint32_t kk, uint32_t kk1,
-                                  double g, double center, const Reg& R, ListShared<CAP>& sm) {
+__device__ SetStats list_classify(const KeyList& list, uint32_t kk, uint32_t kk1, double g,
+                                  double center, const Reg& R, ListShared<CAP>& sm) {
   constexpr bool CUBIC = (PC == kP43);
   const double g_abs = g + center;
   double t_hi;
@@ -680,36 +669,30 @@ __device__ SetStats list_classify(const uint32_t* list, uint32_t cn, uint32_t kk
   const uint32_t k_last = max(last_key_above(g_abs), kk1);
   uint32_t above = 0, cnt = 0, kmin = 0xffffffffu, kmax = 0u;
   Sums S{0.0, 0.0, 0.0};
-  for (uint32_t j0 = threadIdx.x; j0 < cn; j0 += 8 * kWT) {     // eight loads in flight
-    uint32_t key[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-      key[i] = j0 + uint32_t(i) * kWT < cn ? list[j0 + uint32_t(i) * kWT] : 0xffffffffu;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const bool real = j0 + uint32_t(i) * kWT < cn;
-      const bool in = real && key[i] >= k_first && key[i] <= k_last;
-      above += (real && key[i] < k_first) ? 1u : 0u;
-      if (in) {
-        ++cnt;
-        kmin = min(kmin, key[i]);
-        kmax = max(kmax, key[i]);
-        const double d = double(key_to_float(key[i])) - center;
-        S.s1 += d;
-        if (CUBIC) { S.s2 += d * d; S.s3 += d * d * d; }
+  list.each([&](uint32_t key) {
+    above += key < k_first ? 1u : 0u;
+    if (key >= k_first && key <= k_last) {
+      ++cnt;
+      if (CUBIC) {                             // (p = 2 needs no bracket, and the ends as thresholds only)
+        kmin = min(kmin, key);
+        kmax = max(kmax, key);
       }
+      const double d = double(key_to_float(key)) - center;
+      S.s1 += d;
+      if (CUBIC) { S.s2 += d * d; S.s3 += d * d * d; }
     }
-  }
+  });
+  // (the wavefronts' results are read one per lane: sixteen LDS reads of each by every wavefront and
+  // shuffles through LDS took 5 us of a pass)
   const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
-#pragma unroll
-  for (int off = kWave >> 1; off >= 1; off >>= 1) {
-    above += __shfl_xor(above, off, kWave);
-    cnt += __shfl_xor(cnt, off, kWave);
-    kmin = min(kmin, uint32_t(__shfl_xor(kmin, off, kWave)));
-    kmax = max(kmax, uint32_t(__shfl_xor(kmax, off, kWave)));
-    S.s1 += __shfl_xor(S.s1, off, kWave);
-    if (CUBIC) { S.s2 += __shfl_xor(S.s2, off, kWave); S.s3 += __shfl_xor(S.s3, off, kWave); }
+  above = lanes_sum<kWave>(above);
+  cnt = lanes_sum<kWave>(cnt);
+  if (CUBIC) {
+    kmin = lanes_min<kWave>(kmin);
+    kmax = lanes_max<kWave>(kmax);
   }
+  S.s1 = lanes_sum<kWave>(S.s1);
+  if (CUBIC) { S.s2 = lanes_sum<kWave>(S.s2); S.s3 = lanes_sum<kWave>(S.s3); }
   __syncthreads();
   if (lane == 0) {
     sm.red[0][w] = above;
@@ -719,25 +702,55 @@ __device__ SetStats list_classify(const uint32_t* list, uint32_t cn, uint32_t kk
     sm.wave_sums[w] = S;
   }
   __syncthreads();
-  SetStats st{0u, 0u, 0xffffffffu, 0u, Sums{0.0, 0.0, 0.0}};
-#pragma unroll
-  for (int q = 0; q < kWW; ++q) {
-    st.above += sm.red[0][q];
-    st.cnt += sm.red[1][q];
-    st.kmin = min(st.kmin, sm.red[2][q]);
-    st.kmax = max(st.kmax, sm.red[3][q]);
-    st.S.s1 += sm.wave_sums[q].s1;
-    if (CUBIC) { st.S.s2 += sm.wave_sums[q].s2; st.S.s3 += sm.wave_sums[q].s3; }
-  }
+  const int q = lane & (kWW - 1);
+  SetStats st;
+  st.above = lanes_sum<kWW>(sm.red[0][q]);
+  st.cnt = lanes_sum<kWW>(sm.red[1][q]);
+  // (0x80000000 would be -0.0, which compares equal to the +0.0 it excludes; no value has that key)
+  st.kmin = CUBIC ? lanes_min<kWW>(sm.red[2][q]) : (k_first == 0x80000000u ? 0x80000001u : k_first);
+  st.kmax = CUBIC ? lanes_max<kWW>(sm.red[3][q]) : k_last;
+  S = sm.wave_sums[q];
+  st.S = Sums{lanes_sum<kWW>(S.s1), 0.0, 0.0};
+  if (CUBIC) { st.S.s2 = lanes_sum<kWW>(S.s2); st.S.s3 = lanes_sum<kWW>(S.s3); }
   return st;
 }
 
-// The row's unsorted candidate list (keys ka, tangent payload pa) -> RowInfo in list coordinates.
+// d gamma (Prop. 7) from the row's unsorted list and its tangent (pa, by list position): the block's
+// elements are those whose value lies in [lo_incl, hi_incl].
 template <bool MAG, int PC, int CAP>
-__device__ RowInfo solve_unsorted_list(const uint32_t* ka, const uint32_t* pa, uint32_t cn,
-                                       int64_t k64, uint32_t klo, uint32_t khi, const Reg& R,
-                                       bool want_jvp, ListShared<CAP>& sm) {
+__device__ __forceinline__ double list_dgamma(const KeyList& list, const uint32_t* pa, const RowInfo& ri,
+                                              int64_t k, const Reg& R, ListShared<CAP>& sm) {
   using P = Pool<MAG, PC>;
+  double num = 0.0, den = 0.0;
+  for (uint32_t j0 = threadIdx.x; j0 < list.cn; j0 += 12 * kWT) {       // twelve loads in flight
+    uint32_t pay[12];
+#pragma unroll
+    for (int i = 0; i < 12; ++i) {
+      const uint32_t j = j0 + uint32_t(i) * kWT;
+      pay[i] = j < list.cn ? pa[j] : 0u;
+    }
+#pragma unroll
+    for (int i = 0; i < 12; ++i) {
+      const uint32_t j = j0 + uint32_t(i) * kWT;
+      const float sv = key_to_float(j < list.cn ? list.at(j) : 0u);
+      if (j < list.cn && sv >= ri.lo_incl && sv <= ri.hi_incl) {
+        const double wgt = P::jac_weight(double(sv) - ri.center, ri.gamma);
+        num += wgt * double(__uint_as_float(pay[i]));
+        den += wgt;
+      }
+    }
+  }
+  wide_sum2(num, den, sm);
+  return num / P::jac_denominator(den, double(k - ri.a + 1), R);
+}
+
+// The row's unsorted candidate list -> RowInfo in list coordinates.  pa: its tangent by list position,
+// null when d gamma is not wanted (or is the caller's).
+template <bool MAG, int PC, int CAP>
+__device__ RowInfo solve_unsorted_list(const KeyList& list, const uint32_t* pa, int64_t k64, uint32_t klo,
+                                       uint32_t khi, const Reg& R, ListShared<CAP>& sm) {
+  using P = Pool<MAG, PC>;
+  const uint32_t cn = list.cn;
   const int64_t k = k64;
   RowInfo ri;
   ri.src = 0;
@@ -756,22 +769,18 @@ __device__ RowInfo solve_unsorted_list(const uint32_t* ka, const uint32_t* pa, u
   const int nbits = span == 0 ? 0 : 32 - __clz(int(span));
   // s_k and s_{k+1}: the keys of ranks k and k + 1
   uint32_t below, equal;
-  const uint32_t kk = list_select<CAP>(ka, cn, klo, nbits, uint32_t(k), &below, &equal, sm);
+  const uint32_t kk = list_select<CAP>(list, klo, nbits, uint32_t(k), &below, &equal, sm);
   uint32_t kk1 = kk;
   if (uint32_t(k) + 1u > below + equal) {       // rank k + 1 is the next larger key
     uint32_t nk = 0xffffffffu;
-    for (uint32_t j = threadIdx.x; j < cn; j += kWT) {
-      const uint32_t key = ka[j];
+    list.each([&](uint32_t key) {
       if (key > kk) nk = min(nk, key);
-    }
-#pragma unroll
-    for (int off = kWave >> 1; off >= 1; off >>= 1) nk = min(nk, uint32_t(__shfl_xor(nk, off, kWave)));
+    });
+    nk = lanes_min<kWave>(nk);
     __syncthreads();
     if ((threadIdx.x & (kWave - 1)) == 0) sm.red[0][threadIdx.x / kWave] = nk;
     __syncthreads();
-#pragma unroll
-    for (int q = 0; q < kWW; ++q) nk = min(nk, sm.red[0][q]);
-    kk1 = nk;
+    kk1 = lanes_min<kWW>(sm.red[0][threadIdx.x & (kWW - 1)]);
   }
   const float fk = key_to_float(kk), fk1 = key_to_float(kk1);
   const double center = P::kCentered ? double(fk) : 0.0;
@@ -796,7 +805,7 @@ __device__ RowInfo solve_unsorted_list(const uint32_t* ka, const uint32_t* pa, u
   double lo = -1e300, hi = 1e300;
   bool from_piece = false;                      // g is the root of the piece classified last
   for (int it = 0; it < 200; ++it) {
-    const SetStats nx = list_classify<MAG, PC, CAP>(ka, cn, kk, kk1, g, center, R, sm);
+    const SetStats nx = list_classify<MAG, PC, CAP>(list, kk, kk1, g, center, R, sm);
     const bool same = nx.above == st.above && nx.cnt == st.cnt;
     st = nx;
     if (same && from_piece) break;              // the set at its own pooled value: done
@@ -813,7 +822,7 @@ __device__ RowInfo solve_unsorted_list(const uint32_t* ka, const uint32_t* pa, u
   ri.gamma = g;
   ri.hi_incl = key_to_float(st.kmin);
   ri.lo_incl = key_to_float(st.kmax);
-  if (want_jvp) ri.dgamma = list_dgamma<MAG, PC, CAP>(ka, pa, cn, ri, k, R, sm);
+  if (pa != nullptr) ri.dgamma = list_dgamma<MAG, PC, CAP>(list, pa, ri, k, R, sm);
   return ri;
 }
 
@@ -821,6 +830,8 @@ __device__ RowInfo solve_unsorted_list(const uint32_t* ka, const uint32_t* pa, u
 template <bool MAG, int PC, int CAP>
 __device__ RowInfo solve_lds_list(uint32_t cn, int64_t k, uint32_t klo, uint32_t khi, const Reg& R,
                                   ListShared<CAP>& sm) {
+  if (PC == kP2 && cn > kSortedMax)
+    return solve_unsorted_list<MAG, PC, CAP>(KeyList{sm.keys_a, nullptr, cn, cn}, nullptr, k, klo, khi, R, sm);
   const uint32_t span = khi - klo;
   const int nbits = span == 0 ? 0 : 32 - __clz(int(span));
   const uint32_t* skeys = sm.keys_a;

@@ -9,11 +9,12 @@
 //   2. copies the candidates into the row's dense list in the "a" arrays (key, index payload) and
 //      their keys into LDS (list position -> tile by bisection over the offsets);
 //   3. sorts the KEYS.  The outputs are computed from values, so no permutation is needed and
-//      equal keys may come in any order.  Lists of up to kWideLdsCap keys: one bucket pass in LDS
-//      (bucket = leading bits of key - klo, about two keys per bucket; LDS atomics hand out the
-//      places inside a bucket, a count of the smaller keys of the bucket orders them); lists
-//      whose keys crowd into few buckets take LSD radix passes in LDS.  Longer lists are not
-//      sorted at all: their block is found as a set of values (sort_solve.hpp);
+//      equal keys may come in any order.  Lists of up to kSortedMax keys (p = 4/3: kWideLdsCap): one
+//      bucket pass in LDS (bucket = leading bits of key - klo, about two keys per bucket; LDS atomics
+//      hand out the places inside a bucket, a count of the smaller keys of the bucket orders them);
+//      lists whose keys crowd into few buckets take LSD radix passes in LDS.  Longer lists are not
+//      sorted at all: their block is found as a set of values, with the first 32768 keys in LDS
+//      (sort_solve.hpp);
 //   4. grows the block on the sorted keys (long_solve.hpp);
 //   5. adds up the tangent over the block's elements, found by value in the unsorted list
 //      (Prop. 7), and writes the row's RowInfo: gamma, d gamma and the block's value window.
@@ -232,7 +233,19 @@ __global__ __launch_bounds__(kWT) void wide_finish_kernel(
       }
     }
     __syncthreads();
-    ri = solve_unsorted_list<MAG, PC, kWideLdsCap>(ka, pa, cn, k, klo, khi, R, want_jvp, sm);
+    // its first keys into LDS (twelve loads in flight)
+    const uint32_t near = min(cn, uint32_t(2 * kWideLdsCap));
+    for (uint32_t j0 = threadIdx.x; j0 < near; j0 += 12 * kWT) {
+      uint32_t key[12];
+#pragma unroll
+      for (int i = 0; i < 12; ++i) key[i] = j0 + uint32_t(i) * kWT < near ? ka[j0 + uint32_t(i) * kWT] : 0u;
+#pragma unroll
+      for (int i = 0; i < 12; ++i)
+        if (j0 + uint32_t(i) * kWT < near) sm.keys[j0 + uint32_t(i) * kWT] = key[i];
+    }
+    __syncthreads();
+    ri = solve_unsorted_list<MAG, PC, kWideLdsCap>(KeyList{sm.keys, ka, near, cn}, want_jvp ? pa : nullptr, k,
+                                                   klo, khi, R, sm);
   }
   if (threadIdx.x == 0) info[row] = ri;
 }

@@ -1,0 +1,35 @@
+"""Candidate lists of long rows that are solved without sorting them (csrc/sort_solve.hpp): list lengths
+around the largest sorted list (4096), the largest one gathered through LDS (16384) and the largest part
+held in LDS (32768); ties at the block's ends and around zero.  Oracle; bar: that of test_gpu_parity."""
+import numpy as np
+import pytest
+
+from tests.test_gpu_parity import P2, dev, gpu, host, run_case  # noqa: F401  (gpu: the fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+# n around 2^18: with and without the second histogram level
+@pytest.mark.parametrize("n", [40000, 262144, 300001])
+@pytest.mark.parametrize("width", [4000, 4200, 16000, 17000, 32700, 33500])
+def test_list_lengths(gpu, oracle, n, width):
+    r = np.random.default_rng(n + width)
+    k = n // 10
+    # uniform values: a window of 2 lambda around s_k holds about `width` elements
+    x = r.random(size=(2, n)).astype(np.float32) + 1.0
+    t = r.normal(size=x.shape).astype(np.float32)
+    lam = min(0.5 * width / n, 0.09)
+    run_case(gpu, oracle, "mask", x, t, k, P2, lam, check_perm=False)
+    run_case(gpu, oracle, "mag", x - 2.0, t, k, P2, lam, check_perm=False)
+
+
+def test_ties_at_the_ends_and_around_zero(gpu, oracle):
+    n = 60000
+    r = np.random.default_rng(9)
+    x = np.round(r.normal(size=(3, n)) * 64).astype(np.float32) / 64          # binary fractions: exact sums
+    x[1] = np.where(x[1] == 0, np.float32(-0.0), x[1])
+    t = r.normal(size=x.shape).astype(np.float32)
+    for k in (n // 2, n // 2 + 700, n // 2 - 11000, n // 5):
+        for lam in (0.125, 0.5, 1.0):
+            run_case(gpu, oracle, "mask", x, t, k, P2, lam, check_perm=False)
+            run_case(gpu, oracle, "mag", x, t, k, P2, lam, check_perm=False)
