@@ -186,7 +186,8 @@ int topk_mask_sparse_fwd(const float* theta, int64_t rows, int64_t n, int64_t k,
  *   out, jvp_out [rows][n] out (out may be NULL in the *_jvp call).
  *   Rows up to TOPK_GENERAL_ROW_MAX elements (TOPK_ERR_INVALID beyond).  Up to TOPK_SHORT_ROW_MAX
  *   elements the lanes of a wavefront build the partition of a row together and no workspace is
- *   needed; longer rows are sorted completely and then solved by one workgroup each, with
+ *   needed; longer rows are solved by one workgroup each, after a complete sort (forward of the
+ *   identity form with p = 2: without one where the values allow it), with
  *   topk_workspace_bytes(TOPK_OP_GENERAL, rows, n, 0, p) bytes of workspace (TOPK_ERR_WORKSPACE
  *   without).  The partition is built in rounds that remove all violating block boundaries at
  *   once; rows on which only one boundary violates at a time fall back to the sequential walk of
