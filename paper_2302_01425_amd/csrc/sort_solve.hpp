@@ -575,17 +575,21 @@ __device__ __forceinline__ void wide_sum2(double& x, double& y, ListShared<CAP>&
 // s_k and s_{k+1} come from a radix selection on the keys (11 bits per pass).
 
 // The list that the passes go over: its first `near` keys in LDS (2 CAP of them at most), the others in global memory.  (36669 keys: a pass from global memory alone, eight
-// loads in flight, takes 8 us, 5 of them waiting.)
+// loads in flight, takes 8 us, 5 of them waiting.)  NEAR = false: all of it in global memory (p = 4/3,
+// whose passes are bound by the power sums: with a part in LDS 4 x 4 M takes 353 us instead of 344).
+template <bool NEAR>
 struct KeyList {
   const uint32_t* lds;
   const uint32_t* mem;
   uint32_t near, cn;
-  __device__ __forceinline__ uint32_t at(uint32_t j) const { return j < near ? lds[j] : mem[j]; }
+  __device__ __forceinline__ uint32_t at(uint32_t j) const { return NEAR && j < near ? lds[j] : mem[j]; }
   template <class F>
   __device__ __forceinline__ void each(F f) const {
+    if constexpr (NEAR) {
 #pragma unroll 4
-    for (uint32_t j = threadIdx.x; j < near; j += kWT) f(lds[j]);
-    for (uint32_t j0 = near + threadIdx.x; j0 < cn; j0 += 8 * kWT) {     // eight loads in flight
+      for (uint32_t j = threadIdx.x; j < near; j += kWT) f(lds[j]);
+    }
+    for (uint32_t j0 = (NEAR ? near : 0u) + threadIdx.x; j0 < cn; j0 += 8 * kWT) {     // eight loads in flight
       uint32_t key[8];
 #pragma unroll
       for (int i = 0; i < 8; ++i) key[i] = j0 + uint32_t(i) * kWT < cn ? mem[j0 + uint32_t(i) * kWT] : 0u;
@@ -598,8 +602,8 @@ struct KeyList {
 
 // key of rank r (1-based) in ascending key order of the list; also the number of keys below it and
 // the number equal to it
-template <int CAP>
-__device__ uint32_t list_select(const KeyList& list, uint32_t klo, int nbits, uint32_t rank,
+template <int CAP, bool NEAR>
+__device__ uint32_t list_select(const KeyList<NEAR>& list, uint32_t klo, int nbits, uint32_t rank,
                                 uint32_t* below_out, uint32_t* equal_out, ListShared<CAP>& sm) {
   uint32_t prefix = 0, pmask = 0, r = rank - 1, equal = list.cn;   // r: 0-based rank among the matches
   for (int top = nbits; top > 0;) {
@@ -656,8 +660,8 @@ __device__ __forceinline__ uint32_t last_key_above(double T) {
 // below T_hi(g) = g + lambda (mask), g (1 + lambda) (magnitude, p = 2), g + lambda g^(1/3)
 // (magnitude, p = 4/3: where the one-element cubic at g changes sign); one below s_{k+1} iff its
 // value lies above g; the values from s_{k+1} to s_k (keys kk .. kk1) always.
-template <bool MAG, int PC, int CAP>
-__device__ SetStats list_classify(const KeyList& list, uint32_t kk, uint32_t kk1, double g,
+template <bool MAG, int PC, int CAP, bool NEAR>
+__device__ SetStats list_classify(const KeyList<NEAR>& list, uint32_t kk, uint32_t kk1, double g,
                                   double center, const Reg& R, ListShared<CAP>& sm) {
   constexpr bool CUBIC = (PC == kP43);
   const double g_abs = g + center;
@@ -717,22 +721,25 @@ __device__ SetStats list_classify(const KeyList& list, uint32_t kk, uint32_t kk1
 
 // d gamma (Prop. 7) from the row's unsorted list and its tangent (pa, by list position): the block's
 // elements are those whose value lies in [lo_incl, hi_incl].
-template <bool MAG, int PC, int CAP>
-__device__ __forceinline__ double list_dgamma(const KeyList& list, const uint32_t* pa, const RowInfo& ri,
+template <bool MAG, int PC, int CAP, bool NEAR>
+__device__ __forceinline__ double list_dgamma(const KeyList<NEAR>& list, const uint32_t* pa, const RowInfo& ri,
                                               int64_t k, const Reg& R, ListShared<CAP>& sm) {
   using P = Pool<MAG, PC>;
   double num = 0.0, den = 0.0;
-  for (uint32_t j0 = threadIdx.x; j0 < list.cn; j0 += 12 * kWT) {       // twelve loads in flight
-    uint32_t pay[12];
+  constexpr int kFlight = NEAR ? 12 : 6;         // tangents (NEAR = false: and keys) in flight
+  for (uint32_t j0 = threadIdx.x; j0 < list.cn; j0 += kFlight * kWT) {
+    uint32_t pay[kFlight], key[kFlight];
 #pragma unroll
-    for (int i = 0; i < 12; ++i) {
+    for (int i = 0; i < kFlight; ++i) {
       const uint32_t j = j0 + uint32_t(i) * kWT;
       pay[i] = j < list.cn ? pa[j] : 0u;
+      if (!NEAR) key[i] = j < list.cn ? list.mem[j] : 0u;
     }
 #pragma unroll
-    for (int i = 0; i < 12; ++i) {
+    for (int i = 0; i < kFlight; ++i) {
       const uint32_t j = j0 + uint32_t(i) * kWT;
-      const float sv = key_to_float(j < list.cn ? list.at(j) : 0u);
+      if (NEAR) key[i] = j < list.cn ? list.at(j) : 0u;
+      const float sv = key_to_float(key[i]);
       if (j < list.cn && sv >= ri.lo_incl && sv <= ri.hi_incl) {
         const double wgt = P::jac_weight(double(sv) - ri.center, ri.gamma);
         num += wgt * double(__uint_as_float(pay[i]));
@@ -746,8 +753,8 @@ __device__ __forceinline__ double list_dgamma(const KeyList& list, const uint32_
 
 // The row's unsorted candidate list -> RowInfo in list coordinates.  pa: its tangent by list position,
 // null when d gamma is not wanted (or is the caller's).
-template <bool MAG, int PC, int CAP>
-__device__ RowInfo solve_unsorted_list(const KeyList& list, const uint32_t* pa, int64_t k64, uint32_t klo,
+template <bool MAG, int PC, int CAP, bool NEAR>
+__device__ RowInfo solve_unsorted_list(const KeyList<NEAR>& list, const uint32_t* pa, int64_t k64, uint32_t klo,
                                        uint32_t khi, const Reg& R, ListShared<CAP>& sm) {
   using P = Pool<MAG, PC>;
   const uint32_t cn = list.cn;
@@ -831,7 +838,7 @@ template <bool MAG, int PC, int CAP>
 __device__ RowInfo solve_lds_list(uint32_t cn, int64_t k, uint32_t klo, uint32_t khi, const Reg& R,
                                   ListShared<CAP>& sm) {
   if (PC == kP2 && cn > kSortedMax)
-    return solve_unsorted_list<MAG, PC, CAP>(KeyList{sm.keys_a, nullptr, cn, cn}, nullptr, k, klo, khi, R, sm);
+    return solve_unsorted_list<MAG, PC, CAP>(KeyList<true>{sm.keys_a, nullptr, cn, cn}, nullptr, k, klo, khi, R, sm);
   const uint32_t span = khi - klo;
   const int nbits = span == 0 ? 0 : 32 - __clz(int(span));
   const uint32_t* skeys = sm.keys_a;

@@ -233,8 +233,9 @@ __global__ __launch_bounds__(kWT) void wide_finish_kernel(
       }
     }
     __syncthreads();
-    // its first keys into LDS (twelve loads in flight)
-    const uint32_t near = min(cn, uint32_t(2 * kWideLdsCap));
+    // p = 2: its first keys into LDS (twelve loads in flight)
+    constexpr bool kNear = PC == kP2;
+    const uint32_t near = kNear ? min(cn, uint32_t(2 * kWideLdsCap)) : 0u;
     for (uint32_t j0 = threadIdx.x; j0 < near; j0 += 12 * kWT) {
       uint32_t key[12];
 #pragma unroll
@@ -244,7 +245,7 @@ __global__ __launch_bounds__(kWT) void wide_finish_kernel(
         if (j0 + uint32_t(i) * kWT < near) sm.keys[j0 + uint32_t(i) * kWT] = key[i];
     }
     __syncthreads();
-    ri = solve_unsorted_list<MAG, PC, kWideLdsCap>(KeyList{sm.keys, ka, near, cn}, want_jvp ? pa : nullptr, k,
+    ri = solve_unsorted_list<MAG, PC, kWideLdsCap>(KeyList<kNear>{sm.keys, ka, near, cn}, want_jvp ? pa : nullptr, k,
                                                    klo, khi, R, sm);
   }
   if (threadIdx.x == 0) info[row] = ri;
