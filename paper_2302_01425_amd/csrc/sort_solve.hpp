@@ -761,6 +761,68 @@ __device__ __forceinline__ double list_dgamma(const KeyList<NEAR>& list, const u
   return num / P::jac_denominator(den, double(k - ri.a + 1), R);
 }
 
+// p = 2: elements whose value is a threshold of the final set tie with the block, and the strict tests
+// decide about them, not the threshold, which has been rounded twice (magnitude, lambda = 0.75: some
+// thresholds come out above a value that they equal).  The set is taken without the copies of such
+// values and gets back those that violate; the pooled value stays the same.
+template <bool MAG, int CAP, bool NEAR>
+__device__ void settle_ties(const KeyList<NEAR>& list, uint32_t kk, uint32_t kk1, int64_t k, double center,
+                            const Reg& R, SetStats* st, double* g, ListShared<CAP>& sm) {
+  using P = Pool<MAG, kP2>;
+  const double g_abs = *g + center, t_hi = MAG ? g_abs * R.one_p_lambda : g_abs + R.lambda;
+  const double eps = 1e-12 * (fabs(g_abs) + R.lambda);
+  const float f_lo = float(g_abs), f_hi = float(t_hi);
+  const uint32_t k_lo = desc_key(f_lo), k_hi = desc_key(f_hi);
+  // (the values from s_{k+1} to s_k, keys kk .. kk1, are members in any case)
+  bool out_lo = fabs(double(f_lo) - g_abs) <= eps && k_lo > kk1;
+  bool out_hi = fabs(double(f_hi) - t_hi) <= eps && k_hi < kk;
+  if (!out_lo && !out_hi) return;                // (uniform)
+  uint32_t n_lo = 0u, n_hi = 0u;                 // copies of the two values
+  list.each([&](uint32_t key) {
+    n_lo += key == k_lo ? 1u : 0u;
+    n_hi += key == k_hi ? 1u : 0u;
+  });
+  double c_lo = double(n_lo), c_hi = double(n_hi);
+  wide_sum2(c_lo, c_hi, sm);
+  out_lo = out_lo && c_lo > 0.0;
+  out_hi = out_hi && c_hi > 0.0;
+  if (!out_lo && !out_hi) return;
+  const double x_lo = double(f_lo) - center, x_hi = double(f_hi) - center;
+  double cnt = double(st->cnt), above = double(st->above);
+  Sums S = st->S;
+  if (out_lo && k_lo <= st->kmax) {
+    S.s1 -= c_lo * x_lo;
+    cnt -= c_lo;
+  }
+  if (out_hi && k_hi >= st->kmin) {
+    S.s1 -= c_hi * x_hi;
+    cnt -= c_hi;
+    above += c_hi;
+  }
+  if (out_lo) st->kmax = k_lo - 1u;
+  if (out_hi) st->kmin = k_hi == 0x7fffffffu ? 0x80000001u : k_hi + 1u;      // (0x80000000: see above)
+#pragma unroll 1
+  for (int turn = 0; turn < 2; ++turn) {         // (taking in one value can only change the test of the other)
+    if (out_hi && P::left_violates(x_hi, cnt, double(k) - above, S, R)) {
+      S.s1 += c_hi * x_hi;
+      cnt += c_hi;
+      above -= c_hi;
+      st->kmin = k_hi;
+      out_hi = false;
+    }
+    if (out_lo && P::right_violates(x_lo, cnt, double(k) - above, S, R)) {
+      S.s1 += c_lo * x_lo;
+      cnt += c_lo;
+      st->kmax = k_lo;
+      out_lo = false;
+    }
+  }
+  st->cnt = uint32_t(cnt);
+  st->above = uint32_t(above);
+  st->S = S;
+  *g = P::pooled(cnt, double(k) - above, S, R, 0.0, 0.0);
+}
+
 // The row's unsorted candidate list -> RowInfo in list coordinates.  pa: its tangent by list position,
 // null when d gamma is not wanted (or is the caller's).
 template <bool MAG, int PC, int CAP, bool NEAR>
@@ -832,6 +894,7 @@ __device__ RowInfo solve_unsorted_list(const KeyList<NEAR>& list, const uint32_t
     from_piece = g2 > lo && g2 < hi;
     g = from_piece ? g2 : 0.5 * (lo + hi);
   }
+  if constexpr (PC == kP2) settle_ties<MAG, CAP, NEAR>(list, kk, kk1, k, center, R, &st, &g, sm);
   ri.a = int64_t(st.above) + 1;
   ri.b = int64_t(st.above) + int64_t(st.cnt);
   ri.wa = ri.a;

@@ -33,3 +33,22 @@ def test_ties_at_the_ends_and_around_zero(gpu, oracle):
         for lam in (0.125, 0.5, 1.0):
             run_case(gpu, oracle, "mask", x, t, k, P2, lam, check_perm=False)
             run_case(gpu, oracle, "mag", x, t, k, P2, lam, check_perm=False)
+
+
+# An element x above the block whose singleton minimiser x / (1 + lambda) equals the pooled value exactly does
+# not violate: it stays outside, and its output follows its own tangent alone.  lambda = 0.75, gamma = 4 x / 7 is
+# no float64 number, and for these x the rounded gamma times the rounded 1 + lambda is above x.  Block of 8 q
+# elements: q copies of a < x (top-k positions), 7 q of b > gamma, q a + 7 q b = gamma (8 q + 0.75 q).
+@pytest.mark.parametrize("x,a,b", [(29, 26, 17), (58, 52, 34), (123, 118, 71), (253, 250, 145)])
+@pytest.mark.parametrize("q", [600, 2400, 5000])
+def test_exact_ties_at_the_upper_end(gpu, oracle, x, a, b, q):
+    n, copies, above = 60000, 50, 3000
+    r = np.random.default_rng(x + q)
+    v = np.full(n, 1.0, dtype=np.float32)
+    v[:above] = 8 * x
+    v[above:above + copies] = x
+    v[above + copies:above + copies + q] = a
+    v[above + copies + q:above + copies + 8 * q] = b
+    rows = np.stack([r.permutation(v) * r.choice([-1.0, 1.0], size=n) for _ in range(2)]).astype(np.float32) / 64
+    t = r.normal(size=rows.shape).astype(np.float32)
+    run_case(gpu, oracle, "mag", rows, t, above + copies + q, P2, 0.75, check_perm=False)
