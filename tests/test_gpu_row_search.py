@@ -80,3 +80,23 @@ def test_unaligned_arrays_and_special_values(gpu, oracle, n):
         gpu.topk_mask_jvp(v[0], v[1], n // 4, P2, 0.5, out=v[2], jvp_out=v[3])
         close(host(v[2]), ref["out"], "unaligned fwd")
         close(host(v[3]), ref["jvp"], "unaligned jvp")
+
+
+# Magnitude, p = 2: a kept entry above the block is x / (1 + lambda) with one float32 rounding, whatever shape of
+# the kernel the number of rows selects (1 / (1 + lambda) itself is rounded to float64: one
+# output in 2^28 may round the other way, none of these do).
+@pytest.mark.parametrize("n", [600, 1000, 1500, 1537, 2000, 2046, 3000, 9000])
+def test_kept_entries_are_rounded_once(gpu, n):
+    r = np.random.default_rng(n)
+    x = r.normal(size=(300, n)).astype(np.float32)
+    t = r.normal(size=x.shape).astype(np.float32)
+    k, lam = 200, 1e-3
+    inv = 1.0 / (1.0 + lam)
+    many, d_many = (host(a) for a in gpu.topkmag_jvp(dev(x), dev(t), k, P2, lam))
+    few, d_few = (host(a) for a in gpu.topkmag_jvp(dev(x[:4]), dev(t[:4]), k, P2, lam))
+    # (clear of the block, which reaches up to s_{k+1} (1 + lambda))
+    top = np.abs(x) > 1.01 * np.sort(np.abs(x), axis=1)[:, [n - k]]
+    for y, d, rows in ((many, d_many, 300), (few, d_few, 4)):
+        m = top[:rows]
+        assert np.array_equal(y[m], (x[:rows][m].astype(np.float64) * inv).astype(np.float32))
+        assert np.array_equal(d[m], (t[:rows][m].astype(np.float64) * inv).astype(np.float32))
