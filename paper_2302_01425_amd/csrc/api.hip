@@ -72,9 +72,11 @@ bool value_wide(bool mag, int pc, int64_t n) {
 //     15.5 / 17, k = 205 23 / 18; 512, k = 256 20 / 19.  With p = 4/3 the float64 steps cost more here:
 //     700, k = 64 31 / 37, k = 350 32 / 26; 1500, k = 64 40 / 26;
 //   * top-k in magnitude with p = 4/3, which they do not have: 400 elements 121 / 48.
-bool search_rows(bool mag, int pc, int64_t n, int64_t k) {
+// fused: the operators built on the mask and the loss, whose rows of up to 2048 elements know no long-row
+// route (abs_fused below).
+bool search_rows(bool mag, int pc, int64_t n, int64_t k, bool fused = false) {
   if (topk::routes().short_kernel != TOPK_SHORT_ROW_KERNEL_AUTO) return false;
-  if (is_long(n) && long_mode() != kAuto) return false;
+  if (is_long(n) && long_mode() != kAuto && !(fused && n <= 2048)) return false;
   if (n < topk::kRowSearchMin || n > topk::kRowSearchMax) return false;
   if (n > 2048) return true;
   if (mag && pc == topk::kP43) return true;
@@ -247,7 +249,7 @@ int run_abs_operator(bool signed_mask, const float* x, const float* tangent, int
   if (x == nullptr || out == nullptr) return TOPK_ERR_NULL;
   if (need_jvp && (jvp == nullptr || tangent == nullptr)) return TOPK_ERR_NULL;
   // rows of up to 2048 elements: one fused kernel, no scratch
-  const bool search = search_rows(false, pc, n, k);
+  const bool search = search_rows(false, pc, n, k, true);
   if (abs_fused(n) && !search) {
     begin();
     const int frc = topk::launch_short_rows_fused_variant(
@@ -545,7 +547,7 @@ int topk_mask_loss(const float* theta, const float* target, int64_t rows, int64_
     const double lam_over_p = lambda / (pc == topk::kP2 ? 2.0 : 4.0 / 3.0);
     hipStream_t st = static_cast<hipStream_t>(stream);
     int frc = -2;
-    if (search_rows(false, pc, n, k)) {
+    if (search_rows(false, pc, n, k, true)) {
       if (n > 2048) {                      // (no scratch is used, but rows of this length ask for it)
         SortBuffers B;
         const int wrc = carve(rows, n, &B);

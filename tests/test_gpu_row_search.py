@@ -100,3 +100,30 @@ def test_kept_entries_are_rounded_once(gpu, n):
         m = top[:rows]
         assert np.array_equal(y[m], (x[:rows][m].astype(np.float64) * inv).astype(np.float32))
         assert np.array_equal(d[m], (t[:rows][m].astype(np.float64) * inv).astype(np.float32))
+
+
+# The header promises the same results on every route; rows of up to 2048 elements of these operators take no
+# long-row route, whatever is set, and the ones that the root search takes are those with k = 0 or k > 48.
+@pytest.mark.parametrize("n", [600, 1025, 1500, 2048])
+def test_operators_built_on_the_mask_on_every_route(gpu, oracle, n):
+    r = np.random.default_rng(n)
+    x = r.normal(size=(3, n)).astype(np.float32)
+    t = r.normal(size=x.shape).astype(np.float32)
+    routes = [(gpu.TOPK_ROUTE_LONG_ROWS, v) for v in range(5)] + [(gpu.TOPK_ROUTE_SHORT_ROW_KERNEL, v) for v in range(3)]
+    for k in (0, 48, 65, n // 3, n):
+        for p, lam in ((P2, 0.3), (P43, 0.05)):
+            refs = {name: getattr(oracle, name)(x, k, p, lam, tangent=t) for name in ("topk_signed_mask", "topk_masked_value")}
+            ref_loss, ref_grad = oracle.fenchel_young_loss(x, t, k, p, lam)
+            for which, value in routes:
+                gpu.set_route(which, value)
+                try:
+                    for name, ref in refs.items():
+                        o, j = (host(a) for a in getattr(gpu, name + "_jvp")(dev(x), dev(t), k, p, lam))
+                        close(o, ref["out"], (name, k, which, value))
+                        close(j, ref["jvp"], (name + " jvp", k, which, value))
+                        close(host(getattr(gpu, name + "_fwd")(dev(x), k, p, lam)), ref["out"], (name, k, which, value))
+                    loss, grad = (host(a) for a in gpu.topk_mask_loss(dev(x), dev(t), k, p, lam))
+                    close(grad, ref_grad, ("grad", k, which, value))
+                    close(loss, ref_loss, ("loss", k, which, value))
+                finally:
+                    gpu.set_route(which, 0)
