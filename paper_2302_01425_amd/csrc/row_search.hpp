@@ -961,9 +961,11 @@ __global__ __launch_bounds__(NT == 64 ? 256 : NT) void row_search_kernel(
         y = ab ? 1.0f : 0.0f;
         yd = ab ? 1.0 : 0.0;
       } else if (!CUBIC) {
-        // (one rounding: the float32 product of the rounded factor has two)
-        y = ab ? float(double(xv) * R.inv_1pl) : 0.0f;
-        if (!LIST_TAU && want_jvp && ab && v != 0.0f) dy = float(double(tr[q]) * R.inv_1pl);
+        // (up to 2048 elements one rounding, whatever the shape, as in the kernels of those lengths; above, the
+        // float32 product of the other long-row routes, whose results are the same bit for bit)
+        y = ab ? (n > 2048 ? xv * float(R.inv_1pl) : float(double(xv) * R.inv_1pl)) : 0.0f;
+        if (!LIST_TAU && want_jvp && ab && v != 0.0f)
+          dy = n > 2048 ? tr[q] * float(R.inv_1pl) : float(double(tr[q]) * R.inv_1pl);
       } else if (__any(ab)) {
         double gd, slope = 0.0;
         above_mag43(double(v), R, want_jvp, &gd, &slope);
