@@ -66,12 +66,14 @@ bool value_wide(bool mag, int pc, int64_t n) {
 
 // Rows of row_search.hpp: dense outputs from the row in registers, without a sort.  Rows above 2048
 // elements, whatever k and p.  Shorter ones only where the kernels that order values in one wavefront
-// are slower (16384 x 256: 13 us there, 27 here; us for 4 M elements, forward + JVP):
-//   * they order a few candidates when k <= 64, but about k = 48 the candidates stop fitting, and then
-//     the whole row is sorted: 1000 elements, k = 33 16 there, 18 here; k = 100 24 / 19; 2048, k = 33
-//     15.5 / 17, k = 205 23 / 18; 512, k = 256 20 / 19.  With p = 4/3 the float64 steps cost more here:
-//     700, k = 64 31 / 37, k = 350 32 / 26; 1500, k = 64 40 / 26;
-//   * top-k in magnitude with p = 4/3, which they do not have: 400 elements 121 / 48.
+// are slower:
+//   * those order a few candidates when k <= 64, but about k = 48 the candidates stop fitting, and then
+//     the whole row is sorted.  Above 1024 elements that costs more than the search (forward + JVP, us;
+//     sort / search): 2048 elements, 4 M in all, k = 33 15.5 / 17, k = 205 23 / 18; k = 100, 64 x 1200
+//     12.9 / 9.1, 2000 x 1200 20.6 / 16.6.  Up to 1024 it does not, and takes the same time whatever the
+//     values: k = 100, normal values 64 x 1000 8.3 / 9.4, 1000 x 1000 9.9 / 13.2, 1000 x 600 9.0 / 13.1, whole
+//     numbers 1000 x 1000 10.1 / 22.0; p = 4/3 11.7 / 14.4 and 12.6 / 23.5;
+//   * top-k in magnitude with p = 4/3, which they do not have: 4096 x 400 121 / 27.
 // fused: the operators built on the mask and the loss, whose rows of up to 2048 elements know no long-row
 // route (abs_fused below).
 bool search_rows(bool mag, int pc, int64_t n, int64_t k, bool fused = false) {
@@ -80,7 +82,7 @@ bool search_rows(bool mag, int pc, int64_t n, int64_t k, bool fused = false) {
   if (n < topk::kRowSearchMin || n > topk::kRowSearchMax) return false;
   if (n > 2048) return true;
   if (mag && pc == topk::kP43) return true;
-  return n > 512 && (k == 0 || k > (pc == topk::kP2 || n > 1024 ? 48 : 64));
+  return n > 1024 && (k == 0 || k > 48);
 }
 
 struct Layout {

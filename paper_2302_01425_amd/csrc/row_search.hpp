@@ -1060,7 +1060,7 @@ int launch_row_search_shape(int var, bool mag, int pc, bool vec, const float* x,
                        loss, lam_over_p);                                                             \
     return 0;                                                                                         \
   } while (0)
-  if constexpr (NT * E <= 512) {         // (only the operator that the short-row kernels do not have)
+  if constexpr (NT * E <= 1024) {        // (only the operator that the short-row kernels do not have)
     if (var == kSearchPlain && mag && pc == kP43) TOPK_SEARCH(true, kP43, kSearchPlain);
   } else if (var == kSearchPlain) {
     if (!mag && pc == kP2) TOPK_SEARCH(false, kP2, kSearchPlain);

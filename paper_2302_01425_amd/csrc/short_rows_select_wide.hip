@@ -1,7 +1,7 @@
 // Launchers of the values-only short-row kernel (short_rows_value.hpp) for rows of 129 .. 2048
 // elements: 32 or 64 lanes per row with 8, 16 or 32 elements per lane; one row (two for 256
 // elements) per wavefront.  With k <= lanes per row only the values above the threshold T are
-// ordered; otherwise the whole row goes through the float network in registers, up to 512 elements
+// ordered; otherwise the whole row goes through the float network in registers, up to 1024 elements
 // (longer ones with k > lanes: row_search.hip).
 #include "short_rows_value.hpp"
 
@@ -21,7 +21,7 @@ int launch_wide_mode(const float* x, const float* t, float* out, float* jvp, int
     hipLaunchKernelGGL((short_rows_value_kernel<GL, E, MAG, PC, VEC, FULL, MODE, true, WPB>),
                        dim3((unsigned)blocks), dim3(WPB * kWave), 0, st, x, t, out, jvp, rows, n, k, R,
                        il, i1, nullptr, 0.0);
-  } else if constexpr (C::NP <= 512) {
+  } else if constexpr (C::NP <= 1024) {
     hipLaunchKernelGGL((short_rows_value_kernel<GL, E, MAG, PC, VEC, FULL, MODE, false, WPB>),
                        dim3((unsigned)blocks), dim3(WPB * kWave), 0, st, x, t, out, jvp, rows, n, k, R,
                        il, i1, nullptr, 0.0);

@@ -18,7 +18,7 @@ int launch_var_mode(const float* x, const float* t, float* out, float* jvp, floa
     hipLaunchKernelGGL((short_rows_value_kernel<GL, E, false, PC, VEC, FULL, MODE, true, WPB, VAR>),
                        dim3((unsigned)blocks), dim3(WPB * kWave), 0, st, x, t, out, jvp, rows, n, k, R,
                        il, i1, loss, lam_over_p);
-  } else if constexpr (C::NP <= 512) {
+  } else if constexpr (C::NP <= 1024) {
     hipLaunchKernelGGL((short_rows_value_kernel<GL, E, false, PC, VEC, FULL, MODE, false, WPB, VAR>),
                        dim3((unsigned)blocks), dim3(WPB * kWave), 0, st, x, t, out, jvp, rows, n, k, R,
                        il, i1, loss, lam_over_p);
