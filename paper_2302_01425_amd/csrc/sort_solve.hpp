@@ -761,33 +761,60 @@ __device__ __forceinline__ double list_dgamma(const KeyList<NEAR>& list, const u
   return num / P::jac_denominator(den, double(k - ri.a + 1), R);
 }
 
-// p = 2: elements whose value is a threshold of the final set tie with the block, and the strict tests
+// p = 2: elements within rounding of a threshold of the final set tie with the block, and the strict tests
 // decide about them, not the threshold, which has been rounded twice (magnitude, lambda = 0.75: some
-// thresholds come out above a value that they equal).  The set is taken without the copies of such
-// values and gets back those that violate; the pooled value stays the same.
+// thresholds come out above a value that they equal).  The set is taken without the copies of such a
+// value and gets them back if they violate; the pooled value stays the same.
 template <bool MAG, int CAP, bool NEAR>
 __device__ void settle_ties(const KeyList<NEAR>& list, uint32_t kk, uint32_t kk1, int64_t k, double center,
                             const Reg& R, SetStats* st, double* g, ListShared<CAP>& sm) {
   using P = Pool<MAG, kP2>;
   const double g_abs = *g + center, t_hi = MAG ? g_abs * R.one_p_lambda : g_abs + R.lambda;
-  const double eps = 1e-12 * (fabs(g_abs) + R.lambda);
-  const float f_lo = float(g_abs), f_hi = float(t_hi);
-  const uint32_t k_lo = desc_key(f_lo), k_hi = desc_key(f_hi);
-  // (the values from s_{k+1} to s_k, keys kk .. kk1, are members in any case)
-  bool out_lo = fabs(double(f_lo) - g_abs) <= eps && k_lo > kk1;
-  bool out_hi = fabs(double(f_hi) - t_hi) <= eps && k_hi < kk;
+  const double eps = 1e-12 * (fabs(g_abs) + (MAG ? 0.0 : R.lambda)) * (MAG ? R.one_p_lambda : 1.0);
+  // keys of the values within eps of the thresholds (they run against the values), without those from s_{k+1} to
+  // s_k (keys kk .. kk1), which are members in any case
+  const uint32_t lo_a = max(first_key_below(g_abs + eps), kk1 + 1u), lo_b = last_key_above(g_abs - eps);
+  const uint32_t hi_a = first_key_below(t_hi + eps), hi_b = min(last_key_above(t_hi - eps), kk - 1u);
+  bool out_lo = lo_a <= lo_b, out_hi = hi_a <= hi_b;
   if (!out_lo && !out_hi) return;                // (uniform)
-  uint32_t n_lo = 0u, n_hi = 0u;                 // copies of the two values
+  uint32_t n_lo = 0u, n_hi = 0u, k_lo = 0xffffffffu, k_hi = 0xffffffffu, z_lo = 0u, z_hi = 0u;
   list.each([&](uint32_t key) {
-    n_lo += key == k_lo ? 1u : 0u;
-    n_hi += key == k_hi ? 1u : 0u;
+    if (key >= lo_a && key <= lo_b) {
+      ++n_lo;
+      k_lo = min(k_lo, key);
+      z_lo = max(z_lo, key);
+    }
+    if (key >= hi_a && key <= hi_b) {
+      ++n_hi;
+      k_hi = min(k_hi, key);
+      z_hi = max(z_hi, key);
+    }
   });
   double c_lo = double(n_lo), c_hi = double(n_hi);
   wide_sum2(c_lo, c_hi, sm);
-  out_lo = out_lo && c_lo > 0.0;
-  out_hi = out_hi && c_hi > 0.0;
+  if (!(c_lo > 0.0) && !(c_hi > 0.0)) return;
+  // the value itself: the smallest and the largest key agree (more than one value that close to a threshold,
+  // both next to zero, stay where the threshold puts them)
+  const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+  k_lo = lanes_min<kWave>(k_lo);
+  k_hi = lanes_min<kWave>(k_hi);
+  z_lo = lanes_max<kWave>(z_lo);
+  z_hi = lanes_max<kWave>(z_hi);
+  __syncthreads();
+  if (lane == 0) {
+    sm.red[0][w] = k_lo;
+    sm.red[1][w] = k_hi;
+    sm.red[2][w] = z_lo;
+    sm.red[3][w] = z_hi;
+  }
+  __syncthreads();
+  const int q = lane & (kWW - 1);
+  k_lo = lanes_min<kWW>(sm.red[0][q]);
+  k_hi = lanes_min<kWW>(sm.red[1][q]);
+  out_lo = c_lo > 0.0 && k_lo == lanes_max<kWW>(sm.red[2][q]);
+  out_hi = c_hi > 0.0 && k_hi == lanes_max<kWW>(sm.red[3][q]);
   if (!out_lo && !out_hi) return;
-  const double x_lo = double(f_lo) - center, x_hi = double(f_hi) - center;
+  const double x_lo = double(key_to_float(k_lo)) - center, x_hi = double(key_to_float(k_hi)) - center;
   double cnt = double(st->cnt), above = double(st->above);
   Sums S = st->S;
   if (out_lo && k_lo <= st->kmax) {
@@ -889,7 +916,12 @@ __device__ RowInfo solve_unsorted_list(const KeyList<NEAR>& list, const uint32_t
     st = nx;
     if (same && from_piece) break;              // the set at its own pooled value: done
     const double g2 = pooled_of(st);
-    if (g2 == g) break;                         // g is the root of the piece it lies on
+    // g is the root of the piece it lies on, up to rounding (with an element at a threshold the set may
+    // change for ever between the two sides of it)
+    if (fabs(g2 - g) <= 1e-13 * (fabs(g + center) + (MAG && PC == kP2 ? 0.0 : R.lambda))) {
+      g = g2;
+      break;
+    }
     if (g2 > g) lo = g; else hi = g;
     from_piece = g2 > lo && g2 < hi;
     g = from_piece ? g2 : 0.5 * (lo + hi);

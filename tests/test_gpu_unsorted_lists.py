@@ -52,3 +52,19 @@ def test_exact_ties_at_the_upper_end(gpu, oracle, x, a, b, q):
     rows = np.stack([r.permutation(v) * r.choice([-1.0, 1.0], size=n) for _ in range(2)]).astype(np.float32) / 64
     t = r.normal(size=rows.shape).astype(np.float32)
     run_case(gpu, oracle, "mag", rows, t, above + copies + q, P2, 0.75, check_perm=False)
+
+
+# gamma = 0 exactly: elements at 0 and at lambda tie with the block and stay outside.  Block of 3 m elements: m copies
+# of 0.5 (top-k positions), 2 m of 0.25, 0.5 m + 0.25 (2 m) = lambda m; lambda = 1, and, scaled by an odd number, the
+# same with a gamma that is zero up to rounding.
+@pytest.mark.parametrize("m", [2000, 8000])
+@pytest.mark.parametrize("scale", [1.0, 3.0])
+def test_exact_ties_around_zero(gpu, oracle, m, scale):
+    n, above, at_lambda, zeros = 60000, 3000, 30, 7000
+    v = np.full(n, -2.0, dtype=np.float32)
+    for value, count in ((0.0, zeros), (0.25, 2 * m), (0.5, m), (1.0, at_lambda), (5.0, above)):
+        v = np.r_[np.full(count, value, dtype=np.float32), v]
+    r = np.random.default_rng(m)
+    x = np.stack([r.permutation(v[:n]) for _ in range(2)]) * np.float32(scale)
+    t = r.normal(size=x.shape).astype(np.float32)
+    run_case(gpu, oracle, "mask", x, t, above + at_lambda + m, P2, scale, check_perm=False)
