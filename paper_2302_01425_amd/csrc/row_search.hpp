@@ -205,11 +205,14 @@ __device__ __forceinline__ float sort16_desc(float v, int lane) {
   v = sort16_stage<1>(v, lane);
   return v;
 }
-// sum over the four DPP rows of the value in lane i of each
-__device__ __forceinline__ float rows_sum(float v, int i) {
-  return (uniform_f32(v, i) + uniform_f32(v, 16 + i)) + (uniform_f32(v, 32 + i) + uniform_f32(v, 48 + i));
+// mean over the first `rows` (uniform, 1 .. 4) DPP rows of the value in lane i of each
+__device__ __forceinline__ float rows_mean(float v, int i, int rows) {
+  float t = uniform_f32(v, i);
+  if (rows >= 4) return 0.25f * ((t + uniform_f32(v, 16 + i)) + (uniform_f32(v, 32 + i) + uniform_f32(v, 48 + i)));
+  if (rows >= 2) t += uniform_f32(v, 16 + i);
+  if (rows >= 3) t += uniform_f32(v, 32 + i);
+  return rows >= 3 ? t * (1.0f / 3.0f) : (rows == 2 ? 0.5f * t : t);
 }
-
 __device__ __forceinline__ float cbrt_approx(float v) {      // v > 0; a starting point only
   return __builtin_amdgcn_exp2f(__builtin_amdgcn_logf(v) * (1.0f / 3.0f));
 }
@@ -438,18 +441,16 @@ __global__ __launch_bounds__(NT == 64 ? 256 : NT) void row_search_kernel(
       const float q_all = float(k) / float(NT * E), q_n = float(k) / float(n);
       float mx = val(0), share = q_n, per = float(n);  // per: elements per unit of share
       float f[2] = {0.0f, 0.0f};
-      int below_r = 1;                                 // ranks between the two values of f[1]
+      int below_r;                                     // ranks between the two values of f[1]
       if (n < 4 * NT) {
-        // (some lanes hold nothing: the middle of the row's values by rank)
-        float lo = inf, hi = -inf;
+        // (one group of four per thread, and none in the last threads)
+        if (q_n < 0.375f) {
 #pragma unroll
-        for (int r = 0; r < E; ++r) {
-          lo = fminf(lo, val(r));
-          hi = fmaxf(hi, val(r));
+          for (int r = 1; r < 4; ++r) mx = fmaxf(mx, val(r));
+          const float rest = __builtin_amdgcn_exp2f(3.0f * __builtin_amdgcn_logf(1.0f - q_n));
+          share = 1.0f - rest * (1.0f - q_n);
+          per = float(n) * 0.25f * __builtin_amdgcn_rcpf(rest);
         }
-        grp.min_max(lo, hi);
-        f[0] = hi - (hi - lo) * q_n;
-        f[1] = (hi - lo) * (1.0f / 16.0f);
       } else if (q_all * float(E) < 2.0f) {
 #pragma unroll
         for (int r = 1; r < E; ++r) mx = fmaxf(mx, val(r));
@@ -469,18 +470,23 @@ __global__ __launch_bounds__(NT == 64 ? 256 : NT) void row_search_kernel(
       const int j0 = i0 > 1 ? i0 - 1 : 0, j1 = i0 < 14 ? i0 + 2 : 15;
       below_r = j1 - j0;
       constexpr int kSampling = W < 4 ? W : 4;         // wavefronts that take part
-      if (n >= 4 * NT && (W <= 4 || threadIdx.x < kSampling * kWave)) {
+      // every row of 16 lanes estimates the quantile, and the mean of the estimates is taken; in rows of fewer
+      // than 4 NT elements those whose lanes all hold four elements
+      const int full = n >= 4 * NT ? 4 * kSampling : (n + shift) / 64;
+      int mine = 4;
+      if (n < 4 * NT) mine = min(4, full - (W > 1 ? 4 * __builtin_amdgcn_readfirstlane(int(threadIdx.x) / kWave) : 0));
+      if (mine > 0 && (W <= 4 || threadIdx.x < kSampling * kWave || n < 4 * NT)) {
         mx = fmaxf(mx, -3.0e38f);                      // (NaN padding)
         mx = sort16_desc(mx, lane);
-        // every 16 lanes estimate the quantile; the mean of the estimates is taken
-        const float a = 0.25f * rows_sum(mx, i0), b = 0.25f * rows_sum(mx, i0 < 15 ? i0 + 1 : 15);
-        const float far = 0.25f * rows_sum(mx, j1), last = far > -1.0e37f ? far : a;
+        const float a = rows_mean(mx, i0, mine), b = rows_mean(mx, i0 < 15 ? i0 + 1 : 15, mine);
+        const float far = rows_mean(mx, j1, mine), last = far > -1.0e37f ? far : a;
         f[0] = b > -1.0e37f ? a + (b - a) * (r - float(i0)) : a;
-        f[1] = 0.25f * rows_sum(mx, j0) - last;
+        f[1] = rows_mean(mx, j0, mine) - last;
       }
       if constexpr (W > 1) {
-        f[0] = lane == 0 ? f[0] * (1.0f / kSampling) : 0.0f;       // mean over the wavefronts
-        f[1] = lane == 0 ? f[1] * (1.0f / kSampling) : 0.0f;
+        const float part = n >= 4 * NT ? 1.0f / kSampling : float(mine) * __builtin_amdgcn_rcpf(float(full));
+        f[0] = (lane == 0 && mine > 0) ? f[0] * part : 0.0f;       // (zero in wavefronts that have no part)
+        f[1] = (lane == 0 && mine > 0) ? f[1] * part : 0.0f;
         grp.template sum<0, 2, 0>(nullptr, f, nullptr);
       }
       g = f[0];

@@ -8,7 +8,8 @@ from tests.test_gpu_parity import P2, P43, close, dev, gpu, host, run_case  # no
 
 pytestmark = pytest.mark.gpu
 
-EDGES = [129, 255, 256, 509, 512, 513, 1021, 1024, 1533, 1537, 2045, 2048, 2049, 3069, 3072, 3073, 4093, 4096,
+EDGES = [129, 255, 256, 509, 512, 513, 1021, 1024, 1533, 1537, 2045, 2046, 2047, 2048, 2049, 3069, 3072, 3073, 4093,
+         4094, 4095, 4096,
          5117, 5120, 6141, 8189, 8192, 10237, 12285, 16381, 16384, 20477, 24573, 32765, 32766, 32768]
 
 
