@@ -36,9 +36,11 @@ int launch_row_search(int var, bool mag, int pc, const float* x, const float* ta
   // to fill the chip without (32: 108 registers and half the wavefronts; 8192 elements, p = 2: 512
   // rows 16.5 us with 512 threads against 19.0 with 256, 2048 rows 50.3 / 48.5; p = 4/3 65.1 / 52.9),
   // and 8 where there are not even as many rows as compute units (4096 elements, 256 rows: 512
-  // threads 9.8 us, 256 threads 11.4).
+  // threads 9.8 us, 256 threads 11.4), or four rows per workgroup would leave compute units without one
+  // (1200 elements, 300 / 1000 / 1500 rows: 14.7 / 15.2 / 16.7 us with 64 threads, 10.4 / 12.5 / 15.8 with
+  // 256; 2000 elements, 128 against 256 threads: 12.0 / 13.2 / 15.6 and 10.5 / 13.2 / 15.7).
+  if (rows <= 256 || (rows <= 1536 && n > 1024)) TOPK_SHAPE(b, 256, 8);
   if (rows <= 256) {
-    TOPK_SHAPE(b, 256, 8);
     TOPK_SHAPE(c, 512, 8);
     TOPK_SHAPE(f, 1024, 8);
     TOPK_SHAPE(g, 1024, 16);
