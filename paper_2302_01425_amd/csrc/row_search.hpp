@@ -213,6 +213,15 @@ __device__ __forceinline__ float rows_mean(float v, int i, int rows) {
   if (rows >= 3) t += uniform_f32(v, 32 + i);
   return rows >= 3 ? t * (1.0f / 3.0f) : (rows == 2 ? 0.5f * t : t);
 }
+// floats in numeric order as unsigned words, and back (between the images of two numbers lie numbers only)
+__device__ __forceinline__ uint32_t ordered_of(float f) {
+  const uint32_t b = __float_as_uint(f);
+  return (b >> 31) ? ~b : b | 0x80000000u;
+}
+__device__ __forceinline__ float float_of_ordered(uint32_t o) {
+  return __uint_as_float((o >> 31) ? o & 0x7fffffffu : ~o);
+}
+
 __device__ __forceinline__ float cbrt_approx(float v) {      // v > 0; a starting point only
   return __builtin_amdgcn_exp2f(__builtin_amdgcn_logf(v) * (1.0f / 3.0f));
 }
@@ -286,6 +295,7 @@ __global__ __launch_bounds__(NT == 64 ? 256 : NT) void row_search_kernel(
   constexpr int kListMax = NT * 4;                     // list entries of a row
   __shared__ float2 lists[RPB][kListMax];              // (value, index and sign)
   SearchGroup<NT> grp{red};
+  constexpr int kSecantMax = 16;                       // steps of phase 2; then the root is found from s_k
 
   const int lane = threadIdx.x & (kWave - 1);
   const int tid = NT == 64 ? lane : int(threadIdx.x);              // thread of the group
@@ -431,6 +441,10 @@ __global__ __launch_bounds__(NT == 64 ? 256 : NT) void row_search_kernel(
   bool done = !solve;
   const float lam = float(R.lambda), il = float(R.inv_lambda);
   float g = 0.0f;
+  float w_lo = MAG ? 0.0f : -inf, w_hi = inf;          // the root lies in between
+  bool below = false, above = false;                   // the signs of Psi at w_lo and w_hi have been seen
+  bool near = false;                                   // g is next to the root
+  float spare = 0.3f;                                  // block widths that g may be off
   auto width_at = [&](float at) { return !MAG ? lam : (CUBIC ? lam * cbrt_approx(at) : lam * at); };
   if (!done) {
     // ---- 1. a guess of s_k, and of the number of elements per unit of value around it ------------
@@ -503,12 +517,12 @@ __global__ __launch_bounds__(NT == 64 ? 256 : NT) void row_search_kernel(
     }
     // ---- 2. secant steps on Psi, float32 ----------------------------------------------------------------
     {
-      float lo = MAG ? 0.0f : -inf, hi = inf, f_lo = 0.0f, f_hi = 0.0f, g_old = g, f_old = 0.0f;
-      bool below = false, above = false;               // a point of either sign has been seen
+      float f_lo = 0.0f, f_hi = 0.0f, g_old = g, f_old = 0.0f;
       int side = 0;
       const float kf = float(k);
+      dens = fminf(dens, float(n) * __builtin_amdgcn_rcpf(width_at(g)));        // (no block holds more than the row)
 #pragma unroll 1
-      for (int it = 0; it < 40; ++it) {
+      for (int it = 0; it < kSecantMax; ++it) {
         const float width = width_at(g);
         const float h = !MAG ? il : __builtin_amdgcn_rcpf(width);
         float f[1] = {0.0f};
@@ -520,20 +534,23 @@ __global__ __launch_bounds__(NT == 64 ? 256 : NT) void row_search_kernel(
           pass_fence(r, f[0]);
         }
         grp.template sum<0, 1, 0>(nullptr, f, nullptr);
-        const float F = f[0] - kf;
+        const float F = f[0] - kf, in_width = dens * width;
         // near enough: the exact steps converge from a distance of some hundredths of a block
-        if (!(fabsf(F) > fmaxf(0.3f, 0.01f * dens * width))) break;
+        if (!(fabsf(F) > fmaxf(0.3f, 0.01f * in_width))) {
+          near = F == F;
+          break;
+        }
         const float slope = (f_old - F) * __builtin_amdgcn_rcpf(g - g_old);
         if (it > 0 && slope > 0.0f && slope < inf) dens = slope;
         // (an end that stays while the other one moves twice counts half: Illinois)
         if (F > 0.0f) {
-          lo = g;
+          w_lo = g;
           f_lo = F;
           if (side == 1) f_hi *= 0.5f;
           side = 1;
           below = true;
         } else {
-          hi = g;
+          w_hi = g;
           f_hi = F;
           if (side == -1) f_lo *= 0.5f;
           side = -1;
@@ -545,14 +562,23 @@ __global__ __launch_bounds__(NT == 64 ? 256 : NT) void row_search_kernel(
         if (below && above) {
           float wgt = f_lo * __builtin_amdgcn_rcpf(f_lo - f_hi);
           wgt = fminf(fmaxf(wgt, 0.05f), 0.95f);
-          next = lo + (hi - lo) * wgt;
+          next = w_lo + (w_hi - w_lo) * wgt;
         } else {
           next = g + F * __builtin_amdgcn_rcpf(dens);
           if (MAG) next = fmaxf(next, 0.25f * g);
           if (it > 1) dens *= 0.5f;                    // (further each time, until the root is passed)
         }
-        if (!(next > lo && next < hi) || next == g) break;         // (the bracket is used up; NaN)
+        if (!(next > w_lo && next < w_hi) || next == g) {          // (the bracket is used up; NaN)
+          near = below && above;
+          break;
+        }
         g = next;
+        if (it == kSecantMax / 2 - 1 && below && above) {
+          // (rows of few different values: Psi jumps.)  One value left: it is s_k
+          float first, last;
+          neighbours(float_next_up(w_hi + 1.01f * width), float_next_down(w_lo), &first, &last);
+          if (!(first < last)) break;
+        }
         if (MAG && !below && it == 2) {
           // (the root far below the guess: perhaps at zero.)  s_{k+1} = 0: nothing pools, and the top k
           // are the positive values and some zeros
@@ -565,14 +591,24 @@ __global__ __launch_bounds__(NT == 64 ? 256 : NT) void row_search_kernel(
           }
         }
       }
+      if (dens * width_at(g) < 6.0f) spare = 1.2f;
+      // (uniform values that live on, out of the vector registers)
+      spare = uniform_f32(spare, 0);
+      g = uniform_f32(g, 0);
+      w_lo = uniform_f32(w_lo, 0);
+      w_hi = uniform_f32(w_hi, 0);
     }
   }
   if (!done) {
     // ---- 3. the list of the elements that may belong to the block ----------------------------------------
     float2* list = lists[RPB > 1 ? int(threadIdx.x) / NT : 0];
-    const float width_g = width_at(g), mid = g + 0.5f * width_g, half = 0.8f * width_g;
+    // (with 0.3 of a block's width to spare on either side, or more where a width holds but a few elements:
+    // then a root may be that far from a value of Psi below 0.3; the last term is for blocks narrower than
+    // the spacing of floats)
+    const float width_g = width_at(g), mid = g + 0.5f * width_g;
+    const float half = (0.5f + spare) * width_g + 5e-7f * fabsf(mid);
     uint32_t above_list = 0u;
-    {
+    if (near) {
       uint32_t c0 = 0u, c1 = 0u;
 #pragma unroll
       for (int r = 0; r < E; ++r) {
@@ -603,7 +639,7 @@ __global__ __launch_bounds__(NT == 64 ? 256 : NT) void row_search_kernel(
       if constexpr (W > 1) __syncthreads();
       else __builtin_amdgcn_wave_barrier();
     }
-    use_list = len <= uint32_t(kListMax);
+    use_list = near && len <= uint32_t(kListMax);
     auto list_pass = [&](auto& G, int first, int step, float lo, float hi, float c32, uint32_t* above,
                          uint32_t* members) -> Sums {
       double d[3] = {0.0, 0.0, 0.0};
@@ -630,48 +666,55 @@ __global__ __launch_bounds__(NT == 64 ? 256 : NT) void row_search_kernel(
     };
     // ---- 4. exact steps ------------------------------------------------------------------------------------
     float c32 = P::kCentered ? g : 0.0f;
-    center = double(c32);
+    center = uniform_f64(double(c32), 0);
     gamma = double(g) - center;
     auto upper_end = [&](double ga) -> double {        // values below it are below their cap at gamma
       if (!MAG) return ga + R.lambda;
       if (!CUBIC) return ga * R.one_p_lambda;
       return ga + R.lambda * cbrt_f64(ga);
     };
-    const double slack = CUBIC ? 1e-11 : 1e-12;
+    // rounding of a threshold (magnitude, p = 2: relative; else lambda takes part in its sums)
+    auto slack_of = [&](double t) -> double { return (CUBIC ? 1e-11 : 1e-12) * (fabs(t) + (MAG && !CUBIC ? 0.0 : R.lambda)); };
     bool grow = true;                                  // the growth with the strict tests is needed
+    // does an element lie within rounding of one of the two thresholds?  (Not only the float next to it: around
+    // zero there are many.)
+    auto at_a_tie = [&](auto& G, auto solo, int first, int step, double ga, double t_hi) -> bool {
+      constexpr bool SOLO = decltype(solo)::value;
+      const double s1 = slack_of(ga), s2 = slack_of(t_hi);
+      if (!(fabs(double(float(ga)) - ga) <= s1) && !(fabs(double(float(t_hi)) - t_hi) <= s2)) return false;   // (mostly)
+      const float a1 = float_above(ga - s1), b1 = float_below(ga + s1);
+      const float a2 = float_above(t_hi - s2), b2 = float_below(t_hi + s2);
+      uint32_t c = 0u;
+      if (SOLO || use_list) {                          // (the thresholds lie inside the list's window)
+#pragma unroll 1
+        for (uint32_t j = first; j < len; j += step) {
+          const float v = list[j].x;
+          c += ((v >= a1 && v <= b1) || (v >= a2 && v <= b2)) ? 1u : 0u;
+        }
+      } else if constexpr (!SOLO) {
+#pragma unroll
+        for (int r = 0; r < E; ++r) {
+          float v = val(r);
+          opaque(v);
+          c += ((v >= a1 && v <= b1) || (v >= a2 && v <= b2)) ? 1u : 0u;
+          pass_fence(r, c);
+        }
+      }
+      G.template sum<0, 0, 1>(nullptr, nullptr, &c);
+      return c != 0u;
+    };
+    // While the list is used the steps stay inside its window; a root that turns out to lie outside, or
+    // that some twenty passes over the registers do not reach, is found from s_k below.
+    const float soft = (spare - 0.05f) * width_g + 2e-7f * fabsf(g);
     // The steps, by the group G whose threads are first, first + step, ..  SOLO: one wavefront on the
     // list alone; it returns false, with gamma as far as it came, when the registers are needed.
     auto exact_steps = [&](auto& G, auto solo, int first, int step) -> bool {
       constexpr bool SOLO = decltype(solo)::value;
-      // does an element lie within rounding of one of the two thresholds?
-      auto at_a_tie = [&](double ga, double t_hi) -> bool {
-        const double eps = slack * (fabs(ga) + R.lambda);
-        const float n1 = float(ga), n2 = float(t_hi);
-        const bool near1 = fabs(double(n1) - ga) <= eps, near2 = fabs(double(n2) - t_hi) <= eps;
-        if (!near1 && !near2) return false;
-        uint32_t c = 0u;
-        if (SOLO || use_list) {                        // (the thresholds lie inside the list's window)
-#pragma unroll 1
-          for (uint32_t j = first; j < len; j += step) {
-            const float v = list[j].x;
-            c += ((near1 && v == n1) || (near2 && v == n2)) ? 1u : 0u;
-          }
-        } else if constexpr (!SOLO) {
-#pragma unroll
-          for (int r = 0; r < E; ++r) {
-            float v = val(r);
-            opaque(v);
-            c += ((near1 && v == n1) || (near2 && v == n2)) ? 1u : 0u;
-            pass_fence(r, c);
-          }
-        }
-        G.template sum<0, 0, 1>(nullptr, nullptr, &c);
-        return c != 0u;
-      };
-      double blo = -1e300, bhi = 1e300;
+      double blo = use_list ? double(g - soft) - center : -1e300, bhi = use_list ? double(g + soft) - center : 1e300;
+      bool settled = false, lo_seen = false, hi_seen = false;        // (signs of Psi at blo and bhi)
       uint32_t ab = 0xffffffffu, cn = 0xffffffffu;
 #pragma unroll 1
-      for (int it = 0; it < 48; ++it) {
+      for (int it = 0; it < (use_list ? 32 : 20); ++it) {
         const double ga = gamma + center;
         const double t_hi = upper_end(ga);
         lo_f = float_above(ga);
@@ -686,8 +729,8 @@ __global__ __launch_bounds__(NT == 64 ? 256 : NT) void row_search_kernel(
         } else if constexpr (!SOLO) {
           if (it > 0) count_pass(lo_f, hi_f, &na, &nc);
         }
-        if (it > 0 && na == ab && nc == cn) {          // gamma is the pooled value of its own set
-          grow = at_a_tie(ga, t_hi);
+        if (it > 0 && (settled || (na == ab && nc == cn))) {       // gamma is the pooled value of its own set
+          grow = at_a_tie(G, solo, first, step, ga, t_hi);
           have = true;
           return true;
         }
@@ -697,61 +740,88 @@ __global__ __launch_bounds__(NT == 64 ? 256 : NT) void row_search_kernel(
         ab = na;
         cn = nc;
         double next = gamma;
-        bool ok = false;                               // next is a pooled value inside the bracket
+        bool ok = false, leave = false;                // next is a pooled value inside the bracket; a pooled value
         if (cn == 0u) {
           if (int(ab) == k) {                          // Psi = 0 on an empty set: nothing pools
-            grow = at_a_tie(ga, t_hi);
+            grow = at_a_tie(G, solo, first, step, ga, t_hi);
             return true;
           }
-          if (int(ab) > k) blo = gamma; else bhi = gamma;
+          if (int(ab) > k) {
+            blo = gamma;
+            lo_seen = true;
+          } else {
+            bhi = gamma;
+            hi_seen = true;
+          }
         } else {
           cnt = double(cn);
           m = double(k) - double(ab);
           const double dlo = double(lo_f) - center, dhi = double(hi_f) - center;
           // the cubic's root lies above (smallest member - lambda), resp. 0, and below the largest member
-          if (CUBIC && !(m > 0.0)) {
-            blo = gamma;                               // (more than k elements above: no such root)
+          if (!(m > 0.0)) {
+            blo = gamma;                               // (k or more elements above)
+            lo_seen = true;
+          } else if (m > cnt) {
+            bhi = gamma;                               // (fewer than k elements that far)
+            hi_seen = true;
           } else {
             next = pooled_of(S, cnt, m, gamma, MAG ? -center : dlo - R.lambda, dhi);
-            if (next == gamma) ok = true;
-            else if (next > gamma) blo = gamma;
-            else bhi = gamma;
+            // gamma is the pooled value of its own set up to rounding: the end of the iteration, even if an
+            // element at a threshold changes sides (for ever, sometimes)
+            settled = fabsf(float(next - gamma)) <= (CUBIC ? 1e-12f : 1e-13f) * (fabsf(g) + (MAG && !CUBIC ? 0.0f : lam));
+            if (next > gamma) {
+              blo = gamma;
+              lo_seen = true;
+            } else {
+              bhi = gamma;
+              hi_seen = true;
+            }
+            leave = true;
           }
           // a single member next to a gap in which Psi = 0: its own minimiser is the end of that gap.
           // The test of the pair (s_k, s_{k+1}) decides whether there is a block at all
           if (cn == 1u && (int(ab) == k || int(ab) + 1 == k)) {
-            if constexpr (SOLO) {
-              return false;
-            } else {
-              float sk, sk1;
-              neighbours(lo_f, hi_f, &sk, &sk1);
-              const float member = float(S.s1 + center);
-              if (int(ab) == k) sk1 = member; else sk = member;
-              if (!P::seed_violates(double(sk) - center, double(sk1) - center, R, center)) {
-                hi_f = sk1;                            // (s_{k+1} < s_k: the top k are above it)
-                grow = false;
-                return true;
-              }
-              const double dk = double(sk) - center, dk1 = double(sk1) - center;
-              next = pooled_of(Sums{dk + dk1, dk * dk + dk1 * dk1, dk * dk * dk + dk1 * dk1 * dk1}, 2.0, 1.0,
-                               gamma, MAG ? -center : dk1 - R.lambda, dk);
-              ab = 0xffffffffu;                        // (another set: cannot end the iteration)
+            if constexpr (SOLO) return false;          // (the neighbours may lie outside the list)
+            float sk = inf, sk1 = -inf;
+            if constexpr (!SOLO) neighbours(lo_f, hi_f, &sk, &sk1);
+            const float member = float(S.s1 + center);
+            if (int(ab) == k) sk1 = member; else sk = member;
+            if (!P::seed_violates(double(sk) - center, double(sk1) - center, R, center)) {
+              hi_f = sk1;                              // (s_{k+1} < s_k: the top k are above it)
+              grow = false;
+              return true;
             }
+            const double dk = double(sk) - center, dk1 = double(sk1) - center;
+            next = pooled_of(Sums{dk + dk1, dk * dk + dk1 * dk1, dk * dk * dk + dk1 * dk1 * dk1}, 2.0, 1.0,
+                             gamma, MAG ? -center : dk1 - R.lambda, dk);
+            ab = 0xffffffffu;                          // (another set: cannot end the iteration)
+            leave = true;
           }
-          if (next > blo && next < bhi) ok = true;
+          // outside the list's window, where it was looked for?  On without the list
+          if (use_list && leave && !settled && ((!lo_seen && next < blo) || (!hi_seen && next > bhi))) {
+            gamma = next;
+            use_list = false;
+            if (SOLO) return false;
+            blo = -1e300;
+            bhi = 1e300;
+            ab = 0xffffffffu;
+            continue;
+          }
+          if (settled || (next > blo && next < bhi)) ok = true;
         }
         if (!ok) {
+          if (use_list && it >= 3 && !(lo_seen && hi_seen)) return true;       // (no root in the window)
           const double w = t_hi - ga;
-          next = blo > -1e299 && bhi < 1e299 ? 0.5 * (blo + bhi) : (blo > -1e299 ? gamma + w : gamma - w);
+          next = blo > -1e299 && bhi < 1e299 ? 0.5 * (blo + bhi) : gamma + ldexp(blo > -1e299 ? w : -w, 2 * it);
           if (MAG && !(next + center > 0.0)) next = 0.5 * ga - center;
           ab = 0xffffffffu;                            // (not a pooled value)
         }
         if (!(fabs(next) < 1e300)) return true;
-        gamma = next;
+        gamma = uniform_f64(next, 0);
       }
       return true;
     };
-    bool finished = false;
+    bool finished = !near;                             // (then nothing is known: from s_k)
     if constexpr (W > 1) {
       // lists of up to 16 elements per lane: the first wavefront alone, without barriers, and the
       // float64 arithmetic of a step once and not once per wavefront
@@ -774,81 +844,154 @@ __global__ __launch_bounds__(NT == 64 ? 256 : NT) void row_search_kernel(
       }
     }
     if (!finished) exact_steps(grp, std::false_type{}, tid, NT);
-    // ---- 5. growth with the strict tests (ties, and whatever did not converge) -------------------------------
+    // ---- 5. from s_k, and growth with the strict tests (ties, and whatever did not converge) -----------------
+    // A few passes per binary digit and step of the set, whatever the values: 8 x 32768 values of 1e-30 in
+    // magnitude with p = 4/3 and lambda = 0.1 (gamma is about 1e-87) 275 ms when the block was grown from s_k
+    // one value at a time.
     if (grow) {
       use_list = false;
       // values are taken relative to an element of the row: differences of inputs with few bits, and the
       // sums of their powers, are exact then, and an exact tie is seen as one
-      float seed = inf;
+      float seed_lo = inf, seed_hi = -inf;             // members of the block in any case
+      const bool settled = have;
       if (have) {                                      // only what is certain
         const double ga = gamma + center, t_hi = upper_end(ga);
-        const double eps = slack * (fabs(ga) + R.lambda);
-        lo_f = float_above(ga + eps);
-        hi_f = float_below(t_hi - eps);
-        float dummy = -inf;
+        lo_f = float_above(ga + slack_of(ga));
+        hi_f = float_below(t_hi - slack_of(t_hi));
+        float a = inf, b = -inf;
 #pragma unroll
         for (int r = 0; r < E; ++r) {
           const float v = val(r);
-          seed = fminf(seed, (v >= lo_f && v <= hi_f) ? v : inf);
+          a = fminf(a, (v >= lo_f && v <= hi_f) ? v : inf);
+          pass_fence(r, a);
         }
-        grp.min_max(seed, dummy);
+        grp.min_max(a, b);
+        seed_lo = a;
       }
-      if (!(seed < inf)) {
-        // s_k, bit by bit: the largest value with at least k elements at or above it
-        uint32_t ord = 0u;
-        uint32_t ge = uint32_t(n), d0;
+      if (!(seed_lo < inf)) {
+        // s_k: bisection of the interval [lo, hi] of values that holds it, over the floats in their order.
+        // The ends move in to the nearest elements every fourth step, and as soon as k elements lie at or above
+        // the lower end: then s_k is the smallest of them.  (4 to 24 passes.)
+        have = false;
+        float a = inf, b = -inf;
+#pragma unroll
+        for (int r = 0; r < E; ++r) {
+          a = fminf(a, val(r));
+          b = fmaxf(b, val(r));
+          pass_fence(r, a, b);
+        }
+        grp.min_max(a, b);
+        uint32_t lo = ordered_of(a), hi = ordered_of(b), ge = uint32_t(n);
 #pragma unroll 1
-        for (int bit = 31; bit >= 0; --bit) {
-          const uint32_t cand = ord | (1u << bit);
-          const float fv = __uint_as_float((cand & 0x80000000u) ? (cand & 0x7fffffffu) : ~cand);
-          uint32_t at;
-          count_pass(inf, float_next_down(fv), &at, &d0);          // elements >= fv
-          if (fv == fv && int(at) >= k) {
-            ord = cand;
+        for (int step = 1; lo < hi && step <= 64; ++step) {
+          uint32_t cand = hi - (hi - lo) / 2u;         // (above lo)
+          if (below && above && step <= 2) {           // (the secant's bracket)
+            const uint32_t h = step == 1 ? ordered_of(w_lo) : ordered_of(w_hi + 1.01f * width_at(w_hi)) + 1u;
+            if (h > lo && h <= hi) cand = h;
+          }
+          uint32_t at, d0;
+          count_pass(inf, float_next_down(float_of_ordered(cand)), &at, &d0);      // elements >= cand
+          if (int(at) >= k) {
+            lo = cand;
             ge = at;
+          } else {
+            hi = cand - 1u;
+          }
+          if (int(at) == k || (step & 3) == 0 || step == 2) {
+            float c_lo = float_of_ordered(lo), c_hi = float_of_ordered(hi);
+            opaque(c_lo);
+            opaque(c_hi);
+            a = inf;
+            b = -inf;
+#pragma unroll
+            for (int r = 0; r < E; ++r) {
+              const float v = val(r);
+              a = fminf(a, v >= c_lo ? v : inf);
+              b = fmaxf(b, v <= c_hi ? v : -inf);
+              pass_fence(r, a, b);
+            }
+            grp.min_max(a, b);
+            lo = ordered_of(a);
+            hi = int(at) == k ? lo : ordered_of(b);
           }
         }
-        const float sk = __uint_as_float((ord & 0x80000000u) ? (ord & 0x7fffffffu) : ~ord);
-        lo_f = sk;
-        hi_f = int(ge) > k ? sk : float_next_down(sk);             // tied with s_{k+1}: the ties are the seed
-        seed = sk;
-      }
-      if (P::kCentered) {
-        c32 = seed;
-        center = double(c32);
-      }
-      have = true;
+        const float sk = float_of_ordered(lo);
+        float sk1 = sk, dummy;                         // (tied with s_{k+1}: the ties are the seed)
+        if (int(ge) <= k) neighbours(sk, inf, &dummy, &sk1);
+        if (P::kCentered) {
+          c32 = sk;
+          center = double(c32);
+        }
+        const double dk = double(sk) - center, dk1 = double(sk1) - center;
+        if (sk1 > -inf && P::seed_violates(dk, dk1, R, center)) {
+          seed_lo = sk1;
+          seed_hi = sk;
+          have = true;
+        } else {
+          hi_f = sk1;                                  // (s_{k+1} < s_k, or zeros: the top k are above it)
+        }
+        if (have && !settled) {
+          // the set of the block as in solve_unsorted_list (sort_solve.hpp), in passes over the registers
+          gamma = P::pooled(2.0, 1.0, Sums{dk + dk1, dk * dk + dk1 * dk1, dk * dk * dk + dk1 * dk1 * dk1}, R,
+                            MAG ? -center : dk1 - R.lambda, dk, center);
+          double blo = -1e300, bhi = 1e300;
+          uint32_t ab = 0xffffffffu, cn = 0xffffffffu;
+          bool piece = false, found_it = false;
 #pragma unroll 1
-      for (int step = 0; step < 2 * n + 8; ++step) {
-        float wa, wb;
-        neighbours(lo_f, hi_f, &wa, &wb);
-        uint32_t ab, cn, ca, cb, d0;
-        const Sums S = sums_pass(lo_f, hi_f, c32, &ab, &cn);
-        count_pass(inf, wa, &ca, &d0);                 // elements above wa
-        ca = ab - ca;                                  // copies of wa
-        count_pass(inf, float_next_down(wb), &cb, &d0);
-        cb = cb - ab - cn;                             // copies of wb
-        if (!(wa < inf)) ca = 0u;
-        if (!(wb > -inf)) cb = 0u;
-        if (cn == 0u) {
-          if (int(ab) == k) {
-            if (ca == 0u || cb == 0u || !P::seed_violates(double(wa) - center, double(wb) - center, R, center)) {
-              have = false;
+          for (int it = 0; it < 200 && !found_it; ++it) {
+            const double ga = gamma + center;
+            lo_f = fminf(float_above(ga), seed_lo);
+            hi_f = fmaxf(float_below(upper_end(ga)), seed_hi);
+            uint32_t na, nc;
+            const Sums S = sums_pass(lo_f, hi_f, c32, &na, &nc);
+            const bool same = na == ab && nc == cn;
+            ab = na;
+            cn = nc;
+            cnt = double(cn);
+            m = double(k) - double(ab);
+            found_it = same && piece;
+            if (found_it) break;
+            const double next = P::pooled(cnt, m, S, R, MAG ? -center : double(lo_f) - center - R.lambda,
+                                          double(hi_f) - center, center);
+            found_it = fabs(next - gamma) <= 0.1 * slack_of(ga);
+            if (found_it) {
+              gamma = next;
               break;
             }
-            hi_f = wa;
-            lo_f = wb;
-          } else if (int(ab) < k) {                    // s_k is the next value below, or further down
-            if (cb == 0u) { have = false; break; }
-            lo_f = wb;
-            hi_f = int(ab + cb) > k ? wb : float_next_down(wb);
-          } else {
-            if (ca == 0u) { have = false; break; }
-            hi_f = wa;
-            lo_f = int(ab - ca) < k ? wa : float_next_up(wa);
+            if (next > gamma) blo = gamma; else bhi = gamma;
+            piece = next > blo && next < bhi;
+            gamma = piece ? next : 0.5 * (blo + bhi);
           }
-          continue;
+          const double ga = gamma + center, t_hi = upper_end(ga);
+          if (found_it) {
+            grow = at_a_tie(grp, std::false_type{}, tid, NT, ga, t_hi);
+            if (grow) {
+              seed_lo = fminf(float_above(ga + slack_of(ga)), seed_lo);
+              seed_hi = fmaxf(float_below(t_hi - slack_of(t_hi)), seed_hi);
+            }
+          }
         }
+        if (have && grow) {
+          lo_f = seed_lo;
+          hi_f = seed_hi;
+        }
+      } else if (P::kCentered) {
+        c32 = seed_lo;
+        center = double(c32);
+      }
+      // Values are added to the block at its ends as long as one of the two next ones violates: one at a time,
+      // and after eight of those as many as do on either side in turn, found by bisection (a value that does not
+      // violate ends the run: neither do those beyond it).
+      bool right = false;
+#pragma unroll 1
+      for (int step = 0; have && grow && step < 2 * n + 8; ++step) {
+        float wa, wb;
+        neighbours(lo_f, hi_f, &wa, &wb);
+        uint32_t ab, cn, ca, cb;
+        const Sums S = sums_pass(lo_f, hi_f, c32, &ab, &cn);
+        count_pass(wb, wa, &ca, &cb);                  // elements above wa, and from wb to wa
+        cb = wb > -inf ? ca + cb - ab - cn : 0u;       // copies of wb and of wa
+        ca = wa < inf ? ab - ca : 0u;
         cnt = double(cn);
         m = double(k) - double(ab);
         const bool add_l = ca > 0u && P::left_violates(double(wa) - center, cnt, m, S, R, center);
@@ -860,6 +1003,31 @@ __global__ __launch_bounds__(NT == 64 ? 256 : NT) void row_search_kernel(
         }
         if (add_l) hi_f = wa;
         if (add_r) lo_f = wb;
+        if (step < 8) continue;
+        right = !right;
+        // the values up to `in` are dealt with, none beyond `out` is added
+        uint32_t in = ordered_of(right ? lo_f : hi_f), out = ordered_of(right ? -3.4028235e38f : 3.4028235e38f);
+#pragma unroll 1
+        for (int turn = 0; turn < 40 && (right ? out < in : out > in); ++turn) {
+          const float at = float_of_ordered(right ? out + (in - out) / 2u : out - (out - in) / 2u);
+          // the element at `at` or next to it on the block's side, and the block up to it
+          float va, vb;
+          neighbours(right ? lo_f : float_next_up(at), right ? float_next_down(at) : inf, &va, &vb);
+          const float v = right ? va : vb;
+          if (right ? v >= lo_f : v <= hi_f) {         // (none in between)
+            in = ordered_of(at);
+            continue;
+          }
+          const Sums T = sums_pass(right ? float_next_up(v) : lo_f, right ? hi_f : float_next_down(v), c32, &ab, &cn);
+          const double c = double(cn), mm = double(k) - double(ab), d = double(v) - center;
+          if (right ? P::right_violates(d, c, mm, T, R, center) : P::left_violates(d, c, mm, T, R, center)) {
+            if (right) lo_f = v;
+            else hi_f = v;
+            in = ordered_of(at);
+          } else {
+            out = right ? ordered_of(v) + 1u : ordered_of(v) - 1u;
+          }
+        }
       }
     }
   }

@@ -129,3 +129,79 @@ def test_operators_built_on_the_mask_on_every_route(gpu, oracle, n):
                     close(loss, ref_loss, ("loss", k, which, value))
                 finally:
                     gpu.set_route(which, 0)
+
+
+def hard_rows(r, n):
+    """Rows whose values are far from what a guess from a few order statistics says, and a lambda for each."""
+    x = r.normal(size=n)
+    return {"masked": (np.where(r.random(n) < 0.5, -1e9, x), 0.1),
+            "masked, lowest float": (np.where(r.random(n) < 0.85, -3.4028235e38, x), 0.1),
+            "heavy tails": (x * np.exp(4 * r.normal(size=n)), 0.1),
+            "one far value": (np.r_[x[:-1], 1e9], 0.1),
+            "whole numbers": (np.round(2 * x), 1e-3),
+            "two values": ((r.random(n) < 0.5) * 1.0, 0.05),
+            "probabilities": (np.exp(3 * x) / np.exp(3 * x).sum(), 1e-6),
+            "few non-zeros": (x * (r.random(n) < 0.05), 0.1),
+            "sorted": (np.sort(x), 0.1),
+            "far from zero": (300 * x + 5000, 0.1),
+            "much smaller than lambda": (1e-30 * x, 0.1)}
+
+
+# Few and many rows; 4094: fewer elements than four per thread.
+@pytest.mark.parametrize("rows,n", [(3, 1500), (300, 3000), (3, 4094), (3, 20000)])
+def test_values_far_from_the_guess(gpu, oracle, rows, n):
+    r = np.random.default_rng(rows * n)
+    t = r.normal(size=(rows, n)).astype(np.float32)
+    for name, (v, lam) in hard_rows(r, n).items():
+        print(name, flush=True)
+        x = np.stack([r.permutation(v) if name != "sorted" else v for _ in range(rows)]).astype(np.float32)
+        for k in (65, n // 10, n // 2):
+            # (a block of lowest floats: lambda is lost beside them in the oracle's float64 sums)
+            if "lowest" in name and k > n // 10:
+                continue
+            run_case(gpu, oracle, "mask", x, t, k, P2, lam, check_perm=False)
+            if "lowest" in name:
+                continue
+            run_case(gpu, oracle, "mag", x, t, k, P2, lam, check_perm=False)
+            if rows == 3 and n < 5000 and lam < 0.01:
+                run_case(gpu, oracle, "mask", x, t, k, P43, lam, check_perm=False)
+
+
+# The search takes some dozens of passes over a row at most, whatever the values: 2 ms for a few rows is more
+# than ten times what any of these takes (growing the block of a row of 32768 elements one value at a time: 275 ms).
+def test_time_does_not_depend_on_the_values(gpu):
+    import torch
+    n = 32768
+    r = np.random.default_rng(3)
+    t = torch.zeros((8, n), device="cuda")
+    for name, (v, lam) in hard_rows(r, n).items():
+        x = dev(np.broadcast_to(v.astype(np.float32), (8, n)).copy())
+        for p in (P2, P43):
+            for k in (65, n // 10, n // 2):
+                for f in (gpu.topk_mask_jvp, gpu.topkmag_jvp):
+                    f(x, t, k, p, lam)
+                    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+                    a.record()
+                    f(x, t, k, p, lam)
+                    b.record()
+                    b.synchronize()
+                    assert a.elapsed_time(b) < 2.0, (name, p, k, f.__name__, a.elapsed_time(b))
+
+
+# gamma = 0 exactly: elements at 0 and at lambda tie with the block and stay outside, their outputs follow their own
+# tangents (0 and, above, 0).  Block: m copies of 0.5 (top-k positions), 2 m of 0.25: 0.5 m + 0.25 (2 m) = lambda m.
+# The sums of the search are taken relative to its first guess: gamma comes out some 1e-17 off zero, where floats
+# are dense.  60000: candidate lists of long rows (csrc/sort_solve.hpp) of 6050 and 24050 members and more.
+@pytest.mark.parametrize("rows,n,m", [(3, 1500, 100), (300, 1500, 100), (300, 3000, 40), (3, 20000, 3000), (2, 60000, 2000),
+                                      (2, 60000, 8000)])
+def test_ties_around_zero(gpu, oracle, rows, n, m):
+    above, at_lambda, zeros = n // 20, 30, n // 8
+    v = np.full(n, -2.0, dtype=np.float32)
+    for value, count in ((0.0, zeros), (0.25, 2 * m), (0.5, m), (1.0, at_lambda), (5.0, above)):
+        v = np.r_[np.full(count, value, dtype=np.float32), v]
+    v = v[:n]
+    for seed in range(4):
+        r = np.random.default_rng(rows + n + seed)
+        x = np.stack([r.permutation(v) for _ in range(rows)])
+        t = r.normal(size=x.shape).astype(np.float32)
+        run_case(gpu, oracle, "mask", x, t, above + at_lambda + m, P2, 1.0, check_perm=False)
