@@ -45,6 +45,9 @@ constexpr int kNT = 1024;                       // threads of a row's workgroup
 constexpr int kNW = kNT / kWave;
 constexpr int kItems = 2816;                    // items of a row (44 bytes of LDS each)
 constexpr int kMaxRounds = 256;
+// values of a bin that are ordered by counting: 62 ns for each of them (and twice that above 1024 items),
+// against 8 us for the network over all items (2000 equal values: 300 us a call by counting, see the test)
+constexpr uint32_t kCountMax = 64;
 constexpr int kWTile = 2048;                    // positions of a tile of weights
 constexpr int kWThreads = 256;
 constexpr int kWPer = kWTile / kWThreads;
@@ -71,6 +74,7 @@ struct SearchShared {
   DD wave_dd[kNW];
   unsigned long long wave_u[kNW];
   int nb, bad;
+  uint32_t most;                                // values in the fullest bin that holds items
   struct {
     int lo, hi;                                 // every bin in between is one item
   } gap;
@@ -320,19 +324,30 @@ __global__ __launch_bounds__(kNT) void general_search_kernel(
   const int tiles = (n + kWTile - 1) / kWTile;
 
   // ---- 1. histogram with sums; the tiles' offsets of the prefix sums of w ---------------------------
-  for (int i = tid; i < kSelBins; i += kNT) {
-    sm.bins[i] = 0;
-#pragma unroll
-    for (int c = 0; c < kCopies - 1; ++c) sm.u.extra[c][i] = 0;
-  }
   DD tile_total{0.0, 0.0};
   bool tile_bad = false;
   if (tid < kWave && lane < tiles) {
     tile_total = wtotal[wrow * kWTiles + lane];
     tile_bad = wbad[wrow * kWTiles + lane] != 0;
   }
-  if (tid == 0) sm.gap = {-1, kSelBins};
+  for (int i = tid; i < kSelBins; i += kNT) {
+    sm.bins[i] = 0;
+#pragma unroll
+    for (int c = 0; c < kCopies - 1; ++c) sm.u.extra[c][i] = 0;
+  }
+  if (tid < kWave) {
+    const bool bad = __any(tile_bad);
+    if (lane == 0) sm.bad = bad;
+  }
+  if (tid == 0) {
+    sm.gap = {-1, kSelBins};
+    sm.most = 0;
+  }
   __syncthreads();
+  if (sm.bad) {                                  // weights that are not non-increasing: nothing to look for
+    if (tid == 0) todo[row] = 1;
+    return;
+  }
   {
     const int copy = lane % kCopies;
     unsigned long long* hist = copy == 0 ? sm.bins : sm.u.extra[copy - 1];
@@ -345,8 +360,6 @@ __global__ __launch_bounds__(kNT) void general_search_kernel(
     const DD t = wave_inclusive_dd(tile_total, lane);
     if (lane < tiles) sm.toff[lane + 1] = t;
     if (lane == 0) sm.toff[0] = DD{0.0, 0.0};
-    const bool bad = __any(tile_bad);
-    if (lane == 0) sm.bad = bad;
   }
   __syncthreads();
 
@@ -356,7 +369,7 @@ __global__ __launch_bounds__(kNT) void general_search_kernel(
   double sum[kPer];
   uint32_t mine = 0, used = 0;
   DD mysum{0.0, 0.0};
-  bool bad = sm.bad != 0;
+  bool bad = false;
 #pragma unroll
   for (int q = 0; q < kPer; ++q) {
     const uint32_t b = uint32_t(tid * kPer + q);
@@ -464,6 +477,7 @@ __global__ __launch_bounds__(kNT) void general_search_kernel(
     nc += open[q] ? cnt[q] : 0u;
     // the nearest open bins around the middle of the row
     if (open[q]) {
+      atomicMax(&sm.most, cnt[q]);
       if (at + cnt[q] <= uint32_t(n) / 2) atomicMax(&sm.gap.lo, tid * kPer + q);
       else atomicMin(&sm.gap.hi, tid * kPer + q);
     }
@@ -510,22 +524,53 @@ __global__ __launch_bounds__(kNT) void general_search_kernel(
       if (b - gap0 >= gap_n && (lookup[2 * b + 1] >> 16)) sm.key[atomicAdd(&lookup[2 * b], 1u)] = key;
     });
     __syncthreads();
-    // order inside a bin by counting (a few dozen values: the row's weights separate the rest)
     uint32_t k[3], dst[3];
+    if (sm.most <= kCountMax) {
+      // order inside a bin by counting (a few dozen values: the row's weights separate the rest)
 #pragma unroll
-    for (int r = 0; r < 3; ++r) {
-      const uint32_t t = uint32_t(tid + r * kNT);
-      dst[r] = 0xffffffffu;
-      if (t < uint32_t(T)) {
-        k[r] = sm.key[t];
-        const uint32_t l = lookup[2 * (k[r] >> 20) + 1], m = l >> 16, at = l & 0xffffu;
-        if (m != 0) {
-          uint32_t less = 0;
-          for (uint32_t j = at; j < at + m; ++j) {
-            const uint32_t o = sm.key[j];
-            less += (o < k[r] || (o == k[r] && j < t)) ? 1u : 0u;
+      for (int r = 0; r < 3; ++r) {
+        const uint32_t t = uint32_t(tid + r * kNT);
+        dst[r] = 0xffffffffu;
+        if (t < uint32_t(T)) {
+          k[r] = sm.key[t];
+          const uint32_t l = lookup[2 * (k[r] >> 20) + 1], m = l >> 16, at = l & 0xffffu;
+          if (m != 0) {
+            uint32_t less = 0;
+            for (uint32_t j = at; j < at + m; ++j) {
+              const uint32_t o = sm.key[j];
+              less += (o < k[r] || (o == k[r] && j < t)) ? 1u : 0u;
+            }
+            dst[r] = at + less;
           }
-          dst[r] = at + less;
+        }
+      }
+    } else {
+      // full bins (many equal values): the items are in the order of their bins, one network over all of them
+      // leaves the bins in place and orders the values inside (items beyond T count as largest)
+      const int pairs = 1 << (31 - __clz(T - 1));                    // half the next power of two
+      for (int size = 2; size <= 2 * pairs; size <<= 1) {
+        for (int s = size >> 1; s >= 1; s >>= 1) {
+          for (int p = tid; p < pairs; p += kNT) {
+            const int a = (p & ~(s - 1)) * 2 + (p & (s - 1));
+            const int b = s == size >> 1 ? a + size - 1 - 2 * (p & (s - 1)) : a + s;
+            if (b < T) {
+              const uint32_t ka = sm.key[a], kb = sm.key[b];
+              if (ka > kb) {
+                sm.key[a] = kb;
+                sm.key[b] = ka;
+              }
+            }
+          }
+          __syncthreads();
+        }
+      }
+#pragma unroll
+      for (int r = 0; r < 3; ++r) {
+        const uint32_t t = uint32_t(tid + r * kNT);
+        dst[r] = 0xffffffffu;
+        if (t < uint32_t(T)) {
+          k[r] = sm.key[t];
+          if (lookup[2 * (k[r] >> 20) + 1] >> 16) dst[r] = t;
         }
       }
     }

@@ -61,3 +61,37 @@ def test_rows_and_weights_left_to_the_kernel_that_sorts(gpu):
             assert np.array_equal(np.isfinite(got), np.isfinite(ref))
             ok = np.isfinite(ref)
             assert (np.abs(got[ok] - ref[ok]) <= 1e-5 + 1.2e-7 * np.abs(ref[ok])).all()
+
+
+# Bins whose values are ordered by counting (up to 64) and by a network over all items, the most items that a row
+# may have (2816), rows of one value: equal and different values that share a bin.
+@pytest.mark.parametrize("m", [2, 63, 64, 65, 66, 700, 2047, 2800, 2815, 2816, 2817])
+def test_full_bins(gpu, oracle, m):
+    n = 6000
+    r = np.random.default_rng(m)
+    base = np.where(np.arange(n) < n // 2, -40.0, 40.0) + r.normal(size=n)
+    x = np.stack([base, base, base, np.full(n, 0.7)]).astype(np.float32)
+    x[0, r.choice(n, m, replace=False)] = 0.7                                  # equal values
+    x[1, r.choice(n, m, replace=False)] = 1.0 + 0.1 * r.random(size=m)         # different ones, one bin of 1/8
+    x[2, r.choice(n, m, replace=False)] = np.round(1.0 + 0.1 * r.random(size=m), 2)
+    for name, w in weight_rows(n).items():
+        for lam in (1e-6, 1e-3, 0.1, 3.0):
+            w32 = w.astype(np.float32)
+            ref = oracle.topk_general(x, w32, P2, lam, "id")["out"]
+            close(host(gpu.topk_general_fwd(dev(x), dev(w32), gpu.TOPK_PHI_IDENTITY, P2, lam)), ref, f"{name} {lam}")
+
+
+# 1000 rows of 2000 equal values: 1200 us when the bin's values are ordered by counting, 200 us with a complete sort
+def test_time_of_rows_of_one_value(gpu):
+    import torch
+    x = torch.full((1000, 2000), 0.7, device="cuda")
+    w = torch.arange(2000, 0, -1, device="cuda", dtype=torch.float32)
+    times = []
+    for _ in range(4):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        gpu.topk_general_fwd(x, w, gpu.TOPK_PHI_IDENTITY, P2, 0.1)
+        b.record()
+        b.synchronize()
+        times.append(a.elapsed_time(b))
+    assert min(times) < 0.6, times
