@@ -37,6 +37,7 @@
 #include "pooling.hpp"
 #include "launch.hpp"
 #include "general_pav.hpp"
+#include "sort_network.hpp"
 
 namespace topk {
 namespace {
@@ -546,24 +547,8 @@ __global__ __launch_bounds__(kNT) void general_search_kernel(
       }
     } else {
       // full bins (many equal values): the items are in the order of their bins, one network over all of them
-      // leaves the bins in place and orders the values inside (items beyond T count as largest)
-      const int pairs = 1 << (31 - __clz(T - 1));                    // half the next power of two
-      for (int size = 2; size <= 2 * pairs; size <<= 1) {
-        for (int s = size >> 1; s >= 1; s >>= 1) {
-          for (int p = tid; p < pairs; p += kNT) {
-            const int a = (p & ~(s - 1)) * 2 + (p & (s - 1));
-            const int b = s == size >> 1 ? a + size - 1 - 2 * (p & (s - 1)) : a + s;
-            if (b < T) {
-              const uint32_t ka = sm.key[a], kb = sm.key[b];
-              if (ka > kb) {
-                sm.key[a] = kb;
-                sm.key[b] = ka;
-              }
-            }
-          }
-          __syncthreads();
-        }
-      }
+      // leaves the bins in place and orders the values inside
+      lds_sort<kNT>(sm.key, T);
 #pragma unroll
       for (int r = 0; r < 3; ++r) {
         const uint32_t t = uint32_t(tid + r * kNT);

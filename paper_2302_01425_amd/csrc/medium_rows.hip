@@ -22,6 +22,7 @@
 #include "long_solve.hpp"
 #include "pooling.hpp"
 #include "radix.hpp"
+#include "sort_network.hpp"
 
 namespace topk {
 namespace {
@@ -474,8 +475,27 @@ __global__ __launch_bounds__(kFinishThreads) void finish_kernel(uint32_t* keys_a
 }
 
 // Complete sort of the rows with todo[row] != 0, one workgroup per row: (key, index) into the "a"
-// arrays.  For the few rows that general_search.hip hands over; the launch costs 3 us when there
-// are none, twelve launches of the multi-workgroup sort would cost 30.
+// arrays.  For the rows that general_search.hip hands over: none mostly, and then the launch costs 3 us (twelve
+// launches of the multi-workgroup sort would cost 30), but all of a call's rows where lambda is far below the
+// distances of the values or the weights increase.  Rows of up to kRowNetMax elements: a bitonic network on
+// (key, index) words in LDS, bound by its exchanges (4000 x 3000: 385 us, radix passes of one workgroup per
+// row 510, the multi-workgroup sort 380).  Longer ones: radix passes through global memory (64 x 40000 380 us,
+// 4 x 131072 1030, where the multi-workgroup sort takes 135 on the whole chip).
+constexpr int kRowNetMax = 8192;
+__global__ __launch_bounds__(kFinishThreads) void row_sort_net_kernel(const float* __restrict__ x_all,
+                                                     uint32_t* __restrict__ keys_a, uint32_t* __restrict__ idx_a,
+                                                     const uint32_t* __restrict__ todo, int n) {
+  __shared__ unsigned long long word[kRowNetMax];
+  if (todo[blockIdx.x] == 0) return;
+  const int64_t base = int64_t(blockIdx.x) * n;
+  for (int e = threadIdx.x; e < n; e += kFinishThreads)
+    word[e] = (unsigned long long)desc_key(x_all[base + e]) << 32 | uint32_t(e);
+  lds_sort<kFinishThreads>(word, n);
+  for (int e = threadIdx.x; e < n; e += kFinishThreads) {
+    keys_a[base + e] = uint32_t(word[e] >> 32);
+    idx_a[base + e] = uint32_t(word[e]);
+  }
+}
 __global__ __launch_bounds__(kFinishThreads) void row_sort_kernel(const float* __restrict__ x_all,
                                                      uint32_t* keys_a, uint32_t* idx_a,
                                                      uint32_t* keys_b, uint32_t* idx_b,
@@ -551,8 +571,13 @@ int launch_medium_rows_sparse(int pc, const SortBuffers& B, const float* x, int6
 int launch_row_sort(const SortBuffers& B, const float* x, int64_t rows, int64_t n,
                     const uint32_t* todo, hipStream_t st) {
   if (n > kMediumRowMax || rows > 0x7fffffffLL) return -1;
-  hipLaunchKernelGGL(row_sort_kernel, dim3(unsigned(rows)), dim3(kFinishThreads), 0, st, x, B.keys_a,
-                     B.idx_a, B.keys_b, B.idx_b, todo, int(n));
+  if (n < 2) return -1;
+  if (n <= kRowNetMax)
+    hipLaunchKernelGGL(row_sort_net_kernel, dim3(unsigned(rows)), dim3(kFinishThreads), 0, st, x, B.keys_a,
+                       B.idx_a, todo, int(n));
+  else
+    hipLaunchKernelGGL(row_sort_kernel, dim3(unsigned(rows)), dim3(kFinishThreads), 0, st, x, B.keys_a,
+                       B.idx_a, B.keys_b, B.idx_b, todo, int(n));
   return 0;
 }
 

@@ -120,4 +120,37 @@ __device__ __forceinline__ void make_keys(const float (&v)[E], int e0, int n, do
 }
 
 
+// Ascending sort of w[0, n) in LDS by NT threads (all of them call it, n >= 2 uniform, NT a multiple of 64): the
+// bitonic network in mirror form, in which the smaller word always moves down; words beyond n would count as
+// largest and are not there.  A wavefront's 64 exchanges of a stage with s <= 64 stay inside 128 words, so that
+// barriers are needed around the longer ones only (15 of the 78 stages of 4096 words).
+template <int NT, class T>
+__device__ __forceinline__ void lds_sort(T* w, int n) {
+  const int pairs = 1 << (31 - __clz(n - 1));          // half the next power of two
+#pragma unroll 1
+  for (int size = 2; size <= 2 * pairs; size <<= 1) {
+    if (size == 2 || size >= 256) __syncthreads();
+#pragma unroll 1
+    for (int s = size >> 1; s >= 1; s >>= 1) {
+      for (int p = threadIdx.x; p < pairs; p += NT) {
+        const int off = p & (s - 1), a = (p - off) * 2 + off, b = s == size >> 1 ? a + size - 1 - 2 * off : a + s;
+        if (b < n) {
+          const T wa = w[a], wb = w[b];
+          if (wa > wb) {
+            w[a] = wb;
+            w[b] = wa;
+          }
+        }
+      }
+      if (s >= 128) {
+        __syncthreads();
+      } else {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+      }
+    }
+  }
+  __syncthreads();
+}
+
 }  // namespace topk

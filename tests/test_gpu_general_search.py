@@ -95,3 +95,16 @@ def test_time_of_rows_of_one_value(gpu):
         b.synchronize()
         times.append(a.elapsed_time(b))
     assert min(times) < 0.6, times
+
+
+# Rows that are left to the kernel that sorts: lengths around the longest one that a network in LDS sorts (8192) and
+# powers of two, with ties (equal keys keep their index order); against the oracle.
+@pytest.mark.parametrize("n", [1025, 2048, 2049, 4096, 4097, 8191, 8192, 8193])
+def test_rows_left_over_are_sorted(gpu, oracle, n):
+    r = np.random.default_rng(n)
+    x = np.stack([r.normal(size=n), np.round(r.normal(size=n) * 8) / 8, np.full(n, 0.5), np.sort(r.normal(size=n))]).astype(np.float32)
+    up = np.arange(1, n + 1, dtype=np.float32)                                 # increasing: every row is left over
+    few = (1.0 / (1.0 + np.arange(n))).astype(np.float32)
+    for w, lam in ((up, 0.01), (up, 3.0), (few, 1e-7)):
+        ref = oracle.topk_general(x, w, P2, lam, "id")["out"]
+        close(host(gpu.topk_general_fwd(dev(x), dev(w), gpu.TOPK_PHI_IDENTITY, P2, lam)), ref, f"{lam}")
