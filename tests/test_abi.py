@@ -83,6 +83,18 @@ def test_binding_refuses_cpu_tensors(lib):
         b.topk_mask_fwd(torch.zeros(2, 8), 2, 2.0, 1.0)
 
 
+def test_current_stream_without_private_functions(monkeypatch):
+    import types
+    import torch
+    from paper_2302_01425_amd import binding as b
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=1234))
+    for name in ("_raw_stream", "_raw_device"):
+        with monkeypatch.context() as m:
+            m.setattr(b, name, None)
+            assert b._stream(None) == 1234
+    assert b._stream(types.SimpleNamespace(cuda_stream=77)) == 77 and b._stream(5) == 5
+
+
 def test_argument_validation_of_the_wider_entry_points(lib):
     from paper_2302_01425_amd import binding as b
     one = ctypes.c_void_p(256)          # never dereferenced: validation happens first
