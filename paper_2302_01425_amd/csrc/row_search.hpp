@@ -599,46 +599,48 @@ __global__ __launch_bounds__(NT == 64 ? 256 : NT) void row_search_kernel(
       w_hi = uniform_f32(w_hi, 0);
     }
   }
+  // the elements within `half` of `mid` go to the list, if they fit; the number of those above them
+  uint32_t above_list = 0u;
+  float2* list = lists[RPB > 1 ? int(threadIdx.x) / NT : 0];
+  auto gather = [&](float mid, float half) __attribute__((always_inline)) {
+    uint32_t c0 = 0u, c1 = 0u;
+#pragma unroll
+    for (int r = 0; r < E; ++r) {
+      const float t = val(r) - mid;
+      c0 += fabsf(t) <= half ? 1u : 0u;
+      c1 += t > half ? 1u : 0u;
+      pass_fence(r, c0, c1);
+    }
+    uint32_t total, c = c0 | (c1 << 16);
+    uint32_t at = (grp.scan(c, &total) & 0xffffu) - c0;
+    list_at = at;
+    list_mid = mid;
+    list_half = half;
+    len = total & 0xffffu;
+    above_list = total >> 16;
+    if (len <= uint32_t(kListMax)) {
+#pragma unroll
+      for (int r = 0; r < E; ++r) {
+        const float v = val(r);
+        if (fabsf(v - mid) <= half) {
+          const uint32_t e = uint32_t(((r >> 2) * NT + tid) * 4 - shift + (r & 3));
+          list[at] = make_float2(v, __uint_as_float(e | (__float_as_uint(xr[r]) & 0x80000000u)));
+          ++at;
+        }
+        pass_fence(r, at);
+      }
+    }
+    if constexpr (W > 1) __syncthreads();
+    else __builtin_amdgcn_wave_barrier();
+  };
   if (!done) {
     // ---- 3. the list of the elements that may belong to the block ----------------------------------------
-    float2* list = lists[RPB > 1 ? int(threadIdx.x) / NT : 0];
     // (with 0.3 of a block's width to spare on either side, or more where a width holds but a few elements:
     // then a root may be that far from a value of Psi below 0.3; the last term is for blocks narrower than
     // the spacing of floats)
     const float width_g = width_at(g), mid = g + 0.5f * width_g;
     const float half = (0.5f + spare) * width_g + 5e-7f * fabsf(mid);
-    uint32_t above_list = 0u;
-    if (near) {
-      uint32_t c0 = 0u, c1 = 0u;
-#pragma unroll
-      for (int r = 0; r < E; ++r) {
-        const float t = val(r) - mid;
-        c0 += fabsf(t) <= half ? 1u : 0u;
-        c1 += t > half ? 1u : 0u;
-        pass_fence(r, c0, c1);
-      }
-      uint32_t total, c = c0 | (c1 << 16);
-      uint32_t at = (grp.scan(c, &total) & 0xffffu) - c0;
-      list_at = at;
-      list_mid = mid;
-      list_half = half;
-      len = total & 0xffffu;
-      above_list = total >> 16;
-      if (len <= uint32_t(kListMax)) {
-#pragma unroll
-        for (int r = 0; r < E; ++r) {
-          const float v = val(r);
-          if (fabsf(v - mid) <= half) {
-            const uint32_t e = uint32_t(((r >> 2) * NT + tid) * 4 - shift + (r & 3));
-            list[at] = make_float2(v, __uint_as_float(e | (__float_as_uint(xr[r]) & 0x80000000u)));
-            ++at;
-          }
-          pass_fence(r, at);
-        }
-      }
-      if constexpr (W > 1) __syncthreads();
-      else __builtin_amdgcn_wave_barrier();
-    }
+    if (near) gather(mid, half);
     use_list = near && len <= uint32_t(kListMax);
     auto list_pass = [&](auto& G, int first, int step, float lo, float hi, float c32, uint32_t* above,
                          uint32_t* members) -> Sums {
@@ -1029,6 +1031,13 @@ __global__ __launch_bounds__(NT == 64 ? 256 : NT) void row_search_kernel(
           }
         }
       }
+      // the tangents go through the list again (600 x 20000 values on a grid of 1/16, lambda = 1e-3: 101 us, 137 with a
+      // pass over the row in the caches instead)
+      if (have && want_jvp) {
+        const float mid_b = 0.5f * lo_f + 0.5f * hi_f;
+        gather(mid_b, fmaxf(hi_f - mid_b, mid_b - lo_f));
+        use_list = len <= uint32_t(kListMax);
+      }
     }
   }
 
@@ -1074,7 +1083,6 @@ __global__ __launch_bounds__(NT == 64 ? 256 : NT) void row_search_kernel(
       }
     };
     if (use_list) {
-      float2* list = lists[RPB > 1 ? int(threadIdx.x) / NT : 0];
 #pragma unroll 1
       for (uint32_t j = tid; j < len; j += NT) {
         const float2 q = list[j];
@@ -1161,7 +1169,7 @@ __global__ __launch_bounds__(NT == 64 ? 256 : NT) void row_search_kernel(
           float tau = 0.0f;
           if constexpr (LIST_TAU) {
             if (use_list) {
-              if (listed[r]) tau = lists[RPB > 1 ? int(threadIdx.x) / NT : 0][list_at++].y;
+              if (listed[r]) tau = list[list_at++].y;
             } else if (in) {
               tau = tangent[first_of(c) + r];
             }

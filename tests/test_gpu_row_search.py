@@ -1,6 +1,7 @@
 """The kernel that finds a row's pooled value by root search in registers (csrc/row_search.hpp): row
-lengths at the edges of its shapes, few and many rows, unaligned arrays, blocks from none to most of
-the row, ties at the block's ends.  Bar: that of test_gpu_parity (1e-5 + one float32 ulp)."""
+lengths at the edges of its shapes for few rows and for many, rows whose values are far from its first
+guess, unaligned arrays, blocks from none to most of the row, ties at the block's ends and around zero,
+every route.  Bar: that of test_gpu_parity (1e-5 + one float32 ulp)."""
 import numpy as np
 import pytest
 
@@ -13,6 +14,7 @@ EDGES = [129, 255, 256, 509, 512, 513, 1021, 1024, 1533, 1537, 2045, 2046, 2047,
          5117, 5120, 6141, 8189, 8192, 10237, 12285, 16381, 16384, 20477, 24573, 32765, 32766, 32768]
 
 
+# (three rows: the shapes of up to 256 rows, 8 or 16 elements per thread up to 16384 elements)
 @pytest.mark.parametrize("n", EDGES)
 def test_lengths_at_the_edges_of_the_shapes(gpu, oracle, n):
     r = np.random.default_rng(n)
@@ -26,6 +28,49 @@ def test_lengths_at_the_edges_of_the_shapes(gpu, oracle, n):
             run_case(gpu, oracle, "mag", x, t, k, p, lam, check_perm=False)
     run_case(gpu, oracle, "mask", x, t, n // 3, P2, 20.0, check_perm=False)     # a block longer than the list
     run_case(gpu, oracle, "mag", x, t, n // 3, P2, 20.0, check_perm=False)
+
+
+# Every shape (threads per row x elements per thread) that more than 256 rows select, at the longest row that fits it
+# with aligned and with unaligned rows; the row counts are just above a threshold and no multiple of four.
+SHAPES = [(259, 512), (259, 1024), (259, 2045), (1541, 1536), (1541, 2048), (259, 3072), (259, 4096), (259, 5120),
+          (259, 6144), (259, 8192), (1027, 8192), (259, 10240), (259, 12288), (259, 16384), (515, 16384), (259, 20480),
+          (259, 24576), (259, 32768)]
+
+
+@pytest.mark.parametrize("rows,n", SHAPES + [(rows, n - 3) for rows, n in SHAPES if n % 4 == 0])
+def test_every_shape_at_its_longest_rows(gpu, oracle, rows, n):
+    r = np.random.default_rng(rows + n)
+    x = r.normal(size=(rows, n)).astype(np.float32)
+    t = r.normal(size=x.shape).astype(np.float32)
+    some = sorted({0, 1, 2, rows // 2, rows - 3, rows - 2, rows - 1})          # (all of the last workgroup)
+    xd, td, k = dev(x), dev(t), n // 10
+    for p, lam in ((P2, 0.02), (P43, 0.02)):
+        for op in (gpu.topk_mask_jvp, gpu.topkmag_jvp):
+            print(op.__name__, rows, n, k, p, lam, flush=True)
+            ref = (oracle.topk_mask if op is gpu.topk_mask_jvp else oracle.topkmag)(x[some], k, p, lam, tangent=t[some])
+            o, j = (host(a) for a in op(xd, td, k, p, lam))
+            close(o[some], ref["out"], (op.__name__, p))
+            close(j[some], ref["jvp"], (op.__name__, p, "jvp"))
+
+
+@pytest.mark.parametrize("rows,n", [(259, 600), (259, 1021), (259, 1533), (1541, 1533), (1541, 1536), (1541, 2045), (259, 3069)])
+def test_operators_built_on_the_mask_and_the_loss_many_rows(gpu, oracle, rows, n):
+    r = np.random.default_rng(rows + n)
+    x = r.normal(size=(rows, n)).astype(np.float32)
+    t = r.normal(size=x.shape).astype(np.float32)
+    some = sorted({0, 1, 2, rows // 2, rows - 3, rows - 2, rows - 1})
+    xd, td, k = dev(x), dev(t), n // 5
+    for p, lam in ((P2, 0.3), (P43, 0.05)):
+        for name in ("topk_signed_mask", "topk_masked_value"):
+            print(name, rows, n, k, p, lam, flush=True)
+            ref = getattr(oracle, name)(x[some], k, p, lam, tangent=t[some])
+            o, j = (host(a) for a in getattr(gpu, name + "_jvp")(xd, td, k, p, lam))
+            close(o[some], ref["out"], name)
+            close(j[some], ref["jvp"], name + " jvp")
+        ref_loss, ref_grad = oracle.fenchel_young_loss(x[some], t[some], k, p, lam)
+        loss, grad = (host(a) for a in gpu.topk_mask_loss(xd, td, k, p, lam))
+        close(grad[some], ref_grad, "grad")
+        close(loss[some], ref_loss, "loss")
 
 
 @pytest.mark.parametrize("rows,n", [(300, 1000), (300, 2000), (300, 3000), (300, 4096), (600, 8190), (1100, 8192),
