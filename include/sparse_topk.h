@@ -190,8 +190,10 @@ int topk_mask_sparse_fwd(const float* theta, int64_t rows, int64_t n, int64_t k,
  *   identity form with p = 2: without one where the values allow it), with
  *   topk_workspace_bytes(TOPK_OP_GENERAL, rows, n, 0, p) bytes of workspace (TOPK_ERR_WORKSPACE
  *   without).  The partition is built in rounds that remove all violating block boundaries at
- *   once; rows on which only one boundary violates at a time fall back to the sequential walk of
- *   the block stack and are slow.  Other arguments and errors as topk_mask_fwd / topk_mask_jvp.
+ *   once; rows on which only one boundary violates at a time are slow: with p = 2 they fall back to the
+ *   sequential walk of the block stack, except rows of up to TOPK_SHORT_ROW_MAX elements with one weight
+ *   vector for all rows, which stay with the rounds (at most n - 1).  Other arguments and errors as
+ *   topk_mask_fwd / topk_mask_jvp.
  */
 int topk_general_fwd(const float* x, const float* w, int64_t w_stride, int64_t rows, int64_t n,
                      int phi, double p, double lambda, float* out, void* stream);

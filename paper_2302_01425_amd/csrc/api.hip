@@ -72,7 +72,8 @@ bool value_wide(bool mag, int pc, int64_t n) {
 //     sort / search): 2048 elements, 4 M in all, k = 33 15.5 / 17, k = 205 23 / 18; k = 100, 64 x 1200
 //     12.9 / 9.1, 2000 x 1200 20.6 / 16.6.  Up to 1024 it does not, and takes the same time whatever the
 //     values: k = 100, normal values 64 x 1000 8.3 / 9.4, 1000 x 1000 9.9 / 13.2, 1000 x 600 9.0 / 13.1, whole
-//     numbers 1000 x 1000 10.1 / 22.0; p = 4/3 11.7 / 14.4 and 12.6 / 23.5;
+//     numbers 1000 x 1000 10.1 / 22.0; p = 4/3 11.7 / 14.4 and 12.6 / 23.5.  (It loses on large batches of
+//     normal values alone: 16384 x 1024 56 / 49, p = 4/3 69 / 56);
 //   * top-k in magnitude with p = 4/3, which they do not have: 4096 x 400 121 / 27.
 // fused: the operators built on the mask and the loss, whose rows of up to 2048 elements know no long-row
 // route (abs_fused below).

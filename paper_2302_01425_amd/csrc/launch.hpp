@@ -120,7 +120,8 @@ int launch_short_argsort_fast(int np, int lg, bool vec, const float* x, int32_t*
 int launch_short_rows_fast_sparse(int np, int lg, bool vec, int pc, const float* x, int64_t rows,
                                   int n, int k, const Reg& R, const SparseOut& sp, hipStream_t st);
 
-// Rows of 129 .. kRowSearchMax elements, dense outputs, no scratch (row_search.hpp).  var: 0 the
+// Rows of 1025 .. kRowSearchMax elements (top-k in magnitude with p = 4/3: from kRowSearchMin; below 1025
+// the short-row kernels have the rest), dense outputs, no scratch (row_search.hpp).  var: 0 the
 // operator itself, 1 signed mask, 2 x o mask(|x|), 3 Fenchel-Young loss (tangent = target, out = the
 // gradient, loss[rows]).  Returns 0, -1 (too many rows) or -2 (no shape: above 32765 elements where
 // rows do not all start at a 16-byte boundary).

@@ -14,20 +14,23 @@
 //
 //   1. a first guess from order statistics: the maxima of 1, 8 or all elements of a lane are sorted 16
 //      at a time; the quantile of those maxima that corresponds to rank k estimates s_k;
-//   2. bracketed secant steps on Psi in float32 (2 to 5 on the inputs measured; no derivative: an
-//      evaluation is a subtraction, a clamped product and an addition per element): they only have
-//      to come near the root;
+//   2. bracketed secant steps on Psi in float32 (2 to 5 on normal values, sixteen at most; no
+//      derivative: an evaluation is a subtraction, a clamped product and an addition per element):
+//      they only have to come near the root.  Rows of few different values, on which Psi jumps, go
+//      on from s_k (5) as soon as the bracket holds one value;
 //   3. the elements within a third of the block's width of the block at g go to a list in LDS;
 //   4. exact steps on the list: the members of the block at g are counted and their power sums taken in
 //      float64, the pooled value of that set is the next g (the root of the piece of Psi that g lies
 //      on); when the set no longer changes the value is final.  The membership thresholds are floats,
 //      so a set is described by two counts.  (Lists that do not fit, and steps that leave the list's
 //      window, take passes over the registers instead.)
-//   5. where a threshold lies within rounding of a float32 value, an element with that value would be
-//      a tie of the strict tests: then (and when the steps above did not converge) the block is grown
-//      from the elements that certainly belong to it with the strict tests of the PAV loop
-//      themselves (pooling.hpp), one neighbouring value per step.  The decisions are the same as
-//      those of the kernels that order the row.
+//   5. where the steps above did not come to a value: s_k by bisection over the floats in their order,
+//      then the set of the block from the pair (s_k, s_{k+1}) on, in passes over the registers whose
+//      number is bounded whatever the values.  And where a threshold lies within rounding of an
+//      element's value, that element would be a tie of the strict tests: the block is grown from the
+//      elements that certainly belong to it with the strict tests of the PAV loop themselves
+//      (pooling.hpp), one neighbouring value per step.  The decisions are the same as those of the
+//      kernels that order the row.
 //
 // The kernels that order values need (log n)^2 / 2 exchanges per element; a step here costs 5 to 8
 // instructions per element.
