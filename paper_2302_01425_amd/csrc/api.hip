@@ -198,11 +198,8 @@ int run_operator(bool mag, const float* x, const float* tangent, int64_t rows, i
   // streaming steps of a row are spread over many workgroups (separate launches) and only the
   // sort + solve of its candidates is left to one.
   if (!trivial && (mode == kWide || (mode == kAuto && n > 32765))) {
-    const bool refine = n > (int64_t(1) << 18);
-    if (topk::launch_wide_select(mag, pc, refine, x, need_jvp ? tangent : nullptr, rows, n, k, R, B,
-                                 st) != 0)
-      return TOPK_ERR_INVALID;
-    if (topk::launch_wide_finish(mag, pc, B, need_jvp, refine, rows, n, k, R, st) != 0)
+    if (topk::launch_wide_window(mag, pc, x, rows, n, k, R, B, st) != 0) return TOPK_ERR_INVALID;
+    if (topk::launch_wide_solve(mag, pc, B, x, need_jvp ? tangent : nullptr, rows, n, k, R, st) != 0)
       return TOPK_ERR_INVALID;
     if (topk::launch_wide_dense(mag, pc, B, x, need_jvp ? tangent : nullptr, out,
                                 need_jvp ? jvp : nullptr, rows, n, R, st) != 0)

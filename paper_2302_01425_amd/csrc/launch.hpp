@@ -54,6 +54,9 @@ constexpr int kSel2Bits = 8;              // further key bits of the second one
 constexpr int kSel2Bins = 1 << kSel2Bits;
 constexpr int kSelSlices = 16;            // partial sums a histogram is left in (see radix_sort.hip)
 
+constexpr int kWideGroups = 16;           // groups of workgroups of a row in the wide route (wide_rows.hip)
+constexpr int kWideCounters = 1 + kWideGroups;     // arrival counters of a row: the row itself, then the groups
+
 // Device scratch of the long-row path (all carved out of the caller's workspace).
 struct SortBuffers {
   uint32_t* keys_a;   // [rows*n] sorted keys end here
@@ -169,17 +172,13 @@ int launch_medium_rows(bool mag, int pc, const SortBuffers& B, const float* x, c
 // index order, as a dense list per row in the "a" arrays; B.sel[row] = {window, length, above}.
 int launch_candidate_lists(bool mag, int pc, const float* x, int64_t rows, int64_t n, int64_t k,
                            const Reg& R, const SortBuffers& B, hipStream_t st);
-// Wide route (rows that several workgroups share; 0 < k < n): the same candidate selection with
-// the candidates left in the tiles' slots of the "b" arrays (B.tcnt, B.tabove); one workgroup per
-// row then collects them, sorts their keys, grows the block and adds up the tangent over it
-// (B.info[row]: gamma, d gamma and the block's value window); one dense pass computes every
-// output from its element's value.  refine: second histogram level (worth it for very long rows).
-// tangent (may be null): the candidates carry their tangent as payload instead of their index.
-int launch_wide_select(bool mag, int pc, bool refine, const float* x, const float* tangent,
-                       int64_t rows, int64_t n, int64_t k, const Reg& R, const SortBuffers& B,
-                       hipStream_t st);
-int launch_wide_finish(bool mag, int pc, const SortBuffers& B, bool want_jvp, bool dense,
-                       int64_t rows, int64_t n, int64_t k, const Reg& R, hipStream_t st);
+// Wide route (rows that several workgroups share; 0 < k < n): the key window of every row (B.sel: the first level
+// of that selection); gamma, d gamma and the block's value window (B.info) from two more launches, without a sort
+// (wide_rows.hip); one dense pass computes every output from its element's value.
+int launch_wide_window(bool mag, int pc, const float* x, int64_t rows, int64_t n, int64_t k, const Reg& R,
+                       const SortBuffers& B, hipStream_t st);
+int launch_wide_solve(bool mag, int pc, const SortBuffers& B, const float* x, const float* tangent, int64_t rows,
+                      int64_t n, int64_t k, const Reg& R, hipStream_t st);
 int launch_wide_dense(bool mag, int pc, const SortBuffers& B, const float* x, const float* tangent,
                       float* out, float* jvp, int64_t rows, int64_t n, const Reg& R,
                       hipStream_t st);

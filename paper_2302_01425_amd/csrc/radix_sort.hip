@@ -364,23 +364,21 @@ __global__ __launch_bounds__(kThreads) void reduce_partials_kernel(const uint32_
 // below and s_{k+1} from above; the key window [klo, khi] holds both bins and every element that
 // passes the necessary conditions for joining the block (pooling.hpp: left_candidate,
 // right_candidate) for ANY s_k, s_{k+1} inside those bins.  Requires 1 <= k < n.
-// bins2 (may be null): the row's partial histograms of the second level, cleared here because the
-// compaction pass adds to them.
+// The first `clear` words of the row's part of bins2 are cleared: the partial histograms of the second level, to which
+// the compaction pass adds, resp. the counters of the wide route.
 constexpr int kWinThreads = 1024;              // four bins per thread: every slice's load in flight
 template <bool MAG>
 __global__ __launch_bounds__(kWinThreads) void select_window_kernel(const uint32_t* __restrict__ bins,
                                                                     RowSel* __restrict__ sel,
                                                                     int64_t k, int gcopies, Reg R,
-                                                                    bool cubic,
-                                                                    uint32_t* __restrict__ bins2) {
+                                                                    bool cubic, uint32_t* __restrict__ bins2,
+                                                                    int clear) {
   constexpr int kPerThread = kSelBins / kWinThreads;
   static_assert(kPerThread == 4, "a thread reads its bins of one slice as one uint4");
   __shared__ uint32_t wave_tot[kWinThreads / kWave];
   __shared__ uint32_t found[2];
   const int64_t row = blockIdx.x;
-  if (bins2 != nullptr)
-    for (int i = threadIdx.x; i < kSelSlices * 2 * kSel2Bins; i += kWinThreads)
-      bins2[row * (kSelSlices * 2 * kSel2Bins) + i] = 0u;
+  for (int i = threadIdx.x; i < clear; i += kWinThreads) bins2[row * (kSelSlices * 2 * kSel2Bins) + i] = 0u;
   const uint32_t* b = bins + row * gcopies * kSelBins;
   uint32_t c[kPerThread] = {0u, 0u, 0u, 0u}, mine = 0;
   for (int g0 = 0; g0 < gcopies; g0 += kSelSlices) {
@@ -481,21 +479,16 @@ __global__ __launch_bounds__(kThreads) void select_refine_kernel(const uint32_t*
 // written with full wavefronts; candidates inside the histogram bins of positions k and k+1 are
 // also counted by their next kSel2Bits key bits (second selection level: added to the row's
 // partial histograms bins2[row][tile % kSelSlices], which the window kernel has cleared).
-// TAU: the payload of a candidate is not its index but the bits of its tangent in sorted-value
-// coordinates (t, or sign(x) t for the magnitude operator; 0 without a tangent): what the wide
-// route needs, whose outputs are computed from values.
-template <bool MAG, bool HIST2 = true, bool TAU = false>
+template <bool MAG>
 __global__ __launch_bounds__(kThreads) void select_compact_kernel(
     const float* __restrict__ x, const RowSel* __restrict__ sel, uint32_t* __restrict__ keys_out,
     uint32_t* __restrict__ idx_out, uint32_t* __restrict__ tcnt, uint32_t* __restrict__ tabove,
-    uint32_t* __restrict__ bins2, int64_t n, int tiles,
-    const float* __restrict__ tangent = nullptr) {
+    uint32_t* __restrict__ bins2, int64_t n, int tiles) {
   __shared__ uint32_t wave_cand[kWaves], wave_above[kWaves];
   __shared__ uint32_t kbuf[kTile];
   __shared__ uint32_t ibuf[kTile];
-  __shared__ uint32_t h2[HIST2 ? 2 * kSel2Bins : 1];
-  if (HIST2)
-    for (int i = threadIdx.x; i < 2 * kSel2Bins; i += kThreads) h2[i] = 0;
+  __shared__ uint32_t h2[2 * kSel2Bins];
+  for (int i = threadIdx.x; i < 2 * kSel2Bins; i += kThreads) h2[i] = 0;
   const int64_t row = blockIdx.x / tiles;
   const int tile = blockIdx.x % tiles;
   const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
@@ -537,26 +530,12 @@ __global__ __launch_bounds__(kThreads) void select_compact_kernel(
     total += wave_cand[q];
     above += wave_above[q];
   }
-  float tq[TAU ? kItems : 1];              // the candidates' tangents: all loads in flight at once
-  if (TAU) {
-#pragma unroll
-    for (int i = 0; i < kItems; ++i) {
-      const int64_t e = tile_first + chunk + i * kWave + lane;
-      tq[i] = (tangent != nullptr && pos[i] != 0xffffffffu) ? tangent[row_base + e] : 0.0f;
-    }
-  }
 #pragma unroll
   for (int i = 0; i < kItems; ++i) {
     if (pos[i] != 0xffffffffu) {
       const int64_t e = tile_first + chunk + i * kWave + lane;
       kbuf[before + pos[i]] = first_key<MAG>(val[i]);
-      if (TAU) {
-        float t = tq[TAU ? i : 0];
-        if (MAG) t = val[i] == 0.0f ? 0.0f : (val[i] < 0.0f ? -t : t);
-        ibuf[before + pos[i]] = __float_as_uint(t);
-      } else {
-        ibuf[before + pos[i]] = MAG ? ((uint32_t(e) << 1) | (__float_as_uint(val[i]) >> 31)) : uint32_t(e);
-      }
+      ibuf[before + pos[i]] = MAG ? ((uint32_t(e) << 1) | (__float_as_uint(val[i]) >> 31)) : uint32_t(e);
     }
   }
   __syncthreads();
@@ -564,56 +543,35 @@ __global__ __launch_bounds__(kThreads) void select_compact_kernel(
     const uint32_t key = kbuf[j];
     keys_out[row_base + tile_first + j] = key;
     idx_out[row_base + tile_first + j] = ibuf[j];
-    if (HIST2) {
-      const uint32_t top = key >> kSelShift;
-      const uint32_t sub = (key >> (kSelShift - kSel2Bits)) & (kSel2Bins - 1);
-      if (top == bin_k) atomicAdd(&h2[sub], 1u);
-      if (top == bin_k1) atomicAdd(&h2[kSel2Bins + sub], 1u);
-    }
+    const uint32_t top = key >> kSelShift;
+    const uint32_t sub = (key >> (kSelShift - kSel2Bits)) & (kSel2Bins - 1);
+    if (top == bin_k) atomicAdd(&h2[sub], 1u);
+    if (top == bin_k1) atomicAdd(&h2[kSel2Bins + sub], 1u);
   }
   if (threadIdx.x == 0) {
     tcnt[row * tiles + tile] = total;
     tabove[row * tiles + tile] = above;
   }
-  if (HIST2) {
-    // the tile's few non-empty counters are added to one of the row's kSelSlices partial histograms
-    __syncthreads();
-    uint32_t* dst = bins2 + (row * kSelSlices + tile % kSelSlices) * (2 * kSel2Bins);
-    for (int i = threadIdx.x; i < 2 * kSel2Bins; i += kThreads)
-      if (h2[i] != 0u) atomicAdd(&dst[i], h2[i]);
-  }
+  // the tile's few non-empty counters are added to one of the row's kSelSlices partial histograms
+  __syncthreads();
+  uint32_t* dst = bins2 + (row * kSelSlices + tile % kSelSlices) * (2 * kSel2Bins);
+  for (int i = threadIdx.x; i < 2 * kSel2Bins; i += kThreads)
+    if (h2[i] != 0u) atomicAdd(&dst[i], h2[i]);
 }
 
 // Second compaction, in place, of every tile's slot to the refined window; adds the elements
 // that fall above it to the tile's count of elements above.
-// TAU: the surviving candidates' index payloads are replaced by tangent bits (see
-// select_compact_kernel); MAG says how the payload encodes the index.
 // A workgroup takes kWaves consecutive tiles of a row, one wavefront per tile: a slot of the first
 // level holds a few dozen entries, and with one tile per workgroup the kernel was a chain of
 // dependent latencies per tile.  Slots of more than kWaveSlot entries (a window that holds a
 // quarter of the row) are left to the whole workgroup, one after the other.
 constexpr int kWaveSlot = kItems * kWave;         // 1024 entries: kItems per lane
 
-template <bool TAU, bool MAG>
-__device__ __forceinline__ uint32_t recompact_payload(uint32_t key, uint32_t id, int64_t row_base,
-                                                      const float* __restrict__ tangent) {
-  if (!TAU) return id;
-  float t = 0.0f;
-  if (tangent != nullptr) {
-    t = tangent[row_base + (MAG ? (id >> 1) : id)];
-    // the key of |x| = 0 is that of +0.0: sign(0) = 0
-    if (MAG) t = key == 0x7fffffffu ? 0.0f : ((id & 1u) ? -t : t);
-  }
-  return __float_as_uint(t);
-}
-
 // one wavefront, a slot of at most kWaveSlot entries
-template <bool TAU, bool MAG>
 __device__ __forceinline__ void recompact_tile_wave(uint32_t klo, uint32_t khi, uint32_t* keys,
                                                     uint32_t* idx, uint32_t* tcnt_p,
                                                     uint32_t* tabove_p, int64_t slot,
-                                                    int64_t row_base, int nvalid,
-                                                    const float* __restrict__ tangent) {
+                                                    int nvalid) {
   const int lane = threadIdx.x & (kWave - 1);
   uint32_t key[kItems], id[kItems], pos[kItems];
   uint32_t ncand = 0, nabove = 0;
@@ -645,7 +603,7 @@ __device__ __forceinline__ void recompact_tile_wave(uint32_t klo, uint32_t khi, 
     if (i * kWave >= nvalid) continue;
     if (pos[i] != 0xffffffffu) {
       keys[slot + pos[i]] = key[i];
-      idx[slot + pos[i]] = recompact_payload<TAU, MAG>(key[i], id[i], row_base, tangent);
+      idx[slot + pos[i]] = id[i];
     }
   }
   if (lane == 0) {
@@ -655,13 +613,10 @@ __device__ __forceinline__ void recompact_tile_wave(uint32_t klo, uint32_t khi, 
 }
 
 // the whole workgroup, any slot
-template <bool TAU, bool MAG>
 __device__ __forceinline__ void recompact_tile_block(uint32_t klo, uint32_t khi, uint32_t* keys,
                                                      uint32_t* idx, uint32_t* tcnt_p,
                                                      uint32_t* tabove_p, int64_t slot,
-                                                     int64_t row_base, int nvalid,
-                                                     const float* __restrict__ tangent,
-                                                     uint32_t* wave_cand, uint32_t* wave_above) {
+                                                     int nvalid, uint32_t* wave_cand, uint32_t* wave_above) {
   const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
   const int chunk = w * (kTile / kWaves);
   uint32_t key[kItems], id[kItems], pos[kItems];
@@ -694,7 +649,7 @@ __device__ __forceinline__ void recompact_tile_block(uint32_t klo, uint32_t khi,
   for (int i = 0; i < kItems; ++i) {
     if (pos[i] != 0xffffffffu) {
       keys[slot + before + pos[i]] = key[i];
-      idx[slot + before + pos[i]] = recompact_payload<TAU, MAG>(key[i], id[i], row_base, tangent);
+      idx[slot + before + pos[i]] = id[i];
     }
   }
   if (threadIdx.x == 0) {
@@ -704,11 +659,9 @@ __device__ __forceinline__ void recompact_tile_block(uint32_t klo, uint32_t khi,
   __syncthreads();                         // (wave_cand, wave_above are used again for the next tile)
 }
 
-template <bool TAU = false, bool MAG = false>
 __global__ __launch_bounds__(kThreads) void select_recompact_kernel(
     const RowSel* __restrict__ sel, uint32_t* __restrict__ keys, uint32_t* __restrict__ idx,
-    uint32_t* __restrict__ tcnt, uint32_t* __restrict__ tabove, int64_t n, int tiles, int groups,
-    const float* __restrict__ tangent = nullptr) {
+    uint32_t* __restrict__ tcnt, uint32_t* __restrict__ tabove, int64_t n, int tiles, int groups) {
   __shared__ uint32_t wave_cand[kWaves], wave_above[kWaves];
   const int64_t row = blockIdx.x / groups;
   const int tile0 = (blockIdx.x % groups) * kWaves;
@@ -719,18 +672,16 @@ __global__ __launch_bounds__(kThreads) void select_recompact_kernel(
   const int nv = mine < tiles ? int(tcnt[row * tiles + mine]) : 0;
   if (!__syncthreads_or(nv > kWaveSlot)) {
     if (nv > 0)
-      recompact_tile_wave<TAU, MAG>(klo, khi, keys, idx, tcnt + row * tiles + mine,
-                                    tabove + row * tiles + mine, row_base + int64_t(mine) * kTile,
-                                    row_base, nv, tangent);
+      recompact_tile_wave(klo, khi, keys, idx, tcnt + row * tiles + mine, tabove + row * tiles + mine,
+                          row_base + int64_t(mine) * kTile, nv);
     return;
   }
   for (int q = 0; q < kWaves && tile0 + q < tiles; ++q) {
     const int tile = tile0 + q;
     const int nvalid = int(tcnt[row * tiles + tile]);
     if (nvalid == 0) continue;
-    recompact_tile_block<TAU, MAG>(klo, khi, keys, idx, tcnt + row * tiles + tile,
-                                   tabove + row * tiles + tile, row_base + int64_t(tile) * kTile,
-                                   row_base, nvalid, tangent, wave_cand, wave_above);
+    recompact_tile_block(klo, khi, keys, idx, tcnt + row * tiles + tile, tabove + row * tiles + tile,
+                         row_base + int64_t(tile) * kTile, nvalid, wave_cand, wave_above);
   }
 }
 
@@ -891,7 +842,7 @@ void candidate_lists(const float* x, int64_t rows, int64_t n, int64_t k, const R
   hipLaunchKernelGGL(reduce_partials_kernel, dim3(unsigned(rows * slices * (kSelBins / 128))),
                      dim3(kThreads), 0, st, B.hpart, B.bins, parts, slices, kSelBins);
   hipLaunchKernelGGL((select_window_kernel<MAG>), dim3(unsigned(rows)), dim3(kWinThreads), 0, st,
-                     B.bins, B.sel, k, slices, R, cubic, B.bins2);
+                     B.bins, B.sel, k, slices, R, cubic, B.bins2, kSelSlices * 2 * kSel2Bins);
   // first-level candidates into the per-tile slots of the "b" arrays; second level; slots
   // narrowed in place; dense lists
   hipLaunchKernelGGL((select_compact_kernel<MAG>), dim3(blocks), dim3(kThreads), 0, st, x, B.sel,
@@ -899,70 +850,40 @@ void candidate_lists(const float* x, int64_t rows, int64_t n, int64_t k, const R
   hipLaunchKernelGGL((select_refine_kernel<MAG>), dim3(unsigned(rows)), dim3(kThreads), 0, st,
                      B.bins2, B.sel, kSelSlices, R, cubic);
   const int groups = (tiles + kWaves - 1) / kWaves;
-  hipLaunchKernelGGL((select_recompact_kernel<false, false>), dim3(unsigned(rows * groups)),
+  hipLaunchKernelGGL(select_recompact_kernel, dim3(unsigned(rows * groups)),
                      dim3(kThreads), 0, st, B.sel, B.keys_b, B.idx_b, B.tcnt, B.tabove, n, tiles,
-                     groups, nullptr);
+                     groups);
   hipLaunchKernelGGL(select_offsets_kernel, dim3(unsigned(rows)), dim3(kOffThreads), 0, st, B.tcnt,
                      B.tabove, B.toff, B.taboff, B.sel, tiles);
   hipLaunchKernelGGL(select_gather_kernel, dim3(unsigned(rows * groups)), dim3(kThreads), 0, st,
                      B.tcnt, B.toff, B.keys_b, B.idx_b, B.keys_a, B.idx_a, n, tiles, groups);
 }
 
-// The candidate selection of the wide route: the same levels, but the candidates stay in the
-// per-tile slots of the "b" arrays (B.tcnt / B.tabove per tile); the workgroup that sorts and
-// solves a row collects them itself.  The sum of the first level's partial histograms is only
-// launched when there are more partials than the window kernel adds up itself; `refine`: second
-// histogram level (its partial histograms are added up by the compaction pass).
+// The first level alone, for the wide route (wide_rows.hip): the key window of every row.  The sum of the partial
+// histograms is only launched when there are more of them than the window kernel adds up itself.
 template <bool MAG>
-void wide_select(const float* x, const float* tangent, int64_t rows, int64_t n, int64_t k,
-                 const Reg& R, bool cubic, bool refine, const SortBuffers& B, hipStream_t st) {
-  const int tiles = int((n + kTile - 1) / kTile);
-  const unsigned blocks = unsigned(rows * tiles);
+void wide_window(const float* x, int64_t rows, int64_t n, int64_t k, const Reg& R, bool cubic, const SortBuffers& B,
+                 hipStream_t st) {
   const int parts = sel_parts(rows, n);
   const int64_t span = sel_span(rows, n);
   hipLaunchKernelGGL((select_hist_kernel<MAG>), dim3(unsigned(rows * parts)), dim3(kSelThreads), 0,
                      st, x, B.hpart, n, span, parts);
-  if (parts > kSelSlices) {
+  const bool sum = parts > kSelSlices;
+  if (sum)
     hipLaunchKernelGGL(reduce_partials_kernel, dim3(unsigned(rows * kSelSlices * (kSelBins / 128))),
                        dim3(kThreads), 0, st, B.hpart, B.bins, parts, kSelSlices, kSelBins);
-    hipLaunchKernelGGL((select_window_kernel<MAG>), dim3(unsigned(rows)), dim3(kWinThreads), 0, st,
-                       B.bins, B.sel, k, kSelSlices, R, cubic, refine ? B.bins2 : nullptr);
-  } else {
-    hipLaunchKernelGGL((select_window_kernel<MAG>), dim3(unsigned(rows)), dim3(kWinThreads), 0, st,
-                       B.hpart, B.sel, k, parts, R, cubic, refine ? B.bins2 : nullptr);
-  }
-  if (!refine) {
-    hipLaunchKernelGGL((select_compact_kernel<MAG, false, true>), dim3(blocks), dim3(kThreads), 0,
-                       st, x, B.sel, B.keys_b, B.idx_b, B.tcnt, B.tabove, B.bins2, n, tiles,
-                       tangent);
-    return;
-  }
-  hipLaunchKernelGGL((select_compact_kernel<MAG, true, false>), dim3(blocks), dim3(kThreads), 0, st,
-                     x, B.sel, B.keys_b, B.idx_b, B.tcnt, B.tabove, B.bins2, n, tiles, nullptr);
-  hipLaunchKernelGGL((select_refine_kernel<MAG>), dim3(unsigned(rows)), dim3(kThreads), 0, st,
-                     B.bins2, B.sel, kSelSlices, R, cubic);
-  const int groups = (tiles + kWaves - 1) / kWaves;
-  hipLaunchKernelGGL((select_recompact_kernel<true, MAG>), dim3(unsigned(rows * groups)),
-                     dim3(kThreads), 0, st, B.sel, B.keys_b, B.idx_b, B.tcnt, B.tabove, n, tiles,
-                     groups, tangent);
-  // thousands of tiles with a few candidates each: the row's dense (key, tangent) list is put
-  // together here, by all compute units, and not by the one workgroup that solves the row
-  hipLaunchKernelGGL(select_offsets_kernel, dim3(unsigned(rows)), dim3(kOffThreads), 0, st, B.tcnt,
-                     B.tabove, B.toff, B.taboff, B.sel, tiles);
-  hipLaunchKernelGGL(select_gather_kernel, dim3(unsigned(rows * groups)), dim3(kThreads), 0, st,
-                     B.tcnt, B.toff, B.keys_b, B.idx_b, B.keys_a, B.idx_a, n, tiles, groups);
+  hipLaunchKernelGGL((select_window_kernel<MAG>), dim3(unsigned(rows)), dim3(kWinThreads), 0, st,
+                     sum ? B.bins : B.hpart, B.sel, k, sum ? kSelSlices : parts, R, cubic, B.bins2, kWideCounters);
 }
 
 }  // namespace
 
-int launch_wide_select(bool mag, int pc, bool refine, const float* x, const float* tangent,
-                       int64_t rows, int64_t n, int64_t k, const Reg& R, const SortBuffers& B,
-                       hipStream_t st) {
-  const int64_t tiles = radix_tiles(n);
+int launch_wide_window(bool mag, int pc, const float* x, int64_t rows, int64_t n, int64_t k, const Reg& R,
+                       const SortBuffers& B, hipStream_t st) {
   if (k < 1 || k >= n) return -1;
-  if (rows * tiles > 0x7fffffffLL || rows * kRadix > 0x7fffffffLL) return -1;
-  if (mag) wide_select<true>(x, tangent, rows, n, k, R, pc == kP43, refine, B, st);
-  else wide_select<false>(x, tangent, rows, n, k, R, pc == kP43, refine, B, st);
+  if (rows * radix_tiles(n) > 0x7fffffffLL || rows * kRadix > 0x7fffffffLL) return -1;
+  if (mag) wide_window<true>(x, rows, n, k, R, pc == kP43, B, st);
+  else wide_window<false>(x, rows, n, k, R, pc == kP43, B, st);
   return 0;
 }
 

@@ -39,6 +39,7 @@
 #include <type_traits>
 
 #include "common.hpp"
+#include "group.hpp"
 #include "pooling.hpp"
 #include "launch.hpp"
 #include "wave.hpp"
@@ -93,13 +94,8 @@ struct SearchGroup {
   }
   // inclusive prefix sum over the threads of the group, and the total
   __device__ __forceinline__ uint32_t scan(uint32_t v, uint32_t* total) {
-    v += dpp_or0<0x111, 0xF>(v);
-    v += dpp_or0<0x112, 0xF>(v);
-    v += dpp_or0<0x114, 0xF>(v);
-    v += dpp_or0<0x118, 0xF>(v);
-    v += dpp_or0<0x142, 0xA>(v);
-    v += dpp_or0<0x143, 0xC>(v);
-    uint32_t all = uint32_t(__builtin_amdgcn_readlane(int(v), kWave - 1));
+    uint32_t all;
+    v = wave_inclusive_scan(v, &all);
     if constexpr (W > 1) {
       const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
       SearchRed* b = buf + (turn & 1) * W;
@@ -121,21 +117,8 @@ struct SearchGroup {
     *b = c >> 16;
   }
   // smallest a, largest b of the group
-  template <int CTRL, int ROWS>
-  static __device__ __forceinline__ void min_max_step(float& a, float& b) {     // (vacated lanes: own value)
-    const int ia = int(__float_as_uint(a)), ib = int(__float_as_uint(b));
-    a = fminf(a, __uint_as_float(uint32_t(__builtin_amdgcn_update_dpp(ia, ia, CTRL, ROWS, 0xF, false))));
-    b = fmaxf(b, __uint_as_float(uint32_t(__builtin_amdgcn_update_dpp(ib, ib, CTRL, ROWS, 0xF, false))));
-  }
   __device__ __forceinline__ void min_max(float& a, float& b) {
-    min_max_step<0x111, 0xF>(a, b);
-    min_max_step<0x112, 0xF>(a, b);
-    min_max_step<0x114, 0xF>(a, b);
-    min_max_step<0x118, 0xF>(a, b);
-    min_max_step<0x142, 0xA>(a, b);
-    min_max_step<0x143, 0xC>(a, b);
-    a = uniform_f32(a, kWave - 1);
-    b = uniform_f32(b, kWave - 1);
+    wave_min_max(a, b);
     if constexpr (W > 1) {
       const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
       SearchRed* s = buf + (turn & 1) * W;
@@ -173,22 +156,6 @@ __device__ __forceinline__ void pass_fence(int r, T& a, Rest&... rest) {
   }
 }
 
-// largest float strictly below T / smallest float strictly above T
-__device__ __forceinline__ float float_next_down(float f) {
-  const uint32_t b = __float_as_uint(f);
-  if ((b << 1) == 0u) return __uint_as_float(0x80000001u);
-  return __uint_as_float((b >> 31) ? b + 1u : b - 1u);
-}
-__device__ __forceinline__ float float_next_up(float f) { return -float_next_down(-f); }
-__device__ __forceinline__ float float_below(double T) {
-  const float f = float(T);
-  return double(f) >= T ? float_next_down(f) : f;
-}
-__device__ __forceinline__ float float_above(double T) {
-  const float f = float(T);
-  return double(f) <= T ? float_next_up(f) : f;
-}
-
 // 16 values per DPP row of lanes, in descending order of the row's lanes (bitonic network, mirror form)
 template <int LM>
 __device__ __forceinline__ float sort16_stage(float v, int lane) {
@@ -216,15 +183,6 @@ __device__ __forceinline__ float rows_mean(float v, int i, int rows) {
   if (rows >= 3) t += uniform_f32(v, 32 + i);
   return rows >= 3 ? t * (1.0f / 3.0f) : (rows == 2 ? 0.5f * t : t);
 }
-// floats in numeric order as unsigned words, and back (between the images of two numbers lie numbers only)
-__device__ __forceinline__ uint32_t ordered_of(float f) {
-  const uint32_t b = __float_as_uint(f);
-  return (b >> 31) ? ~b : b | 0x80000000u;
-}
-__device__ __forceinline__ float float_of_ordered(uint32_t o) {
-  return __uint_as_float((o >> 31) ? o & 0x7fffffffu : ~o);
-}
-
 __device__ __forceinline__ float cbrt_approx(float v) {      // v > 0; a starting point only
   return __builtin_amdgcn_exp2f(__builtin_amdgcn_logf(v) * (1.0f / 3.0f));
 }
@@ -936,7 +894,7 @@ __global__ __launch_bounds__(NT == 64 ? 256 : NT) void row_search_kernel(
           hi_f = sk1;                                  // (s_{k+1} < s_k, or zeros: the top k are above it)
         }
         if (have && !settled) {
-          // the set of the block as in solve_unsorted_list (sort_solve.hpp), in passes over the registers
+          // the set of the block by threshold steps from the pair on, in passes over the registers
           gamma = P::pooled(2.0, 1.0, Sums{dk + dk1, dk * dk + dk1 * dk1, dk * dk * dk + dk1 * dk1 * dk1}, R,
                             MAG ? -center : dk1 - R.lambda, dk, center);
           double blo = -1e300, bhi = 1e300;

@@ -236,7 +236,7 @@ def test_time_does_not_depend_on_the_values(gpu):
 # gamma = 0 exactly: elements at 0 and at lambda tie with the block and stay outside, their outputs follow their own
 # tangents (0 and, above, 0).  Block: m copies of 0.5 (top-k positions), 2 m of 0.25: 0.5 m + 0.25 (2 m) = lambda m.
 # The sums of the search are taken relative to its first guess: gamma comes out some 1e-17 off zero, where floats
-# are dense.  60000: candidate lists of long rows (csrc/sort_solve.hpp) of 6050 and 24050 members and more.
+# are dense.  60000: candidate lists of long rows (csrc/wide_rows.hip) of 6050 and 24050 members and more.
 @pytest.mark.parametrize("rows,n,m", [(3, 1500, 100), (300, 1500, 100), (300, 3000, 40), (3, 20000, 3000), (2, 60000, 2000),
                                       (2, 60000, 8000)])
 def test_ties_around_zero(gpu, oracle, rows, n, m):

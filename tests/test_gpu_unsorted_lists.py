@@ -1,4 +1,4 @@
-"""Candidate lists of long rows that are solved without sorting them (csrc/sort_solve.hpp): list lengths
+"""Candidate lists of long rows that are solved without sorting them (csrc/wide_rows.hip): list lengths
 around the largest sorted list (4096), the largest one gathered through LDS (16384) and the largest part
 held in LDS (32768); ties at the block's ends and around zero.  Oracle; bar: that of test_gpu_parity."""
 import numpy as np

@@ -1,0 +1,84 @@
+"""Long rows, dense outputs (csrc/wide_rows.hip): row lengths at the edges of the parts that workgroups take, counts added
+up directly and in groups, 16-bit and 32-bit counts, lists of every kind (empty middle, one wavefront, one workgroup, longer
+than LDS), ties and infinities.  Against the oracle with the bar of test_gpu_parity where it is quick, else bit for
+bit against the routes that sort."""
+import numpy as np
+import pytest
+
+from tests.test_gpu_parity import P2, P43, dev, gpu, host, long_rows_route, run_case  # noqa: F401  (gpu: the fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+def _same_as_sorted(gpu, op, x, t, k, p, lam, mode="select"):
+    print(f"case op={op} shape={tuple(x.shape)} k={k} p={p:.4f} lam={lam}", flush=True)
+    fn = gpu.topk_mask_jvp if op == "mask" else gpu.topkmag_jvp
+    o, j = (host(a) for a in fn(x, t, k, p, lam))
+    with long_rows_route(gpu, mode):
+        o2, j2 = (host(a) for a in fn(x, t, k, p, lam))
+    assert np.array_equal(o, o2)
+    err = np.abs(j.astype(np.float64) - j2)
+    assert (err <= 2.4e-7 * np.abs(j2) + 1e-9).all(), float(err.max())      # (two roundings of d gamma's sum)
+    with long_rows_route(gpu, "wide"):
+        o3, j3 = (host(a) for a in fn(x, t, k, p, lam))
+    assert np.array_equal(o, o3) and np.array_equal(j, j3)                   # and again: the same bits
+
+
+# parts of 16384 elements; 37 parts and more are counted in groups
+@pytest.mark.parametrize("rows,n", [(1, 32769), (3, 49151), (2, 49153), (1, 524289), (1, 600001)])
+def test_row_lengths(gpu, oracle, rows, n):
+    r = np.random.default_rng(n)
+    x = r.normal(size=(rows, n)).astype(np.float32)
+    t = r.normal(size=x.shape).astype(np.float32)
+    for k, lam in ((1, 0.01), (n // 10, 0.1), (n - 1, 0.01), (n // 2, 1e-6)):
+        run_case(gpu, oracle, "mask", x, t, k, P2, lam, check_perm=False)
+        run_case(gpu, oracle, "mag", x, t, k, P2, lam, check_perm=False)
+    run_case(gpu, oracle, "mask", x, t, n // 10, P43, 0.003, check_perm=False)
+    run_case(gpu, oracle, "mag", x, t, n // 10, P43, 0.003, check_perm=False)
+
+
+# 34 x 500000: parts of more than 65536 elements, counts of 32 bits.  64 x 262144: parts of 65536 elements, of which
+# one holds nothing but one value (a 16-bit count runs over)
+@pytest.mark.parametrize("rows,n", [(34, 500000), (64, 262144)])
+def test_counts(gpu, rows, n):
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(n)
+    x = torch.randn((rows, n), generator=g, device="cuda")
+    t = torch.randn((rows, n), generator=g, device="cuda")
+    x[1, 65536:131072] = 1.25
+    x[2, :65536] = 1.75
+    for op, p, lam in (("mask", P2, 0.1), ("mag", P2, 0.05), ("mask", P43, 0.02)):
+        _same_as_sorted(gpu, op, x, t, n // 10, p, lam)
+
+
+# a block that is most of the row; lists of equal values that fit a wavefront, a workgroup, or nothing
+@pytest.mark.parametrize("copies", [500, 2049, 6200, 40000])
+def test_lists_of_equal_values(gpu, oracle, copies):
+    n = 100000
+    r = np.random.default_rng(copies)
+    x = r.normal(size=(2, n)).astype(np.float32)
+    x[:, :copies] = np.float32(1.25)
+    x[1] = r.permutation(x[1])
+    t = r.normal(size=x.shape).astype(np.float32)
+    above = int((x[0] > 1.25).sum())
+    for k in (above + 1, above + copies // 2, above + copies):
+        for lam in (1e-7, 1e-3, 0.5):
+            run_case(gpu, oracle, "mask", x, t, k, P2, lam, check_perm=False)
+            run_case(gpu, oracle, "mag", x, t, k, P2, lam, check_perm=False)
+        run_case(gpu, oracle, "mask", x, t, k, P43, 1e-3, check_perm=False)
+
+
+def test_wide_blocks_infinities_and_signs_of_zero(gpu, oracle):
+    n = 70000
+    r = np.random.default_rng(3)
+    x = r.normal(size=(4, n)).astype(np.float32)
+    x[1] = np.abs(x[1]) * (r.random(n) < 0.02)                # s_k an exact zero
+    x[1, ::7] *= -1.0
+    x[2, : n // 2] = -np.inf                                  # masked out
+    x[3, :3] = np.inf
+    t = r.normal(size=x.shape).astype(np.float32)
+    for k in (10, n // 10, n // 3):
+        for lam in (1e-3, 1.0, 30.0):
+            run_case(gpu, oracle, "mask", x, t, k, P2, lam, check_perm=False)
+            run_case(gpu, oracle, "mag", x[:2], t[:2], k, P2, lam, check_perm=False)
+    run_case(gpu, oracle, "mask", x, t, n // 10, P43, 1e-3, check_perm=False)
