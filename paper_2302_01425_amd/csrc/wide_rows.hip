@@ -11,8 +11,8 @@
 //             (an element counts 1 if its singleton minimiser lies above g, 0 if its value lies below g and
 //             its output in between).  With every element moved to the lower (upper) end of its bin Psi is
 //             bounded from below (above), so the counts alone bracket gamma between bin edges, a bin or two
-//             apart.  All workgroups of a row search that bracket, each for itself (sixteen edges at a time,
-//             one per wavefront), and then work through their own part of the candidates: bins that lie between
+//             apart.  All workgroups of a row find that bracket, each for itself (one edge per thread, from prefix sums
+//             over the bins), and then work through their own part of the candidates: bins that lie between
 //             the two thresholds whatever gamma in the bracket are members (power sums and moments of the tangent,
 //             added up in float64), bins a threshold may fall into go to the row's list.  The workgroup that
 //             finishes last has the sums of the sure members and a list of some hundred elements, on which it
@@ -58,12 +58,17 @@ struct Window {
   float v_top, v_bot;
   double base, scale, width;                     // of a bin: base + j width; scale = 1 / width
 };
+// Zeros do not pool in the magnitude operator (0 is no larger than any pooled value) and their outputs are 0: they
+// are left out of the window, which for rows that are mostly zeros would hold nothing else (1 x 16.7 M, 95 % zeros:
+// 28.9 ms with them, 97 us without).
+template <bool MAG>
 __device__ __forceinline__ Window window_of(const RowSel& s) {
   Window w;
   // key order is reversed value order, and -0 == +0 either way (bound_value clamps the keys beyond the infinities,
   // which would decode to NaN)
   w.v_top = float(bound_value(s.klo));
   w.v_bot = float(bound_value(s.khi));
+  if (MAG && !(w.v_bot > 0.0f)) w.v_bot = __uint_as_float(1u);
   w.base = double(w.v_bot);
   const double span = double(w.v_top) - w.base;
   // (infinities in the window: everything in bin 0)
@@ -175,7 +180,7 @@ __global__ __launch_bounds__(kThreads) void wide_collect_kernel(
   float next[kItems];
   load(first, next);
   for (int i = threadIdx.x; i < kFineBins; i += kThreads) bins[i] = 0u;
-  const Window win = window_of(sel[row]);
+  const Window win = window_of<MAG>(sel[row]);
   uint32_t* val_out = slot_val + row * n + first;
   uint32_t* idx_out = slot_idx + row * n + first;
   uint2* stage = stage_all[w];
@@ -665,7 +670,7 @@ __global__ __launch_bounds__(kThreads) void wide_solve_kernel(
     }
   };
   load_candidates(0u);
-  const Window win = window_of(sel[row]);
+  const Window win = window_of<MAG>(sel[row]);
   over = lanes_sum<kWave>(over);
   if (lane == 0) sm.counts[w] = over;
   __syncthreads();                               // the bins are there
@@ -707,7 +712,8 @@ __global__ __launch_bounds__(kThreads) void wide_solve_kernel(
   }
   const uint32_t candidates = sm.sum_c[kFineBins];
   const double k_win = double(k_row) - double(above_window); // top-k positions in the window
-  if (!(k_win >= 1.0 && k_win < double(candidates))) {       // (NaN among the values)
+  // (no more positive values than top-k positions, for the magnitude operator; NaN among the values)
+  if (!(k_win >= 1.0 && k_win < double(candidates))) {
     if (block == 0 && threadIdx.x == 0) {
       RowInfo ri;
       ri.a = ri.wa = 1;
@@ -785,7 +791,6 @@ __global__ __launch_bounds__(kThreads) void wide_solve_kernel(
   const bool none_sure = !(win.scale > 0.0);     // (a single value, or infinities: everything is listed)
   const int top = l1 > h1 ? l1 : h1;
   auto is_sure = [&](int b) { return !none_sure && b > l1 && b < h0; };
-  auto is_above = [&](int b) { return !none_sure && b > top; };
   auto is_listed = [&](int b) { return none_sure || (b >= l0 && b <= top && !is_sure(b)); };
   Sure sure;
   uint32_t len = 0u;                             // of the row's list

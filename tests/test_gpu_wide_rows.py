@@ -65,7 +65,8 @@ def test_lists_of_equal_values(gpu, oracle, copies):
         for lam in (1e-7, 1e-3, 0.5):
             run_case(gpu, oracle, "mask", x, t, k, P2, lam, check_perm=False)
             run_case(gpu, oracle, "mag", x, t, k, P2, lam, check_perm=False)
-        run_case(gpu, oracle, "mask", x, t, k, P43, 1e-3, check_perm=False)
+        if copies < 7000:                    # (the oracle's p = 4/3 pooling is quadratic in the block)
+            run_case(gpu, oracle, "mask", x, t, k, P43, 1e-3, check_perm=False)
 
 
 def test_wide_blocks_infinities_and_signs_of_zero(gpu, oracle):
@@ -77,8 +78,8 @@ def test_wide_blocks_infinities_and_signs_of_zero(gpu, oracle):
     x[2, : n // 2] = -np.inf                                  # masked out
     x[3, :3] = np.inf
     t = r.normal(size=x.shape).astype(np.float32)
-    for k in (10, n // 10, n // 3):
-        for lam in (1e-3, 1.0, 30.0):
-            run_case(gpu, oracle, "mask", x, t, k, P2, lam, check_perm=False)
-            run_case(gpu, oracle, "mag", x[:2], t[:2], k, P2, lam, check_perm=False)
-    run_case(gpu, oracle, "mask", x, t, n // 10, P43, 1e-3, check_perm=False)
+    for k, lam in ((10, 1.0), (n // 10, 1e-3), (n // 3, 1.0), (n // 10, 30.0)):
+        run_case(gpu, oracle, "mask", x, t, k, P2, lam, check_perm=False)
+        run_case(gpu, oracle, "mag", x[:2], t[:2], k, P2, lam, check_perm=False)
+    run_case(gpu, oracle, "mask", x[:2], t[:2], n // 10, P43, 1e-3, check_perm=False)
+    run_case(gpu, oracle, "mag", x[:2], t[:2], n // 10, P43, 1e-3, check_perm=False)
