@@ -10,6 +10,8 @@
 #include <hip/hip_runtime.h>
 
 #include "common.hpp"
+#include "cubic.hpp"
+#include "group.hpp"
 #include "pooling.hpp"
 #include "launch.hpp"
 #include "long_solve.hpp"
@@ -112,6 +114,8 @@ __global__ __launch_bounds__(kThreads) void wide_dense_kernel(
   float* out = out_all != nullptr ? out_all + base : nullptr;
   float* jvp = jvp_all != nullptr ? jvp_all + base : nullptr;
   const bool have_block = ri.a <= ri.b;
+  constexpr bool PACK = MAG && PC == kP43;
+  __shared__ float2 pack_all[PACK ? kThreads / kWave : 1][PACK ? kPackMax : 1];
   auto elem = [&](int i) -> int64_t {
     return VEC ? first + (int64_t(i / 4) * kThreads + threadIdx.x) * 4 + (i % 4)
                : first + int64_t(i) * kThreads + threadIdx.x;
@@ -139,6 +143,24 @@ __global__ __launch_bounds__(kThreads) void wide_dense_kernel(
       tv[i] = (stream_t && e < n) ? load_stream(tangent + e) : 0.0f;
     }
   }
+  // p = 4/3: the cubics of the elements above the block, packed (unless they are too many)
+  float2* pack = pack_all[PACK ? threadIdx.x / kWave : 0];
+  uint32_t pack_at = 0u;
+  bool packed = false;
+  if constexpr (PACK) {
+    uint32_t c = 0u, total;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) c += (elem(i) < n && fabsf(xv[i]) > ri.hi_incl) ? 1u : 0u;
+    pack_at = wave_inclusive_scan(c, &total) - c;
+    packed = total <= kPackMax;
+    if (packed && total > 0u) {
+      uint32_t to = pack_at;
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        if (elem(i) < n && fabsf(xv[i]) > ri.hi_incl) pack[to++] = make_float2(fabsf(xv[i]), tv[i]);
+      packed_above_mag43(pack, total, R, jvp != nullptr);
+    }
+  }
   float yo[8], dout[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
@@ -164,9 +186,13 @@ __global__ __launch_bounds__(kThreads) void wide_dense_kernel(
       }
     } else if (above) {
       if constexpr (MAG && PC == kP43) {
-        if (xv[i] != 0.0f) {
-          double g, slope;
-          P::above_both(double(v), R, 0.0, &g, &slope);
+        if (packed) {
+          const float2 q = pack[pack_at++];
+          y = v == 0.0f ? 0.0f : (neg ? -q.x : q.x);
+          d = v == 0.0f ? 0.0f : q.y;
+        } else if (v != 0.0f) {
+          double g, slope = 0.0;
+          above_mag43(double(v), R, jvp != nullptr, &g, &slope);
           y = float(neg ? -g : g);
           if (jvp != nullptr) d = float(slope * double(tv[i]));
         }

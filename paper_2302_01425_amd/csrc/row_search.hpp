@@ -39,6 +39,7 @@
 #include <type_traits>
 
 #include "common.hpp"
+#include "cubic.hpp"
 #include "group.hpp"
 #include "pooling.hpp"
 #include "launch.hpp"
@@ -183,51 +184,6 @@ __device__ __forceinline__ float rows_mean(float v, int i, int rows) {
   if (rows >= 3) t += uniform_f32(v, 32 + i);
   return rows >= 3 ? t * (1.0f / 3.0f) : (rows == 2 ? 0.5f * t : t);
 }
-__device__ __forceinline__ float cbrt_approx(float v) {      // v > 0; a starting point only
-  return __builtin_amdgcn_exp2f(__builtin_amdgcn_logf(v) * (1.0f / 3.0f));
-}
-
-// cube root of a positive double to rounding: float32 start (1e-6), two Newton steps whose quotients are
-// small corrections
-__device__ __forceinline__ double cbrt_f64(double v) {
-  const float f = float(v);
-  if (!(f > 1e-36f)) return cbrt(fmax(v, 0.0));
-  float c32 = cbrt_approx(f);
-  const float third = __builtin_amdgcn_rcpf(3.0f * c32 * c32);
-  double c = double(c32);
-  c -= double(float(c * c * c - v) * third);
-  c -= double(float(c * c * c - v) * third);
-  return c;
-}
-
-// y and dy/dtau of a top-k element s > 0 above the block for the magnitude operator with p = 4/3: the
-// root g of (g - s)^3 + lambda^3 g = 0.  With g = s - lambda w it is w^3 + lambda w = s and g = w^3.
-// float32 Halley steps from the upper bound min(s / lambda, s^(1/3)) bring w to float32 precision (the
-// function is convex there: two steps bring any start, off by 47 % at most, to 5e-7), one float64 Newton
-// step to 1e-12; its quotient is a small correction, for which float32 precision is enough.  (The
-// safeguarded float64 solve of pooling.hpp takes some 150 instructions per element.)
-__device__ __forceinline__ void above_mag43(double s, const Reg& R, bool want_slope, double* g, double* slope) {
-  const float s32 = float(s), l32 = float(R.lambda);
-  float w = fminf(s32 * float(R.inv_lambda), cbrt_approx(s32));
-#pragma unroll
-  for (int it = 0; it < 2; ++it) {
-    const float rD = __builtin_amdgcn_rcpf(fmaf(3.0f * w, w, l32));
-    const float step = (fmaf(w * w, w, l32 * w) - s32) * rD;
-    w -= step * __builtin_amdgcn_rcpf(1.0f - 3.0f * w * rD * step);
-  }
-  double wd = double(w);
-  const double F = fma(wd, fma(wd, wd, R.lambda), -s);
-  wd -= double(float(F) * __builtin_amdgcn_rcpf(fmaf(3.0f * w, w, l32)));
-  const double u = R.lambda * wd;
-  *g = u > 0.75 * s ? wd * wd * wd : s - u;            // (without cancellation either way)
-  if (want_slope) {
-    const double a = 3.0 * wd * wd, b = a + R.lambda;
-    double r = double(__builtin_amdgcn_rcpf(float(b)));
-    r = fma(fma(-b, r, 1.0), r, r);
-    *slope = a * fma(fma(-b, r, 1.0), r, r);
-  }
-}
-
 // NT threads per row (64: four rows per workgroup of 256 threads, no barriers; more: one row per
 // workgroup), at most E elements per thread.  VAR as in short_rows_value.hpp (the operators built on
 // the mask, MAG = false).  Any of out / jvp may be null for the plain operators.  vec: x, tangent, out
@@ -1077,11 +1033,39 @@ __global__ __launch_bounds__(NT == 64 ? 256 : NT) void row_search_kernel(
     if constexpr (W == 1) __builtin_amdgcn_wave_barrier();
     dgamma = d[0] / P::jac_denominator(CUBIC ? d[1] : cnt, m, R);
   }
+  // top-k in magnitude, p = 4/3: the cubics of the elements above the block, packed, eight elements of every lane at
+  // a time (unless more than half of them are above)
+  constexpr bool PACK = MAG && CUBIC;
+  static_assert(!PACK || kListMax * RPB == int(kPackMax) * (W * RPB), "the list has room for every wavefront");
+  uint32_t pack_at = 0u;
+  bool packed = false;
+  float2* pack = list + (W > 1 ? (threadIdx.x / kWave) * kPackMax : 0u);
+  if constexpr (PACK && W > 1) __syncthreads();        // (the list has been read)
   double acc = 0.0, ysum = 0.0;                        // of the loss
 #pragma unroll
   for (int c = 0; c < Q; ++c) {
     opaque(lo_f);
     opaque(hi_f);
+    if constexpr (PACK) {
+      if ((c & 1) == 0) {
+        constexpr int kGroup = 8;
+        const int r1 = 4 * c + kGroup < E ? 4 * c + kGroup : E;
+        uint32_t cnt_above = 0u, total;
+#pragma unroll
+        for (int r = 4 * c; r < r1; ++r) cnt_above += is_above(val(r)) ? 1u : 0u;
+        pack_at = wave_inclusive_scan(cnt_above, &total) - cnt_above;
+        packed = total <= kPackMax;
+        if (packed && total > 0u) {
+          uint32_t to = pack_at;
+#pragma unroll
+          for (int r = 4 * c; r < r1; ++r) {
+            const float v = val(r);
+            if (is_above(v)) pack[to++] = make_float2(v, want_jvp ? tr[r] : 0.0f);
+          }
+          packed_above_mag43(pack, total, R, want_jvp);
+        }
+      }
+    }
     float yv[4], jv[4];
     bool some = false;
     bool listed[4];
@@ -1109,6 +1093,12 @@ __global__ __launch_bounds__(NT == 64 ? 256 : NT) void row_search_kernel(
         y = ab ? (n > 2048 ? xv * float(R.inv_1pl) : float(double(xv) * R.inv_1pl)) : 0.0f;
         if (!LIST_TAU && want_jvp && ab && v != 0.0f)
           dy = n > 2048 ? tr[q] * float(R.inv_1pl) : float(double(tr[q]) * R.inv_1pl);
+      } else if (packed) {
+        if (ab) {
+          const float2 q2 = pack[pack_at++];
+          y = v == 0.0f ? 0.0f : (neg ? -q2.x : q2.x);
+          dy = v == 0.0f ? 0.0f : q2.y;
+        }
       } else if (__any(ab)) {
         double gd, slope = 0.0;
         above_mag43(double(v), R, want_jvp, &gd, &slope);
