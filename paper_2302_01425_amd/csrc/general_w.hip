@@ -505,6 +505,130 @@ __global__ __launch_bounds__((GenCfg<GL, E, PC == kP43>::WPB * kWave)) void gene
   }
 }
 
+// ---- sort on 32-bit words ----------------------------------------------------------------------------
+// first block start in the lanes after this one / last block start in the lanes before it, for rows that take a whole
+// wavefront: moves inside the rows of 16 lanes instead of twelve trips through the LDS crossbar
+__device__ __forceinline__ int wave_after_min(int v, int none) {
+#define TOPK_STEP(CTRL) v = min(v, __builtin_amdgcn_update_dpp(v, v, CTRL, 0xF, 0xF, false))
+  TOPK_STEP(0x101);
+  TOPK_STEP(0x102);
+  TOPK_STEP(0x104);
+  TOPK_STEP(0x108);
+#undef TOPK_STEP
+  const int m3 = __builtin_amdgcn_readlane(v, 48), m2 = min(m3, __builtin_amdgcn_readlane(v, 32));
+  const int m1 = min(m2, __builtin_amdgcn_readlane(v, 16));
+  const int lane = threadIdx.x & (kWave - 1);
+  const int later = lane < 16 ? m1 : (lane < 32 ? m2 : (lane < 48 ? m3 : none));
+  return min(__builtin_amdgcn_update_dpp(none, v, 0x101, 0xF, 0xF, false), min(later, none));
+}
+__device__ __forceinline__ int wave_before_max(int v, int none) {
+#define TOPK_STEP(CTRL) v = max(v, __builtin_amdgcn_update_dpp(v, v, CTRL, 0xF, 0xF, false))
+  TOPK_STEP(0x111);
+  TOPK_STEP(0x112);
+  TOPK_STEP(0x114);
+  TOPK_STEP(0x118);
+#undef TOPK_STEP
+  const int m0 = __builtin_amdgcn_readlane(v, 15), m1 = max(m0, __builtin_amdgcn_readlane(v, 31));
+  const int m2 = max(m1, __builtin_amdgcn_readlane(v, 47));
+  const int lane = threadIdx.x & (kWave - 1);
+  const int earlier = lane < 16 ? none : (lane < 32 ? m0 : (lane < 48 ? m1 : m2));
+  return max(__builtin_amdgcn_update_dpp(none, v, 0x111, 0xF, 0xF, false), max(earlier, none));
+}
+template <int GL>
+__device__ __forceinline__ int row_after_min(int v, int lr, int none) {
+  if constexpr (GL == kWave) return wave_after_min(v, none);
+  else return lanes_after_min<GL>(v, lr, none);
+}
+template <int GL>
+__device__ __forceinline__ int row_before_max(int v, int lr, int none) {
+  if constexpr (GL == kWave) return wave_before_max(v, none);
+  else return lanes_before_max<GL>(v, lr, none);
+}
+template <int GL>
+__device__ __forceinline__ double row_exclusive_scan(double v, int lr) {
+  if constexpr (GL == kWave) {
+    v += row_shr_f64<1>(v);
+    v += row_shr_f64<2>(v);
+    v += row_shr_f64<4>(v);
+    v += row_shr_f64<8>(v);
+    const double t0 = uniform_f64(v, 15), t1 = t0 + uniform_f64(v, 31), t2 = t1 + uniform_f64(v, 47);
+    const int lane = threadIdx.x & (kWave - 1);
+    const double before = lane < 16 ? 0.0 : (lane < 32 ? t0 : (lane < 48 ? t1 : t2));
+    return row_shr_f64<1>(v) + before;
+  } else {
+    return group_exclusive_scan_f64<GL>(v, lr);
+  }
+}
+// Sorted (key, field) words of a row (as SortRuns on make_keys_row makes them) by way of 32-bit words: the leading
+// 32 - log2(NP) bits of the key of a value less a value from the middle of the row, and the element's number.  The
+// difference never falls as the value rises, so that only values with the same leading bits may come in the wrong
+// order (some ten pairs in a row of 1024 normal values), which a few rounds of exchanges between neighbours set right; where
+// they do not (many values that agree to 13 bits, far from that middle) the row is sorted as it was.
+// xs: the row in LDS by element.  JVP with rank weights, lambda = 0.1, this and the scans above, us before / after:
+// 4096 x 1024 57.4 / 46.8, 6697 x 425 43.9 / 35.9, 69 x 538 23.9 / 19.2 (with 75 % of the cycles vector instructions,
+// 4100 a wavefront).
+template <int GL, int E, bool MAG, int IDXB>
+__device__ __forceinline__ void sort_row(const float (&xin)[E], const float* xs, int lr, int n, double (&K)[E]) {
+  constexpr int NP = GL * E;
+  float mid;
+  {
+    float a = xs[n / 6], b = xs[n / 2], c = xs[n - 1 - n / 6];
+    if (MAG) {
+      a = fabsf(a);
+      b = fabsf(b);
+      c = fabsf(c);
+    }
+    mid = __builtin_amdgcn_fmed3f(a, b, c);
+    mid = fabsf(mid) < 1e37f ? mid : 0.0f;
+  }
+  uint32_t W[E];
+#pragma unroll
+  for (int r = 0; r < E; ++r) {
+    const int e = r * GL + lr;
+    const uint32_t key = desc_key((MAG ? fabsf(xin[r]) : xin[r]) - mid);
+    W[r] = ((e < n ? key : kSentinelKey) & ~uint32_t(NP - 1)) | uint32_t(e);
+  }
+  SortRuns<GL, E, NP>::run(W, lr);
+#pragma unroll
+  for (int r = 0; r < E; ++r) {
+    const uint32_t e = W[r] & uint32_t(NP - 1);
+    uint32_t key = kSentinelKey, field = (1u << IDXB) - 1u;
+    if (int(e) < n) {
+      const float v = xs[e];
+      key = desc_key(MAG ? fabsf(v) : v);
+      field = MAG ? ((e << 1) | (__float_as_uint(v) >> 31)) : e;
+    }
+    K[r] = pack<IDXB>(key, field);
+  }
+  constexpr int kRepairs = 5;
+#pragma unroll 1
+  for (int round = 0;; ++round) {
+    // (the neighbour in the next lane; the last lane of a row has none)
+    const double next = __shfl_down(K[0], 1, kWave);
+    bool wrong = lr != GL - 1 && K[E - 1] > next;
+#pragma unroll
+    for (int r = 1; r < E; ++r) wrong |= K[r - 1] > K[r];
+    if (!__any(wrong)) return;
+    if (round == kRepairs) break;
+#pragma unroll
+    for (int odd = 0; odd < 2; ++odd) {
+#pragma unroll
+      for (int r = 1 - odd; r + 1 < E; r += 2) {
+        const double lo = min_f64(K[r], K[r + 1]), hi = max_f64(K[r], K[r + 1]);
+        K[r] = lo;
+        K[r + 1] = hi;
+      }
+      if (odd == 0) {                            // with the first and the last of the neighbouring lanes
+        const double after = __shfl_down(K[0], 1, kWave), before = __shfl_up(K[E - 1], 1, kWave);
+        if (lr != GL - 1) K[E - 1] = min_f64(K[E - 1], after);
+        if (lr != 0) K[0] = max_f64(K[0], before);
+      }
+    }
+  }
+  make_keys_row<GL, E, false, MAG, IDXB>(xin, lr, n, K);
+  SortRuns<GL, E, NP>::run(K, lr);
+}
+
 // ---- p = 2 with one weight vector for all rows ------------------------------------------------------
 // The same rounds in 16 bytes of LDS per element instead of 38, so that twice (rows above 512
 // elements) to four times as many wavefronts hide each other's latency.  The prefix sums of w are those
@@ -514,8 +638,8 @@ __global__ __launch_bounds__((GenCfg<GL, E, PC == kP43>::WPB * kWave)) void gene
 // the arrays of the rounds before and after these.  There is no hand-over to the sequential walk: a
 // round costs one walk step per moved block and two lane scans, and a row of n elements settles in n - 1
 // rounds at most.
-// JVP, us, against the kernel above: 4096 x 1024 (lambda = 0.1) 103 -> 55, 6697 x 425 206 -> 94,
-// 2061 x 186 40 -> 26, 69 x 538 (lambda = 0.0065) 113 -> 58; 1024 rows of 1024 that lose one boundary per
+// JVP, us, against the kernel above: 4096 x 1024 (lambda = 0.1) 103 -> 55 (47 with the sort on 32-bit words),
+// 6697 x 425 206 -> 94, 2061 x 186 40 -> 26, 69 x 538 (lambda = 0.0065) 113 -> 58; 1024 rows of 1024 that lose one boundary per
 // round 1740 (walk after 288 rounds, at the time) -> 1060.
 template <int GL, int E>
 struct LeanCfg {
@@ -566,8 +690,16 @@ __global__ __launch_bounds__((LeanCfg<GL, E>::WPB * kWave)) void general_shared_
 #pragma unroll
   for (int r = 0; r < E; ++r) in_w[r * GL + lr] = win[r];
   double K[E];
-  make_keys_row<GL, E, false, MAG, IDXB>(xin, lr, n, K);
-  SortRuns<GL, E, NP>::run(K, lr);
+  if constexpr (GL >= 32) {                  // (shorter rows: no faster, 8192 x 100 19.6 / 19.6)
+    float* xs = reinterpret_cast<float*>(P1.p) + NP;       // (after the weights)
+#pragma unroll
+    for (int r = 0; r < E; ++r) xs[r * GL + lr] = xin[r];
+    __builtin_amdgcn_wave_barrier();
+    sort_row<GL, E, MAG, IDXB>(xin, xs, lr, n, K);
+  } else {
+    make_keys_row<GL, E, false, MAG, IDXB>(xin, lr, n, K);
+    SortRuns<GL, E, NP>::run(K, lr);
+  }
   __builtin_amdgcn_wave_barrier();
   float s32[E];
   uint32_t field[E];
@@ -599,7 +731,7 @@ __global__ __launch_bounds__((LeanCfg<GL, E>::WPB * kWave)) void general_shared_
       t1 += real ? double(s32[r]) : 0.0;
       tw += double(win[r]);                  // (0 beyond the row)
     }
-    double r1 = group_exclusive_scan_f64<GL>(t1, lr), rw = group_exclusive_scan_f64<GL>(tw, lr);
+    double r1 = row_exclusive_scan<GL>(t1, lr), rw = row_exclusive_scan<GL>(tw, lr);
     const bool weights = wv == 0 && rg == 0;
     double gs[E];
 #pragma unroll
@@ -635,7 +767,7 @@ __global__ __launch_bounds__((LeanCfg<GL, E>::WPB * kWave)) void general_shared_
   for (;;) {
     const int first = hm ? e0 + __builtin_ctz(hm) : n;
     const int top = hm ? 31 - __builtin_clz(hm) : 0;
-    nxt = lanes_after_min<GL>(first, lr, n);
+    nxt = row_after_min<GL>(first, lr, n);
     if (first_time) {
       // everything longer than one element
       moved = hm & ~(hm >> 1);
@@ -645,7 +777,7 @@ __global__ __launch_bounds__((LeanCfg<GL, E>::WPB * kWave)) void general_shared_
       moved |= 1u << top;
     }
     nxt_seen = nxt;
-    const int before = lanes_before_max<GL>(hm ? 2 * (e0 + top) + int((moved >> top) & 1u) : -1, lr, -1);
+    const int before = row_before_max<GL>(hm ? 2 * (e0 + top) + int((moved >> top) & 1u) : -1, lr, -1);
     for (uint32_t m = moved; m != 0;) {
       const int r = __builtin_ctz(m);
       m &= m - 1;
@@ -690,7 +822,7 @@ __global__ __launch_bounds__((LeanCfg<GL, E>::WPB * kWave)) void general_shared_
   }
 
   // ---- y; d gamma of every block (Prop. 7) from prefix sums of the tangent ----------------------------
-  const int prv = lanes_before_max<GL>(hm ? e0 + 31 - __builtin_clz(hm) : -1, lr, -1);
+  const int prv = row_before_max<GL>(hm ? e0 + 31 - __builtin_clz(hm) : -1, lr, -1);
   auto start_of = [&](int r) {
     const uint32_t upto = hm & ((2u << r) - 1u);
     const int b = upto ? e0 + 31 - __builtin_clz(upto) : prv;
@@ -709,7 +841,7 @@ __global__ __launch_bounds__((LeanCfg<GL, E>::WPB * kWave)) void general_shared_
     double tq = 0.0;
 #pragma unroll
     for (int r = 0; r < E; ++r) tq += double(tau[r]);
-    double rq = group_exclusive_scan_f64<GL>(tq, lr);
+    double rq = row_exclusive_scan<GL>(tq, lr);
     __builtin_amdgcn_wave_barrier();
 #pragma unroll
     for (int r = 0; r < E; ++r) {

@@ -38,16 +38,21 @@ __device__ __forceinline__ void sort_stage(double (&K)[E], int lr) {
   }
 }
 
+template <int GL, int E, int M>
+__device__ __forceinline__ void sort_stage(uint32_t (&K)[E], int lr);
+
 template <int GL, int E, int STRIDE>
 struct HalfCleaners {
-  static __device__ __forceinline__ void run(double (&K)[E], int lr) {
+  template <class T>
+  static __device__ __forceinline__ void run(T (&K)[E], int lr) {
     sort_stage<GL, E, STRIDE>(K, lr);
     HalfCleaners<GL, E, STRIDE / 2>::run(K, lr);
   }
 };
 template <int GL, int E>
 struct HalfCleaners<GL, E, 0> {
-  static __device__ __forceinline__ void run(double (&)[E], int) {}
+  template <class T>
+  static __device__ __forceinline__ void run(T (&)[E], int) {}
 };
 
 // Bitonic merge sort in its "mirror" form: merging two sorted runs of SIZE/2 starts with the
@@ -55,7 +60,8 @@ struct HalfCleaners<GL, E, 0> {
 // is ascending.
 template <int GL, int E, int SIZE>
 struct SortRuns {
-  static __device__ __forceinline__ void run(double (&K)[E], int lr) {
+  template <class T>
+  static __device__ __forceinline__ void run(T (&K)[E], int lr) {
     SortRuns<GL, E, SIZE / 2>::run(K, lr);
     sort_stage<GL, E, SIZE - 1>(K, lr);
     HalfCleaners<GL, E, SIZE / 4>::run(K, lr);
@@ -63,8 +69,41 @@ struct SortRuns {
 };
 template <int GL, int E>
 struct SortRuns<GL, E, 1> {
-  static __device__ __forceinline__ void run(double (&)[E], int) {}
+  template <class T>
+  static __device__ __forceinline__ void run(T (&)[E], int) {}
 };
+
+// The same network on 32-bit words: an exchange inside a lane is two instructions, one between lanes a move and a median
+// (of the two words and the end of the range that the lane's side is to take).  The float64 form takes two to three
+// times as long (minima and moves of two registers each, select by comparison).
+// (written out and not as assembly: the moves that read the result in the next stage need two instructions in between,
+// which the compiler sees to for its own instructions only)
+__device__ __forceinline__ uint32_t median_u32(uint32_t a, uint32_t b, uint32_t c) {
+  return max(min(a, b), min(max(a, b), c));
+}
+template <int GL, int E, int M>
+__device__ __forceinline__ void sort_stage(uint32_t (&K)[E], int lr) {
+  constexpr int RM = M & (E - 1);
+  constexpr int LM = M / E;
+  if constexpr (LM == 0) {
+#pragma unroll
+    for (int r = 0; r < E; ++r) {
+      const int r2 = r ^ RM;
+      if (r < r2) {
+        const uint32_t lo = min(K[r], K[r2]), hi = max(K[r], K[r2]);
+        K[r] = lo;
+        K[r2] = hi;
+      }
+    }
+  } else {
+    const uint32_t end = (lr & top_bit(LM)) == 0 ? 0u : 0xffffffffu;
+    uint32_t O[E];
+#pragma unroll
+    for (int r = 0; r < E; ++r) O[r] = lane_xor<LM>(K[r ^ RM]);
+#pragma unroll
+    for (int r = 0; r < E; ++r) K[r] = median_u32(K[r], O[r], end);
+  }
+}
 
 // ---- packing -----------------------------------------------------------------------------------
 template <int IDXB>
