@@ -7,12 +7,15 @@ tensor is not a contiguous float32 tensor on the GPU, the call raises.
 from __future__ import annotations
 
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 
 import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "lib", "libsparse_topk.so")
+CALL_PATH = os.path.join(_HERE, "lib", "_call.so")
 
 (TOPK_OP_MASK_FWD, TOPK_OP_MASK_JVP, TOPK_OP_MAG_FWD, TOPK_OP_MAG_JVP, TOPK_OP_ARGSORT,
  TOPK_OP_SIGNED_MASK, TOPK_OP_MASKED_VALUE, TOPK_OP_GENERAL, TOPK_OP_MASK_SPARSE) = range(9)
@@ -79,7 +82,37 @@ def load() -> ctypes.CDLL:
     L.topk_strerror.argtypes = [ci]
     L.topk_strerror.restype = ctypes.c_char_p
     _lib = L
+    _load_call(L)
     return L
+
+
+# The native call path (csrc/host/call.cpp): what the functions below do where nothing is out of the ordinary, in one
+# step.  It returns None where something is, and the Python code makes the call; so does everything where it was not
+# built, or was built for another torch.
+_call = None
+_CALL_ENTRIES = ("topk_mask_fwd", "topk_mask_jvp", "topk_mask_vjp", "topkmag_fwd", "topkmag_jvp", "topkmag_vjp",
+                 "topk_signed_mask_fwd", "topk_signed_mask_jvp", "topk_masked_value_fwd", "topk_masked_value_jvp",
+                 "topk_mask_sparse_fwd", "topk_mask_loss")
+(_MASK_FWD, _MASK_JVP, _MASK_VJP, _MAG_FWD, _MAG_JVP, _MAG_VJP, _SIGNED_FWD, _SIGNED_JVP, _MASKED_FWD, _MASKED_JVP,
+ _SPARSE, _LOSS) = range(len(_CALL_ENTRIES))
+
+
+def _load_call(L: ctypes.CDLL) -> None:
+    global _call
+    if not os.path.exists(CALL_PATH) or _raw_stream is None:
+        return
+    try:
+        loader = importlib.machinery.ExtensionFileLoader("_call", CALL_PATH)
+        module = importlib.util.module_from_spec(importlib.util.spec_from_loader("_call", loader))
+        loader.exec_module(module)
+    except ImportError:
+        return
+    if module.torch_version() != torch.__version__:
+        return
+    module.setup(_raw_stream, _check,
+                 tuple((name, ctypes.cast(getattr(L, name), ctypes.c_void_p).value) for name in _CALL_ENTRIES))
+    module.workspace_device(-1 if _ws_index is None else _ws_index)
+    _call = module
 
 
 def strerror(code: int) -> str:
@@ -91,9 +124,9 @@ def _check(rc: int, what: str) -> None:
         raise TopkError(f"{what}: {strerror(rc)} (code {rc})")
 
 
-# The calls of small batches are bound by this file: 64 x 16 takes 3 us on the GPU and took 12 us per
-# call here, of which the launch is 2.5, the foreign call 1.5 and the rest what the checks below
-# read of the tensors (each attribute 0.1 us).  So every attribute is read once, tensors allocated by
+# The calls of small batches that the native path does not take are bound by this file: 64 x 16 takes 3 us on the GPU
+# and 8 us per call here (4 on the native path), of which the launch is 2.5, the foreign call 1.5 and the rest what
+# the checks below read of the tensors (each attribute 0.1 us).  So every attribute is read once, tensors allocated by
 # the call itself are not checked against the others, and the library says itself whether its
 # workspace is too small (_enqueue).
 _F32 = torch.float32
@@ -161,10 +194,14 @@ def set_workspace(t: torch.Tensor | None) -> None:
     if t is None:
         _check(load().topk_set_workspace(None, 0), "topk_set_workspace")
         _ws_tensor = _ws_index = None
+        if _call is not None:
+            _call.workspace_device(-1)
         return
     _check(load().topk_set_workspace(ctypes.c_void_p(t.data_ptr()), t.numel() * t.element_size()),
            "topk_set_workspace")
     _ws_tensor, _ws_index = t, t.get_device()
+    if _call is not None:
+        _call.workspace_device(_ws_index)
 
 
 def ensure_workspace(op: int, rows: int, n: int, k: int, p: float, device) -> None:
@@ -225,6 +262,10 @@ def set_route(which: int, value: int) -> None:
 
 
 def topk_mask_fwd(theta, k, p, lam, out=None, stream=None):
+    if _call is not None:
+        r = _call.fwd(_MASK_FWD, theta, k, p, lam, out, stream)
+        if r is not None:
+            return r
     theta = _dev_f32(theta, "theta")
     rows, n = theta.shape
     out = _out(out, theta, "out", (theta,))
@@ -235,6 +276,10 @@ def topk_mask_fwd(theta, k, p, lam, out=None, stream=None):
 
 def topk_mask_jvp(theta, tangent, k, p, lam, out=None, jvp_out=None, want_out=True, stream=None):
     """Returns (out, jvp_out); out is None when want_out is False and no out tensor was given."""
+    if _call is not None:
+        r = _call.jvp(_MASK_JVP, theta, tangent, k, p, lam, out, jvp_out, want_out, stream)
+        if r is not None:
+            return r
     theta = _dev_f32(theta, "theta")
     tangent = _like(tangent, theta, "tangent")
     rows, n = theta.shape
@@ -270,6 +315,10 @@ def topk_mask_jvp_static(theta, tangent, k, p, lam, out, jvp_out, stream=None):
 
 
 def topkmag_fwd(x, k, p, lam, out=None, stream=None):
+    if _call is not None:
+        r = _call.fwd(_MAG_FWD, x, k, p, lam, out, stream)
+        if r is not None:
+            return r
     x = _dev_f32(x, "x")
     rows, n = x.shape
     out = _out(out, x, "out", (x,))
@@ -279,6 +328,10 @@ def topkmag_fwd(x, k, p, lam, out=None, stream=None):
 
 
 def topkmag_jvp(x, tangent, k, p, lam, out=None, jvp_out=None, want_out=True, stream=None):
+    if _call is not None:
+        r = _call.jvp(_MAG_JVP, x, tangent, k, p, lam, out, jvp_out, want_out, stream)
+        if r is not None:
+            return r
     x = _dev_f32(x, "x")
     tangent = _like(tangent, x, "tangent")
     rows, n = x.shape
@@ -316,6 +369,10 @@ def topk_mask_sparse_fwd(theta, k, p, lam, max_nnz, idx_out=None, val_out=None, 
                          stream=None):
     """Returns (idx [rows, max_nnz] int32, val [rows, max_nnz] float32, nnz [rows] int32); the three
     tensors may be passed in (contiguous, on the GPU, of those shapes and types)."""
+    if _call is not None and idx_out is None and val_out is None and nnz_out is None:
+        r = _call.sparse(_SPARSE, theta, k, p, lam, max_nnz, stream)
+        if r is not None:
+            return r
     theta = _dev_f32(theta, "theta")
     rows, n = theta.shape
     shape = (rows, int(max_nnz))
@@ -384,28 +441,48 @@ def topk_mask_dykstra_fwd(theta, k, lam, iters, out=None, stream=None):
 
 
 def topk_signed_mask_fwd(x, k, p, lam, out=None, stream=None):
+    if _call is not None:
+        r = _call.fwd(_SIGNED_FWD, x, k, p, lam, out, stream)
+        if r is not None:
+            return r
     return _abs_variant("topk_signed_mask", TOPK_OP_SIGNED_MASK, x, None, k, p, lam, out, None, stream)
 
 
 def topk_signed_mask_jvp(x, tangent, k, p, lam, out=None, jvp_out=None, stream=None):
     """Returns (out, jvp_out)."""
+    if _call is not None:
+        r = _call.jvp(_SIGNED_JVP, x, tangent, k, p, lam, out, jvp_out, True, stream)
+        if r is not None:
+            return r
     return _abs_variant("topk_signed_mask", TOPK_OP_SIGNED_MASK, x, tangent, k, p, lam, out, jvp_out,
                         stream)
 
 
 def topk_masked_value_fwd(x, k, p, lam, out=None, stream=None):
+    if _call is not None:
+        r = _call.fwd(_MASKED_FWD, x, k, p, lam, out, stream)
+        if r is not None:
+            return r
     return _abs_variant("topk_masked_value", TOPK_OP_MASKED_VALUE, x, None, k, p, lam, out, None,
                         stream)
 
 
 def topk_masked_value_jvp(x, tangent, k, p, lam, out=None, jvp_out=None, stream=None):
     """Returns (out, jvp_out)."""
+    if _call is not None:
+        r = _call.jvp(_MASKED_JVP, x, tangent, k, p, lam, out, jvp_out, True, stream)
+        if r is not None:
+            return r
     return _abs_variant("topk_masked_value", TOPK_OP_MASKED_VALUE, x, tangent, k, p, lam, out,
                         jvp_out, stream)
 
 
 def topk_mask_vjp(theta, cotangent, k, p, lam, out=None, vjp_out=None, want_out=True, stream=None):
     """Returns (out, vjp_out); out is None when want_out is False and no out tensor was given."""
+    if _call is not None:
+        r = _call.jvp(_MASK_VJP, theta, cotangent, k, p, lam, out, vjp_out, want_out, stream)
+        if r is not None:
+            return r
     theta = _dev_f32(theta, "theta")
     cotangent = _like(cotangent, theta, "cotangent")
     rows, n = theta.shape
@@ -422,6 +499,10 @@ def topk_mask_vjp(theta, cotangent, k, p, lam, out=None, vjp_out=None, want_out=
 
 
 def topkmag_vjp(x, cotangent, k, p, lam, out=None, vjp_out=None, want_out=True, stream=None):
+    if _call is not None:
+        r = _call.jvp(_MAG_VJP, x, cotangent, k, p, lam, out, vjp_out, want_out, stream)
+        if r is not None:
+            return r
     x = _dev_f32(x, "x")
     cotangent = _like(cotangent, x, "cotangent")
     rows, n = x.shape
@@ -439,6 +520,10 @@ def topkmag_vjp(x, cotangent, k, p, lam, out=None, vjp_out=None, want_out=True, 
 
 def topk_mask_loss(theta, target, k, p, lam, loss_out=None, grad_out=None, stream=None):
     """Returns (loss [rows], grad [rows][n])."""
+    if _call is not None and loss_out is None and grad_out is None:
+        r = _call.loss(_LOSS, theta, target, k, p, lam, stream)
+        if r is not None:
+            return r
     theta = _dev_f32(theta, "theta")
     target = _like(target, theta, "target")
     rows, n = theta.shape

@@ -1,10 +1,12 @@
-"""Builds the HIP library (gfx950) in-tree with hipcc: csrc/*.hip -> lib/libsparse_topk.so."""
+"""Builds in-tree: the HIP library (gfx950) with hipcc, csrc/*.hip -> lib/libsparse_topk.so, and the native call path of
+the binding with the host compiler, csrc/host/call.cpp -> lib/_call.so."""
 from __future__ import annotations
 
 import glob
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -24,11 +26,32 @@ def sources():
     return sorted(glob.glob(os.path.join(CSRC, "*.hip")))
 
 
+CALL_SRC = os.path.join(CSRC, "host", "call.cpp")
+CALL_LIB = os.path.join(LIBDIR, "_call.so")
+
+
+def call_command():
+    """Host C++ against the headers of the torch that is installed; its libraries are found by name among those that it
+    has loaded."""
+    import torch
+    home = os.path.dirname(torch.__file__)
+    inc = os.path.join(home, "include")
+    return [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall",
+            "-Wno-sign-compare", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+            f'-DTOPK_TORCH_VERSION="{torch.__version__}"',
+            "-isystem", inc, "-isystem", os.path.join(inc, "torch", "csrc", "api", "include"),
+            "-isystem", sysconfig.get_paths()["include"], CALL_SRC, "-o", CALL_LIB,
+            "-L" + os.path.join(home, "lib"), "-lc10", "-ltorch_cpu", "-ltorch_python"]
+
+
 def build_library(verbose: bool = True) -> str:
     """Compile every translation unit and link the shared library.  Always recompiles."""
     os.makedirs(LIBDIR, exist_ok=True)
     objs = []
-    procs = []
+    cmd = call_command()
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    procs = [(CALL_SRC, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True))]
     for src in sources():
         obj = os.path.join(LIBDIR, os.path.basename(src)[:-4] + ".o")
         cmd = [HIPCC, *FLAGS, "-c", src, "-o", obj]
