@@ -386,17 +386,17 @@ static int run_general(int phi, const float* x, const float* w, int64_t w_stride
   // is needed and the row is not sorted (64 x 65536, lambda = 0.1: see general_search.hip).  The other
   // forms need more than the sums of the values (p = 4/3), the tangent by sorted position (JVP) or
   // have not been carried over (magnitude).  general_rounds > 0 asks for the kernel of the rounds.
-  const uint32_t* todo = nullptr;
   if (!mag && pc == topk::kP2 && !need_jvp && topk::routes().general_rounds == 0 &&
       (w_stride == 0 || rows <= 65535)) {
+    const uint32_t* todo = nullptr;
     if (topk::launch_general_search(gb, B, x, w, w_stride, out, rows, n, make_reg(lambda), st, &todo) != 0 ||
-        topk::launch_row_sort(B, x, rows, n, todo, st) != 0)
+        topk::launch_general_rest(B, gb, x, w, w_stride, out, rows, n, make_reg(lambda), st, todo) != 0)
       return TOPK_ERR_INVALID;
-  } else if (topk::launch_segmented_sort(mag, x, rows, n, B, st) != 0) {
-    return TOPK_ERR_INVALID;
+    return finish();
   }
-  if (topk::launch_general_long(mag, pc, B, gb, x, w, w_stride, need_jvp ? tangent : nullptr, out,
-                                need_jvp ? jvp : nullptr, rows, n, make_reg(lambda), st, todo) != 0)
+  if (topk::launch_segmented_sort(mag, x, rows, n, B, st) != 0 ||
+      topk::launch_general_long(mag, pc, B, gb, x, w, w_stride, need_jvp ? tangent : nullptr, out,
+                                need_jvp ? jvp : nullptr, rows, n, make_reg(lambda), st) != 0)
     return TOPK_ERR_INVALID;
   return finish();
 }

@@ -13,10 +13,13 @@
 // through the sort's index payload.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "common.hpp"
 #include "pooling.hpp"
 #include "launch.hpp"
 #include "general_pav.hpp"
+#include "row_sort.hpp"
 
 namespace topk {
 namespace {
@@ -139,15 +142,12 @@ __device__ __forceinline__ void block_neighbours(int first, int last, int n, Sca
 }
 
 template <bool MAG, int PC>
-__global__ __launch_bounds__(kGT) void general_long_kernel(
-    uint32_t* keys_all, const uint32_t* __restrict__ idx_all, const float* __restrict__ x_all,
+__device__ __forceinline__ void general_long_row(
+    ScanShared& sm, int64_t row, uint32_t* keys_all, const uint32_t* __restrict__ idx_all, const float* __restrict__ x_all,
     const float* __restrict__ w_all, int64_t w_stride, const float* __restrict__ tangent_all,
-    float* __restrict__ out_all, float* __restrict__ jvp_all, GeneralBuffers gb, int n, Reg R,
-    int max_rounds, const uint32_t* __restrict__ todo) {
+    float* __restrict__ out_all, float* __restrict__ jvp_all, const GeneralBuffers& gb, int n, const Reg& R,
+    int max_rounds) {
   constexpr bool CUBIC = (PC == kP43);
-  __shared__ ScanShared sm;
-  const int64_t row = blockIdx.x;
-  if (todo != nullptr && todo[row] == 0) return;   // solved already (general_search.hip)
   const int64_t base = row * int64_t(n);
   const int64_t qbase = row * int64_t(n + 1);
   const int t = threadIdx.x;
@@ -484,6 +484,42 @@ __global__ __launch_bounds__(kGT) void general_long_kernel(
   }
 }
 
+// (77 registers for p = 2; held to 64, so that two workgroups share a compute unit, 4000 x 3000 goes from 1034 to 905 us
+// and 64 x 40000 in magnitude from 992 to 1039)
+template <bool MAG, int PC>
+__global__ __launch_bounds__(kGT) void general_long_kernel(
+    uint32_t* keys_all, const uint32_t* idx_all, const float* __restrict__ x_all, const float* __restrict__ w_all,
+    int64_t w_stride, const float* __restrict__ tangent_all, float* __restrict__ out_all,
+    float* __restrict__ jvp_all, GeneralBuffers gb, int n, Reg R, int max_rounds) {
+  __shared__ ScanShared sm;
+  general_long_row<MAG, PC>(sm, blockIdx.x, keys_all, idx_all, x_all, w_all, w_stride, tangent_all, out_all,
+                            jvp_all, gb, n, R, max_rounds);
+}
+
+// The rows that general_search.hip hands over (todo[row] != 0): none mostly, but all of a call's rows where lambda
+// is far below the distances of the values or the weights increase.  One workgroup sorts its row and goes on as
+// above; a launch without such rows takes 3 us (and one of its own for the sort took as much again).
+// Network: 64 registers and two workgroups per compute unit (4000 x 3000, lambda = 1e-6: 1014 us in two launches, 1185 in
+// one with 75 registers, 832 with 64).
+template <class SORT>
+constexpr int kRestWaves = std::is_same<SORT, RowSortNet>::value ? 8 : 4;
+template <class SORT>
+__global__ __launch_bounds__(kGT, kRestWaves<SORT>) void general_rest_kernel(
+    uint32_t* keys_a, uint32_t* idx_a, uint32_t* keys_b, uint32_t* idx_b, const float* __restrict__ x_all,
+    const float* __restrict__ w_all, int64_t w_stride, float* __restrict__ out_all, GeneralBuffers gb, int n,
+    Reg R, int max_rounds, const uint32_t* __restrict__ todo) {
+  __shared__ union {
+    SORT sort;
+    ScanShared scan;
+  } sm;
+  const int64_t row = blockIdx.x, base = row * int64_t(n);
+  if (todo[row] == 0) return;
+  row_sort(sm.sort, x_all + base, keys_a + base, idx_a + base, keys_b + base, idx_b + base, n);
+  __syncthreads();
+  general_long_row<false, kP2>(sm.scan, row, keys_a, idx_a, x_all, w_all, w_stride, nullptr, out_all, nullptr,
+                               gb, n, R, max_rounds);
+}
+
 }  // namespace
 
 size_t general_long_bytes(int64_t rows, int64_t n, int pc) {
@@ -511,24 +547,37 @@ GeneralBuffers general_long_carve(void* ptr, int64_t rows, int64_t n, int pc) {
 }
 
 // The rows are sorted already: B.keys_a holds the sorted keys (overwritten with the sorted values),
-// B.idx_a the index payload (index * 2 + sign bit for the magnitude form).  todo (may be null): only
-// the rows whose entry is not zero.
+// B.idx_a the index payload (index * 2 + sign bit for the magnitude form).
 int launch_general_long(bool mag, int pc, const SortBuffers& B, const GeneralBuffers& gb,
                         const float* x, const float* w, int64_t w_stride, const float* tangent,
                         float* out, float* jvp, int64_t rows, int64_t n, const Reg& R,
-                        hipStream_t st, const uint32_t* todo) {
+                        hipStream_t st) {
   if (n <= 1024 || n > kGeneralLongMax || rows > 0x7fffffffLL) return -1;
   const int forced = routes().general_rounds;          // test control
   const int max_rounds = forced > 0 ? forced : (pc == kP43 ? int(n) + 1 : 32 + int(n) / 4);
 #define TOPK_GENERAL_LONG(M, P)                                                                   \
   hipLaunchKernelGGL((general_long_kernel<M, P>), dim3(unsigned(rows)), dim3(kGT), 0, st, B.keys_a, \
-                     B.idx_a, x, w, w_stride, tangent, out, jvp, gb, int(n), R, max_rounds, todo)
+                     B.idx_a, x, w, w_stride, tangent, out, jvp, gb, int(n), R, max_rounds)
   if (!mag && pc == kP2) TOPK_GENERAL_LONG(false, kP2);
   else if (!mag && pc == kP43) TOPK_GENERAL_LONG(false, kP43);
   else if (mag && pc == kP2) TOPK_GENERAL_LONG(true, kP2);
   else if (mag && pc == kP43) TOPK_GENERAL_LONG(true, kP43);
   else return -1;
 #undef TOPK_GENERAL_LONG
+  return 0;
+}
+
+int launch_general_rest(const SortBuffers& B, const GeneralBuffers& gb, const float* x, const float* w,
+                        int64_t w_stride, float* out, int64_t rows, int64_t n, const Reg& R, hipStream_t st,
+                        const uint32_t* todo) {
+  if (n <= 1024 || n > kGeneralLongMax || rows > 0x7fffffffLL) return -1;
+  const int max_rounds = 32 + int(n) / 4;
+#define TOPK_GENERAL_REST(S)                                                                                    \
+  hipLaunchKernelGGL((general_rest_kernel<S>), dim3(unsigned(rows)), dim3(kGT), 0, st, B.keys_a, B.idx_a,       \
+                     B.keys_b, B.idx_b, x, w, w_stride, out, gb, int(n), R, max_rounds, todo)
+  if (n <= kRowNetMax) TOPK_GENERAL_REST(RowSortNet);
+  else TOPK_GENERAL_REST(MedShared<kGT>);
+#undef TOPK_GENERAL_REST
   return 0;
 }
 

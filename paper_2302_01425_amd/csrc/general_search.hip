@@ -26,11 +26,11 @@
 // rounds, values that are not finite, or weights that are not non-increasing are left to the kernel
 // that sorts the row (todo[row] = 1).
 //
-// 64 x 65536, lambda = 0.1: 909 us with a complete sort and the partition over all positions, 54 us
-// here; 64 x 1631 139 -> 36; 9 x 123069 1760 -> 85; 15 x 4899, lambda = 0.0034, 514 -> 40.  Bound by the
-// vector instructions of the three passes on the compute units that have a row (64 rows: a quarter of
-// them; 8, 6 and 9 us at 65536), the float64 scans (5 us each) and the rounds (1 to 2.5 us for a
-// majorant of 230 items, 95 us where 67 rounds are needed).
+// 64 x 65536, lambda = 0.1: 909 us with a complete sort and the partition over all positions, 47 us
+// here (54 before the first pass was shared by several workgroups, the scans left the LDS crossbar and the rows that
+// are left over had one launch instead of two); 8 x 131072 72 -> 55, 64 x 8192 37 -> 31.  Bound by the vector instructions
+// of the passes on the compute units that have a row (64 rows: a quarter of them; 6 and 9 us for the second and third at
+// 65536), the rounds (1 to 2.5 us for a majorant of 230 items, 95 us where 67 rounds are needed) and three launches.
 #include <hip/hip_runtime.h>
 
 #include "common.hpp"
@@ -38,6 +38,7 @@
 #include "launch.hpp"
 #include "general_pav.hpp"
 #include "sort_network.hpp"
+#include "wave.hpp"
 
 namespace topk {
 namespace {
@@ -82,46 +83,62 @@ struct SearchShared {
 };
 static_assert(sizeof(SearchShared) <= 160 * 1024, "LDS of a compute unit");
 
-__device__ __forceinline__ DD shfl_up_dd(const DD& v, int off) {
-  return DD{__shfl_up(v.h, off, kWave), __shfl_up(v.l, off, kWave)};
+// Scans over the lanes by moves inside the rows of 16 lanes and three row totals, not through the LDS crossbar (a step
+// of which waits some 100 cycles: the kernel below makes seven scans of six steps).
+template <int OFF>
+__device__ __forceinline__ DD row_shr_dd(const DD& v) {
+  return DD{row_shr_f64<OFF>(v.h), row_shr_f64<OFF>(v.l)};
 }
-__device__ __forceinline__ DD wave_inclusive_dd(DD v, int lane) {
-#pragma unroll
-  for (int off = 1; off < kWave; off <<= 1) {
-    const DD o = shfl_up_dd(v, off);
-    if (lane >= off) v = dd_add(o, v);
+__device__ __forceinline__ DD lane_dd(const DD& v, int lane) {
+  return DD{uniform_f64(v.h, lane), uniform_f64(v.l, lane)};
+}
+template <int LANES>
+__device__ __forceinline__ DD row_inclusive_dd(DD v) {          // inside every row of 16 lanes, LANES of them used
+  v = dd_add(row_shr_dd<1>(v), v);
+  v = dd_add(row_shr_dd<2>(v), v);
+  if constexpr (LANES > 4) {
+    v = dd_add(row_shr_dd<4>(v), v);
+    v = dd_add(row_shr_dd<8>(v), v);
   }
   return v;
+}
+// what lies in the rows of lanes before this lane's
+__device__ __forceinline__ DD rows_before_dd(const DD& row_inc, int lane) {
+  const DD b1 = lane_dd(row_inc, 15), b2 = dd_add(b1, lane_dd(row_inc, 31)), b3 = dd_add(b2, lane_dd(row_inc, 47));
+  const DD zero{0.0, 0.0};
+  return lane < 16 ? zero : (lane < 32 ? b1 : (lane < 48 ? b2 : b3));
+}
+__device__ __forceinline__ DD wave_inclusive_dd(const DD& v, int lane) {
+  const DD in_row = row_inclusive_dd<16>(v);
+  return dd_add(rows_before_dd(in_row, lane), in_row);
 }
 // exclusive scans of one value per thread over NW wavefronts; two barriers each
 template <int NW>
 __device__ __forceinline__ DD scan_dd(const DD& v, DD* wave_tot, DD* total) {
-  const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
-  const DD inc = wave_inclusive_dd(v, lane);
-  DD prev = shfl_up_dd(inc, 1);
-  if (lane == 0) prev = DD{0.0, 0.0};
-  if (lane == kWave - 1) wave_tot[w] = inc;
+  const int lane = threadIdx.x & (kWave - 1), w = __builtin_amdgcn_readfirstlane(int(threadIdx.x) / kWave);
+  const DD in_row = row_inclusive_dd<16>(v), rows = rows_before_dd(in_row, lane);
+  const DD prev = dd_add(rows, row_shr_dd<1>(in_row));
+  if (lane == kWave - 1) wave_tot[w] = dd_add(rows, in_row);
   __syncthreads();
-  DD tot = wave_tot[lane & (NW - 1)];            // the wavefronts' totals: scanned by the lanes of each
-#pragma unroll
-  for (int off = 1; off < NW; off <<= 1) {
-    const DD o = shfl_up_dd(tot, off);
-    if ((lane & (NW - 1)) >= off) tot = dd_add(o, tot);
-  }
-  const DD before{__shfl(tot.h, w > 0 ? w - 1 : 0, kWave), __shfl(tot.l, w > 0 ? w - 1 : 0, kWave)};
-  *total = DD{__shfl(tot.h, NW - 1, kWave), __shfl(tot.l, NW - 1, kWave)};
+  const DD tot = row_inclusive_dd<NW>(wave_tot[lane & (NW - 1)]);      // the wavefronts' totals, in the first NW lanes
+  *total = lane_dd(tot, NW - 1);
   __syncthreads();
-  return w > 0 ? dd_add(before, prev) : prev;
+  return w > 0 ? dd_add(lane_dd(tot, w - 1), prev) : prev;
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ unsigned long long dpp_or0_u64(unsigned long long v) {
+  return (unsigned long long)dpp_or0<CTRL, ROWS>(uint32_t(v >> 32)) << 32 | dpp_or0<CTRL, ROWS>(uint32_t(v));
 }
 __device__ __forceinline__ unsigned long long scan_u64(unsigned long long v, unsigned long long* wave_tot,
                                                        unsigned long long* total) {
   const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
   unsigned long long inc = v;
-#pragma unroll
-  for (int off = 1; off < kWave; off <<= 1) {
-    const unsigned long long o = __shfl_up(inc, off, kWave);
-    if (lane >= off) inc += o;
-  }
+  inc += dpp_or0_u64<0x111, 0xF>(inc);
+  inc += dpp_or0_u64<0x112, 0xF>(inc);
+  inc += dpp_or0_u64<0x114, 0xF>(inc);
+  inc += dpp_or0_u64<0x118, 0xF>(inc);
+  inc += dpp_or0_u64<0x142, 0xA>(inc);
+  inc += dpp_or0_u64<0x143, 0xC>(inc);
   if (lane == kWave - 1) wave_tot[w] = inc;
   __syncthreads();
   unsigned long long before = 0, all = 0;
@@ -138,18 +155,16 @@ __device__ __forceinline__ unsigned long long scan_u64(unsigned long long v, uns
 
 // Prefix sums of the weights inside tiles of kWTile positions (local[r][i], i = 0 .. n), the tiles'
 // totals, and whether a tile holds weights that increase or are not finite.  grid (tiles, weight rows)
-__global__ __launch_bounds__(kWThreads) void weight_prefix_kernel(const float* __restrict__ w_all, int n,
-                                                                  DD* __restrict__ local,
-                                                                  DD* __restrict__ total,
-                                                                  uint32_t* __restrict__ bad) {
-  __shared__ DD wave_dd[kWThreads / kWave];
-  const float* w = w_all + int64_t(blockIdx.y) * n;
-  DD* loc = local + int64_t(blockIdx.y) * (n + 1);
-  const int e0 = blockIdx.x * kWTile + threadIdx.x * kWPer;
+// (by threads 0 .. kWThreads - 1; kTileBarriers barriers)
+constexpr int kTileBarriers = 3;
+__device__ __forceinline__ void weight_prefix_tile(const float* __restrict__ w, int n, int tile,
+                                                   DD* __restrict__ loc, DD* __restrict__ total,
+                                                   uint32_t* __restrict__ bad, DD* wave_dd, uint32_t* any) {
+  const int e0 = tile * kWTile + threadIdx.x * kWPer;
   float v[kWPer];
   bool odd = false;
   float before = e0 > 0 && e0 < n ? w[e0 - 1] : 3.4028235e38f;
-  DD t{0.0, 0.0};
+  DD sum{0.0, 0.0};
 #pragma unroll
   for (int i = 0; i < kWPer; ++i) {
     v[i] = e0 + i < n ? w[e0 + i] : 0.0f;
@@ -157,20 +172,32 @@ __global__ __launch_bounds__(kWThreads) void weight_prefix_kernel(const float* _
       odd = odd || !(v[i] <= before) || !(fabsf(v[i]) <= 3.4028235e38f);
       before = v[i];
     }
-    t = dd_add(t, double(v[i]));
+    sum = dd_add(sum, double(v[i]));
   }
+  if (threadIdx.x == 0) *any = 0u;
   DD all;
-  DD run = scan_dd<kWThreads / kWave>(t, wave_dd, &all);
+  DD run = scan_dd<kWThreads / kWave>(sum, wave_dd, &all);
 #pragma unroll
   for (int i = 0; i < kWPer; ++i) {
     if (e0 + i <= n) loc[e0 + i] = run;
     run = dd_add(run, double(v[i]));
   }
-  const int any = __syncthreads_or(odd);
+  if (odd) *any = 1u;
+  __syncthreads();
   if (threadIdx.x == 0) {
-    total[blockIdx.y * kWTiles + blockIdx.x] = all;
-    bad[blockIdx.y * kWTiles + blockIdx.x] = any != 0;
+    total[tile] = all;
+    bad[tile] = *any;
   }
+}
+__global__ __launch_bounds__(kWThreads) void weight_prefix_kernel(const float* __restrict__ w_all, int n,
+                                                                  DD* __restrict__ local,
+                                                                  DD* __restrict__ total,
+                                                                  uint32_t* __restrict__ bad) {
+  __shared__ DD wave_dd[kWThreads / kWave];
+  __shared__ uint32_t any;
+  const int64_t r = blockIdx.y;
+  weight_prefix_tile(w_all + r * n, n, blockIdx.x, local + r * (n + 1), total + r * kWTiles, bad + r * kWTiles,
+                     wave_dd, &any);
 }
 
 // every element of the row, eight 16-byte loads per thread in flight where rows are aligned
@@ -203,6 +230,60 @@ __device__ __forceinline__ void each_value(const float* __restrict__ x, int n, F
       for (int i = 0; i < 8; ++i)
         if (e0 + i * kNT < n) f(q[i]);
     }
+  }
+}
+
+// count << 40 | sum of the low 20 mantissa bits of every bin of the 12 leading key bits, in COPIES histograms
+template <bool VEC, int COPIES>
+__device__ __forceinline__ void count_values(const float* __restrict__ x, int n, unsigned long long* bins,
+                                             unsigned long long (*extra)[kSelBins]) {
+  const int copy = int(threadIdx.x & (kWave - 1)) % COPIES;
+  unsigned long long* hist = copy == 0 ? bins : extra[copy - 1];
+  each_value<VEC>(x, n, [&](float v) {
+    atomicAdd(&hist[desc_key(v) >> (32 - kSelBits)],
+              (1ull << 40) | (unsigned long long)(__float_as_uint(v) & 0xfffffu));
+  });
+}
+
+// Few rows (fewer than compute units): the first pass over a row is shared by `parts` workgroups, whose counts the search
+// kernel adds up, in the launch that makes the prefix sums of the weights.
+// part_bins[row][parts][kSelBins].
+template <bool VEC>
+__global__ __launch_bounds__(kNT) void general_prepare_kernel(
+    const float* __restrict__ x_all, const float* __restrict__ w_all, int n, int tiles, int weight_blocks,
+    DD* __restrict__ local, DD* __restrict__ total, uint32_t* __restrict__ bad,
+    unsigned long long* __restrict__ part_bins, int parts, int part_len) {
+  constexpr int kPartCopies = 2;                 // (two workgroups to a compute unit: the weights' come on top of the parts)
+  __shared__ unsigned long long bins[kSelBins], extra[kPartCopies - 1][kSelBins];
+  __shared__ DD wave_dd[kWThreads / kWave];
+  __shared__ uint32_t any;
+  if (int(blockIdx.x) < weight_blocks) {
+    if (threadIdx.x >= kWThreads) {              // (uniform over a wavefront)
+#pragma unroll
+      for (int i = 0; i < kTileBarriers; ++i) __syncthreads();
+      return;
+    }
+    const int64_t r = blockIdx.x / tiles;
+    weight_prefix_tile(w_all + r * n, n, int(blockIdx.x % tiles), local + r * (n + 1), total + r * kWTiles,
+                       bad + r * kWTiles, wave_dd, &any);
+    return;
+  }
+  const int64_t b = int64_t(blockIdx.x) - weight_blocks, row = b / parts;
+  const int first = int(b % parts) * part_len, len = n - first < part_len ? n - first : part_len;
+  for (int i = threadIdx.x; i < kSelBins; i += kNT) {
+    bins[i] = 0;
+#pragma unroll
+    for (int c = 0; c < kPartCopies - 1; ++c) extra[c][i] = 0;
+  }
+  __syncthreads();
+  count_values<VEC, kPartCopies>(x_all + row * n + first, len, bins, extra);
+  __syncthreads();
+  unsigned long long* dst = part_bins + b * kSelBins;
+  for (int i = threadIdx.x; i < kSelBins; i += kNT) {
+    unsigned long long h = bins[i];
+#pragma unroll
+    for (int c = 0; c < kPartCopies - 1; ++c) h += extra[c][i];
+    dst[i] = h;
   }
 }
 
@@ -282,7 +363,9 @@ __device__ int majorant(SearchShared& sm, int T, double lambda, int* which) {
     for (;;) {                                   // every round but the last one removes a block
       const int lo = lane < nb ? L[lane] : T, hi = lane < nb ? L[lane + 1] : T;
       const double g = lane < nb ? item_gamma(sm, lo, hi, lambda) : 0.0;
-      const double gp = __shfl_up(g, 1, kWave);
+      const double g15 = uniform_f64(g, 15), g31 = uniform_f64(g, 31), g47 = uniform_f64(g, 47);
+      double gp = row_shr_f64<1>(g);             // (of the lane before)
+      if ((lane & 15) == 0) gp = lane < 32 ? g15 : (lane < 48 ? g31 : g47);
       const bool keep = lane < nb && !(lane > 0 && gp < g);
       const unsigned long long km = __ballot(keep);
       const int left = __popcll(km);
@@ -315,7 +398,8 @@ template <bool VEC>
 __global__ __launch_bounds__(kNT) void general_search_kernel(
     const float* __restrict__ x_all, const float* __restrict__ w_all, int64_t w_stride,
     const DD* __restrict__ wlocal, const DD* __restrict__ wtotal, const uint32_t* __restrict__ wbad,
-    float* __restrict__ out_all, uint32_t* __restrict__ todo, int n, double lambda, double inv_lambda) {
+    float* __restrict__ out_all, uint32_t* __restrict__ todo, const unsigned long long* __restrict__ part_bins,
+    int parts, int n, double lambda, double inv_lambda) {
   __shared__ SearchShared sm;
   const int64_t row = blockIdx.x, wrow = w_stride != 0 ? row : 0;
   const float* x = x_all + row * n;
@@ -331,10 +415,12 @@ __global__ __launch_bounds__(kNT) void general_search_kernel(
     tile_total = wtotal[wrow * kWTiles + lane];
     tile_bad = wbad[wrow * kWTiles + lane] != 0;
   }
-  for (int i = tid; i < kSelBins; i += kNT) {
-    sm.bins[i] = 0;
+  if (parts == 1) {
+    for (int i = tid; i < kSelBins; i += kNT) {
+      sm.bins[i] = 0;
 #pragma unroll
-    for (int c = 0; c < kCopies - 1; ++c) sm.u.extra[c][i] = 0;
+      for (int c = 0; c < kCopies - 1; ++c) sm.u.extra[c][i] = 0;
+    }
   }
   if (tid < kWave) {
     const bool bad = __any(tile_bad);
@@ -349,14 +435,7 @@ __global__ __launch_bounds__(kNT) void general_search_kernel(
     if (tid == 0) todo[row] = 1;
     return;
   }
-  {
-    const int copy = lane % kCopies;
-    unsigned long long* hist = copy == 0 ? sm.bins : sm.u.extra[copy - 1];
-    each_value<VEC>(x, n, [&](float v) {
-      atomicAdd(&hist[desc_key(v) >> (32 - kSelBits)],
-                (1ull << 40) | (unsigned long long)(__float_as_uint(v) & 0xfffffu));
-    });
-  }
+  if (parts == 1) count_values<VEC, kCopies>(x, n, sm.bins, sm.u.extra);
   if (tid < kWave) {
     const DD t = wave_inclusive_dd(tile_total, lane);
     if (lane < tiles) sm.toff[lane + 1] = t;
@@ -371,12 +450,38 @@ __global__ __launch_bounds__(kNT) void general_search_kernel(
   uint32_t mine = 0, used = 0;
   DD mysum{0.0, 0.0};
   bool bad = false;
+  unsigned long long hsum[kPer];
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) hsum[q] = 0;
+  if (parts == 1) {
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      hsum[q] = sm.bins[tid * kPer + q];
+#pragma unroll
+      for (int c = 0; c < kCopies - 1; ++c) hsum[q] += sm.u.extra[c][tid * kPer + q];
+    }
+  } else {
+    const ulonglong2* src = reinterpret_cast<const ulonglong2*>(part_bins + row * parts * kSelBins + tid * kPer);
+    for (int q0 = 0; q0 < parts; q0 += 4) {      // eight 16-byte loads in flight
+      ulonglong2 h[4][kPer / 2];
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int q = 0; q < kPer / 2; ++q)
+          h[i][q] = q0 + i < parts ? src[int64_t(q0 + i) * (kSelBins / 2) + q] : make_ulonglong2(0ull, 0ull);
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int q = 0; q < kPer / 2; ++q) {
+          hsum[2 * q] += h[i][q].x;
+          hsum[2 * q + 1] += h[i][q].y;
+        }
+    }
+  }
 #pragma unroll
   for (int q = 0; q < kPer; ++q) {
     const uint32_t b = uint32_t(tid * kPer + q);
-    unsigned long long h = sm.bins[b];
-#pragma unroll
-    for (int c = 0; c < kCopies - 1; ++c) h += sm.u.extra[c][b];
+    const unsigned long long h = hsum[q];
     cnt[q] = uint32_t(h >> 40);
     const uint32_t top = b >= uint32_t(kSelBins) / 2 ? b : (~b & 0x7ffu);     // leading bits of the float
     const uint32_t e = (top >> 3) & 0xffu;
@@ -690,16 +795,38 @@ int launch_general_search(const GeneralBuffers& gb, const SortBuffers& B, const 
   DD* total = gb.p1;
   uint32_t* bad = gb.hi_of;
   const int tiles = int((n + kWTile - 1) / kWTile);
-  // (n a multiple of the tile: one more tile would hold position n alone, which is never looked up)
-  hipLaunchKernelGGL(weight_prefix_kernel, dim3(unsigned(tiles), unsigned(wrows)), dim3(kWThreads), 0, st,
-                     w, int(n), gb.pw, total, bad);
   const bool vec = n % 4 == 0 && ((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(out)) & 15) == 0;
+  // parts of a row that the first pass is shared by: as many as there are compute units for each row, of at least
+  // 8192 elements (below, the 32 KB of counts of a part cost as much as its elements), at most as many as B.bins has room
+  // for (64 x 65536, lambda = 0.1: 45.9 us in this kernel with one workgroup
+  // per row, 38.7 with four, and 5.4 / 9.2 in the launch before it)
+  static_assert(kSelSlices * kSelBins * 4 >= 8 * kSelBins * 8, "eight parts");
+  int64_t parts = 256 / rows;
+  if (parts > n / 8192) parts = n / 8192;
+  parts = parts > 8 ? 8 : (parts < 1 ? 1 : parts);
+  int64_t part_len = (n + parts - 1) / parts;
+  part_len = (part_len + 3) / 4 * 4;
+  unsigned long long* part_bins = reinterpret_cast<unsigned long long*>(B.bins);
+  // (n a multiple of the tile: one more tile would hold position n alone, which is never looked up)
+  if (parts > 1) {
+    const int weight_blocks = int(wrows) * tiles;
+    const dim3 grid{unsigned(weight_blocks + rows * parts)};
+    if (vec)
+      hipLaunchKernelGGL(general_prepare_kernel<true>, grid, dim3(kNT), 0, st, x, w, int(n), tiles, weight_blocks,
+                         gb.pw, total, bad, part_bins, int(parts), int(part_len));
+    else
+      hipLaunchKernelGGL(general_prepare_kernel<false>, grid, dim3(kNT), 0, st, x, w, int(n), tiles, weight_blocks,
+                         gb.pw, total, bad, part_bins, int(parts), int(part_len));
+  } else {
+    hipLaunchKernelGGL(weight_prefix_kernel, dim3(unsigned(tiles), unsigned(wrows)), dim3(kWThreads), 0, st,
+                       w, int(n), gb.pw, total, bad);
+  }
   if (vec)
     hipLaunchKernelGGL(general_search_kernel<true>, dim3(unsigned(rows)), dim3(kNT), 0, st, x, w, w_stride,
-                       gb.pw, total, bad, out, B.dtot, int(n), R.lambda, R.inv_lambda);
+                       gb.pw, total, bad, out, B.dtot, part_bins, int(parts), int(n), R.lambda, R.inv_lambda);
   else
     hipLaunchKernelGGL(general_search_kernel<false>, dim3(unsigned(rows)), dim3(kNT), 0, st, x, w, w_stride,
-                       gb.pw, total, bad, out, B.dtot, int(n), R.lambda, R.inv_lambda);
+                       gb.pw, total, bad, out, B.dtot, part_bins, int(parts), int(n), R.lambda, R.inv_lambda);
   *todo = B.dtot;
   return 0;
 }

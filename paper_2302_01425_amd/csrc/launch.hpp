@@ -230,16 +230,17 @@ GeneralBuffers general_long_carve(void* ptr, int64_t rows, int64_t n, int pc);
 int launch_general_long(bool mag, int pc, const SortBuffers& B, const GeneralBuffers& gb,
                         const float* x, const float* w, int64_t w_stride, const float* tangent,
                         float* out, float* jvp, int64_t rows, int64_t n, const Reg& R,
-                        hipStream_t st, const uint32_t* todo = nullptr);
+                        hipStream_t st);
 // The same operator without a sort of the row (identity phi, p = 2, forward only; 1024 < n <=
 // kGeneralLongMax, at most 65535 rows of weights).  Rows it cannot settle get a non-zero entry in todo[rows] (which lies in B.dtot):
-// launch_row_sort and launch_general_long then do those.
+// launch_general_rest then does those.
 int launch_general_search(const GeneralBuffers& gb, const SortBuffers& B, const float* x,
                           const float* w, int64_t w_stride, float* out, int64_t rows, int64_t n,
                           const Reg& R, hipStream_t st, const uint32_t** todo);
-// rows with todo[row] != 0: sorted keys and index payload into the "a" arrays, one workgroup per row
-int launch_row_sort(const SortBuffers& B, const float* x, int64_t rows, int64_t n,
-                    const uint32_t* todo, hipStream_t st);
+// rows with todo[row] != 0: sorted and solved by one workgroup each, in one launch
+int launch_general_rest(const SortBuffers& B, const GeneralBuffers& gb, const float* x, const float* w,
+                        int64_t w_stride, float* out, int64_t rows, int64_t n, const Reg& R, hipStream_t st,
+                        const uint32_t* todo);
 
 // Relaxed top-k mask, p = 2, by `iters` iterations of Dykstra's alternating projections (Alg. 1)
 // on the sorted row instead of the exact block search; n <= 1024.
