@@ -8,7 +8,7 @@
 namespace topk {
 namespace {
 
-template <int GL, int E, bool MAG, int PC, bool VEC, bool FULL, int MODE>
+template <int GL, int E, bool MAG, int PC, bool VEC, bool FULL, int MODE, bool SHIFT>
 int launch_wide_mode(const float* x, const float* t, float* out, float* jvp, int64_t rows, int n, int k,
                      const Reg& R, hipStream_t st) {
   using C = SelCfg<GL, E>;
@@ -18,11 +18,11 @@ int launch_wide_mode(const float* x, const float* t, float* out, float* jvp, int
   if (blocks > 0x7fffffffLL) return -1;
   const float il = float(R.inv_lambda), i1 = float(R.inv_1pl);
   if (k >= 1 && k <= GL && k < n) {
-    hipLaunchKernelGGL((short_rows_value_kernel<GL, E, MAG, PC, VEC, FULL, MODE, true, WPB>),
+    hipLaunchKernelGGL((short_rows_value_kernel<GL, E, MAG, PC, VEC, FULL, MODE, true, WPB, kVarPlain, SHIFT>),
                        dim3((unsigned)blocks), dim3(WPB * kWave), 0, st, x, t, out, jvp, rows, n, k, R,
                        il, i1, nullptr, 0.0);
   } else if constexpr (C::NP <= 1024) {
-    hipLaunchKernelGGL((short_rows_value_kernel<GL, E, MAG, PC, VEC, FULL, MODE, false, WPB>),
+    hipLaunchKernelGGL((short_rows_value_kernel<GL, E, MAG, PC, VEC, FULL, MODE, false, WPB, kVarPlain, SHIFT>),
                        dim3((unsigned)blocks), dim3(WPB * kWave), 0, st, x, t, out, jvp, rows, n, k, R,
                        il, i1, nullptr, 0.0);
   } else {
@@ -32,27 +32,36 @@ int launch_wide_mode(const float* x, const float* t, float* out, float* jvp, int
 }
 
 // mask: p = 2 and p = 4/3; magnitude: p = 2
-template <int GL, int E, bool VEC, bool FULL>
+template <int GL, int E, bool VEC, bool FULL, bool SHIFT = false>
 int launch_wide_shape2(bool mag, int pc, const float* x, const float* t, float* out, float* jvp,
                        int64_t rows, int n, int k, const Reg& R, hipStream_t st) {
   const int mode = (jvp == nullptr) ? 0 : (out == nullptr ? 1 : 2);
 #define TOPK_MODE_CALL(MAGV, PCV, M) \
-  return launch_wide_mode<GL, E, MAGV, PCV, VEC, FULL, M>(x, t, out, jvp, rows, n, k, R, st)
+  return launch_wide_mode<GL, E, MAGV, PCV, VEC, FULL, M, SHIFT>(x, t, out, jvp, rows, n, k, R, st)
+  // (rows_shifted refuses a forward alone, and magnitude below 1024)
+#define TOPK_FORWARD_CALL(MAGV, PCV, M) \
+  do {                                  \
+    if constexpr (SHIFT) return -2;     \
+    else TOPK_MODE_CALL(MAGV, PCV, M);  \
+  } while (0)
   if (!mag && pc == kP2) {
-    if (mode == 0) TOPK_MODE_CALL(false, kP2, 0);
+    if (mode == 0) TOPK_FORWARD_CALL(false, kP2, 0);
     if (mode == 1) TOPK_MODE_CALL(false, kP2, 1);
     TOPK_MODE_CALL(false, kP2, 2);
   }
   if (!mag && pc == kP43) {
-    if (mode == 0) TOPK_MODE_CALL(false, kP43, 0);
+    if (mode == 0) TOPK_FORWARD_CALL(false, kP43, 0);
     if (mode == 1) TOPK_MODE_CALL(false, kP43, 1);
     TOPK_MODE_CALL(false, kP43, 2);
   }
-  if (mag && pc == kP2) {
-    if (mode == 0) TOPK_MODE_CALL(true, kP2, 0);
-    if (mode == 1) TOPK_MODE_CALL(true, kP2, 1);
-    TOPK_MODE_CALL(true, kP2, 2);
+  if constexpr (!SHIFT || GL * E >= 1024) {
+    if (mag && pc == kP2) {
+      if (mode == 0) TOPK_FORWARD_CALL(true, kP2, 0);
+      if (mode == 1) TOPK_MODE_CALL(true, kP2, 1);
+      TOPK_MODE_CALL(true, kP2, 2);
+    }
   }
+#undef TOPK_FORWARD_CALL
 #undef TOPK_MODE_CALL
   return -2;
 }
@@ -63,6 +72,8 @@ int launch_wide_shape(bool vec, bool mag, int pc, const float* x, const float* t
   if (vec && n == GL * E)
     return launch_wide_shape2<GL, E, true, true>(mag, pc, x, t, out, jvp, rows, n, k, R, st);
   if (vec) return launch_wide_shape2<GL, E, true, false>(mag, pc, x, t, out, jvp, rows, n, k, R, st);
+  if (rows_shifted<GL, E>(mag, n, x, jvp != nullptr ? t : nullptr, out, jvp))
+    return launch_wide_shape2<GL, E, false, false, true>(mag, pc, x, t, out, jvp, rows, n, k, R, st);
   return launch_wide_shape2<GL, E, false, false>(mag, pc, x, t, out, jvp, rows, n, k, R, st);
 }
 

@@ -5,7 +5,7 @@
 namespace topk {
 namespace {
 
-template <int GL, int E, int PC, bool VEC, bool FULL, int MODE, int VAR>
+template <int GL, int E, int PC, bool VEC, bool FULL, int MODE, int VAR, bool SHIFT>
 int launch_var_mode(const float* x, const float* t, float* out, float* jvp, float* loss,
                     double lam_over_p, int64_t rows, int n, int k, const Reg& R, hipStream_t st) {
   using C = SelCfg<GL, E>;
@@ -15,11 +15,11 @@ int launch_var_mode(const float* x, const float* t, float* out, float* jvp, floa
   if (blocks > 0x7fffffffLL) return -1;
   const float il = float(R.inv_lambda), i1 = float(R.inv_1pl);
   if (k >= 1 && k <= GL && k < n) {
-    hipLaunchKernelGGL((short_rows_value_kernel<GL, E, false, PC, VEC, FULL, MODE, true, WPB, VAR>),
+    hipLaunchKernelGGL((short_rows_value_kernel<GL, E, false, PC, VEC, FULL, MODE, true, WPB, VAR, SHIFT>),
                        dim3((unsigned)blocks), dim3(WPB * kWave), 0, st, x, t, out, jvp, rows, n, k, R,
                        il, i1, loss, lam_over_p);
   } else if constexpr (C::NP <= 1024) {
-    hipLaunchKernelGGL((short_rows_value_kernel<GL, E, false, PC, VEC, FULL, MODE, false, WPB, VAR>),
+    hipLaunchKernelGGL((short_rows_value_kernel<GL, E, false, PC, VEC, FULL, MODE, false, WPB, VAR, SHIFT>),
                        dim3((unsigned)blocks), dim3(WPB * kWave), 0, st, x, t, out, jvp, rows, n, k, R,
                        il, i1, loss, lam_over_p);
   } else {
@@ -28,29 +28,36 @@ int launch_var_mode(const float* x, const float* t, float* out, float* jvp, floa
   return 0;
 }
 
-template <int GL, int E, bool VEC, bool FULL>
+template <int GL, int E, bool VEC, bool FULL, bool SHIFT = false>
 int launch_var_shape2(int var, int pc, const float* x, const float* t, float* out, float* jvp,
                       float* loss, double lam_over_p, int64_t rows, int n, int k, const Reg& R,
                       hipStream_t st) {
 #define TOPK_VAR_CALL(PCV, M, V) \
-  return launch_var_mode<GL, E, PCV, VEC, FULL, M, V>(x, t, out, jvp, loss, lam_over_p, rows, n, k, R, st)
+  return launch_var_mode<GL, E, PCV, VEC, FULL, M, V, SHIFT>(x, t, out, jvp, loss, lam_over_p, rows, n, k, R, st)
+  // (rows_shifted refuses a forward alone)
+#define TOPK_FORWARD_CALL(PCV, M, V) \
+  do {                               \
+    if constexpr (SHIFT) return -2;  \
+    else TOPK_VAR_CALL(PCV, M, V);   \
+  } while (0)
   const bool with_jvp = jvp != nullptr;
   if (var == kVarLoss) {
     if (pc == kP2) TOPK_VAR_CALL(kP2, 0, kVarLoss);
     if (pc == kP43) TOPK_VAR_CALL(kP43, 0, kVarLoss);
   }
   if (var == kVarSigned) {
-    if (pc == kP2 && !with_jvp) TOPK_VAR_CALL(kP2, 0, kVarSigned);
+    if (pc == kP2 && !with_jvp) TOPK_FORWARD_CALL(kP2, 0, kVarSigned);
     if (pc == kP2) TOPK_VAR_CALL(kP2, 2, kVarSigned);
-    if (pc == kP43 && !with_jvp) TOPK_VAR_CALL(kP43, 0, kVarSigned);
+    if (pc == kP43 && !with_jvp) TOPK_FORWARD_CALL(kP43, 0, kVarSigned);
     if (pc == kP43) TOPK_VAR_CALL(kP43, 2, kVarSigned);
   }
   if (var == kVarMasked) {
-    if (pc == kP2 && !with_jvp) TOPK_VAR_CALL(kP2, 0, kVarMasked);
+    if (pc == kP2 && !with_jvp) TOPK_FORWARD_CALL(kP2, 0, kVarMasked);
     if (pc == kP2) TOPK_VAR_CALL(kP2, 2, kVarMasked);
-    if (pc == kP43 && !with_jvp) TOPK_VAR_CALL(kP43, 0, kVarMasked);
+    if (pc == kP43 && !with_jvp) TOPK_FORWARD_CALL(kP43, 0, kVarMasked);
     if (pc == kP43) TOPK_VAR_CALL(kP43, 2, kVarMasked);
   }
+#undef TOPK_FORWARD_CALL
 #undef TOPK_VAR_CALL
   return -2;
 }
@@ -63,6 +70,8 @@ int launch_var_shape(bool vec, int var, int pc, const float* x, const float* t, 
     return launch_var_shape2<GL, E, true, true>(var, pc, x, t, out, jvp, loss, lam_over_p, rows, n, k, R, st);
   if (vec)
     return launch_var_shape2<GL, E, true, false>(var, pc, x, t, out, jvp, loss, lam_over_p, rows, n, k, R, st);
+  if (rows_shifted<GL, E>(false, n, x, t, out, jvp))
+    return launch_var_shape2<GL, E, false, false, true>(var, pc, x, t, out, jvp, loss, lam_over_p, rows, n, k, R, st);
   return launch_var_shape2<GL, E, false, false>(var, pc, x, t, out, jvp, loss, lam_over_p, rows, n, k, R, st);
 }
 

@@ -162,14 +162,71 @@ __device__ __forceinline__ void sort_listed(float* ls, int lr) {
 //               form of Prop. 2 at its maximiser y.
 constexpr int kVarPlain = 0, kVarSigned = 1, kVarMasked = 2, kVarLoss = 3;
 
+// SHIFT (VEC and FULL false): rows that do not all start at a 16-byte boundary, dealt float4 by float4 at the natural
+// alignment of the addresses: register r of lane lr holds element ((r / 4) * GL + lr) * 4 + r % 4 - shift, shift =
+// the row's first address in words modulo 4, so that only the two groups at the row's ends are accessed element by
+// element.  (Reading those two whole as well, into the rows beside, measured the same.)
+template <int GL, int E>
+__device__ __forceinline__ void load_row_shifted(const float* __restrict__ p, int64_t base, int lr, int n, int shift,
+                                                 float (&v)[E]) {
+#pragma unroll
+  for (int c = 0; c < E / 4; ++c) {
+    const int off = (c * GL + lr) * 4 - shift;
+    float4 q = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (off >= 0 && off + 4 <= n) q = load4_stream(p + base + off);
+    v[4 * c] = q.x; v[4 * c + 1] = q.y; v[4 * c + 2] = q.z; v[4 * c + 3] = q.w;
+  }
+#pragma unroll
+  for (int c = 0; c < E / 4; ++c) {
+    const int off = (c * GL + lr) * 4 - shift;
+    if ((off < 0 || off + 4 > n) && off < n) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (off + r >= 0 && off + r < n) v[4 * c + r] = p[base + off + r];
+    }
+  }
+}
+template <int GL, int E>
+__device__ __forceinline__ void store_row_shifted(float* __restrict__ p, int64_t base, int lr, int n, int shift,
+                                                  const float (&v)[E]) {
+#pragma unroll
+  for (int c = 0; c < E / 4; ++c) {
+    const int off = (c * GL + lr) * 4 - shift;
+    if (off >= 0 && off + 4 <= n) {
+      store4_stream(p + base + off, make_float4(v[4 * c], v[4 * c + 1], v[4 * c + 2], v[4 * c + 3]));
+    } else if (off < n) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (off + r >= 0 && off + r < n) p[base + off + r] = v[4 * c + r];
+    }
+  }
+}
+// Is SHIFT possible (all arrays agree modulo 16 bytes, and a row fits the GL * E elements of its lanes with its shift)
+// and worth it?  With a tangent or a target only: three or four arrays are then accessed (forward alone, two arrays,
+// it loses: 4096 x 1021 10.8 us element by element, 11.8 so), and not where short rows leave most lanes of the last
+// accesses idle.  Mask with its JVP, element by element against so (us): 16384 x 149 16.3 / 16.7, x 211 17.9 / 16.1;
+// 8192 x 261 16.1 / 16.2, x 401 18.7 / 16.1; 4096 x 517 15.1 / 13.3, x 1021 19.2 / 15.0; 2000 x 1027 20.3 / 14.3,
+// x 2045 35.2 / 24.5 (p = 4/3 40.7 / 29.5).  The loss: 4096 x 1021 18.2 / 13.3, 2000 x 1601 26.2 / 18.1.  The
+// magnitude gains less, float64 being more of it: 16384 x 211 17.4 / 17.6, 8192 x 401 18.5 / 18.8; 4096 x 517
+// 15.1 / 15.6, x 1021 18.2 / 16.5; 2000 x 1601 19.5 / 17.1.
+template <int GL, int E>
+inline bool rows_shifted(bool mag, int n, const void* x, const void* t, const void* out, const void* jvp) {
+  constexpr int NP = GL * E;
+  const uintptr_t at = reinterpret_cast<uintptr_t>(x) & 15u;
+  auto agrees = [&](const void* q) { return q == nullptr || (reinterpret_cast<uintptr_t>(q) & 15u) == at; };
+  if (t == nullptr || n + 3 > NP || !agrees(t) || !agrees(out) || !agrees(jvp)) return false;
+  return mag ? NP >= 1024 && 16 * n >= 9 * NP : NP >= 1024 || 4 * n >= 3 * NP;
+}
+
 template <int GL, int E, bool MAG, int PC, bool VEC, bool FULL, int MODE, bool SELECT, int WPB,
-          int VAR = kVarPlain>
+          int VAR = kVarPlain, bool SHIFT = false>
 __global__ __launch_bounds__(WPB * kWave) void short_rows_value_kernel(
     const float* __restrict__ x, const float* __restrict__ tangent, float* __restrict__ out,
     float* __restrict__ jvp, int64_t rows, int n, int k, Reg R, float inv_lambda32,
     float inv_1pl32, float* __restrict__ loss = nullptr, double lam_over_p = 0.0) {
   static_assert(VAR == kVarPlain || !MAG, "the variants are built on the mask");
   static_assert(VAR != kVarLoss || MODE == 0, "the loss is a forward quantity");
+  static_assert(!SHIFT || (!VEC && !FULL && E % 4 == 0), "as described above");
   constexpr bool ABS = MAG || VAR == kVarSigned || VAR == kVarMasked;   // values ordered: |x|
   constexpr bool LOSS = VAR == kVarLoss;
   using P = Pool<MAG, PC>;
@@ -193,14 +250,28 @@ __global__ __launch_bounds__(WPB * kWave) void short_rows_value_kernel(
   // ---- load ------------------------------------------------------------------------------------
   // (lanes with 16 or more elements fetch the tangent only when the block is known: registers)
   constexpr bool LATE_TANGENT = E >= 16;
+  const int shift = SHIFT ? int((reinterpret_cast<uintptr_t>(x + base) >> 2) & 3u) : 0;
+  auto fetch = [&](const float* p, float (&to)[E]) {
+    if constexpr (SHIFT) load_row_shifted<GL, E>(p, base, lr, nn, shift, to);
+    else load_row<GL, E, VEC, true>(p, base, lr, nn, to);
+  };
+  auto put = [&](float* p, const float (&from)[E]) {
+    if constexpr (SHIFT) store_row_shifted<GL, E>(p, base, lr, nn, shift, from);
+    else store_row<GL, E, VEC, true>(p, base, lr, nn, from);
+  };
+  auto is_real = [&](int r) {
+    if (FULL) return true;
+    if (SHIFT) return uint32_t(elem_of<GL, E, true>(lr, r) - shift) < uint32_t(nn);
+    return elem_of<GL, E, VEC>(lr, r) < nn;
+  };
   float xin[E], tin[E];
-  load_row<GL, E, VEC, true>(x, base, lr, nn, xin);
-  if ((want_jvp || LOSS) && !LATE_TANGENT) load_row<GL, E, VEC, true>(tangent, base, lr, nn, tin);
+  fetch(x, xin);
+  if ((want_jvp || LOSS) && !LATE_TANGENT) fetch(tangent, tin);
   float v[E];                                        // the values that are ordered; padding -inf
 #pragma unroll
   for (int r = 0; r < E; ++r) {
     const float a = ABS ? fabsf(xin[r]) : xin[r];
-    v[r] = (FULL || elem_of<GL, E, VEC>(lr, r) < nn) ? a : neg_inf();
+    v[r] = is_real(r) ? a : neg_inf();
   }
 
   // ---- order the values that can matter ------------------------------------------------------------
@@ -377,7 +448,7 @@ __global__ __launch_bounds__(WPB * kWave) void short_rows_value_kernel(
   }
 
   // ---- outputs, element by element in the original places -----------------------------------------
-  if ((want_jvp || LOSS) && LATE_TANGENT) load_row<GL, E, VEC, true>(tangent, base, lr, nn, tin);
+  if ((want_jvp || LOSS) && LATE_TANGENT) fetch(tangent, tin);
   const bool have = a <= b;
   const float g32 = float(MAG ? gamma - double(c32) : gamma);   // pooled value relative to s_k
   bool abv[E], inb[E];
@@ -483,7 +554,7 @@ __global__ __launch_bounds__(WPB * kWave) void short_rows_value_kernel(
     double acc = 0.0, ysum = 0.0;
 #pragma unroll
     for (int r = 0; r < E; ++r) {
-      const bool real = FULL || elem_of<GL, E, VEC>(lr, r) < nn;
+      const bool real = is_real(r);
       double yd = double(yv[r]), yp = yd * yd;       // y^p: p = 2, or the exact ends of p = 4/3
       if (CUBIC) {
         // y = t^3 and y^(4/3) = t^4 with t = (s - gamma) / lambda, before their rounding.  (A float64 cube root of
@@ -506,8 +577,8 @@ __global__ __launch_bounds__(WPB * kWave) void short_rows_value_kernel(
     if (valid && lr == 0) loss[row] = float(acc);
   }
   if (!valid) return;
-  if (want_out) store_row<GL, E, VEC, true>(out, base, lr, nn, yv);
-  if (want_jvp) store_row<GL, E, VEC, true>(jvp, base, lr, nn, jv);
+  if (want_out) put(out, yv);
+  if (want_jvp) put(jvp, jv);
 }
 
 }  // namespace
