@@ -44,14 +44,32 @@ def call_command():
             "-L" + os.path.join(home, "lib"), "-lc10", "-ltorch_cpu", "-ltorch_python"]
 
 
+def build_call(verbose: bool = True) -> bool:
+    """Compile the native call path.  The binding works without it, so a failure (no host compiler, other torch headers)
+    is reported and leaves none behind, not one of an earlier build either."""
+    os.makedirs(LIBDIR, exist_ok=True)
+    if os.path.exists(CALL_LIB):
+        os.remove(CALL_LIB)
+    try:
+        cmd = call_command()
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        done = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+        why, ok = done.stdout.strip(), done.returncode == 0
+    except (ImportError, AttributeError, OSError) as e:
+        why, ok = repr(e), False
+    if why and (verbose or not ok):
+        print(why, file=sys.stdout if ok else sys.stderr, flush=True)
+    if not ok:
+        print(f"WARNING: {CALL_SRC} was not built; calls take the Python path", file=sys.stderr, flush=True)
+    return ok
+
+
 def build_library(verbose: bool = True) -> str:
-    """Compile every translation unit and link the shared library.  Always recompiles."""
+    """Compile every translation unit and link the shared library, then the native call path.  Always recompiles."""
     os.makedirs(LIBDIR, exist_ok=True)
     objs = []
-    cmd = call_command()
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    procs = [(CALL_SRC, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True))]
+    procs = []
     for src in sources():
         obj = os.path.join(LIBDIR, os.path.basename(src)[:-4] + ".o")
         cmd = [HIPCC, *FLAGS, "-c", src, "-o", obj]
@@ -75,6 +93,7 @@ def build_library(verbose: bool = True) -> str:
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.check_call(cmd)
+    build_call(verbose)
     return LIB
 
 
