@@ -328,9 +328,10 @@ struct Sure {
   Sums S;                 // of the sure members' centred values
   double center;
   double lo, hi;          // gamma lies in between (absolute)
+  bool coarse;            // lambda is lost beside the distances from this centre: s_k is to be the centre
 };
 struct Block {
-  double gamma;           // centred
+  double gamma, center;   // the pooled value: gamma + center
   double cnt, m;
   float lo, hi;           // members: lo <= value <= hi; everything above hi is before the block
   bool have;
@@ -349,8 +350,8 @@ __device__ __forceinline__ Block boundary_solve(G& grp, EACH each, uint32_t len,
   using P = Pool<MAG, PC>;
   constexpr bool CUBIC = (PC == kP43);
   const float inf = __uint_as_float(0x7f800000u);
-  const double center = sure.center;
-  Block out{0.0, 0.0, 0.0, inf, inf, false};
+  double center = sure.center;
+  Block out{0.0, center, 0.0, 0.0, inf, inf, false};
   float seed_lo = inf, seed_hi = -inf;           // members in any case
   double gamma = 0.0, cnt = 0.0, m = 0.0;
   float lo = inf, hi = -inf;
@@ -440,7 +441,7 @@ __device__ __forceinline__ Block boundary_solve(G& grp, EACH each, uint32_t len,
   // ---- 1. ------------------------------------------------------------------------------------------------------------
   gamma = 0.5 * (sure.lo + sure.hi) - center;
   const bool bracketed = fabs(gamma) < 1e299;
-  bool settled = bracketed && threshold_steps(sure.lo - center, sure.hi - center, 64, sure.cnt > 0.0 ? 64 : 6);
+  bool settled = bracketed && !sure.coarse && threshold_steps(sure.lo - center, sure.hi - center, 64, sure.cnt > 0.0 ? 64 : 6);
   bool grow = true;
   float first = inf, last = -inf;                // the set that is certain
   if (settled) {
@@ -513,6 +514,7 @@ __device__ __forceinline__ Block boundary_solve(G& grp, EACH each, uint32_t len,
     const float sk = float_of_ordered(olo);
     float sk1 = sk, none;                        // (tied with s_{k+1}: the ties are the seed)
     if (ge <= k) neighbours(sk, inf, &none, &sk1);
+    if (sure.coarse && fabsf(sk) < inf) center = double(sk);
     const double dk = double(sk) - center, dk1 = double(sk1) - center;
     if (!P::seed_violates(dk, dk1, R, center)) {
       out.hi = sk1;                              // (s_{k+1} < s_k, or zeros: the top k are above it)
@@ -581,7 +583,7 @@ __device__ __forceinline__ Block boundary_solve(G& grp, EACH each, uint32_t len,
       }
     }
   }
-  out = Block{gamma, cnt, m, lo, hi, true};
+  out = Block{gamma, center, cnt, m, lo, hi, true};
   return out;
 }
 
@@ -806,8 +808,19 @@ __global__ __launch_bounds__(kThreads) void wide_solve_kernel(
   // values are taken relative to a number of few bits near gamma: differences from inputs of few bits, and the sums
   // of their powers, are exact then, and an exact tie is seen as one
   sure.center = 0.0;
-  if (P::kCentered && fabs(g_lo) < 1e38 && fabs(g_hi) < 1e38)
-    sure.center = double(simplest_between(float_above(g_lo), float_below(g_hi)));
+  sure.coarse = false;
+  if constexpr (P::kCentered) {
+    constexpr double kMax = 3.4028234663852886e38;
+    if (fabs(g_lo) <= kMax && fabs(g_hi) <= kMax)
+      sure.center = win.width > 0.0 ? double(simplest_between(fminf(float_above(g_lo), float(kMax)),
+                                                              fmaxf(float_below(g_hi), -float(kMax))))
+                                    : double(win.v_bot);
+    // That number is up to two bins away from the members.  Where lambda (the reach of a block) is a small part of
+    // a bin, as among masked scores of -1e30, the sums of the differences (p = 4/3: of their cubes) would lose it: the
+    // centre has to be one of the elements then.  (Sure members lie a bin apart: the reach is not small.)
+    const double reach = MAG ? fmin(upper_end<MAG, PC>(g_lo, R) - g_lo, upper_end<MAG, PC>(g_hi, R) - g_hi) : R.lambda;
+    sure.coarse = sure.cnt == 0.0 && !(win.width * (CUBIC ? 1.0 / 64.0 : 1e-5) <= reach);
+  }
 
   // ---- this workgroup's candidates ----------------------------------------------------------------------------------
   auto tau_of = [&](float v, uint32_t e) -> float {        // tangent in sorted-value coordinates
@@ -1015,7 +1028,7 @@ __global__ __launch_bounds__(kThreads) void wide_solve_kernel(
     for (uint32_t j = threadIdx.x; j < len; j += kThreads) {
       const float v = in_lds ? sm.value[j] : __uint_as_float(lv[j]);
       if (v >= blk.lo && v <= blk.hi) {
-        const double wgt = P::jac_weight(double(v) - sure.center, blk.gamma);
+        const double wgt = P::jac_weight(double(v) - blk.center, blk.gamma);
         d[0] += wgt * double(__uint_as_float(in_lds ? sm.tau[j] : lt[j]));
         d[1] += wgt;
       }
@@ -1037,7 +1050,7 @@ __global__ __launch_bounds__(kThreads) void wide_solve_kernel(
     ri.a = ri.wa = 1;                            // (the dense pass asks only whether there is a block)
     ri.b = ri.wb = blk.have ? 1 : 0;
     ri.gamma = blk.gamma;
-    ri.center = sure.center;
+    ri.center = blk.center;
     ri.dgamma = dgamma;
     ri.hi_incl = blk.hi;
     ri.lo_incl = blk.lo;

@@ -83,3 +83,47 @@ def test_wide_blocks_infinities_and_signs_of_zero(gpu, oracle):
         run_case(gpu, oracle, "mag", x[:2], t[:2], k, P2, lam, check_perm=False)
     run_case(gpu, oracle, "mask", x[:1], t[:1], n // 10, P43, 1e-3, check_perm=False)
     run_case(gpu, oracle, "mag", x[:2], t[:2], n // 10, P43, 1e-3, check_perm=False)
+
+
+# Scores masked out by a large negative number, with more top-k positions than scores that are left: the block is the
+# masked elements, exact ties, and lambda is lost beside their value, or beside the width of the window that holds it.
+# Of `tied` equal elements that share m positions each gets m / tied, whatever p (float64: one rounding); in
+# magnitude v / (1 + lambda m / tied) m / tied (p = 2), resp. w^3 with w^3 = (v - lambda w) m / tied (p = 4/3).
+@pytest.mark.parametrize("value", [-1e4, -1e9, -1e30, float(np.finfo(np.float32).min)])
+@pytest.mark.parametrize("lam", [1e-6, 1e-2, 1.0, 100.0])
+def test_masked_out_scores_share_what_is_left(gpu, value, lam):
+    n, left, k = 33000, 3000, 9000
+    r = np.random.default_rng(11)
+    x = np.full((2, n), value, dtype=np.float32)
+    x[0, r.permutation(n)[:left]] = r.normal(size=left)
+    x[1] = value                                             # a row of nothing else
+    t = r.normal(size=x.shape).astype(np.float32)
+    masked = x == np.float32(value)
+    for p in (P2, P43):
+        print(f"case value={value} lam={lam} p={p:.4f}", flush=True)
+        o, j = (host(a).astype(np.float64) for a in gpu.topk_mask_jvp(dev(x), dev(t), k, p, lam))
+        for row in range(2):
+            here, tied = masked[row], int(masked[row].sum())
+            y = (k - (n - tied)) / tied
+            assert np.array_equal(o[row, ~here], np.ones(n - tied))
+            assert np.abs(o[row, here] - y).max() <= 1.2e-7 * y
+            slope = (1.0 if p == P2 else 3.0 * y ** (2.0 / 3.0)) / lam
+            want = slope * (t[row].astype(np.float64) - t[row, here].astype(np.float64).mean())
+            assert np.abs(j[row, here] - want[here]).max() <= 2.4e-7 * np.abs(want[here]).max()
+            assert not j[row, ~here].any()
+        mag = np.abs(x)
+        mag[0, ~masked[0]] = 0.0                             # the tied elements are the largest
+        o, _ = gpu.topkmag_jvp(dev(mag), dev(t), k, p, lam)
+        o = host(o).astype(np.float64)
+        for row in range(2):
+            tied, v = int(masked[row].sum()), float(mag[row].max())
+            share = k / tied
+            if p == P2:
+                want = share * v / (1.0 + lam * share)
+            else:                                            # g = v - lambda w with w^3 = share g
+                w = np.cbrt(np.longdouble(share) * v)        # (from above: Newton falls to the root)
+                for _ in range(100):
+                    w -= (w ** 3 - share * (v - lam * w)) / (3 * w ** 2 + lam * share)
+                want = float(w ** 3)
+            assert np.abs(o[row, masked[row]] - want).max() <= 2.4e-7 * want, (o[row, masked[row]][:3], want)
+            assert not o[row, ~masked[row]].any()
