@@ -158,7 +158,7 @@ __global__ __launch_bounds__(kThreads) void wide_dense_kernel(
 #pragma unroll
       for (int i = 0; i < 8; ++i)
         if (elem(i) < n && fabsf(xv[i]) > ri.hi_incl) pack[to++] = make_float2(fabsf(xv[i]), tv[i]);
-      packed_above_mag43(pack, total, R, jvp != nullptr);
+      packed_above_mag43<2>(pack, total, R, jvp != nullptr);
     }
   }
   float yo[8], dout[8];
@@ -192,7 +192,7 @@ __global__ __launch_bounds__(kThreads) void wide_dense_kernel(
           d = v == 0.0f ? 0.0f : q.y;
         } else if (v != 0.0f) {
           double g, slope = 0.0;
-          above_mag43(double(v), R, jvp != nullptr, &g, &slope);
+          above_mag43<2>(double(v), R, jvp != nullptr, &g, &slope);
           y = float(neg ? -g : g);
           if (jvp != nullptr) d = float(slope * double(tv[i]));
         }

@@ -1062,7 +1062,7 @@ __global__ __launch_bounds__(NT == 64 ? 256 : NT) void row_search_kernel(
             const float v = val(r);
             if (is_above(v)) pack[to++] = make_float2(v, want_jvp ? tr[r] : 0.0f);
           }
-          packed_above_mag43(pack, total, R, want_jvp);
+          packed_above_mag43<1>(pack, total, R, want_jvp);
         }
       }
     }
@@ -1101,7 +1101,7 @@ __global__ __launch_bounds__(NT == 64 ? 256 : NT) void row_search_kernel(
         }
       } else if (__any(ab)) {
         double gd, slope = 0.0;
-        above_mag43(double(v), R, want_jvp, &gd, &slope);
+        above_mag43<1>(double(v), R, want_jvp, &gd, &slope);
         const float gf = float(gd);
         const bool some_y = ab && v != 0.0f;
         y = some_y ? (neg ? -gf : gf) : 0.0f;

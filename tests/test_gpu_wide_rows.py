@@ -127,3 +127,54 @@ def test_masked_out_scores_share_what_is_left(gpu, value, lam):
                 want = float(w ** 3)
             assert np.abs(o[row, masked[row]] - want).max() <= 2.4e-7 * want, (o[row, masked[row]][:3], want)
             assert not o[row, ~masked[row]].any()
+
+
+# the largest float32 values above the block, whose cubes and products with lambda are in no float32 (csrc/cubic.hpp)
+@pytest.mark.parametrize("lam", [1e-3, 1.0, 1e12, 1e25])
+def test_largest_values_above_the_block(gpu, lam):
+    n, k = 33000, 3000
+    r = np.random.default_rng(12)
+    x = np.zeros((2, n), dtype=np.float32)
+    x[:, :k] = (2.0 + 1.4 * r.random((2, k))) * 1e38
+    x[1, k:] = r.random(n - k) * 1e-3 + 1e-3
+    t = np.ones_like(x)
+    o, j = (host(a).astype(np.float64) for a in gpu.topkmag_jvp(dev(x), dev(t), k, P43, lam))
+    s = x[:, :k].astype(np.longdouble)
+    w = np.minimum(s / lam, np.cbrt(s))                      # w^3 + lambda w = s
+    for _ in range(60):
+        w -= (w ** 3 + lam * w - s) / (3 * w ** 2 + lam)
+    assert np.array_equal(o[:, :k], (w ** 3).astype(np.float32).astype(np.float64))
+    slope = (3 * w ** 2 / (3 * w ** 2 + lam)).astype(np.float64)
+    assert np.abs(j[:, :k] - slope).max() <= 1.2e-7
+    assert not o[:, k:].any()
+
+
+# Outputs above the block are float64 solutions, rounded once (csrc/cubic.hpp): elements whose solution lies within 4e-13
+# of the middle between two floats, where a solve to 5e-13 rounds some to the wrong one and one in float64 none.  They
+# are near s = lambda^(3/2), where the float32 start of the solve is worst.
+@pytest.mark.parametrize("lam", [0.011, 0.07, 0.3, 1.7, 4.5, 11.0, 29.0, 73.0])
+def test_cubics_above_the_block_to_rounding(gpu, lam):
+    n = 40000
+    s = np.unique((lam ** 1.5 * np.linspace(0.97, 1.04, 1 << 21)).astype(np.float32))
+
+    def solve(v, of):
+        v = v.astype(of)
+        w = np.minimum(v / lam, np.cbrt(v))                  # w^3 + lambda w = s
+        for _ in range(8):
+            w -= (w * (w * w + lam) - v) / (3 * w * w + lam)
+        return w ** 3
+
+    def from_middle(g):
+        f = g.astype(np.float32)
+        step = np.where(g > f, np.nextafter(f, np.float32(np.inf)), np.nextafter(f, np.float32(0.0)))
+        return np.abs(g - (f.astype(g.dtype) + step.astype(g.dtype)) / 2) / g
+
+    s = s[from_middle(solve(s, np.float64)) < 4e-13]
+    g = solve(s, np.longdouble)
+    keep = from_middle(g) > 2e-15
+    s, g = s[keep], g[keep]
+    assert 1 <= len(s) <= n // 2
+    x = np.zeros((1, n), dtype=np.float32)
+    x[0, ::n // len(s)][:len(s)] = s
+    o = host(gpu.topkmag_fwd(dev(x), len(s), P43, lam))
+    assert np.array_equal(o[0, ::n // len(s)][:len(s)], g.astype(np.float32))
