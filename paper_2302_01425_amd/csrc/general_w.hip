@@ -559,69 +559,111 @@ __device__ __forceinline__ double row_exclusive_scan(double v, int lr) {
     return group_exclusive_scan_f64<GL>(v, lr);
   }
 }
+// the number nearest to zero among those of the first 16 lanes
+__device__ __forceinline__ float nearest_zero16(float v) {
+  const uint32_t b = __float_as_uint(v);
+  uint32_t m = (b << 1) | (b >> 31);
+#define TOPK_STEP(CTRL) m = min(m, uint32_t(__builtin_amdgcn_update_dpp(int(m), int(m), CTRL, 0xF, 0xF, false)))
+  TOPK_STEP(0x111);
+  TOPK_STEP(0x112);
+  TOPK_STEP(0x114);
+  TOPK_STEP(0x118);
+#undef TOPK_STEP
+  const uint32_t r = uint32_t(__builtin_amdgcn_readlane(int(m), 15));
+  return __uint_as_float((r >> 1) | (r << 31));
+}
+// a lane's own value from the lane after it / before it (the last / first lane: its own)
+template <int CTRL>
+__device__ __forceinline__ double neighbour_f64(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = int(b), hi = int(b >> 32);
+  const uint32_t l = uint32_t(__builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xF, 0xF, false));
+  const uint32_t h = uint32_t(__builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xF, 0xF, false));
+  return __longlong_as_double((long long)(uint64_t(h) << 32 | l));
+}
+__device__ __forceinline__ double lane_after_f64(double v) { return neighbour_f64<0x130>(v); }
+__device__ __forceinline__ double lane_before_f64(double v) { return neighbour_f64<0x138>(v); }
+// Among the lanes and four others each (in their rows of 16): do two pairs of different values agree in all but the low
+// bits of their words?
+template <int ROR>
+__device__ __forceinline__ unsigned long long pairs_alike(uint32_t word, float v, uint32_t low_bits) {
+  // (moves first: every lane takes part in them)
+  const uint32_t w2 = uint32_t(__builtin_amdgcn_update_dpp(0, int(word), 0x120 + ROR, 0xF, 0xF, false));
+  const int v2 = __builtin_amdgcn_update_dpp(0, int(__float_as_uint(v)), 0x120 + ROR, 0xF, 0xF, false);
+  const bool near = (word ^ w2) <= low_bits, differ = v != __uint_as_float(uint32_t(v2));
+  return __ballot(near & differ);
+}
+__device__ __forceinline__ bool words_collide(uint32_t word, float v, uint32_t low_bits) {
+  const unsigned long long a = pairs_alike<1>(word, v, low_bits), b = pairs_alike<2>(word, v, low_bits);
+  const unsigned long long c = pairs_alike<3>(word, v, low_bits), d = pairs_alike<5>(word, v, low_bits);
+  return __popcll(a) + __popcll(b) + __popcll(c) + __popcll(d) >= 2;
+}
 // Sorted (key, field) words of a row (as SortRuns on make_keys_row makes them) by way of 32-bit words: the leading
-// 32 - log2(NP) bits of the key of a value less a value from the middle of the row, and the element's number.  The
-// difference never falls as the value rises, so that only values with the same leading bits may come in the wrong
-// order (some ten pairs in a row of 1024 normal values), which a few rounds of exchanges between neighbours set right; where
-// they do not (many values that agree to 13 bits, far from that middle) the row is sorted as it was.
-// xs: the row in LDS by element.  JVP with rank weights, lambda = 0.1, this and the scans above, us before / after:
-// 4096 x 1024 57.4 / 46.8, 6697 x 425 43.9 / 35.9, 69 x 538 23.9 / 19.2 (with 75 % of the cycles vector instructions,
-// 4100 a wavefront).
-template <int GL, int E, bool MAG, int IDXB>
-__device__ __forceinline__ void sort_row(const float (&xin)[E], const float* xs, int lr, int n, double (&K)[E]) {
-  constexpr int NP = GL * E;
-  float mid;
-  {
-    float a = xs[n / 6], b = xs[n / 2], c = xs[n - 1 - n / 6];
-    if (MAG) {
-      a = fabsf(a);
-      b = fabsf(b);
-      c = fabsf(c);
+// 32 - log2(NP) bits of the key of a value less one of the row's, and the element's number.  The difference never falls as
+// the value rises, so that only values with the same leading bits may come in the wrong order (some ten pairs in a row
+// of 1024 normal values), which a few rounds of exchanges between neighbours set right.  Of the row's first 16 the value
+// nearest to zero is taken off: a few large ones among many small ones (scores masked out by -1e9) leave the small ones
+// apart then.  Rows with a cluster of values that agree to 13 bits, far from that one, are not settled so and are sorted by
+// complete keys, without the attempt where two of 256 pairs of the row's first 64 elements agree (normal values: one
+// row in 10^5).
+// xs: the row in LDS by element.  JVP with rank weights, lambda = 0.1, us a call, sorted by complete keys (with scans
+// through the LDS crossbar) / so, without a look at the pairs and with the median of three values taken off / so:
+//                                                        4096 x 1024          6697 x 425           69 x 538
+//   normal values                                     54.8 / 44.4 / 44.5   42.8 / 34.6 / 35.2   22.7 / 17.9 / 17.9
+//   half at 0 +- 1e-3, half at 100 +- 1e-3            42.7 / 57.2 / 41.8   31.1 / 39.1 / 30.2   16.5 / 21.7 / 16.0
+//   half normal, half at 100 +- 0.01                  55.6 / 65.3 / 51.5   43.9 / 48.0 / 44.4   23.1 / 26.2 / 20.7
+//   half normal, half at -1e9                         55.9 / 66.2 / 45.1   43.5 / 48.0 / 36.1   23.1 / 26.6 / 18.4
+//   a tenth at 100 +- 1e-3 (half of such rows seen)   54.6 / 65.9 / 65.6   42.8 / 49.1 / 49.3   22.5 / 25.8 / 25.8
+// Rows of up to 256 elements, two to a wavefront, gain 2 % at most and lose up to 27 %: complete keys.
+template <int E, bool MAG, int IDXB>
+__device__ __forceinline__ void sort_row(const float (&xin)[E], const float* xs, int n, double (&K)[E]) {
+  constexpr int GL = kWave, NP = GL * E;
+  const int lr = threadIdx.x & (kWave - 1);
+  const float sample = xin[0], of_row = MAG ? fabsf(sample) : sample;
+  float mid = nearest_zero16(of_row);
+  mid = fabsf(mid) < 1e37f ? mid : 0.0f;
+  auto word = [&](float v) { return desc_key((MAG ? fabsf(v) : v) - mid); };
+  if (!words_collide(word(of_row), of_row, uint32_t(NP - 1))) {
+    uint32_t W[E];
+#pragma unroll
+    for (int r = 0; r < E; ++r) {
+      const int e = r * GL + lr;
+      W[r] = ((e < n ? word(xin[r]) : kSentinelKey) & ~uint32_t(NP - 1)) | uint32_t(e);
     }
-    mid = __builtin_amdgcn_fmed3f(a, b, c);
-    mid = fabsf(mid) < 1e37f ? mid : 0.0f;
-  }
-  uint32_t W[E];
+    SortRuns<GL, E, NP>::run(W, lr);
 #pragma unroll
-  for (int r = 0; r < E; ++r) {
-    const int e = r * GL + lr;
-    const uint32_t key = desc_key((MAG ? fabsf(xin[r]) : xin[r]) - mid);
-    W[r] = ((e < n ? key : kSentinelKey) & ~uint32_t(NP - 1)) | uint32_t(e);
-  }
-  SortRuns<GL, E, NP>::run(W, lr);
-#pragma unroll
-  for (int r = 0; r < E; ++r) {
-    const uint32_t e = W[r] & uint32_t(NP - 1);
-    uint32_t key = kSentinelKey, field = (1u << IDXB) - 1u;
-    if (int(e) < n) {
-      const float v = xs[e];
-      key = desc_key(MAG ? fabsf(v) : v);
-      field = MAG ? ((e << 1) | (__float_as_uint(v) >> 31)) : e;
-    }
-    K[r] = pack<IDXB>(key, field);
-  }
-  constexpr int kRepairs = 5;
-#pragma unroll 1
-  for (int round = 0;; ++round) {
-    // (the neighbour in the next lane; the last lane of a row has none)
-    const double next = __shfl_down(K[0], 1, kWave);
-    bool wrong = lr != GL - 1 && K[E - 1] > next;
-#pragma unroll
-    for (int r = 1; r < E; ++r) wrong |= K[r - 1] > K[r];
-    if (!__any(wrong)) return;
-    if (round == kRepairs) break;
-#pragma unroll
-    for (int odd = 0; odd < 2; ++odd) {
-#pragma unroll
-      for (int r = 1 - odd; r + 1 < E; r += 2) {
-        const double lo = min_f64(K[r], K[r + 1]), hi = max_f64(K[r], K[r + 1]);
-        K[r] = lo;
-        K[r + 1] = hi;
+    for (int r = 0; r < E; ++r) {
+      const uint32_t e = W[r] & uint32_t(NP - 1);
+      uint32_t key = kSentinelKey, field = (1u << IDXB) - 1u;
+      if (int(e) < n) {
+        const float v = xs[e];
+        key = desc_key(MAG ? fabsf(v) : v);
+        field = MAG ? ((e << 1) | (__float_as_uint(v) >> 31)) : e;
       }
-      if (odd == 0) {                            // with the first and the last of the neighbouring lanes
-        const double after = __shfl_down(K[0], 1, kWave), before = __shfl_up(K[E - 1], 1, kWave);
-        if (lr != GL - 1) K[E - 1] = min_f64(K[E - 1], after);
-        if (lr != 0) K[0] = max_f64(K[0], before);
+      K[r] = pack<IDXB>(key, field);
+    }
+    constexpr int kRepairs = 5;
+#pragma unroll 1
+    for (int round = 0;; ++round) {
+      const double next = lane_after_f64(K[0]);
+      bool wrong = lr != GL - 1 && K[E - 1] > next;      // (the last lane has none)
+#pragma unroll
+      for (int r = 1; r < E; ++r) wrong |= K[r - 1] > K[r];
+      if (!__any(wrong)) return;
+      if (round == kRepairs) break;
+#pragma unroll
+      for (int odd = 0; odd < 2; ++odd) {
+#pragma unroll
+        for (int r = 1 - odd; r + 1 < E; r += 2) {
+          const double lo = min_f64(K[r], K[r + 1]), hi = max_f64(K[r], K[r + 1]);
+          K[r] = lo;
+          K[r + 1] = hi;
+        }
+        if (odd == 0) {                            // with the first and the last of the neighbouring lanes
+          const double after = lane_after_f64(K[0]), before = lane_before_f64(K[E - 1]);
+          if (lr != GL - 1) K[E - 1] = min_f64(K[E - 1], after);
+          if (lr != 0) K[0] = max_f64(K[0], before);
+        }
       }
     }
   }
@@ -638,7 +680,7 @@ __device__ __forceinline__ void sort_row(const float (&xin)[E], const float* xs,
 // the arrays of the rounds before and after these.  There is no hand-over to the sequential walk: a
 // round costs one walk step per moved block and two lane scans, and a row of n elements settles in n - 1
 // rounds at most.
-// JVP, us, against the kernel above: 4096 x 1024 (lambda = 0.1) 103 -> 55 (47 with the sort on 32-bit words),
+// JVP, us, against the kernel above: 4096 x 1024 (lambda = 0.1) 103 -> 55 (44 with the sort on 32-bit words),
 // 6697 x 425 206 -> 94, 2061 x 186 40 -> 26, 69 x 538 (lambda = 0.0065) 113 -> 58; 1024 rows of 1024 that lose one boundary per
 // round 1740 (walk after 288 rounds, at the time) -> 1060.
 template <int GL, int E>
@@ -690,12 +732,12 @@ __global__ __launch_bounds__((LeanCfg<GL, E>::WPB * kWave)) void general_shared_
 #pragma unroll
   for (int r = 0; r < E; ++r) in_w[r * GL + lr] = win[r];
   double K[E];
-  if constexpr (GL >= 32) {                  // (shorter rows: no faster, 8192 x 100 19.6 / 19.6)
+  if constexpr (GL == kWave) {               // (see there)
     float* xs = reinterpret_cast<float*>(P1.p) + NP;       // (after the weights)
 #pragma unroll
     for (int r = 0; r < E; ++r) xs[r * GL + lr] = xin[r];
     __builtin_amdgcn_wave_barrier();
-    sort_row<GL, E, MAG, IDXB>(xin, xs, lr, n, K);
+    sort_row<E, MAG, IDXB>(xin, xs, n, K);
   } else {
     make_keys_row<GL, E, false, MAG, IDXB>(xin, lr, n, K);
     SortRuns<GL, E, NP>::run(K, lr);
