@@ -346,29 +346,4 @@ __device__ __forceinline__ uint32_t lanes_sum(uint32_t v) {
   return uint32_t(__builtin_amdgcn_readlane(int(v), LANES - 1));
 }
 
-// smallest / largest of the first LANES lanes (vacated lanes: their own value)
-template <int LANES, class Op>
-__device__ __forceinline__ uint32_t lanes_fold(uint32_t v, Op op) {
-#define TOPK_FOLD(CTRL, ROWS) \
-  v = op(v, uint32_t(__builtin_amdgcn_update_dpp(int(v), int(v), CTRL, ROWS, 0xF, false)))
-  TOPK_FOLD(0x111, 0xF);
-  TOPK_FOLD(0x112, 0xF);
-  TOPK_FOLD(0x114, 0xF);
-  TOPK_FOLD(0x118, 0xF);
-  if constexpr (LANES == 64) {
-    TOPK_FOLD(0x142, 0xA);
-    TOPK_FOLD(0x143, 0xC);
-  }
-#undef TOPK_FOLD
-  return uint32_t(__builtin_amdgcn_readlane(int(v), LANES - 1));
-}
-template <int LANES>
-__device__ __forceinline__ uint32_t lanes_min(uint32_t v) {
-  return lanes_fold<LANES>(v, [](uint32_t a, uint32_t b) { return min(a, b); });
-}
-template <int LANES>
-__device__ __forceinline__ uint32_t lanes_max(uint32_t v) {
-  return lanes_fold<LANES>(v, [](uint32_t a, uint32_t b) { return max(a, b); });
-}
-
 }  // namespace topk

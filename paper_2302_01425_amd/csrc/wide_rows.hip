@@ -52,6 +52,8 @@ constexpr int kPart = kWaves * kStep;            // a workgroup's part is a mult
 // kGroups groups of parts to finish adds those of its group.
 constexpr int kDirectParts = 32;
 constexpr int kGroups = kWideGroups;
+// About one workgroup per compute unit: no row has more parts.
+constexpr int kMaxParts = 256;
 
 // The value window as every kernel of the route sees it: values v_bot .. v_top in kFineBins bins.
 struct Window {
@@ -605,7 +607,7 @@ struct alignas(16) WideShared {
   uint32_t counts[kWaves];
   uint32_t stays[kWaves];
   uint32_t last_block;
-  uint32_t start[kThreads + 1];
+  uint32_t start[kMaxParts];
   float value[kListLds];
   uint32_t tau[kListLds];
   Block block;
@@ -916,15 +918,14 @@ __global__ __launch_bounds__(kThreads) void wide_solve_kernel(
   if (threadIdx.x == 6) publish(sc.listed + row * parts + block, listed);
   if (!arrive_last(&sc.arrived[row * (kSelSlices * 2 * kSel2Bins)], parts, &sm.last_block)) return;
 
-  // ---- the last workgroup of the row: sums and list of all of them, kThreads workgroups at a time --------------------
+  // ---- the last workgroup of the row: sums and list of all of them, one workgroup per thread -------------------------
   uint32_t* lv = long_val + row * n;             // (the slots: every workgroup of the row is done with them)
   uint32_t* lt = long_tau + row * n;
   const bool in_lds = len <= uint32_t(kListLds);
 #pragma unroll
   for (int i = 0; i < 6; ++i) part[i] = 0.0;
-  uint32_t have = 0u;
-  for (int q0 = 0; q0 < parts; q0 += kThreads) {
-    const int q = q0 + int(threadIdx.x);
+  {
+    const int q = int(threadIdx.x);
     uint32_t c = 0u;
     if (q < parts) {
       const double* src = sc.sums + (row * parts + q) * 8;
@@ -935,7 +936,6 @@ __global__ __launch_bounds__(kThreads) void wide_solve_kernel(
     }
     uint32_t wave_total;
     const uint32_t inc = wave_inclusive_scan(c, &wave_total);
-    __syncthreads();
     if (lane == 0) sm.counts[w] = wave_total;
     __syncthreads();
     uint32_t before = 0u, all = 0u;
@@ -945,33 +945,31 @@ __global__ __launch_bounds__(kThreads) void wide_solve_kernel(
       before += i < w ? o : 0u;
       all += o;
     }
-    sm.start[threadIdx.x] = before + inc - c;
+    if (q < kMaxParts) sm.start[q] = before + inc - c;
     __syncthreads();
     for (uint32_t j = threadIdx.x; j < all; j += kThreads) {
       // the workgroup whose entries hold number j: the last start at or before it
-      int from = 0, to = kThreads;
+      int from = 0, to = kMaxParts;
 #pragma unroll
-      for (int t = 0; t < 10; ++t) {
+      for (int t = 0; t < 8; ++t) {
         const int mid = (from + to) / 2;
         if (sm.start[mid] <= j) from = mid;
         else to = mid;
       }
-      const int64_t src = row * n + int64_t(q0 + from) * part_len + (j - sm.start[from]);
+      const int64_t src = row * n + int64_t(from) * part_len + (j - sm.start[from]);
       const uint32_t v = published(list_val + src), t = tangent != nullptr ? published(list_tau + src) : 0u;
-      const uint32_t to_at = have + j;
       if (in_lds) {
-        if (to_at < uint32_t(kListLds)) {
-          sm.value[to_at] = __uint_as_float(v);
-          sm.tau[to_at] = t;
+        if (j < uint32_t(kListLds)) {
+          sm.value[j] = __uint_as_float(v);
+          sm.tau[j] = t;
         }
       } else {
-        lv[to_at] = v;
-        lt[to_at] = t;
+        lv[j] = v;
+        lt[j] = t;
       }
     }
-    have += all;
+    len = all;
   }
-  len = have;
   if (in_lds && threadIdx.x < kListFlight * kWave) {         // (up to the end of the last turn of one wavefront)
     const uint32_t j = len + threadIdx.x;
     if (j < uint32_t(kListLds)) sm.value[j] = __uint_as_float(0x7fc00000u);
@@ -1065,12 +1063,11 @@ __global__ __launch_bounds__(kThreads) void wide_solve_kernel(
 
 int launch_wide_solve(bool mag, int pc, const SortBuffers& B, const float* x, const float* tangent, int64_t rows,
                       int64_t n, int64_t k, const Reg& R, hipStream_t st) {
-  // about one workgroup per compute unit
-  int64_t part_len = (n * rows + 255) / 256;
+  int64_t part_len = (n * rows + kMaxParts - 1) / kMaxParts;
   if (part_len > n) part_len = n;
   part_len = (part_len + kPart - 1) / kPart * kPart;
   const int64_t parts = (n + part_len - 1) / part_len;
-  if (rows * parts > 0x7fffffffLL) return -1;
+  if (parts > kMaxParts || rows * parts > 0x7fffffffLL) return -1;
   const int group_len = int((parts + kGroups - 1) / kGroups);
   WideScratch sc;
   // (parts <= tiles, the 4096-element tiles that the workspace is laid out for: 32 words per part of the 256 per tile
