@@ -1,15 +1,42 @@
-"""Candidate lists of long rows that are solved without sorting them (csrc/wide_rows.hip): list lengths
-around the largest sorted list (4096), the largest one gathered through LDS (16384) and the largest part
-held in LDS (32768); ties at the block's ends and around zero.  Oracle; bar: that of test_gpu_parity."""
+"""Long rows whose candidates are solved without sorting them (csrc/wide_rows.hip).  The exact solve sees the list of those
+elements that a threshold may fall next to: up to 2048 one wavefront solves, up to 6144 a workgroup with the list in LDS,
+longer ones a workgroup with the list in memory.  Lists of distinct values at these edges, windows of some thousand
+candidates (few of which are on the list), ties at the block's ends and around zero.  Oracle; bar: that of test_gpu_parity."""
 import numpy as np
 import pytest
 
-from tests.test_gpu_parity import P2, dev, gpu, host, run_case  # noqa: F401  (gpu: the fixture)
+from tests.test_gpu_parity import P2, P43, dev, gpu, host, long_rows_route, run_case  # noqa: F401  (gpu: the fixture)
 
 pytestmark = pytest.mark.gpu
 
 
-# n around 2^18: with and without the second histogram level
+# A cluster far narrower than a bin, all of which is on the list; the rest of the row is out of reach.  k = 1 and
+# lambda = 1: everything is in the block.  lambda a fraction of the cluster's width: both thresholds are inside.
+@pytest.mark.parametrize("length", [2047, 2048, 2049, 6143, 6144, 6145, 39000])
+def test_lists_of_distinct_values(gpu, oracle, length):
+    n = 40000
+    r = np.random.default_rng(length)
+    for width, k, lam in ((1e-3, 1, 1.0), (1e-4, length // 2, 4e-5), (1e-4, length // 3, 1e-5)):
+        x = np.full((2, n), -100.0, dtype=np.float32)
+        for row in x:
+            row[r.permutation(n)[:length]] = 1.01 + width * r.random(length)
+        t = r.normal(size=x.shape).astype(np.float32)
+        run_case(gpu, oracle, "mask", x, t, k, P2, lam, check_perm=False)
+        x[x < 0] = 0.0
+        run_case(gpu, oracle, "mag", x, t, k, P2, lam, check_perm=False)
+        for op in ("mask", "mag"):
+            if length < 7000:                                # (the oracle's p = 4/3 pooling is quadratic in the block)
+                run_case(gpu, oracle, op, x, t, k, P43, lam, check_perm=False)
+            else:
+                fn = gpu.topk_mask_jvp if op == "mask" else gpu.topkmag_jvp
+                o, j = (host(a) for a in fn(dev(x), dev(t), k, P43, lam))
+                with long_rows_route(gpu, "select"):
+                    o2, j2 = (host(a) for a in fn(dev(x), dev(t), k, P43, lam))
+                assert np.abs(o - o2).max() <= 2.4e-7 * np.abs(o2).max()
+                assert np.abs(j - j2).max() <= 2.4e-7 * np.abs(j2).max()
+
+
+# windows of about `width` candidates, of which the list holds the few next to the block's ends
 @pytest.mark.parametrize("n", [40000, 262144, 300001])
 @pytest.mark.parametrize("width", [4000, 4200, 16000, 17000, 32700, 33500])
 def test_list_lengths(gpu, oracle, n, width):
