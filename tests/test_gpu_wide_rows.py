@@ -24,7 +24,7 @@ def _same_as_sorted(gpu, op, x, t, k, p, lam, mode="select"):
     assert np.array_equal(o, o3) and np.array_equal(j, j3)                   # and again: the same bits
 
 
-# parts of 16384 elements; 37 parts and more are counted in groups
+# parts of 16384 elements; 33 parts (524289 elements) and more are counted in groups
 @pytest.mark.parametrize("rows,n", [(1, 32769), (3, 49151), (2, 49153), (1, 524289), (1, 600001)])
 def test_row_lengths(gpu, oracle, rows, n):
     r = np.random.default_rng(n)
@@ -51,6 +51,21 @@ def test_counts(gpu, rows, n):
         _same_as_sorted(gpu, op, x, t, n // 10, p, lam)
 
 
+# Counts that are added up in groups: 2^24 elements in 256 parts of 65536, eight of which hold nothing but one value of
+# the window, in eight neighbouring bins (a 16-bit count runs over, in either half of the words that two share); and more
+# elements than that, whose counts take 32 bits.
+@pytest.mark.parametrize("n", [1 << 24, (1 << 24) + 4097])
+def test_counts_in_groups(gpu, n):
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(n)
+    x = torch.randn((1, n), generator=g, device="cuda")
+    t = torch.randn((1, n), generator=g, device="cuda")
+    for i, part in enumerate((1, 2, 17, 100, 101, 130, 240, 255)):
+        x[0, part * 65536:(part + 1) * 65536] = 1.25 + 0.00025 * i          # (the mask's s_k is 1.263)
+    for op, k, lam in (("mask", n // 10, 0.1), ("mag", n // 5, 0.05)):
+        _same_as_sorted(gpu, op, x, t, k, P2, lam)
+
+
 # a block that is most of the row; lists of equal values that fit a wavefront, a workgroup, or nothing
 @pytest.mark.parametrize("copies", [500, 2049, 6200, 40000])
 def test_lists_of_equal_values(gpu, oracle, copies):
@@ -67,6 +82,8 @@ def test_lists_of_equal_values(gpu, oracle, copies):
             run_case(gpu, oracle, "mag", x, t, k, P2, lam, check_perm=False)
         if copies < 7000:                    # (the oracle's p = 4/3 pooling is quadratic in the block)
             run_case(gpu, oracle, "mask", x, t, k, P43, 1e-3, check_perm=False)
+            for lam in (1e-7, 1e-3, 0.5):
+                run_case(gpu, oracle, "mag", x, t, k, P43, lam, check_perm=False)
 
 
 def test_wide_blocks_infinities_and_signs_of_zero(gpu, oracle):
@@ -83,6 +100,8 @@ def test_wide_blocks_infinities_and_signs_of_zero(gpu, oracle):
         run_case(gpu, oracle, "mag", x[:2], t[:2], k, P2, lam, check_perm=False)
     run_case(gpu, oracle, "mask", x[:1], t[:1], n // 10, P43, 1e-3, check_perm=False)
     run_case(gpu, oracle, "mag", x[:2], t[:2], n // 10, P43, 1e-3, check_perm=False)
+    # (a block of 60000 zeros: the oracle would take 20 s)
+    _same_as_sorted(gpu, "mask", dev(x[1:2]), dev(t[1:2]), n // 10, P43, 1e-3)
 
 
 # Scores masked out by a large negative number, with more top-k positions than scores that are left: the block is the
