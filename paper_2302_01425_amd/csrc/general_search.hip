@@ -23,10 +23,11 @@
 //
 // One workgroup of 1024 threads per row; the second and third pass read the row from the L2.  Rows
 // with more than 2816 items (tiny lambda: most elements are blocks of their own), more than 256
-// rounds, values that are not finite, or weights that are not non-increasing are left to the kernel
-// that sorts the row (todo[row] = 1).
+// rounds, values that are not finite, or weights that are not non-increasing (the first pass over the row is not
+// made then, unless it is shared and runs beside the check) are left to the kernel that sorts the row
+// (todo[row] = 1).
 //
-// 64 x 65536, lambda = 0.1: 909 us with a complete sort and the partition over all positions, 47 us
+// 64 x 65536, lambda = 0.1: 909 us with a complete sort and the partition over all positions, 46 us
 // here (54 before the first pass was shared by several workgroups, the scans left the LDS crossbar and the rows that
 // are left over had one launch instead of two); 8 x 131072 72 -> 55, 64 x 8192 37 -> 31.  Bound by the vector instructions
 // of the passes on the compute units that have a row (64 rows: a quarter of them; 6 and 9 us for the second and third at
